@@ -80,24 +80,27 @@ __global__ __launch_bounds__(64) void step_marker_kernel(StreamRec* rec, Mirror*
   const uint64_t t = now_ticks();
   if (!end) {
     rec->step_t0 = t;
-    st_agent(&rec->state, kStateBusy);
+    st_relaxed(&rec->state, kStateBusy);
     slot->kind_id = 0;      // the begin marker leaves no trace record of its own
     slot->decision = 0;
     slot->t0 = t;
     slot->t1 = t;
     return;
   }
-  const uint64_t dt = t - rec->step_t0;
-  rec->steps += 1;
-  rec->step_ticks_sum += dt;
+  const uint64_t step_t0 = rec->step_t0, steps = rec->steps + 1, dt = t - step_t0, sum = rec->step_ticks_sum + dt;
+  rec->steps = steps;
+  rec->step_ticks_sum = sum;
   rec->step_ticks_last = dt;
-  st_sys(&mir->step_ticks_last, dt);
-  st_sys(&mir->step_ticks_sum, rec->step_ticks_sum);
-  st_sys(&mir->steps, rec->steps);
   slot->kind_id = kind_id;
   slot->decision = 1;
-  slot->t0 = rec->step_t0;
+  slot->t0 = step_t0;
   slot->t1 = t;
+  // The host looks at the times when the step count has changed, so the count goes out when these have arrived.  (A
+  // system-scope release would do that too, at the price of writing back an L2 full of the step's results three times.)
+  st_sys_relaxed(&mir->step_ticks_last, dt);
+  st_sys_relaxed(&mir->step_ticks_sum, sum);
+  wait_fetches();
+  st_sys_relaxed(&mir->steps, steps);
 }
 
 // Clears the poison of the inference stream after the host has taken note of the first skipped launch.

@@ -21,8 +21,7 @@ struct alignas(128) StreamRec {     // one per stream, in HBM
   uint32_t state;                   // training stream: kStateBusy / kStateIdle (inside a bubble)
   uint32_t seq;                     // number of the current / last bubble (state and seq: one aligned 64-bit word)
   uint32_t site;                    // its site in the step
-  uint32_t launched;                // kernels started on this stream
-  uint32_t completed;               // kernels finished
+  uint32_t pad2, pad3;
   uint32_t skip_from;               // inference stream: first skipped launch (poison), kNone if clear
   uint32_t pad0, pad1;
   uint64_t t_start, t_end;          // last kernel start / end (device wall clock ticks)
@@ -34,7 +33,7 @@ struct alignas(128) StreamRec {     // one per stream, in HBM
   uint64_t steps, step_ticks_sum, step_ticks_last;
   uint64_t bubble_ticks, filled_ticks, infer_ticks;
   uint64_t kernels_run, kernels_skipped, train_kernels;
-  // completion counters of the kernel currently running on this stream (see kernel_end)
+  // completion counters of the kernel currently running on this stream (see kernel_end): zero between kernels
   uint32_t done_top;
   alignas(128) uint32_t done_sub[64 * 32];
   // work counters of the kernel currently running on this stream (kernels that hand out their tiles dynamically: one
@@ -84,6 +83,8 @@ struct KCtl {                       // by-value kernel argument
   uint32_t kind_id;
   uint32_t flags;                   // bit 0: last kernel of its job; bit 1: gated on the poison only (runs beside training);
                                     // bits 8..15: 0, or 1 + log2 of the bound on the spins a block waits for block 0's decision
+  uint32_t nth;                     // training launches: how many monitored kernels of the stream this makes (they are never
+                                    // skipped, so the host knows the count and no block has to read it back)
 };
 constexpr uint32_t kDefaultSpinLog2 = 18;
 
@@ -161,28 +162,37 @@ __device__ __forceinline__ bool gate_decide(const KCtl& c, uint64_t* t0, uint32_
 //     up does not count itself in kernel_end, so a launch that block 0 then lets run never reaches its full count:
 //     it is never reported done, and the kernel that clears the poison (it runs alone on the stream) re-arms the
 //     completion counters it left behind.
-//   * Blocks of an ungated launch never wait.
+//   * Blocks of an ungated launch never wait: block 0 only stores (the training stream's kernel count comes with the
+//     launch), the others do nothing.
 __device__ __forceinline__ uint32_t linear_block() { return blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z); }
 
 __device__ __forceinline__ bool kernel_begin(const KCtl& c) {
   if (c.rec == nullptr) return true;
+  if (c.gate == nullptr) {
+    if (linear_block() == 0 && first_thread()) {
+      const uint64_t t0 = now_ticks();
+      c.slot->kind_id = c.kind_id;
+      st_relaxed(&c.slot->t0, t0);
+      st_relaxed(&c.rec->t_start, t0);
+      st_relaxed(&c.slot->decision, (c.kseq << 2) | 1u);
+      if ((c.kind_id >> 28) == kKindTrain) st_sys_relaxed(&c.mir->t_launched, c.nth);
+    }
+    return true;
+  }
   __shared__ int s_run;
   if (first_thread()) {
     int run = 1;
     if (linear_block() == 0) {
       uint64_t t0 = now_ticks();
       uint32_t bubble = 0;
-      if (c.gate != nullptr) run = gate_decide(c, &t0, &bubble) ? 1 : 0;
+      run = gate_decide(c, &t0, &bubble) ? 1 : 0;
       c.slot->kind_id = c.kind_id;
       st_relaxed(&c.slot->t0, t0);
       if (run) {
         // what the host needs to check this start against the bubble's own stamps (not for launches beside training)
-        if (c.gate != nullptr && !(c.flags & 2u))
+        if (!(c.flags & 2u))
           st_sys_relaxed(&c.mir->i_gate[c.kseq % kGateStamps], (t0 << 24) | ((uint64_t)(c.kseq & 0xFFFFu) << 8) | (bubble & 0xFFu));
         st_relaxed(&c.rec->t_start, t0);
-        const uint32_t l = c.rec->launched + 1;
-        st_relaxed(&c.rec->launched, l);
-        if ((c.kind_id >> 28) == kKindTrain) st_sys_relaxed(&c.mir->t_launched, l);
       } else {
         c.slot->t1 = t0;
         if (ld_relaxed(&c.rec->skip_from) == kNone) {
@@ -192,7 +202,7 @@ __device__ __forceinline__ bool kernel_begin(const KCtl& c) {
         st_sys_relaxed(&c.mir->kernels_skipped, ++c.rec->kernels_skipped);
       }
       st_relaxed(&c.slot->decision, (c.kseq << 2) | (run ? 1u : 2u));
-    } else if (c.gate != nullptr) {
+    } else {
       const uint32_t lg = (c.flags >> 8) & 0xFFu, bound = 1u << (lg ? (lg - 1u > 30u ? 30u : lg - 1u) : kDefaultSpinLog2);
       uint32_t d = 0, spins = 0;
       while (((d = ld_relaxed(&c.slot->decision)) >> 2) != c.kseq && ++spins < bound) __builtin_amdgcn_s_sleep(4);
@@ -214,52 +224,69 @@ __device__ __forceinline__ bool kernel_begin(const KCtl& c) {
 }
 
 // Kernel epilogue.  Every thread calls it after its last global store.  The last block of the grid to leave
-// stamps the end time and bumps the counters.  "Last" is found with a two-level count (64 sub-counters on
-// separate cache lines, then one top counter) so that no address sees more than blocks/64 + 64 atomics;
-// kernels of one stream never overlap, so the counters belong to the stream and the last block re-arms them.
+// stamps the end time and bumps the counters.  Kernels of one stream never overlap, so the counters belong to the
+// stream and the last block re-arms them.
+// How the last block is found: a device-scope atomic takes a round trip of about 0.7 us to the memory side, and
+// atomics on one address serialise there at about 50 ns each.  A grid of up to 32 blocks therefore counts on one
+// counter (one round trip, at most 1.6 us when all leave together); a larger one on a tree of two levels with roughly
+// as many first-level counters (on cache lines of their own) as blocks per counter.  What the last block has to read
+// it reads in one round trip; a training kernel has nothing to read.  (With 64 first-level counters for every grid, the
+// kernel count read back by block 0 and the reads one after the other: step of the two-layer MLP 124 us, now 112; a
+// batch-1 encoder request of 86 launches 1603 -> 1483 us; two-layer decoder of 256 tokens 473 -> 412 us.)
 __device__ __forceinline__ void kernel_end(const KCtl& c, bool ran) {
   if (c.rec == nullptr || !ran) return;
   __syncthreads();
   if (!first_thread()) return;
-  const uint32_t total = grid_blocks(), id = linear_block(), sub = id & 63u;
-  const uint32_t in_sub = (total - sub + 63u) >> 6;
-  uint32_t* cnt = c.rec->done_sub + sub * 32u;
-  if (atomicAdd(cnt, 1u) + 1u != in_sub) return;
-  *cnt = 0;
-  const uint32_t subs = total < 64u ? total : 64u;
-  if (atomicAdd(&c.rec->done_top, 1u) + 1u != subs) return;
-  c.rec->done_top = 0;
+  const uint32_t total = grid_blocks(), id = linear_block();
+  uint32_t arrivals = total;                     // on the top counter
+  if (total > 32u) {
+    const uint32_t lg = total <= 512u ? 4u : (total <= 2048u ? 5u : 6u), n_sub = 1u << lg, sub = id & (n_sub - 1u);
+    const uint32_t in_sub = (total - sub + n_sub - 1u) >> lg;
+    uint32_t* cnt = c.rec->done_sub + sub * 32u;
+    if (atomicAdd(cnt, 1u) + 1u != in_sub) return;
+    *cnt = 0;
+    arrivals = n_sub;
+  }
+  if (arrivals > 1u) {
+    if (atomicAdd(&c.rec->done_top, 1u) + 1u != arrivals) return;
+    c.rec->done_top = 0;
+  }
 #pragma unroll
   for (int x = 0; x < 8; ++x) st_relaxed(&c.rec->tile_next[x * 32], 0u);
   Mirror* m = c.mir;
   StreamRec* r = c.rec;
   const uint64_t t1 = now_ticks();
-  const uint64_t t0 = ld_relaxed(&c.slot->t0);
   c.slot->t1 = t1;
   st_relaxed(&r->t_end, t1);
-  const uint32_t done = r->completed + 1;
-  st_relaxed(&r->completed, done);
   if ((c.kind_id >> 28) == kKindTrain) {
-    st_sys_relaxed(&m->t_completed, done);          // also the count of training kernels run (the host takes differences)
+    st_sys_relaxed(&m->t_completed, c.nth);         // also the count of training kernels run (the host takes differences)
   } else {
-    uint64_t dur = t1 - t0, fill = dur;
+    const uint64_t t0 = ld_relaxed(&c.slot->t0), infer0 = r->infer_ticks, filled0 = r->filled_ticks, run0 = r->kernels_run;
+    uint64_t ib = 0, busy_begin = 0;
+    uint32_t state = kStateBusy;
     if (c.gate != nullptr) {
-      const uint64_t ib = ld_relaxed(&c.gate->t_idle_begin);
-      const uint64_t end = (ld_relaxed(&c.gate->state) == kStateIdle) ? t1 : ld_relaxed(&c.gate->t_busy_begin);
+      ib = ld_relaxed(&c.gate->t_idle_begin);
+      state = ld_relaxed(&c.gate->state);
+      busy_begin = ld_relaxed(&c.gate->t_busy_begin);
+    }
+    const uint64_t dur = t1 - t0;
+    uint64_t fill = dur;
+    if (c.gate != nullptr) {
+      const uint64_t end = state == kStateIdle ? t1 : busy_begin;
       const uint64_t lo = t0 > ib ? t0 : ib, hi = t1 < end ? t1 : end;
       fill = hi > lo ? hi - lo : 0;
     }
-    r->infer_ticks += dur;
-    r->filled_ticks += fill;
-    ++r->kernels_run;
+    r->infer_ticks = infer0 + dur;
+    r->filled_ticks = filled0 + fill;
+    r->kernels_run = run0 + 1;
     // The statistics travel to the host mailbox with the last kernel of a job and with every eighth launch (each
     // store to host memory lengthens the end of the kernel); the progress word travels every time.  It says that the
     // last block is about to leave, not that the kernel's results are visible: the host reports a job done only after
     // an event recorded behind its last kernel has completed.
     if ((c.flags & 1u) || (c.kseq & 7u) == 0u) {
-      st_sys_relaxed(&m->infer_ticks, r->infer_ticks);
-      st_sys_relaxed(&m->filled_ticks, r->filled_ticks);
-      st_sys_relaxed(&m->kernels_run, r->kernels_run);
+      st_sys_relaxed(&m->infer_ticks, infer0 + dur);
+      st_sys_relaxed(&m->filled_ticks, filled0 + fill);
+      st_sys_relaxed(&m->kernels_run, run0 + 1);
     }
     st_sys_relaxed(&m->i_done, c.kseq);
   }

@@ -22,6 +22,7 @@ struct StreamState {
   StreamRec* rec = nullptr;        // HBM
   Slot* ring = nullptr;            // HBM, kRingSlots entries
   uint32_t next_kseq = 1;          // launch numbers start at 1
+  uint32_t counted = 0;            // training kernels launched (the count the kernels report to the mailbox)
   uint32_t kind = 0;
 };
 

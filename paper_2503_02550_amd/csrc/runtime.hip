@@ -119,6 +119,7 @@ static KCtl make_ctl(sif_ctx* c, StreamState& st, uint32_t kind, uint32_t id, co
   k.slot = st.ring + (k.kseq % kRingSlots);
   k.gate = gate; k.cost_ticks = cost_ticks;
   k.kind_id = (kind << 28) | (id & 0x0FFFFFFFu);
+  if (kind == kKindTrain) k.nth = ++st.counted;
   return k;
 }
 

@@ -1,0 +1,53 @@
+"""Kernels at the sizes where a variant begins, ends or leaves a remainder."""
+import numpy as np
+import pytest
+import torch
+
+import synth_inputs as Y
+from oracle import mlp as OM
+
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    import paper_2503_02550_amd as S
+    from paper_2503_02550_amd import params as P
+    from paper_2503_02550_amd.session import Session, mlp_shape
+    from gpu_util import DEV, f32, up, assert_f32_close
+
+
+@pytest.mark.parametrize("batch,hidden", [(1, 8), (32, 1024), (32, 1056), (33, 2048), (512, 1024), (520, 1024), (2048, 1024), (2080, 1024)])
+def test_last_block_is_found_whatever_the_grid(batch, hidden):
+    """A launch is reported done by its last block; grids at the edges of the counting tree (1, 32, 33, 512, 2048
+    blocks and a little more, in 32 x 32 tiles) must all be, twice in a row (the counters are re-armed), with every
+    kernel counted.  Products of fp32 values: the bound of the other fp32 tests, 1e-4 of the largest value."""
+    shape = mlp_shape(8, hidden, 32, batch)
+    p = Y.mlp_params(3, 8, hidden, 32)
+    with Session() as s:
+        m = s.register_inference(shape, P.pack(shape, p))
+        for turn in range(2):
+            x = Y.activations(10 + turn, batch, 8)
+            X, out = f32(x), torch.zeros((batch, 32), device=DEV)
+            torch.cuda.synchronize()
+            s.wait(s.submit_offline(m, X, out, batch), 10.0)
+            y, _ = OM.mlp_forward({k: v.astype(np.float64) for k, v in p.items()}, x)
+            assert_f32_close(up(out), y, f"turn {turn}")
+        assert s.stats().kernels_run == 4
+
+
+@pytest.mark.parametrize("batch,hidden", [(8, 32), (64, 1056)])
+def test_training_kernels_are_counted(batch, hidden):
+    """The count of training kernels that ran, as the kernels report it, is the number launched."""
+    shape = mlp_shape(16, hidden, 16, batch)
+    with Session() as s:
+        s.register_training(shape, P.pack(shape, Y.mlp_params(4, 16, hidden, 16)))
+        n = 0
+        while S.sif_train_op_name(s.ctx, s.train["handle"], n) is not None:
+            n += 1
+        x, t = Y.mlp_batch(0, 0, batch, 16, 16)
+        X, T = f32(x), f32(t)
+        torch.cuda.synchronize()
+        for k in range(1, 4):
+            s.step(X, T)
+            s.sync()
+            assert s.stats().train_kernels == k * n
+            assert s.stats().steps == k

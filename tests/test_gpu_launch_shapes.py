@@ -51,3 +51,20 @@ def test_training_kernels_are_counted(batch, hidden):
             s.sync()
             assert s.stats().train_kernels == k * n
             assert s.stats().steps == k
+
+
+@pytest.mark.parametrize("k_contig_a", [True, False])
+@pytest.mark.parametrize("k_contig_b", [True, False])
+@pytest.mark.parametrize("m,n,k", [(1, 1, 1), (16, 16, 16), (17, 33, 65), (31, 50, 3), (8, 256, 256), (512, 512, 64), (515, 517, 68), (513, 1030, 130)])
+def test_gemm_f32_tiles_and_remainders(m, n, k, k_contig_a, k_contig_b):
+    """Both tile sizes, with 16-byte loads (K contiguous and a multiple of 4) and without, at remainders of M, N and K.
+    Bound: an fp32 sum of k products in any order errs by at most (k + 4) 2^-24 times the sum of their magnitudes."""
+    rng = np.random.default_rng(m * 7 + n * 3 + k)
+    a, b = rng.standard_normal((m, k)).astype(np.float32), rng.standard_normal((n, k)).astype(np.float32)
+    A, Bt = f32(a if k_contig_a else a.T), f32(b if k_contig_b else b.T)
+    c = torch.full((m, n), float("nan"), device=DEV)
+    S.sif_k_gemm_f32(A, *((k, 1) if k_contig_a else (1, m)), Bt, *((1, k) if k_contig_b else (n, 1)), c, n, m, n, k)
+    torch.cuda.synchronize()
+    ref = a.astype(np.float64) @ b.astype(np.float64).T
+    bound = (k + 4) * 2.0 ** -24 * (np.abs(a).astype(np.float64) @ np.abs(b).astype(np.float64).T)
+    assert np.all(np.abs(up(c) - ref) <= bound)

@@ -27,6 +27,35 @@ bool gemm_big_tiles(const sif_gemm_args& a);
 sif_status launch_gemm_f32(const float* a, int64_t a_sm, int64_t a_sk, const float* b, int64_t b_sk, int64_t b_sn,
                            float* c, int64_t ldc, uint32_t m, uint32_t n, uint32_t k, uint32_t epi, const float* bias,
                            float* aux, hipStream_t s, const KCtl& ctl);
+// fp32 products with what the MLP's step does in the same launch (gemm_f32.hip).  Fields below the line are optional.
+struct F32Product {
+  const float* a; const float* b; float* c;
+  int64_t a_sm, a_sk, b_sk, b_sn, ldc;
+  uint32_t m, n, k, epi;
+  const float* bias;
+  float* aux;
+  uint32_t vec, tiles_n;             // filled in by launch_f32
+  // --
+  float* rowsum;                     // [m]: sums of A over k (the bias gradient that belongs to a weight gradient)
+  const float* target;               // mean squared error against the stored result (same layout as c):
+  float* diff; float* loss_part;     //   diff = (c - target) * inv_n, loss_part[tile] = sum of squares
+  float* update; float* rowsum_update;     // parameters that take a step -lr * result at once
+  float inv_n, lr;
+};
+struct F32Launch {
+  F32Product p[2];                   // p[1].c == nullptr: one product
+  uint32_t blocks[3];                // filled in by launch_f32
+  // loss = inv_n / 2 * the sum of loss_part (loss == nullptr: none)
+  uint32_t loss_parts;
+  const float* loss_part; float* loss; float loss_inv_n;
+  // p <- p - lr g for sgd_n parameters (sgd_p == nullptr: none)
+  float lr;
+  float* sgd_p; const float* sgd_g; uint64_t sgd_n;
+};
+F32Product f32_product_of(const float* a, int64_t a_sm, int64_t a_sk, const float* b, int64_t b_sk, int64_t b_sn, float* c, int64_t ldc,
+                          uint32_t m, uint32_t n, uint32_t k, uint32_t epi, const float* bias, float* aux);
+uint32_t f32_loss_parts(uint32_t m, uint32_t n);       // floats of loss_part an m x n result may need (zero where no tile writes)
+sif_status launch_f32(F32Launch l, hipStream_t s, const KCtl& ctl);
 // segs (optional): the output rows go to the segments' buffers instead of y
 struct RowSegs;
 sif_status launch_layernorm_fwd(const void* x, const void* g, const void* b, void* y, float* mean, float* rstd,

@@ -53,6 +53,34 @@ def test_training_kernels_are_counted(batch, hidden):
             assert s.stats().steps == k
 
 
+@pytest.mark.parametrize("bubble", [False, True])
+@pytest.mark.parametrize("d_in,hidden,d_out,batch", [(5, 7, 3, 1), (16, 17, 33, 15), (70, 530, 517, 600), (640, 512, 516, 512)])
+def test_mlp_step_of_shared_launches_matches_the_oracle(d_in, hidden, d_out, batch, bubble):
+    """The step with its update in the last gradient's launch (no bubble) and as a launch of its own (bubble), at sizes
+    of one tile, of remainders and of the wide tile; three steps, tolerances of the other fp32 model tests."""
+    shape = mlp_shape(d_in, hidden, d_out, batch)
+    p0 = Y.mlp_params(6, d_in, hidden, d_out)
+    p0["b1"], p0["b2"] = p0["b1"] + 0.01, p0["b2"] - 0.02
+    ref = {k: v.astype(np.float64) for k, v in p0.items()}
+    with Session() as s:
+        s.register_training(shape, P.pack(shape, p0), par_mode=S.SIF_PAR_FIXED if bubble else S.SIF_PAR_NONE, lr=0.05,
+                            fixed_bubble_ns=50_000 if bubble else 0)
+        loss = torch.zeros(1, device=DEV)
+        for step in range(3):
+            x, t = Y.mlp_batch(1, step, batch, d_in, d_out)
+            X, T = f32(x), f32(t)
+            torch.cuda.synchronize()
+            s.step(X, T, loss)
+            s.sync()
+            rl, ref, rg = OM.mlp_train_step(ref, x, t, 0.05)
+            assert abs(loss.item() - rl) <= 1e-4 * abs(rl), step
+            got_g = P.unpack(shape, up(s.train_tensor("grads", dtype=torch.float32)))
+            got_p = P.unpack(shape, up(s.train["master"]))
+            for k in ref:
+                assert_f32_close(got_g[k], rg[k], f"step {step} grad {k}")
+                assert_f32_close(got_p[k], ref[k], f"step {step} param {k}", 1e-5)
+
+
 @pytest.mark.parametrize("k_contig_a", [True, False])
 @pytest.mark.parametrize("k_contig_b", [True, False])
 @pytest.mark.parametrize("m,n,k", [(1, 1, 1), (16, 16, 16), (17, 33, 65), (31, 50, 3), (8, 256, 256), (512, 512, 64), (515, 517, 68), (513, 1030, 130)])

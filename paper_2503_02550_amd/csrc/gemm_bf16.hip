@@ -2,30 +2,36 @@
 //
 //   C[M,N] = alpha * sum_k A(m,k) B(k,n)   (+ bias, GELU, residual, GELU' multiply)
 //
-// One kernel serves every dense contraction of the training step and of the inference forward pass (the
+// These kernels serve every dense contraction of the training step and of the inference forward pass (the
 // "kernels issued by the training instance" and the inference kernels the Kernel Barrier releases, Sec. 3.1):
 // forward products (A [M][K], B [N][K]), data gradients (B [K][N]), weight gradients (A [K][M], B [K][N]) and
 // the per-head attention products via two batch strides.
 //
-// Tiling: block tile BM x BN, K step 64, WM x WN wavefronts, each owning a (BM/WM) x (BN/WN) tile as a grid of
-// v_mfma_f32_32x32x16_bf16 accumulators.  128x128 with 2x2 wavefronts (64x64 each), two blocks per CU, is the
-// working configuration; 256x256 with 2x4 wavefronts (128x64 each: six operand reads from LDS per eight MFMAs
-// instead of eight, half the global fetches per MFMA), one block per CU, takes over where a fitted timing model
-// says so (many tiles in whole rounds, or a long K).  Operand tiles are staged through LDS with K contiguous (unpadded rows of 128 bytes, XOR-swizzled
-// in 16-byte chunks so that reads and writes spread over the banks); an operand whose memory layout has the other
-// dimension contiguous is staged as it lies and transposed by the LDS read itself (ds_read_b64_tr_b16).  Interior
-// tiles are fetched from global memory straight into LDS, tile t+1 while tile t is multiplied; tiles on a ragged
-// edge of the 128x128 configuration go through registers (two K steps of prefetch) so that they can be zero-filled.
+// Every wavefront owns a grid of v_mfma_f32_32x32x16_bf16 accumulators; operand tiles, 64 k deep, travel from global
+// memory straight into LDS (buffer_load_dwordx4 ... lds) and from there into MFMA operand registers.  LDS holds an
+// operand as it lies in memory: rows of 64 k (128 bytes, XOR-swizzled in 16-byte chunks so that reads spread over the
+// banks) or, where the other dimension is contiguous, k-rows that the LDS read itself transposes (ds_read_b64_tr_b16).
 //
-// What the main loop waits for is neither the MFMA units nor LDS but the operand fetches: a CU sustains about 28 bytes
-// per cycle of loads that miss its L1 (measured; whatever their destination), a 256x256 tile needs 31 bytes per cycle
-// at full MFMA rate and a 128x128 tile twice that.  Hence the large tile wherever it fills the chip, fetches that hand
-// over 32-bit offsets (buffer loads), and result stores that do not claim L2 lines the operand panels are reused from.
+// Two kernels, chosen by a model of their times (gemm_choose):
+//   gemm_ring_kernel   one tile per block, a ring of two to four K steps in LDS.  Tiles from 32x64 (a handful of rows)
+//                      over 64x64, 128x64 and 128x128 to 256x128, so that a product of any size finds one that
+//                      spreads it over the chip.
+//   gemm_pp_kernel     256x256 tiles, persistent blocks, the two wavefronts of a SIMD alternate between memory phases
+//                      and matrix phases: the fewest bytes per product, for what fills the chip with such tiles.
 //
-// Results depend neither on the grid nor on the tile configuration: each output element is reduced over K in one
-// fixed order (ascending, 16 at a time) by one wavefront, so launching a row range of the same problem, or the other
-// configuration, gives bit-identical values.
+// What a K step costs, measured: a compute unit takes in about 65 bytes/ns of fetches when its wavefronts wait for all
+// of them at a barrier and 100 when fetches stay in flight across it; a wavefront issues in order, so everything that
+// is not an MFMA - LDS reads, fetches, address arithmetic, branches - delays the MFMAs behind it unless it stands
+// between them.  Hence: no branch and no address arithmetic in the steady part of a loop (the ring's slots are constants
+// of an unrolled body), fragments of the next K step read between the MFMAs of this one, fetches waited for by count.
+// (Two K steps in LDS, waited for as a whole, were 4096 x 768 x 3072: 37 us, 77 x 768 x 3072: 23 us, 8192 x 768 x 3072:
+// 47 us, 8192 x 2048 x 4096 as a weight gradient: 135 us; now 23, 7.2, 38 and 102.)
+//
+// Results depend neither on the grid nor on the tile: each output element is reduced over K in one fixed order
+// (ascending, 16 at a time) by one wavefront, so launching a row range of the same problem, or another configuration,
+// gives bit-identical values.
 #include <algorithm>
+#include <math.h>
 
 #include "common.h"
 #include "specinf.h"
@@ -37,6 +43,8 @@ constexpr int BK = 64;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 // 16 bytes of a result, stored with the non-temporal hint.  A product's output is written once and read by a later
 // kernel, and the chip's CUs write their tiles in bursts that exceed what the L2 takes in at once: stores that do not
@@ -46,19 +54,19 @@ __device__ __forceinline__ void store_result16(void* p, const uint4& v) {
   const u32x4 x = {v.x, v.y, v.z, v.w};
   __builtin_nontemporal_store(x, reinterpret_cast<u32x4*>(p));
 }
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 struct GemmP {
   const bf16_t* a; const bf16_t* b; void* c; const bf16_t* bias; const void* res; bf16_t* aux;
   uint32_t m, n, k, lda, ldb, ldc, epi, k_causal, batch_inner, tiles_m, tiles_n, k_limit;
   long long a_so, a_si, b_so, b_si, c_so, c_si;
   float alpha;
-  // a launch over several products at once (128x128 tiles, no batch): `group` points to their records in device memory,
-  // each with the number of the launch's first block that works on it (a multiple of 8)
+  // a launch over several products at once (no batch): `group` points to their records in device memory, each with the
+  // number of the launch's first block that works on it (a multiple of 8)
   const GemmP* group;
   uint32_t group_n, tile_base;
 };
 
+// ---------------------------------------------------------------------------------------------- operands in LDS
 // LDS tile: rows x 64 k (bf16), 128 bytes per row = eight 16-byte chunks, no padding.  Chunk c of row r
 // lives at chunk position c ^ key(r).  The key makes eight consecutive rows use eight different chunk positions
 // (conflict-free 16-byte reads with 32 banks) and sixteen consecutive rows sixteen different (row parity, position)
@@ -67,20 +75,19 @@ __device__ __forceinline__ uint32_t swz_key(uint32_t row) { return (row & 7u) ^ 
 __device__ __forceinline__ uint32_t lds_off(uint32_t row, uint32_t chunk) { return row * BK + ((chunk ^ swz_key(row)) << 3); }
 
 // A K-major operand (memory [k][row]) is staged as it lies in memory: LDS tile [64 k][ROWS], 2*ROWS bytes per k,
-// the 64-byte segments (32 rows) of k-row k stored at segment position seg ^ (k % 4).  The MFMA operand - eight
-// consecutive k for one row per lane - is then fetched with the transposing LDS read of gfx950
-// (ds_read_b64_tr_b16): within each group of 16 lanes, source lane s supplies the address of four consecutive rows
-// at k = k0 + s/4, rows r0 + 4*(s%4).., and lane i receives rows r0 + i at k0..k0+3.  Two such reads make one
-// operand; the four k-rows a half-wavefront touches lie in four different 64-byte bank groups.
+// the 64-byte segments (32 rows) of k-row k stored at segment position seg ^ (k % 4) (k % 2 with two segments, none to
+// choose from with one).  The MFMA operand - eight consecutive k for one row per lane - is then fetched with the
+// transposing LDS read of gfx950 (ds_read_b64_tr_b16): within each group of 16 lanes, source lane s supplies the
+// address of four consecutive rows at k = k0 + s/4, rows r0 + 4*(s%4).., and lane i receives rows r0 + i at k0..k0+3.
+// Two such reads make one operand; the four k-rows a half-wavefront touches lie in different 64-byte bank groups.
 typedef short short4_lds __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ uint32_t kmajor_off(uint32_t k, uint32_t row, uint32_t rows_pitch) {
-  return k * rows_pitch + ((((row >> 5) ^ (k & 3u)) << 5) | (row & 31u));
-}
+template <int ROWS>
+__device__ __forceinline__ uint32_t kmajor_key(uint32_t k) { return k & (ROWS >= 128 ? 3u : ROWS / 32 - 1u); }
 template <int ROWS>
 __device__ __forceinline__ bf16x8 kmajor_frag(const bf16_t* tile, uint32_t rowbase32, uint32_t kbase8) {
   // rowbase32: first of the 32 operand rows (a multiple of 32); kbase8: first of this lane half's eight k
   const uint32_t lane = threadIdx.x & 63, s = lane & 15, sw = s >> 2;
-  const bf16_t* p = tile + (kbase8 + sw) * ROWS + ((((rowbase32 >> 5) ^ sw) << 5) | (((lane >> 4) & 1u) * 16 + 4 * (s & 3u)));
+  const bf16_t* p = tile + (kbase8 + sw) * ROWS + ((((rowbase32 >> 5) ^ kmajor_key<ROWS>(sw)) << 5) | (((lane >> 4) & 1u) * 16 + 4 * (s & 3u)));
   typedef __attribute__((address_space(3))) short4_lds* lds_ptr;
   const short4_lds lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)p);
   const short4_lds hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + 4 * ROWS));
@@ -88,105 +95,81 @@ __device__ __forceinline__ bf16x8 kmajor_frag(const bf16_t* tile, uint32_t rowba
   const short8_v v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
   return __builtin_bit_cast(bf16x8, v);
 }
-
-// How the threads of a block cover one operand tile (ROWS rows x 64 k), four 16-byte vectors each
-// (vector v = thread + i * THREADS):
-//   LAYOUT 0: memory [row][k]: row v/8, k chunk v%8.
-//   LAYOUT 1: memory [k][row]: k-row v/(ROWS/8), row chunk v%(ROWS/8).
-// Loads one operand tile into registers.  Vectors outside the logical extents read as zero.  The loads are
-// unconditional (an out-of-range vector reads the operand's first element instead and is zeroed afterwards), so
-// that they can be issued back to back and waited for selectively.
-template <int LAYOUT, int THREADS, int ROWS>
-__device__ __forceinline__ uint32_t load_tile(uint4 (&r)[4], const bf16_t* __restrict__ base, uint32_t ld, uint32_t row0,
-                                              uint32_t rows, uint32_t k0, uint32_t k_end) {
-  bool ok[4];
-  const bf16_t* ptr[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const uint32_t v = threadIdx.x + i * THREADS;
-    if (LAYOUT == 0) {
-      const uint32_t rr = row0 + (v >> 3), kk = k0 + (v & 7) * 8;
-      ok[i] = rr < rows && kk < k_end;
-      ptr[i] = ok[i] ? base + (size_t)rr * ld + kk : base;
-    } else {
-      const uint32_t rr = row0 + (v % (ROWS / 8)) * 8, kk = k0 + v / (ROWS / 8);
-      ok[i] = rr < rows && kk < k_end;
-      ptr[i] = ok[i] ? base + (size_t)kk * ld + rr : base;
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) r[i] = *reinterpret_cast<const uint4*>(ptr[i]);
-  // bit i set = vector i is inside the operand; applied when the registers are written to LDS, not here, so that
-  // nothing waits for the loads before their data is needed
-  return (ok[0] ? 1u : 0u) | (ok[1] ? 2u : 0u) | (ok[2] ? 4u : 0u) | (ok[3] ? 8u : 0u);
+// 32 rows from `rowbase32` (a multiple of 32), k slice ks of 16, as an MFMA operand
+template <int LAYOUT, int ROWS>
+__device__ __forceinline__ bf16x8 operand_frag(const bf16_t* tile, uint32_t rowbase32, int ks) {
+  const uint32_t lane = threadIdx.x & 63, kh = lane >> 5;
+  if (LAYOUT == 0) return *reinterpret_cast<const bf16x8*>(tile + lds_off(rowbase32 + (lane & 31), ks * 2 + kh));
+  return kmajor_frag<ROWS>(tile, rowbase32, ks * 16 + kh * 8);
 }
 
-template <int LAYOUT, int THREADS, int ROWS>
-__device__ __forceinline__ void store_tile(bf16_t* lds, const uint4 (&rin)[4], uint32_t okmask) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const uint32_t keep = (okmask >> i) & 1u ? 0xFFFFFFFFu : 0u;       // folds away for a constant all-ones mask
-    const uint4 r = make_uint4(rin[i].x & keep, rin[i].y & keep, rin[i].z & keep, rin[i].w & keep);
-    const uint32_t v = threadIdx.x + i * THREADS;
-    if (LAYOUT == 0) *reinterpret_cast<uint4*>(lds + lds_off(v >> 3, v & 7)) = r;
-    else *reinterpret_cast<uint4*>(lds + kmajor_off(v / (ROWS / 8), (v % (ROWS / 8)) * 8, ROWS)) = r;
-  }
+// ---------------------------------------------------------------------------------------------- fetches
+// One fetch instruction writes the 64 lanes' 16 bytes to consecutive LDS addresses from the scalar M0 on, 1 KB per
+// wavefront, so a lane's place in the tile is fixed and the swizzle is applied to what it fetches.  The instruction is
+// written as assembly: the compiler would otherwise make every LDS read wait for every fetch in flight.  `volatile` and
+// "memory" keep it in its place between the barriers.
+constexpr uint32_t kOutside = 0x80000000u;      // an offset beyond the resource's extent: the lane's 16 bytes are zeros
+__device__ __forceinline__ void fetch16(const i32x4& rsrc, uint32_t voff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc) : "memory");
 }
-
-// Interior tiles go from global memory straight into LDS (buffer_load_dwordx4 ... lds: no staging registers, no LDS
-// store instructions; the buffer form, whose lanes hand over a 32-bit offset instead of a 64-bit address, runs the
-// products 2-5 % faster than global_load_lds_dwordx4).  One such instruction writes the 64 lanes' 16 bytes to consecutive LDS addresses, 1 KB per
-// wavefront, so the lane's position in the tile is fixed and the swizzle is applied to what it fetches: lane l of
-// wavefront w, instruction i covers
-//   LAYOUT 0: tile row 32*i + 8*w + l/8, chunk position l%8 = logical chunk (l%8) ^ key(row)
-//   LAYOUT 1: k-row 16*i + 4*w + l/16, 16-byte unit l%16 = segment position (l%16)/4 -> logical segment ^ (k%4)
-// (with 256 threads; 512 threads cover twice the rows or k-rows per instruction).
-typedef __attribute__((address_space(3))) void* lds_void_ptr;
-template <int LAYOUT, int ROWS, int THREADS>
-struct DmaStream {
-  static constexpr int NV = ROWS * 8 / THREADS;       // 16-byte vectors per thread and tile
-  const char* tile;
-  size_t step;
+// a buffer resource over the operand from `base` on: raw bytes, extent 2 GB (what a lane's offset within a tile can be,
+// see gemm_fill), so that only a 32-bit offset per lane travels to the memory pipeline
+__device__ __forceinline__ i32x4 operand_rsrc(uint64_t base) {
+  i32x4 r;
+  r[0] = __builtin_amdgcn_readfirstlane((uint32_t)base);
+  r[1] = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
+  r[2] = (int)kOutside;
+  r[3] = 0x00020000;
+  return r;
+}
+// What the threads of a block fetch of one operand tile of ROWS rows and 64 k; instruction i, thread t covers
+//   LAYOUT 0 (memory [row][k]): LDS row (i*THREADS + t) / 8, chunk position t % 8 = logical chunk (t % 8) ^ key(row)
+//   LAYOUT 1 (memory [k][row]): k-row (i*THREADS + t) / (ROWS/8), 16-byte unit t % (ROWS/8), segments swizzled with k
+// The tile may be part PART of a larger one: LDS row r is row (r / G) * GS + PART * G + r % G of it.  Rows past the
+// operand's last one read as zeros, and so does what lies past the end of K in a last, ragged step (issue_last).
+template <int LAYOUT, int ROWS, int THREADS, int G, int GS, int PART>
+struct TileFetch {
+  static_assert(ROWS * 8 % THREADS == 0, "whole 16-byte vectors per thread and tile");
+  static constexpr int NV = ROWS * 8 / THREADS;
   uint32_t voff[NV];
-  // rows >= `rows` (a ragged last tile) fetch the tile's first row instead: what they produce is never stored
-  __device__ __forceinline__ DmaStream(const bf16_t* b, uint32_t ld, uint32_t row0, uint32_t rows, uint32_t k_begin) {
-    if (LAYOUT == 0) {
-      tile = (const char*)(b + (size_t)row0 * ld + k_begin);
-      step = BK * sizeof(bf16_t);
+  __device__ __forceinline__ static uint32_t unit(int i) { return i * THREADS + threadIdx.x; }
+  __device__ __forceinline__ static uint32_t row_of(uint32_t r) { return (r / G) * GS + PART * G + r % G; }
+  __device__ __forceinline__ static uint32_t k_of(int i) {      // first k of the 16 bytes
+    const uint32_t u = unit(i);
+    return LAYOUT == 0 ? ((u & 7u) ^ swz_key(u >> 3)) * 8 : u / (ROWS / 8);
+  }
+  __device__ __forceinline__ void init(uint32_t ld, uint32_t rows_left) {
 #pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        const uint32_t r = i * (THREADS / 8) + (threadIdx.x >> 3), c = (threadIdx.x & 7u) ^ swz_key(r);
-        voff[i] = ((row0 + r < rows ? r : 0u) * ld + c * 8) * (uint32_t)sizeof(bf16_t);
-      }
-    } else {
-      constexpr uint32_t UR = ROWS / 8;          // 16-byte units per k-row
-      tile = (const char*)(b + (size_t)k_begin * ld + row0);
-      step = (size_t)BK * ld * sizeof(bf16_t);
-#pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        const uint32_t k = i * (THREADS / UR) + threadIdx.x / UR, u = threadIdx.x % UR, seg = (u >> 2) ^ (k & 3u);
-        const uint32_t r = seg * 32 + (u & 3u) * 8;
-        voff[i] = (k * ld + (row0 + r < rows ? r : 0u)) * (uint32_t)sizeof(bf16_t);
+    for (int i = 0; i < NV; ++i) {
+      const uint32_t u = unit(i), k = k_of(i);
+      if (LAYOUT == 0) {
+        const uint32_t r = row_of(u >> 3);
+        voff[i] = r < rows_left ? (r * ld + k) * 2u : kOutside;
+      } else {
+        const uint32_t q = u % (ROWS / 8), r = row_of(((q >> 2) ^ kmajor_key<ROWS>(k)) * 32 + (q & 3u) * 8);
+        voff[i] = r < rows_left ? (k * ld + r) * 2u : kOutside;
       }
     }
   }
-  // fetches the next tile into `stage` (a whole tile buffer of ROWS x 64 elements)
-  __device__ __forceinline__ void next(bf16_t* stage) {
-    // the LDS address of a fetch is taken from a scalar register: say that the wavefront number is uniform
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // a buffer resource over the tile's memory (raw bytes, no stride; the extent is left open: every offset below was
-    // formed from a row and a k inside the operand) - only a 32-bit offset per lane then travels to the memory pipeline
-#if defined(__HIP_DEVICE_COMPILE__)      // the resource type exists in the device pass only (with it in the host pass the
-                                         // compiler drops, without a word, the host stubs of most instantiations)
-    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)tile, (short)0, -1, 0x00020000);
-#pragma unroll
-    for (int i = 0; i < NV; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_ptr)(stage + i * (THREADS * 8) + wave * 512), 16, voff[i], 0, 0, 0);
-#endif
-    tile += step;
+  __device__ __forceinline__ void issue(const i32x4& rsrc, uint32_t lds, uint32_t wave, int i) const {
+    fetch16(rsrc, voff[i], lds + i * (THREADS * 16) + wave * 1024);
+  }
+  __device__ __forceinline__ void issue_last(const i32x4& rsrc, uint32_t lds, uint32_t wave, int i, uint32_t k_left) const {
+    fetch16(rsrc, k_of(i) < k_left ? voff[i] : kOutside, lds + i * (THREADS * 16) + wave * 1024);
   }
 };
+// waits until at most N vector memory operations of this wavefront are outstanding (they complete in order)
+template <int N>
+__device__ __forceinline__ void wait_vm() { __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14)); }
+__device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(0xC07F); }
+// a block barrier that waits for nothing by itself (the fences only keep the compiler from moving accesses across it)
+__device__ __forceinline__ void barrier_only() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
 
+// ---------------------------------------------------------------------------------------------- epilogue
 // Epilogue of eight consecutive columns n..n+7 of row m (both inside the result): scale, bias, GELU, GELU' multiply,
 // residual, store; `vec` says that every access may be a 16-byte vector, and then b holds the eight bias values,
 // aux_q the eight auxiliary values (GELU_GRAD) and res_q the eight bf16 residual values.
@@ -245,123 +228,121 @@ __device__ __forceinline__ void gemm_epilogue8(const GemmP& p, size_t c_off, uin
   }
 }
 
-// Epilogue of one wavefront's (TI*32) x 64 part of an output tile, first row mw, first column nw.  The accumulators
-// pass, 32 rows at a time, through a staging area `sW` of the wavefront's own in LDS (8 KB) so that every global
-// access of the epilogue - bias, residual, auxiliary tensor, result - is a 16-byte vector along a row; no block-wide
-// barrier is needed.  Accumulator element r of lane l is row (r/4)*8 + (l/32)*4 + r%4, column l%32 of its 32x32
-// tile.  Chunk c (four floats) of staging row r lives at c ^ (8*((r/4)%2) | r%2): the two half-wavefronts of a
-// store and the eight rows of a load then fall on different banks.  bias_q: the bias of columns nw + 8*(l%8)...
-template <int TI, int TJ>
+// Epilogue of one wavefront's (TI*32) x (TJ*32) part of an output tile, first row mw, first column nw.  The accumulators
+// pass, SR rows (staged as fp32) or 2*SR rows (staged as bf16) at a time, through SR*TJ*128 bytes of LDS of the
+// wavefront's own so that every global access of the epilogue - bias, residual, auxiliary tensor, result - is a 16-byte
+// vector along a row; no block-wide barrier is needed.  Accumulator element r of lane l is row (r/4)*8 + (l/32)*4 + r%4,
+// column l%32 of its 32x32 tile.  bias_q: the bias of columns nw + 8*(l % (TJ*4))...
+template <int TI, int TJ, int SR>
 __device__ __forceinline__ void gemm_store_tile(const GemmP& p, floatx16 (&acc)[TI][TJ], float* sW, uint32_t mw, uint32_t nw, size_t c_off, const uint4& bias_q) {
-  constexpr int WCOLS = TJ * 32;
-  const uint32_t lane = threadIdx.x & 63;
+  constexpr int W = TJ * 32, CPR = W / 8;                 // columns, 8-column chunks per row
+  const uint32_t lane = threadIdx.x & 63, hh = lane >> 5;
   const bool vec_ok = (p.n & 7) == 0 && ((c_off & 7) == 0);
-  const float bias8[8] = {bflo(bias_q.x), bfhi(bias_q.x), bflo(bias_q.y), bfhi(bias_q.y), bflo(bias_q.z), bfhi(bias_q.z), bflo(bias_q.w), bfhi(bias_q.w)};
   // Epilogues that read nothing but the bias (plain, bias, bias + GELU without the pre-activation output) are
   // finished in the accumulator layout, where a lane's column is fixed, and staged as bf16: two vertically adjacent
-  // results share a 32-bit word, the staging area is [16 row pairs][64 columns] words, half the LDS traffic of the
+  // results share a 32-bit word, the staging area is [SR row pairs][W] words, half the LDS traffic of the
   // fp32 staging below.  A lane then reads eight words = eight columns of two rows, separates the rows with byte
   // permutes and stores two 16-byte row vectors.  The arithmetic per element is the same as in gemm_epilogue8.
+  // (Row pairs of the two half-wavefronts differ by two: their columns are swapped in halves, so that they fall on
+  // different banks.)
   const bool packed = vec_ok && (p.epi & (SIF_EPI_RESIDUAL | SIF_EPI_GELU_GRAD | SIF_EPI_OUT_F32)) == 0 &&
                       !((p.epi & SIF_EPI_GELU) && p.aux != nullptr);
   if (packed) {
     uint32_t* sP = reinterpret_cast<uint32_t*>(sW);
+    constexpr int PR = SR < 16 ? SR : 16, PASSES = 16 / PR, RE = 16 / PASSES;      // row pairs and accumulator elements per pass
     float bcol[TJ];
 #pragma unroll
     for (int j = 0; j < TJ; ++j) {
       const uint32_t n = nw + j * 32 + (lane & 31);
       bcol[j] = (p.bias != nullptr && n < p.n) ? bf2f(p.bias[n]) : 0.f;
     }
-    const uint32_t hh = lane >> 5;
 #pragma unroll
-    for (int i = 0; i < TI; ++i) {
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+      for (int ps = 0; ps < PASSES; ++ps) {
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+#pragma unroll
+          for (int r = ps * RE; r < (ps + 1) * RE; r += 2) {
+            float x0 = acc[i][j][r] * p.alpha + bcol[j], x1 = acc[i][j][r + 1] * p.alpha + bcol[j];
+            if (p.epi & SIF_EPI_GELU) { x0 = gelu_fast(x0); x1 = gelu_fast(x1); }
+            const uint32_t pr = (r >> 2) * 4 + hh * 2 + ((r & 3) >> 1) - ps * PR, col = (j * 32 + (lane & 31)) ^ (hh * (W / 2));
+            sP[pr * W + col] = pack_bf2(x0, x1);
+          }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int it = 0; it < (PR * CPR + 63) / 64; ++it) {
+          const uint32_t item = lane + it * 64, pr = item / CPR, c8 = item % CPR;     // PR row pairs x CPR chunks of 8 columns
+          if (PR * CPR >= 64 || item < PR * CPR) {
+            const uint32_t pos = (c8 ^ (((pr >> 1) & 1u) * (CPR / 2))) * 8;
+            const uint4 w0 = *reinterpret_cast<const uint4*>(sP + pr * W + pos), w1 = *reinterpret_cast<const uint4*>(sP + pr * W + pos + 4);
+            const uint4 even = make_uint4(__builtin_amdgcn_perm(w0.y, w0.x, 0x05040100), __builtin_amdgcn_perm(w0.w, w0.z, 0x05040100),
+                                          __builtin_amdgcn_perm(w1.y, w1.x, 0x05040100), __builtin_amdgcn_perm(w1.w, w1.z, 0x05040100));
+            const uint4 odd = make_uint4(__builtin_amdgcn_perm(w0.y, w0.x, 0x07060302), __builtin_amdgcn_perm(w0.w, w0.z, 0x07060302),
+                                         __builtin_amdgcn_perm(w1.y, w1.x, 0x07060302), __builtin_amdgcn_perm(w1.w, w1.z, 0x07060302));
+            const uint32_t m = mw + i * 32 + 2 * (pr + ps * PR), n = nw + c8 * 8;
+            bf16_t* cp = reinterpret_cast<bf16_t*>(p.c) + c_off + (size_t)m * p.ldc + n;
+            if (n < p.n) {
+              if (m < p.m) store_result16(cp, even);
+              if (m + 1 < p.m) store_result16(cp + p.ldc, odd);
+            }
+          }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      }
+    return;
+  }
+  // fp32 staging: SR rows (of the tile's eight-row groups, SR/8 at a time).  Chunk c (four floats) of a staging row lives
+  // at c ^ key(row): the two half-wavefronts of a store and the eight rows of a load then fall on different banks.
+  const float bias8[8] = {bflo(bias_q.x), bfhi(bias_q.x), bflo(bias_q.y), bfhi(bias_q.y), bflo(bias_q.z), bfhi(bias_q.z), bflo(bias_q.w), bfhi(bias_q.w)};
+  constexpr int PASSES = 32 / SR, ITEMS = SR * CPR, ITS = (ITEMS + 63) / 64;
+  auto key = [](uint32_t row) { return (((row >> 2) & 1u) * (W / 8)) | (row & 1u); };
+#pragma unroll
+  for (int i = 0; i < TI; ++i)
+#pragma unroll
+    for (int ps = 0; ps < PASSES; ++ps) {
+      // what the epilogue reads from global memory for this pass is requested before the staging, not inside it
+      uint4 aux_q[ITS], res_q[ITS];
+#pragma unroll
+      for (int it = 0; it < ITS; ++it) {
+        const uint32_t ch = lane + it * 64, row = ch / CPR, c8 = ch % CPR;
+        const uint32_t m = mw + i * 32 + ps * SR + row, n = nw + c8 * 8;
+        aux_q[it] = make_uint4(0, 0, 0, 0); res_q[it] = make_uint4(0, 0, 0, 0);
+        if (vec_ok && m < p.m && n < p.n && (ITEMS >= 64 || ch < ITEMS)) {
+          const size_t idx = c_off + (size_t)m * p.ldc + n;
+          if (p.epi & SIF_EPI_GELU_GRAD) aux_q[it] = *reinterpret_cast<const uint4*>(p.aux + idx);
+          if ((p.epi & (SIF_EPI_RESIDUAL | SIF_EPI_OUT_F32)) == SIF_EPI_RESIDUAL) res_q[it] = *reinterpret_cast<const uint4*>(reinterpret_cast<const bf16_t*>(p.res) + idx);
+        }
+      }
 #pragma unroll
       for (int j = 0; j < TJ; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; r += 2) {
-          float x0 = acc[i][j][r] * p.alpha + bcol[j], x1 = acc[i][j][r + 1] * p.alpha + bcol[j];
-          if (p.epi & SIF_EPI_GELU) { x0 = gelu_fast(x0); x1 = gelu_fast(x1); }
-          const uint32_t pr = (r >> 2) * 4 + hh * 2 + ((r & 3) >> 1), col = (j * 32 + (lane & 31)) ^ (hh << 5);
-          sP[pr * WCOLS + col] = pack_bf2(x0, x1);
+        for (int r = ps * (SR / 2); r < (ps + 1) * (SR / 2); ++r) {
+          const uint32_t row = (r >> 2) * 8 + hh * 4 + (r & 3) - ps * SR, col = j * 32 + (lane & 31);
+          sW[row * W + ((((col >> 2) ^ key(row)) << 2) | (col & 3))] = acc[i][j][r];
         }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
 #pragma unroll
-      for (int it = 0; it < 2; ++it) {
-        const uint32_t item = lane + it * 64, pr = item >> 3, c8 = item & 7;     // 16 row pairs x 8 chunks of 8 columns
-        const uint32_t pos = (c8 ^ (((pr >> 1) & 1u) << 2)) * 8;
-        const uint4 w0 = *reinterpret_cast<const uint4*>(sP + pr * WCOLS + pos), w1 = *reinterpret_cast<const uint4*>(sP + pr * WCOLS + pos + 4);
-        const uint4 even = make_uint4(__builtin_amdgcn_perm(w0.y, w0.x, 0x05040100), __builtin_amdgcn_perm(w0.w, w0.z, 0x05040100),
-                                      __builtin_amdgcn_perm(w1.y, w1.x, 0x05040100), __builtin_amdgcn_perm(w1.w, w1.z, 0x05040100));
-        const uint4 odd = make_uint4(__builtin_amdgcn_perm(w0.y, w0.x, 0x07060302), __builtin_amdgcn_perm(w0.w, w0.z, 0x07060302),
-                                     __builtin_amdgcn_perm(w1.y, w1.x, 0x07060302), __builtin_amdgcn_perm(w1.w, w1.z, 0x07060302));
-        const uint32_t m = mw + i * 32 + 2 * pr, n = nw + c8 * 8;
-        bf16_t* cp = reinterpret_cast<bf16_t*>(p.c) + c_off + (size_t)m * p.ldc + n;
-        if (n < p.n) {
-          if (m < p.m) store_result16(cp, even);
-          if (m + 1 < p.m) store_result16(cp + p.ldc, odd);
+      for (int it = 0; it < ITS; ++it) {
+        const uint32_t ch = lane + it * 64, row = ch / CPR, c8 = ch % CPR;      // SR rows x CPR chunks of 8 columns
+        if (ITEMS >= 64 || ch < ITEMS) {
+          const float4 q0 = *reinterpret_cast<const float4*>(sW + row * W + (((2 * c8) ^ key(row)) << 2));
+          const float4 q1 = *reinterpret_cast<const float4*>(sW + row * W + (((2 * c8 + 1) ^ key(row)) << 2));
+          float v[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
+          const uint32_t m = mw + i * 32 + ps * SR + row, n = nw + c8 * 8;
+          if (m < p.m && n < p.n) gemm_epilogue8(p, c_off, m, n, v, bias8, vec_ok, aux_q[it], res_q[it]);
         }
       }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
     }
-  } else
-#pragma unroll
-  for (int i = 0; i < TI; ++i) {
-    // what the epilogue reads from global memory for this pass is requested before the staging, not inside it
-    uint4 aux_q[WCOLS / 16], res_q[WCOLS / 16];
-#pragma unroll
-    for (int it = 0; it < WCOLS / 16; ++it) {
-      const uint32_t ch = lane + it * 64, row = ch >> 3, c8 = ch & 7;
-      const uint32_t m = mw + i * 32 + row, n = nw + c8 * 8;
-      aux_q[it] = make_uint4(0, 0, 0, 0); res_q[it] = make_uint4(0, 0, 0, 0);
-      if (vec_ok && m < p.m && n < p.n) {
-        const size_t idx = c_off + (size_t)m * p.ldc + n;
-        if (p.epi & SIF_EPI_GELU_GRAD) aux_q[it] = *reinterpret_cast<const uint4*>(p.aux + idx);
-        if ((p.epi & (SIF_EPI_RESIDUAL | SIF_EPI_OUT_F32)) == SIF_EPI_RESIDUAL) res_q[it] = *reinterpret_cast<const uint4*>(reinterpret_cast<const bf16_t*>(p.res) + idx);
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < TJ; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const uint32_t row = (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3), col = j * 32 + (lane & 31);
-        sW[row * WCOLS + ((((col >> 2) ^ ((((row >> 2) & 1) << 3) | (row & 1))) << 2) | (col & 3))] = acc[i][j][r];
-      }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int it = 0; it < WCOLS / 16; ++it) {
-      const uint32_t ch = lane + it * 64, row = ch >> 3, c8 = ch & 7;      // 32 rows x 8 chunks of 8 columns
-      const uint32_t key = (((row >> 2) & 1) << 3) | (row & 1);
-      const float4 q0 = *reinterpret_cast<const float4*>(sW + row * WCOLS + (((2 * c8) ^ key) << 2));
-      const float4 q1 = *reinterpret_cast<const float4*>(sW + row * WCOLS + (((2 * c8 + 1) ^ key) << 2));
-      float v[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
-      const uint32_t m = mw + i * 32 + row, n = nw + c8 * 8;
-      if (m < p.m && n < p.n) gemm_epilogue8(p, c_off, m, n, v, bias8, vec_ok, aux_q[it], res_q[it]);
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-  }
 }
 
-// Scheduling pipeline of one K step, from MFMA number G on (NS slices of NM MFMAs): after each MFMA its share of the
-// next slice's ND LDS reads and of the step's FETCHES global -> LDS fetches.
+// ---------------------------------------------------------------------------------------------- tiles
 template <int V> struct Int { static constexpr int value = V; };
-template <int NM, int ND, int NS, int FETCHES, int G>
-__device__ __forceinline__ void sched_pipeline() {
-  if constexpr (G < NS * NM) {
-    constexpr int ks = G / NM, m = G % NM;
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    if constexpr (ks + 1 < NS) {
-      constexpr int d0 = (m * ND) / NM, d1 = ((m + 1) * ND) / NM;
-      if constexpr (d1 > d0) __builtin_amdgcn_sched_group_barrier(0x100, d1 - d0, 0);
-    }
-    constexpr int f0 = (G * FETCHES) / (NS * NM), f1 = ((G + 1) * FETCHES) / (NS * NM);
-    if constexpr (f1 > f0) __builtin_amdgcn_sched_group_barrier(0x010, f1 - f0, 0);
-    sched_pipeline<NM, ND, NS, FETCHES, G + 1>();
-  }
-}
 
 // Block -> tile.  Consecutive workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2.  Every XCD
 // gets a contiguous run of tiles (tile number pid belongs to XCD pid % 8 and is the (pid / 8)-th of its run), and each
@@ -388,81 +369,270 @@ __device__ __forceinline__ uint32_t gemm_steal_tile(StreamRec* rec, uint32_t tot
   return kNone;
 }
 
-// Registers: two wavefronts per SIMD may take 256 of its 512 each, and the 256x256 configuration would.  It is held to
-// 248 (the attribute counts in pairs): a one-wavefront kernel that sits on a CU for the length of a bubble (the
-// training stream's wait) then still fits beside a block, which otherwise stays off that CU, and the tiles of 255 CUs
-// end a round later (65536 x 768 x 768: 92 -> 153 us beside such a wavefront, 92 with the limit).
-template <int ALAY, int BLAY, int BM, int BN, int WM, int WN, bool EDGE, bool GROUPED = false>
-__global__ __launch_bounds__(64 * WM * WN, BM == 128 ? 2 : 1) __attribute__((amdgpu_num_vgpr(124))) void gemm_bf16_kernel(GemmP p_in, KCtl ctl) {
-  static_assert(!GROUPED || EDGE, "several products in one launch: one block per tile");
-  // (an instantiation of its own for launches over several products: in the others the product's record stays the
+// The product of a launch over several that block `pid` works on; its record, the same for every lane, goes word by word
+// into scalar registers.
+__device__ __forceinline__ void gemm_load_record(GemmP& p, const GemmP* group, uint32_t group_n, uint32_t pid) {
+  uint32_t g = 0;
+  while (g + 1 < group_n && pid >= group[g + 1].tile_base) ++g;
+  static_assert(sizeof(GemmP) % 4 == 0, "copied as 32-bit words");
+  uint32_t words[sizeof(GemmP) / 4];
+  const uint32_t* src = reinterpret_cast<const uint32_t*>(group + g);
+#pragma unroll
+  for (uint32_t w = 0; w < sizeof(GemmP) / 4; ++w) words[w] = __builtin_amdgcn_readfirstlane(src[w]);
+  __builtin_memcpy(&p, words, sizeof(GemmP));
+}
+
+// One tile per block.  A ring of ST K steps in LDS; a wavefront keeps the fragments of two steps in registers, so that
+// those of step t+1 are read, slice by slice, between the MFMAs of step t.  The steady part is a body of whole turns of
+// the ring (every LDS address a constant); what is left - the last ST and a few steps, a ragged last step among them -
+// runs through the same step with the ring's position and its conditions worked out.
+//   LAG = 0: step t's slot is fetched into again in step t, once all wavefronts have their fragments of t in registers
+//            (they wait for these before the barrier): ST steps in flight.
+//   LAG = 1: one step later; nothing is waited for before the barrier but the fetches of step t+1: ST - 1 in flight.
+template <int ALAY, int BLAY, int BM, int BN, int WM, int WN, int ST, int LAG, int OCC, bool GROUPED = false>
+__global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_ring_kernel(GemmP p_in, KCtl ctl) {
+  // (a launch over several products has an instantiation of its own: in the others the product's record stays the
   // kernel argument, in scalar registers)
   GemmP p = p_in;
-  constexpr int THREADS = 64 * WM * WN, TI = BM / (WM * 32), TJ = BN / (WN * 32), WCOLS = TJ * 32;
-  static_assert((BM * 8) % THREADS == 0 && (BN * 8) % THREADS == 0, "whole 16-byte vectors per thread and operand tile");
-  static_assert(!EDGE || (BM * 8 == 4 * THREADS && BN * 8 == 4 * THREADS), "the register path moves four vectors per thread and operand");
-  constexpr int FETCHES = (BM + BN) * 8 / THREADS;      // global -> LDS fetches per thread and K step
-  static_assert(WCOLS == 64, "the epilogue staging is laid out for 64 columns per wavefront");
-  // two tile buffers per operand, as four objects so that the compiler can tell a buffer being filled from the one being read
-  __shared__ __align__(1024) bf16_t sA0[BM * BK];
-  __shared__ __align__(1024) bf16_t sA1[BM * BK];
-  __shared__ __align__(1024) bf16_t sB0[BN * BK];
-  __shared__ __align__(1024) bf16_t sB1[BN * BK];
+  constexpr int THREADS = 64 * WM * WN, TI = BM / (WM * 32), TJ = BN / (WN * 32), AHEAD = LAG ? ST - 1 : ST;
+  constexpr uint32_t SA = BM * BK, SB = BN * BK, STAGE = SA + SB;      // elements
+  typedef TileFetch<ALAY, BM, THREADS, BM, BM, 0> FetchA;
+  typedef TileFetch<BLAY, BN, THREADS, BN, BN, 0> FetchB;
+  constexpr int FA = FetchA::NV, F = FA + FetchB::NV;                  // fetches per thread and K step
+  constexpr int SR = ST * STAGE * 2 >= WM * WN * TJ * 128 * 32 ? 32 : 16;      // staging rows of the epilogue
+  static_assert(ST * STAGE * 2 >= WM * WN * TJ * 128 * SR, "the epilogue is staged in the ring");
+  static_assert(F * (AHEAD - 1) < 64, "the wait counts 63 operations");
+  __shared__ __align__(1024) bf16_t lds[ST * STAGE];
   if (!kernel_begin(ctl)) { kernel_end(ctl, false); return; }
+  if constexpr (GROUPED) gemm_load_record(p, p_in.group, p_in.group_n, blockIdx.x);
 
-  if constexpr (GROUPED) {                     // several products in one launch: which one is this block's
-    uint32_t g = 0;
-    while (g + 1 < p_in.group_n && blockIdx.x >= p_in.group[g + 1].tile_base) ++g;
-    // the record is the same for every lane: word by word into scalar registers
-    static_assert(sizeof(GemmP) % 4 == 0, "copied as 32-bit words");
-    uint32_t words[sizeof(GemmP) / 4];
-    const uint32_t* src = reinterpret_cast<const uint32_t*>(p_in.group + g);
-#pragma unroll
-    for (uint32_t w = 0; w < sizeof(GemmP) / 4; ++w) words[w] = __builtin_amdgcn_readfirstlane(src[w]);
-    __builtin_memcpy(&p, words, sizeof(GemmP));
-  }
-  const uint32_t total_tiles = p.tiles_m * p.tiles_n;
-  auto tile_of = [&](uint32_t pid, uint32_t& tm, uint32_t& tn) { gemm_tile_of(p, total_tiles, pid, tm, tn); };
+  const uint32_t total_tiles = p.tiles_m * p.tiles_n, pid = blockIdx.x - p.tile_base;
   const uint32_t bo = blockIdx.z / p.batch_inner, bi = blockIdx.z % p.batch_inner;
+  uint32_t tile_m = 0, tile_n = 0;
+  if (pid < total_tiles) gemm_tile_of(p, total_tiles, pid, tile_m, tile_n);
+  const uint32_t m0 = tile_m * BM, n0 = tile_n * BN;
+  // (blocks of a group beyond their product's tiles have nothing to do, and of a causal product those whose 128x128 tile
+  // lies above the diagonal)
+  if (pid >= total_tiles || ((p.epi & SIF_EPI_CAUSAL_SKIP) && n0 / 128 > (m0 + BM - 1) / 128)) { kernel_end(ctl, true); return; }
+
+  uint32_t k_begin = 0, k_end = p.k;
+  if (p.k_limit != 0) k_end = min(p.k, p.k_limit - bi * p.k);      // slices of one long K: the last may be shorter
+  if (p.k_causal == 1) k_end = min(p.k, m0 + BM);
+  if (p.k_causal == 2) k_begin = (m0 / BK) * BK;
+  const uint32_t nt = (k_end - k_begin + BK - 1) / BK, full = (k_end - k_begin) / BK, k_rest = (k_end - k_begin) % BK;
+
+  const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = wave / WN, wn = wave % WN;
+  floatx16 acc[TI][TJ];
+#pragma unroll
+  for (int i = 0; i < TI; ++i)
+#pragma unroll
+    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  const size_t c_off = (size_t)(bo * p.c_so + bi * p.c_si);
+  FetchA ta;
+  FetchB tb;
+  ta.init(p.lda, p.m - m0);
+  tb.init(p.ldb, p.n - n0);
   const bf16_t* A = p.a + bo * p.a_so + bi * p.a_si;
   const bf16_t* B = p.b + bo * p.b_so + bi * p.b_si;
-  // The configuration without ragged tiles is launched with one block per CU that works through tiles one after the
-  // other: wavefronts, LDS and the prologue are set up once, the first operand tiles of the next output tile are
-  // fetched while the current one's epilogue runs, and the epilogue's stores drain under the next main loop.  The
-  // other configuration is launched with one block per tile and passes through this loop once.
-  // Which tile comes next: a monitored launch hands its tiles out through counters in the stream's record, one per
-  // XCD (a block takes the tiles of its own XCD's run in order and, when that run is exhausted, helps the others), so
-  // that a block that starts late - its CU was held by a kernel of the other stream - simply takes fewer tiles; with a
-  // fixed share per block the whole launch would wait for the late one.  An unmonitored launch has no record: every
-  // block takes each gridDim.x-th tile (a stride that is a multiple of 8 keeps it on its XCD's run).
+  uint64_t base_a = (uint64_t)(ALAY == 0 ? A + (size_t)m0 * p.lda + k_begin : A + (size_t)k_begin * p.lda + m0);
+  uint64_t base_b = (uint64_t)(BLAY == 0 ? B + (size_t)n0 * p.ldb + k_begin : B + (size_t)k_begin * p.ldb + n0);
+  const uint64_t step_a = ALAY == 0 ? BK * 2 : (uint64_t)BK * p.lda * 2, step_b = BLAY == 0 ? BK * 2 : (uint64_t)BK * p.ldb * 2;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) bf16_t*)lds;
+
+  bf16x8 fa[2][4][TI], fb[2][4][TJ];
+  auto read_slice = [&](const bf16_t* st, int ks, bf16x8 (&a)[TI], bf16x8 (&b)[TJ]) {
+#pragma unroll
+    for (int i = 0; i < TI; ++i) a[i] = operand_frag<ALAY, BM>(st, (wm * TI + i) * 32, ks);
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) b[j] = operand_frag<BLAY, BN>(st + SA, (wn * TJ + j) * 32, ks);
+  };
+  auto mfma_slice = [&](bf16x8 (&a)[TI], bf16x8 (&b)[TJ]) {
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+  };
+  // the next K step into a slot; `last`: the ragged one
+  auto fetch_step = [&](uint32_t slot, bool last) {
+    const uint32_t o = lds0 + slot * (STAGE * 2);
+    const i32x4 ra = operand_rsrc(base_a), rb = operand_rsrc(base_b);
+    if (last) {
+#pragma unroll
+      for (int d = 0; d < F; ++d) { if (d < FA) ta.issue_last(ra, o, wave, d, k_rest); else tb.issue_last(rb, o + SA * 2, wave, d - FA, k_rest); }
+    } else {
+#pragma unroll
+      for (int d = 0; d < F; ++d) { if (d < FA) ta.issue(ra, o, wave, d); else tb.issue(rb, o + SA * 2, wave, d - FA); }
+    }
+    base_a += step_a; base_b += step_b;
+  };
+  for (uint32_t s = 0; s < (uint32_t)AHEAD && s < nt; ++s) fetch_step(s, s >= full);
+  if (nt >= (uint32_t)AHEAD) wait_vm<F * (AHEAD - 1)>(); else wait_vm<0>();
+  if (THREADS > 64) barrier_only();
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) read_slice(lds, ks, fa[0][ks], fb[0][ks]);
+
+  auto steady = [&](auto S, auto P) {          // step in slot S with its fragments in register set P
+    constexpr int s = decltype(S)::value, cur = decltype(P)::value, nx = (s + 1) % ST, fs = (s + AHEAD) % ST;
+    wait_vm<F * (AHEAD - 2)>();                 // the next step has landed
+    if (!LAG) wait_lds();
+    if (THREADS > 64) barrier_only();
+    const uint32_t o = lds0 + fs * (STAGE * 2);
+    const i32x4 ra = operand_rsrc(base_a), rb = operand_rsrc(base_b);
+    base_a += step_a; base_b += step_b;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      read_slice(lds + nx * STAGE, ks, fa[cur ^ 1][ks], fb[cur ^ 1][ks]);
+#pragma unroll
+      for (int d = ks * F / 4; d < (ks + 1) * F / 4; ++d) { if (d < FA) ta.issue(ra, o, wave, d); else tb.issue(rb, o + SA * 2, wave, d - FA); }
+      __builtin_amdgcn_sched_barrier(0);
+      mfma_slice(fa[cur][ks], fb[cur][ks]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  uint32_t t = 0;
+  constexpr uint32_t TURN = ST == 3 ? 6 : ST;      // an even number of steps: the register sets alternate too
+  static_assert(ST >= 2 && ST <= 4, "the turns written out below");
+  while (t + AHEAD + TURN - 1 < full) {
+    if constexpr (ST == 2) { steady(Int<0>(), Int<0>()); steady(Int<1>(), Int<1>()); }
+    if constexpr (ST == 3) {
+      steady(Int<0>(), Int<0>()); steady(Int<1>(), Int<1>()); steady(Int<2>(), Int<0>());
+      steady(Int<0>(), Int<1>()); steady(Int<1>(), Int<0>()); steady(Int<2>(), Int<1>());
+    }
+    if constexpr (ST == 4) { steady(Int<0>(), Int<0>()); steady(Int<1>(), Int<1>()); steady(Int<2>(), Int<0>()); steady(Int<3>(), Int<1>()); }
+    t += TURN;
+  }
+  uint32_t slot = 0;
+  auto step = [&](auto P) {
+    constexpr int cur = decltype(P)::value;
+    const uint32_t nx = slot + 1 == ST ? 0 : slot + 1;
+    if (t + 1 < nt) {
+      if (t + AHEAD - 1 < nt) wait_vm<F * (AHEAD - 2)>(); else wait_vm<0>();
+      if (!LAG) wait_lds();
+      if (THREADS > 64) barrier_only();
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) read_slice(lds + nx * STAGE, ks, fa[cur ^ 1][ks], fb[cur ^ 1][ks]);
+      if (t + AHEAD < nt) fetch_step(LAG ? (slot == 0 ? ST - 1 : slot - 1) : slot, t + AHEAD >= full);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) mfma_slice(fa[cur][ks], fb[cur][ks]);
+    __builtin_amdgcn_sched_barrier(0);
+    slot = nx;
+    ++t;
+  };
+  while (t + 1 < nt) { step(Int<0>()); step(Int<1>()); }
+  if (t < nt) step(Int<0>());
+
+  uint4 bias_q = make_uint4(0, 0, 0, 0);       // the eight columns that this lane finishes in every pass of the epilogue
+  const uint32_t bn = n0 + wn * (TJ * 32) + (lane % (TJ * 4)) * 8;
+  if ((p.n & 7) == 0 && (c_off & 7) == 0 && p.bias != nullptr && bn < p.n) bias_q = *reinterpret_cast<const uint4*>(p.bias + bn);
+  __syncthreads();                             // nobody reads the ring any more: it stages the results
+  gemm_store_tile<TI, TJ, SR>(p, acc, reinterpret_cast<float*>(lds) + wave * (SR * TJ * 32), m0 + wm * (TI * 32), n0 + wn * (TJ * 32), c_off, bias_q);
+  kernel_end(ctl, true);
+}
+
+// 256x256 tiles, eight wavefronts of 128x64, whole K steps.  The wavefronts of the tile's upper and of its lower half -
+// one of each per SIMD - take turns: while one half multiplies (16 MFMAs, nothing else in its instruction stream), the
+// other reads the fragments of its next 16 from LDS and issues fetches, then a barrier swaps them.  Per K step a
+// wavefront has two memory phases: B (kept in registers for both) with the first half of its A rows, then the second
+// half of its A rows.  The parts of a step are therefore read, and free for the fetch of two steps later, at different
+// times: B and the first halves of A are fetched in one phase, the second halves of A in the other, and every fetch has
+// five to six phases (a step and a half, about 1.5 us) to arrive; the counts waited for leave eight younger fetches per
+// wavefront in flight.  Two buffers of each part are 128 KB of LDS; the epilogue has 16 KB of its own for staging.
+// (One phase is 512 cycles of MFMA; a step takes 1.0 us where it was 1.27 with a barrier per step and everything in one
+// stream.  On a full chip the clock falls to what the power allows: 8192^3 800 -> 760 us.)
+//
+// Persistent: a block works through tiles one after the other; the first operand tiles of the next output tile are
+// fetched while the current one's epilogue runs.  Which tile comes next: a monitored launch hands its tiles out through
+// counters in the stream's record, one per XCD (a block takes the tiles of its own XCD's run in order and, when that
+// run is exhausted, helps the others), so that a block that starts late - its CU was held by a kernel of the other
+// stream - simply takes fewer tiles; with a fixed share per block the whole launch would wait for the late one.  An
+// unmonitored launch has no record: every block takes each gridDim.x-th tile (a stride that is a multiple of 8 keeps it
+// on its XCD's run).
+// Registers: two wavefronts per SIMD may take 256 of its 512 each.  The kernel is held to 248 (the attribute counts in
+// pairs): a one-wavefront kernel that sits on a CU for the length of a bubble (the training stream's wait) then still
+// fits beside a block, which otherwise stays off that CU, and the tiles of 255 CUs end a round later.
+template <int ALAY, int BLAY, bool GROUPED = false>
+__global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(124))) void gemm_pp_kernel(GemmP p_in, KCtl ctl) {
+  constexpr int BM = 256, BN = 256, WM = 2, WN = 4, THREADS = 512, TI = 4, TJ = 2, HI = TI / 2, SR = 8;
+  constexpr uint32_t HA = BM / 2 * BK, STAGE = 2 * HA + BN * BK;       // elements: two halves of A, then B
+  typedef TileFetch<ALAY, BM / 2, THREADS, BM / WM / 2, BM / WM, 0> FetchA0;
+  typedef TileFetch<ALAY, BM / 2, THREADS, BM / WM / 2, BM / WM, 1> FetchA1;
+  typedef TileFetch<BLAY, BN, THREADS, BN, BN, 0> FetchB;
+  constexpr int F1 = FetchA1::NV, F0 = FetchA0::NV + FetchB::NV;       // fetches of the second halves of A; of the rest
+  __shared__ __align__(1024) bf16_t lds[2 * STAGE];
+  __shared__ __align__(16) float stage[WM * WN * SR * TJ * 32];
   __shared__ uint32_t s_next;
-  const bool dynamic = !EDGE && ctl.rec != nullptr && gridDim.z == 1 && gridDim.x < total_tiles;
+  if (!kernel_begin(ctl)) { kernel_end(ctl, false); return; }
+  GemmP p = p_in;
+  // (the record of a group's launch says how many blocks' worth of tiles it has in all)
+  const uint32_t all_tiles = GROUPED ? p_in.tiles_m : p_in.tiles_m * p_in.tiles_n;
+  const uint32_t bo = blockIdx.z / p_in.batch_inner, bi = blockIdx.z % p_in.batch_inner;
+  const bool dynamic = ctl.rec != nullptr && gridDim.z == 1 && gridDim.x < all_tiles;
   const uint32_t my_x = blockIdx.x & 7u;
-  auto tiles_of_xcd = [&](uint32_t x) { return gemm_tiles_of_xcd(total_tiles, x); };
-  auto steal = [&]() -> uint32_t { return gemm_steal_tile(ctl.rec, total_tiles, my_x); };
-  uint32_t pid = blockIdx.x - p.tile_base;
+  uint32_t pid = blockIdx.x;
   if (dynamic) {
-    if (threadIdx.x == 0) s_next = steal();
+    if (threadIdx.x == 0) s_next = gemm_steal_tile(ctl.rec, all_tiles, my_x);
     __syncthreads();
     pid = s_next;
   }
-  DmaStream<ALAY, BM, THREADS> ta(A, p.lda, 0, p.m, 0);
-  DmaStream<BLAY, BN, THREADS> tb(B, p.ldb, 0, p.n, 0);
-  bool fetched_ahead = false;
-  while (pid < total_tiles) {
-  uint32_t next_pid = kNone;
-  uint32_t tile_m, tile_n;
-  tile_of(pid, tile_m, tile_n);
-  const uint32_t m0 = tile_m * BM, n0 = tile_n * BN;
-  const bool skip = (p.epi & SIF_EPI_CAUSAL_SKIP) && n0 > m0 + BM - 1;
-  if (!skip) {
-    uint32_t k_begin = 0, k_end = p.k;
-    if (p.k_limit != 0) k_end = min(p.k, p.k_limit - bi * p.k);      // slices of one long K: the last may be shorter
-    if (p.k_causal == 1) k_end = min(p.k, m0 + BM);
-    if (p.k_causal == 2) k_begin = (m0 / BK) * BK;
+  const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = wave / WN, wn = wave % WN;
+  const bool second = wm != 0;                 // the half that is one phase behind
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) bf16_t*)lds;
 
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = wave / WN, wn = wave % WN;
+  FetchA0 ta0;
+  FetchA1 ta1;
+  FetchB tb;
+  uint64_t base_a = 0, base_b = 0, step_a = 0, step_b = 0;
+  uint32_t m0 = 0, n0 = 0, nt = 0;
+  auto fetch_a0b = [&](uint32_t t) {
+    const uint32_t o = lds0 + (t & 1u) * (STAGE * 2);
+    const i32x4 ra = operand_rsrc(base_a + t * step_a), rb = operand_rsrc(base_b + t * step_b);
+#pragma unroll
+    for (int i = 0; i < FetchA0::NV; ++i) ta0.issue(ra, o, wave, i);
+#pragma unroll
+    for (int i = 0; i < FetchB::NV; ++i) tb.issue(rb, o + HA * 4, wave, i);
+  };
+  auto fetch_a1 = [&](uint32_t t) {
+    const uint32_t o = lds0 + (t & 1u) * (STAGE * 2) + HA * 2;
+    const i32x4 ra = operand_rsrc(base_a + t * step_a);
+#pragma unroll
+    for (int i = 0; i < F1; ++i) ta1.issue(ra, o, wave, i);
+  };
+  // sets up tile `id` and fetches what its first two memory phases read, and one part more
+  auto open_tile = [&](uint32_t id) {
+    uint32_t local = id, tile_m, tile_n;
+    if constexpr (GROUPED) {
+      gemm_load_record(p, p_in.group, p_in.group_n, id);
+      local = id - p.tile_base;
+      // (a group pads every product to a multiple of eight tiles: what is beyond has no K steps and stores nothing)
+      if (local >= p.tiles_m * p.tiles_n) { nt = 0; return; }
+    }
+    gemm_tile_of(p, p.tiles_m * p.tiles_n, local, tile_m, tile_n);
+    m0 = tile_m * BM;
+    n0 = tile_n * BN;
+    uint32_t k_end = p.k;
+    if (p.k_limit != 0) k_end = min(p.k, p.k_limit - bi * p.k);      // slices of one long K: the last may be shorter
+    nt = k_end / BK;
+    ta0.init(p.lda, p.m - m0);
+    ta1.init(p.lda, p.m - m0);
+    tb.init(p.ldb, p.n - n0);
+    const bf16_t* A = p.a + bo * p.a_so + bi * p.a_si;
+    const bf16_t* B = p.b + bo * p.b_so + bi * p.b_si;
+    base_a = (uint64_t)(ALAY == 0 ? A + (size_t)m0 * p.lda : A + m0);
+    base_b = (uint64_t)(BLAY == 0 ? B + (size_t)n0 * p.ldb : B + n0);
+    step_a = ALAY == 0 ? BK * 2 : (uint64_t)BK * p.lda * 2;
+    step_b = BLAY == 0 ? BK * 2 : (uint64_t)BK * p.ldb * 2;
+    fetch_a0b(0);
+    fetch_a1(0);
+    if (nt > 1) fetch_a0b(1);
+  };
+  if (pid < all_tiles) open_tile(pid);
+  while (pid < all_tiles) {
+    const uint32_t cm0 = m0, cn0 = n0, cnt = nt;
+    GemmP cp = p;                              // (of a group: the next tile may belong to another product)
     floatx16 acc[TI][TJ];
 #pragma unroll
     for (int i = 0; i < TI; ++i)
@@ -470,176 +640,139 @@ __global__ __launch_bounds__(64 * WM * WN, BM == 128 ? 2 : 1) __attribute__((amd
       for (int j = 0; j < TJ; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-    // A lane stores the same eight columns in every pass of the epilogue: their bias is fetched once, here, so that
-    // the main loop hides the latency.
-    uint4 bias_q = make_uint4(0, 0, 0, 0);
-    {
-      const uint32_t n = n0 + wn * WCOLS + (lane & 7) * 8;
-      const size_t c_off0 = (size_t)(bo * p.c_so + bi * p.c_si);
-      if ((p.n & 7) == 0 && (c_off0 & 7) == 0 && p.bias != nullptr && n < p.n) bias_q = *reinterpret_cast<const uint4*>(p.bias + n);
-    }
-    // Register prefetch two K steps deep: set[t & 1] carries tile t from global memory to LDS.  While tile t is
-    // multiplied out of LDS buffer t & 1, tile t+1 is landing in the other set and the load of tile t+2 is issued
-    // into the set tile t has just left, so every global load has two iterations of MFMA work to hide behind.
-    uint4 ra0[4], rb0[4], ra1[4], rb1[4];
-    const uint32_t fra = wm * (TI * 32) + (lane & 31), frb = wn * (TJ * 32) + (lane & 31), kh = lane >> 5;
-    // Fragments of K slice ks + 1 are read from LDS into a second register set before the MFMAs of slice ks are
-    // issued, so that an LDS read has four MFMAs (128 cycles) to land behind instead of being waited for at once.
-    auto load_frags = [&](const bf16_t* cA, const bf16_t* cB, int ks, bf16x8 (&fa)[TI], bf16x8 (&fb)[TJ]) {
+    const size_t c_off = (size_t)(bo * p.c_so + bi * p.c_si);
+    bf16x8 fa[4][HI], fb[4][TJ];
+    auto read_a = [&](const bf16_t* half) {
 #pragma unroll
-      for (int i = 0; i < TI; ++i)
-        fa[i] = ALAY == 0 ? *reinterpret_cast<const bf16x8*>(cA + lds_off(fra + i * 32, ks * 2 + kh))
-                          : kmajor_frag<BM>(cA, wm * (TI * 32) + i * 32, ks * 16 + kh * 8);
+      for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-      for (int j = 0; j < TJ; ++j)
-        fb[j] = BLAY == 0 ? *reinterpret_cast<const bf16x8*>(cB + lds_off(frb + j * 32, ks * 2 + kh))
-                          : kmajor_frag<BN>(cB, wn * (TJ * 32) + j * 32, ks * 16 + kh * 8);
+        for (int i = 0; i < HI; ++i) fa[ks][i] = operand_frag<ALAY, BM / 2>(half, (wm * HI + i) * 32, ks);
     };
-    // `fetches` says how many global -> LDS fetches were issued just before (they sit in the same scheduling region).
-    // The order wanted for one K step: the reads of slice 0, then per slice its MFMAs with the LDS reads of the next
-    // slice and a share of the fetches spread evenly between them.  A wavefront issues in order, and a fetch that finds
-    // the memory pipeline full holds up the MFMAs behind it, so the fetches must not come in one burst (after a barrier
-    // every wavefront of the CU would issue its burst at the same time).
-    auto compute = [&](const bf16_t* cA, const bf16_t* cB, auto fetches) {
-      constexpr int NS = BK / 16, NM = TI * TJ, ND = (ALAY == 0 ? 1 : 2) * TI + (BLAY == 0 ? 1 : 2) * TJ;
-      bf16x8 fa[2][TI], fb[2][TJ];
-      load_frags(cA, cB, 0, fa[0], fb[0]);
+    auto read_b = [&](const bf16_t* tile) {
 #pragma unroll
-      for (int ks = 0; ks < NS; ++ks) {
-        if (ks + 1 < NS) load_frags(cA, cB, ks + 1, fa[(ks + 1) & 1], fb[(ks + 1) & 1]);
+      for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-        for (int i = 0; i < TI; ++i)
-#pragma unroll
-          for (int j = 0; j < TJ; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks & 1][i], fb[ks & 1][j], acc[i][j], 0, 0, 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x100, ND, 0);                 // LDS reads of slice 0
-      sched_pipeline<NM, ND, NS, decltype(fetches)::value, 0>();
+        for (int j = 0; j < TJ; ++j) fb[ks][j] = operand_frag<BLAY, BN>(tile, (wn * TJ + j) * 32, ks);
     };
-    // The loop takes two K steps per trip (the register sets and LDS buffers alternate by name) and has no exit in
-    // its middle, so that the accumulators stay in the same registers throughout; an odd last tile is done after it.
-    const uint32_t nt = (k_end - k_begin + BK - 1) / BK;
-    uint32_t l_own = 0;
-    // Whole K steps take the direct fetches, also in a tile that is ragged in M or N (its missing rows fetch the tile's
-    // first row and are never stored); a ragged K needs the zero fill of the register path.  Without EDGE the launcher
-    // guarantees whole K steps.
-    const bool interior = !EDGE || ((k_end - k_begin) % BK) == 0;
-    if (interior) {
-      // tile t+1 is fetched into the other pair of buffers while tile t is multiplied; the other block of the CU
-      // covers what the fetch latency exceeds one K step
-      if (!fetched_ahead) {
-        ta = DmaStream<ALAY, BM, THREADS>(A, p.lda, m0, p.m, k_begin);
-        tb = DmaStream<BLAY, BN, THREADS>(B, p.ldb, n0, p.n, k_begin);
-        ta.next(sA0); tb.next(sB0);
-      }
-      wait_fetches();
-      __syncthreads();
-      // the block's next tile is asked for now; the answer is looked at when this tile's main loop is over
-      if (dynamic && threadIdx.x == 0) l_own = atomicAdd(&ctl.rec->tile_next[my_x * 32u], 1u);
-      for (uint32_t t = 0; t + 2 <= nt; t += 2) {
-        ta.next(sA1); tb.next(sB1);
-        compute(sA0, sB0, Int<FETCHES>());
-        wait_fetches();          // every wavefront's part of the next tile has landed before the barrier lets anyone read it
-        __syncthreads();
-        if (t + 2 < nt) { ta.next(sA0); tb.next(sB0); }
-        compute(sA1, sB1, Int<FETCHES>());
-        wait_fetches();
-        __syncthreads();
-      }
-    } else if (EDGE) {
-      uint32_t oka0 = load_tile<ALAY, THREADS, BM>(ra0, A, p.lda, m0, p.m, k_begin, k_end);
-      uint32_t okb0 = load_tile<BLAY, THREADS, BN>(rb0, B, p.ldb, n0, p.n, k_begin, k_end);
-      uint32_t oka1 = load_tile<ALAY, THREADS, BM>(ra1, A, p.lda, m0, p.m, k_begin + BK, k_end);       // reads as zero past k_end
-      uint32_t okb1 = load_tile<BLAY, THREADS, BN>(rb1, B, p.ldb, n0, p.n, k_begin + BK, k_end);
-      store_tile<ALAY, THREADS, BM>(sA0, ra0, oka0);
-      store_tile<BLAY, THREADS, BN>(sB0, rb0, okb0);
-      __syncthreads();
-      for (uint32_t t = 0; t + 2 <= nt; t += 2) {
-        const uint32_t k0 = k_begin + t * BK;
-        oka0 = load_tile<ALAY, THREADS, BM>(ra0, A, p.lda, m0, p.m, k0 + 2 * BK, k_end);
-        okb0 = load_tile<BLAY, THREADS, BN>(rb0, B, p.ldb, n0, p.n, k0 + 2 * BK, k_end);
-        compute(sA0, sB0, Int<0>());
-        store_tile<ALAY, THREADS, BM>(sA1, ra1, oka1);
-        store_tile<BLAY, THREADS, BN>(sB1, rb1, okb1);
-        __syncthreads();
-        oka1 = load_tile<ALAY, THREADS, BM>(ra1, A, p.lda, m0, p.m, k0 + 3 * BK, k_end);
-        okb1 = load_tile<BLAY, THREADS, BN>(rb1, B, p.ldb, n0, p.n, k0 + 3 * BK, k_end);
-        compute(sA1, sB1, Int<0>());
-        store_tile<ALAY, THREADS, BM>(sA0, ra0, oka0);
-        store_tile<BLAY, THREADS, BN>(sB0, rb0, okb0);
-        __syncthreads();
-      }
+    auto multiply = [&](auto H) {
+      constexpr int h = decltype(H)::value;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+        for (int i = 0; i < HI; ++i)
+#pragma unroll
+          for (int j = 0; j < TJ; ++j) acc[h * HI + i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks][i], fb[ks][j], acc[h * HI + i][j], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    if (nt > 1) wait_vm<F1 + F0>(); else wait_vm<F1>();      // B and the first halves of A of step 0
+    barrier_only();
+    uint32_t own = 0;
+    if (dynamic && threadIdx.x == 0) own = atomicAdd(&ctl.rec->tile_next[my_x * 32u], 1u);      // the block's next tile is asked for now
+    if (second) barrier_only();
+    // The waits stand before the barrier behind which the first half reads what they wait for: at the end of its own
+    // matrix phase, at the end of the second half's memory phase.
+    for (uint32_t t = 0; t < nt; ++t) {
+      const bf16_t* cur = lds + (t & 1u) * STAGE;
+      const bool more = t + 1 < nt, more2 = t + 2 < nt;
+      read_b(cur + 2 * HA);
+      read_a(cur);
+      if (more) fetch_a1(t + 1);
+      wait_lds();
+      if (second) { if (more) wait_vm<F0 + F1>(); else wait_vm<0>(); }       // second halves of A, step t
+      barrier_only();
+      multiply(Int<0>());
+      if (!second) { if (more) wait_vm<F0 + F1>(); else wait_vm<0>(); }
+      barrier_only();
+      read_a(cur + HA);
+      if (more2) fetch_a0b(t + 2);
+      wait_lds();
+      if (second && more) { if (more2) wait_vm<F0 + F1>(); else wait_vm<F1>(); }      // B and first halves of A, step t + 1
+      barrier_only();
+      multiply(Int<1>());
+      if (!second && more) { if (more2) wait_vm<F0 + F1>(); else wait_vm<F1>(); }
+      barrier_only();
     }
-    if (nt & 1u) compute(sA0, sB0, Int<0>());
+    if (!second) barrier_only();
 
-    // Epilogue.  Each wavefront passes its accumulators, 32 rows at a time, through a staging area of its own in
-    // LDS (fp32 [32][64], the operand buffers are free by now) so that every global access of the epilogue - bias,
-    // residual, auxiliary tensor, result - is a 16-byte vector along a row; no block-wide barrier is needed after
-    // the first.  Accumulator element r of lane l is row (r/4)*8 + (l/32)*4 + r%4, column l%32 of its 32x32 tile.
-    // Chunk c (four floats) of staging row r lives at c ^ (8*((r/4)%2) | r%2): the two half-wavefronts of a store
-    // and the eight rows of a load then fall on different banks.
-    if (!EDGE && threadIdx.x == 0) {
+    if (threadIdx.x == 0) {
       uint32_t np = kNone;
-      if (dynamic) np = l_own < tiles_of_xcd(my_x) ? l_own * 8u + my_x : steal();
-      else if (pid + gridDim.x < total_tiles) np = pid + gridDim.x;
+      if (dynamic) np = own < gemm_tiles_of_xcd(all_tiles, my_x) ? own * 8u + my_x : gemm_steal_tile(ctl.rec, all_tiles, my_x);
+      else if (pid + gridDim.x < all_tiles) np = pid + gridDim.x;
       s_next = np;
     }
     __syncthreads();
-    // the block's next output tile: its first operand tiles travel into sA0 / sB0 while this epilogue runs (the staging
-    // area below is sA1 / sB1, which the next main loop fills only after its first barrier)
-    fetched_ahead = false;
-    if (!EDGE) next_pid = s_next;
-    if (!EDGE && next_pid < total_tiles) {
-      uint32_t nm, nn;
-      tile_of(next_pid, nm, nn);
-      ta = DmaStream<ALAY, BM, THREADS>(A, p.lda, nm * BM, p.m, 0);
-      tb = DmaStream<BLAY, BN, THREADS>(B, p.ldb, nn * BN, p.n, 0);
-      ta.next(sA0); tb.next(sB0);
-      fetched_ahead = true;
+    pid = s_next;
+    if (pid < all_tiles) open_tile(pid);
+    if (cnt != 0) {
+      uint4 bias_q = make_uint4(0, 0, 0, 0);
+      const uint32_t n = cn0 + wn * 64 + (lane & 7) * 8;
+      if ((cp.n & 7) == 0 && (c_off & 7) == 0 && cp.bias != nullptr && n < cp.n) bias_q = *reinterpret_cast<const uint4*>(cp.bias + n);
+      gemm_store_tile<TI, TJ, SR>(cp, acc, stage + wave * (SR * TJ * 32), cm0 + wm * (TI * 32), cn0 + wn * 64, c_off, bias_q);
     }
-    float* sW = reinterpret_cast<float*>(wave < WM * WN / 2 ? sA1 : sB1) + (wave % (WM * WN / 2)) * (32 * WCOLS);
-    gemm_store_tile<TI, TJ>(p, acc, sW, m0 + wm * (TI * 32), n0 + wn * WCOLS, (size_t)(bo * p.c_so + bi * p.c_si), bias_q);
-  }
-  pid = next_pid;
   }
   kernel_end(ctl, true);
 }
 
 static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
-// 256x256 tiles (one block of eight wavefronts per CU, 128x64 per wavefront: a quarter fewer LDS reads and half the
-// global fetches per MFMA); they need whole K steps - also in the last, shorter slice of a K cut into slices - and no
-// causal skipping
-bool gemm_can_use_big_tiles(const sif_gemm_args& a) {
-  const bool causal = a.k_causal != 0 || (a.epilogue & SIF_EPI_CAUSAL_SKIP);
-  if (causal || (a.k % BK) != 0) return false;
+// ---------------------------------------------------------------------------------------------- configurations
+// What a launch costs, per configuration: 2 us, and per round of tiles `fixed` + `step` * (K steps of 64) us with `slots`
+// tiles on a CU at a time, `step1` with one.  Least squares over 37 shapes from 77 x 768 x 3072 to 8192^3, three operand
+// layouts and three epilogues (each configuration's times are met to 8-17 %); the choice by this model is on average 0.7 %
+// slower than the best configuration of each shape and at worst 18 %.
+struct GemmTiles { uint32_t bm, bn, slots; double fixed, step, step1; };
+enum { kT32x64, kT64x64, kT128x64, kT128x128x1, kT128x128, kT256x128, kT256x256, kNTiles };
+static const GemmTiles kGemmTiles[kNTiles] = {
+    {32, 64, 3, 1.75, 0.380, 0.114}, {64, 64, 2, 1.80, 0.369, 0.171},   {128, 64, 2, 2.40, 0.616, 0.261},  {128, 128, 1, 2.94, 0.436, 0.436},
+    {128, 128, 2, 2.69, 0.958, 0.525}, {256, 128, 1, 4.99, 0.735, 0.735}, {256, 256, 1, 6.68, 1.233, 1.233},
+};
+
+// whole K steps - also in the last, shorter slice of a K cut into slices - and no causal variant: what the 256x256 tiles
+// need
+static bool gemm_causal(const sif_gemm_args& a) { return a.k_causal != 0 || (a.epilogue & SIF_EPI_CAUSAL_SKIP); }
+static bool gemm_whole_steps(const sif_gemm_args& a) {
+  if (gemm_causal(a) || (a.k % BK) != 0) return false;
   if (a.k_limit == 0) return true;
   const uint64_t before_last = (uint64_t)(a.batch_inner - 1) * a.k;
   return a.k_limit > before_last && ((a.k_limit - before_last) % BK) == 0;
 }
 
-// Which configuration is faster follows a two-line model fitted to measurements on gfx950 (time of one round of
-// tiles over the chip, us, K in steps of 64): 128x128, two blocks per CU: 1.0 + 1.19 steps, and a CU that holds a
-// single block runs it faster, so a partly filled round costs about its share (never less than 0.85 of a round);
-// 256x256, one persistent block per CU: 4.0 + 1.75 steps for four times the outputs per block, and a partly filled
-// last round costs a whole one.  (65536 x 2304 x 768: 233 against 289 us, 65536 x 768 x 768: 101 against 122,
-// 65536 x 3072 x 768 + GELU: 351 against 424, 65536 x 768 x 3072: 295 against 360, 8192 x 50304 x 768: 690 against
-// 892, 8192^3: 864 against 1044; the other way round 8192 x 2304 x 768: 47 against 43, 8192 x 3072 x 768: 55 against 52.)
-bool gemm_big_tiles(const sif_gemm_args& a) {
-  if (a.tile == 256) return true;
-  if (a.tile == 128 || !gemm_can_use_big_tiles(a)) return false;
-  const uint64_t batches = (uint64_t)a.batch_outer * a.batch_inner;
-  const uint64_t tiles256 = (uint64_t)((a.m + 255) / 256) * ((a.n + 255) / 256) * batches;
-  const uint64_t tiles128 = (uint64_t)((a.m + 127) / 128) * ((a.n + 127) / 128) * batches;
-  const double steps = (double)(a.k / BK);
-  const double t128 = (1.0 + 1.19 * steps) * std::max(0.85, (double)tiles128 / 512.0);
-  const double t256 = (4.0 + 1.75 * steps) * (double)((tiles256 + 255) / 256);
-  return t256 < t128;
+static double gemm_time_us(const sif_gemm_args& a, int cfg) {
+  const GemmTiles& t = kGemmTiles[cfg];
+  const uint64_t tiles = (uint64_t)((a.m + t.bm - 1) / t.bm) * ((a.n + t.bn - 1) / t.bn) * a.batch_outer * a.batch_inner, round = 256ull * t.slots;
+  const double steps = (double)((a.k + BK - 1) / BK);
+  const uint64_t whole = tiles / round, rest = tiles % round;
+  double us = 2.0 + (double)whole * (t.fixed + t.step * steps);
+  if (rest > 0) {
+    // a last round goes by the CU that holds the most of its tiles
+    const double share = rest <= 256 ? 0.0 : (double)((rest - 1) / 256) / (double)(t.slots - 1);
+    us += t.fixed + (t.step1 + (t.step - t.step1) * share) * steps;
+  }
+  return us;
 }
 
-// checks one product's arguments and fills its kernel record; *big: the 256x256 configuration was chosen
-static sif_status gemm_fill(const sif_gemm_args* a, GemmP& p, bool* big_out) {
+static int gemm_choose(const sif_gemm_args& a) {
+  if (a.tile == 256) return kT256x256;
+  if (a.tile == 128) return kT128x128;
+  int best = kT128x128;
+  double best_us = gemm_time_us(a, best);
+  for (int c = 0; c < kNTiles; ++c) {
+    if (c == kT256x256 && !gemm_whole_steps(a)) continue;
+    if (c == kT256x128 && gemm_causal(a)) continue;       // a causal product stops at the end of its row's 128-column tile
+    const double us = gemm_time_us(a, c);
+    if (us < best_us) { best = c; best_us = us; }
+  }
+  return best;
+}
+
+uint32_t gemm_round_rows(const sif_gemm_args& a) {
+  const GemmTiles& t = kGemmTiles[gemm_choose(a)];
+  return t.bm * std::max(1u, 256u * t.slots / ((a.n + t.bn - 1) / t.bn));
+}
+
+// checks one product's arguments and fills its kernel record for configuration `cfg` (kAuto: the one gemm_choose takes)
+constexpr int kAuto = -1;
+static sif_status gemm_fill(const sif_gemm_args* a, GemmP& p, int cfg, int* cfg_out) {
   if (a == nullptr || a->struct_size != sizeof(sif_gemm_args)) return fail(SIF_E_INVAL, "gemm: bad args struct");
   if (a->m == 0 || a->n == 0 || a->k == 0) return fail(SIF_E_INVAL, "gemm: empty extent");
   if (a->a_layout > 1 || a->b_layout > 1) return fail(SIF_E_INVAL, "gemm: bad layout");
@@ -665,10 +798,10 @@ static sif_status gemm_fill(const sif_gemm_args* a, GemmP& p, bool* big_out) {
     if ((a->bias_dev && !aligned16(a->bias_dev)) || (a->res_dev && !aligned16(a->res_dev)) || (a->aux_dev && !aligned16(a->aux_dev))) return fail(SIF_E_INVAL, "gemm: bias, residual and aux must be 16-byte aligned");
   }
   if (a->tile != 0 && a->tile != 128 && a->tile != 256) return fail(SIF_E_INVAL, "gemm: tile must be 0, 128 or 256");
-  if (a->tile == 256 && !gemm_can_use_big_tiles(*a)) return fail(SIF_E_INVAL, "gemm: 256-wide tiles need k (and the last slice under k_limit) to be a multiple of 64 and no causal variant");
+  if (a->tile == 256 && !gemm_whole_steps(*a)) return fail(SIF_E_INVAL, "gemm: 256-wide tiles need k (and the last slice under k_limit) to be a multiple of 64 and no causal variant");
   const uint64_t batches = (uint64_t)a->batch_outer * a->batch_inner;
-  const bool big = gemm_big_tiles(*a);
-  const uint32_t bm = big ? 256 : 128, bn = bm;
+  if (cfg == kAuto) cfg = gemm_choose(*a);
+  const uint32_t bm = kGemmTiles[cfg].bm, bn = kGemmTiles[cfg].bn;
   p.a = (const bf16_t*)a->a_dev; p.b = (const bf16_t*)a->b_dev; p.c = a->c_dev;
   p.bias = (a->epilogue & (SIF_EPI_BIAS | SIF_EPI_GELU)) ? (const bf16_t*)a->bias_dev : nullptr;
   p.res = a->res_dev; p.aux = (bf16_t*)a->aux_dev;
@@ -679,70 +812,95 @@ static sif_status gemm_fill(const sif_gemm_args* a, GemmP& p, bool* big_out) {
   p.tiles_n = (a->n + bn - 1) / bn; p.tiles_m = (a->m + bm - 1) / bm;
   p.group = nullptr; p.group_n = 0; p.tile_base = 0;
   if (batches > 65535) return fail(SIF_E_INVAL, "gemm: grid too large");
-  *big_out = big;
+  *cfg_out = cfg;
   return SIF_OK;
 }
 
 typedef void (*gemm_kern_fn)(GemmP, KCtl);
-static const gemm_kern_fn kGemm128[2][2] = {{gemm_bf16_kernel<0, 0, 128, 128, 2, 2, true>, gemm_bf16_kernel<0, 1, 128, 128, 2, 2, true>},
-                                            {gemm_bf16_kernel<1, 0, 128, 128, 2, 2, true>, gemm_bf16_kernel<1, 1, 128, 128, 2, 2, true>}};
-static const gemm_kern_fn kGemm256[2][2] = {{gemm_bf16_kernel<0, 0, 256, 256, 2, 4, false>, gemm_bf16_kernel<0, 1, 256, 256, 2, 4, false>},
-                                            {gemm_bf16_kernel<1, 0, 256, 256, 2, 4, false>, gemm_bf16_kernel<1, 1, 256, 256, 2, 4, false>}};
+#define RING(BM, BN, WM, WN, ST, LAG, OCC)                                                                                        \
+  {{gemm_ring_kernel<0, 0, BM, BN, WM, WN, ST, LAG, OCC>, gemm_ring_kernel<0, 1, BM, BN, WM, WN, ST, LAG, OCC>},                  \
+   {gemm_ring_kernel<1, 0, BM, BN, WM, WN, ST, LAG, OCC>, gemm_ring_kernel<1, 1, BM, BN, WM, WN, ST, LAG, OCC>}}
+static const gemm_kern_fn kGemmKernels[kNTiles][2][2] = {
+    RING(32, 64, 1, 2, 4, 1, 2),   RING(64, 64, 2, 2, 4, 1, 2),   RING(128, 64, 2, 2, 3, 0, 2), RING(128, 128, 4, 2, 4, 1, 1),
+    RING(128, 128, 2, 2, 2, 0, 2), RING(256, 128, 4, 2, 3, 0, 1), {{gemm_pp_kernel<0, 0>, gemm_pp_kernel<0, 1>}, {gemm_pp_kernel<1, 0>, gemm_pp_kernel<1, 1>}}};
+static const uint32_t kGemmThreads[kNTiles] = {128, 256, 256, 512, 256, 512, 512};
+#undef RING
 
-sif_status launch_gemm_bf16(const sif_gemm_args* a, hipStream_t stream, const KCtl& ctl) {
+static uint32_t gemm_cus() {
+  static const uint32_t cus = [] {
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 8) n = 256;
+    return (uint32_t)(n / 8 * 8);
+  }();
+  return cus;
+}
+
+static sif_status launch_gemm_cfg(const sif_gemm_args* a, int want, hipStream_t stream, const KCtl& ctl) {
   GemmP p;
-  bool big = false;
-  if (sif_status st = gemm_fill(a, p, &big)) return st;
+  int cfg = 0;
+  if (sif_status st = gemm_fill(a, p, want, &cfg)) return st;
   const uint64_t batches = (uint64_t)a->batch_outer * a->batch_inner;
   // 256x256 tiles: one block per CU, each working through every (number of CUs)-th tile; a stride that is a multiple of
   // 8 keeps a block on the tiles of its own XCD
   uint32_t grid_x = p.tiles_m * p.tiles_n;
-  if (big && batches == 1) {
-    static const uint32_t cus = [] {
-      int dev = 0, n = 0;
-      if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 8) n = 256;
-      return (uint32_t)(n / 8 * 8);
-    }();
-    if (grid_x > cus) grid_x = cus;
-  }
-  dim3 grid(grid_x, 1, (uint32_t)batches);
-  if (big) hipLaunchKernelGGL(kGemm256[a->a_layout][a->b_layout], grid, dim3(512), 0, stream, p, ctl);
-  else hipLaunchKernelGGL(kGemm128[a->a_layout][a->b_layout], grid, dim3(256), 0, stream, p, ctl);
+  if (cfg == kT256x256 && batches == 1) grid_x = std::min(grid_x, gemm_cus());
+  hipLaunchKernelGGL(kGemmKernels[cfg][a->a_layout][a->b_layout], dim3(grid_x, 1, (uint32_t)batches), dim3(kGemmThreads[cfg]), 0, stream, p, ctl);
   return check_launch("gemm_bf16");
 }
+sif_status launch_gemm_bf16(const sif_gemm_args* a, hipStream_t stream, const KCtl& ctl) { return launch_gemm_cfg(a, kAuto, stream, ctl); }
 
-// Several products of the same operand layouts as ONE launch of 128x128 tiles (the weight gradients of a layer: each
-// by itself has too few tiles for the chip and would have to be cut along K, with fp32 partial results written, read
-// again and summed; together they fill it).  gemm_group_fill checks the products and writes their kernel records, to
-// be copied to `gemm_group_bytes(n)` bytes of device memory once; launch_gemm_bf16_group then takes that copy.
+// Several products of the same operand layouts as ONE launch (the weight gradients of a layer: each by itself has too
+// few tiles for the chip and would have to be cut along K, with fp32 partial results written, read again and summed;
+// together they fill it).  gemm_group_fill checks the products, chooses the tiles and writes the kernel records, to be
+// copied to `gemm_group_bytes(n)` bytes of device memory once; launch_gemm_bf16_group then takes that copy.
 uint64_t gemm_group_bytes(uint32_t n) { return (uint64_t)n * sizeof(GemmP); }
 
-sif_status gemm_group_fill(const sif_gemm_args* list, uint32_t n, void* host_records, uint32_t* grid_out) {
-  if (list == nullptr || n == 0 || n > 16 || host_records == nullptr || grid_out == nullptr) return fail(SIF_E_INVAL, "gemm group: bad arguments");
+sif_status gemm_group_fill(const sif_gemm_args* list, uint32_t n, void* host_records, GemmGroup* out) {
+  if (list == nullptr || n == 0 || n > 16 || host_records == nullptr || out == nullptr) return fail(SIF_E_INVAL, "gemm group: bad arguments");
+  // which tiles: the model's time for all products' tiles together, the longest K deciding
+  int cfg = kT128x128;
+  double best = 0.0;
+  for (int c : {(int)kT128x128, (int)kT256x128, (int)kT256x256}) {
+    const GemmTiles& t = kGemmTiles[c];
+    double tiles = 0.0, steps = 0.0;
+    bool ok = true;
+    for (uint32_t i = 0; i < n; ++i) {
+      tiles += (double)((list[i].m + t.bm - 1) / t.bm) * ((list[i].n + t.bn - 1) / t.bn);
+      steps = std::max(steps, (double)((list[i].k + BK - 1) / BK));
+      ok = ok && (c != kT256x256 || gemm_whole_steps(list[i]));
+    }
+    const double round = 256.0 * t.slots, us = std::max(1.0, ceil(tiles / round)) * (t.fixed + t.step * steps);
+    if (ok && (c == kT128x128 || us < best)) { cfg = c; best = us; }
+  }
   GemmP* rec = static_cast<GemmP*>(host_records);
   uint32_t base = 0;
   for (uint32_t i = 0; i < n; ++i) {
     sif_gemm_args a = list[i];
-    a.tile = 128;
     if (a.a_layout != list[0].a_layout || a.b_layout != list[0].b_layout) return fail(SIF_E_INVAL, "gemm group: the products must share their operand layouts");
     if ((uint64_t)a.batch_outer * a.batch_inner != 1) return fail(SIF_E_INVAL, "gemm group: no batched products");
-    bool big = false;
-    if (sif_status st = gemm_fill(&a, rec[i], &big)) return st;
+    a.tile = 0;
+    int got = 0;
+    if (sif_status st = gemm_fill(&a, rec[i], cfg, &got)) return st;
     rec[i].tile_base = base;
     base += (rec[i].tiles_m * rec[i].tiles_n + 7u) & ~7u;       // a multiple of 8 keeps the tile order's idea of the XCDs
   }
-  *grid_out = base;
+  out->tiles = base;
+  out->cfg = cfg;
   return SIF_OK;
 }
 
-sif_status launch_gemm_bf16_group(const void* dev_records, uint32_t n, uint32_t grid, uint32_t a_layout, uint32_t b_layout, hipStream_t stream, const KCtl& ctl) {
-  if (dev_records == nullptr || n == 0 || grid == 0 || a_layout > 1 || b_layout > 1) return fail(SIF_E_INVAL, "gemm group: bad arguments");
+sif_status launch_gemm_bf16_group(const void* dev_records, uint32_t n, const GemmGroup& g, uint32_t a_layout, uint32_t b_layout, hipStream_t stream, const KCtl& ctl) {
+  if (dev_records == nullptr || n == 0 || g.tiles == 0 || a_layout > 1 || b_layout > 1) return fail(SIF_E_INVAL, "gemm group: bad arguments");
   GemmP head = {};
   head.group = static_cast<const GemmP*>(dev_records);
   head.group_n = n;
+  head.batch_inner = 1;
+  head.tiles_m = g.tiles;
   // (instantiated for the layouts of weight gradients, A [K][M] and B [K][N]; other layouts would need their own)
   if (a_layout != SIF_A_ROW_M || b_layout != SIF_B_ROW_N) return fail(SIF_E_INVAL, "gemm group: only A stored [K][M] with B stored [K][N]");
-  hipLaunchKernelGGL((gemm_bf16_kernel<1, 1, 128, 128, 2, 2, true, true>), dim3(grid), dim3(256), 0, stream, head, ctl);
+  if (g.cfg == kT256x256) hipLaunchKernelGGL((gemm_pp_kernel<1, 1, true>), dim3(std::min(g.tiles, gemm_cus())), dim3(512), 0, stream, head, ctl);
+  else if (g.cfg == kT256x128) hipLaunchKernelGGL((gemm_ring_kernel<1, 1, 256, 128, 4, 2, 3, 0, 1, true>), dim3(g.tiles), dim3(512), 0, stream, head, ctl);
+  else hipLaunchKernelGGL((gemm_ring_kernel<1, 1, 128, 128, 2, 2, 2, 0, 2, true>), dim3(g.tiles), dim3(256), 0, stream, head, ctl);
   return check_launch("gemm_bf16_group");
 }
 

@@ -139,12 +139,6 @@ static sif_gemm_args gemm_row_range(const sif_gemm_args& g, uint32_t r0, uint32_
   return part;
 }
 
-uint32_t gemm_round_rows(const sif_gemm_args& a) {
-  // 256x256 tiles run one per CU, 128x128 tiles two per CU
-  if (gemm_big_tiles(a)) return 256 * std::max(1u, 256u / ((a.n + 255) / 256));
-  return 128 * std::max(1u, 512u / ((a.n + 127) / 128));
-}
-
 void split_gemm_rows(const Op& op, uint32_t rows_first, Op& first, Op& rest) {
   const sif_gemm_args& g = op.gemm;
   first = make_gemm_op(op.name, gemm_row_range(g, 0, rows_first));
@@ -275,15 +269,15 @@ static bool emit_wgrad_group(Plan& p, const char* name, const WgradItem* items, 
     flops += gemm_flops(g.a);
   }
   std::vector<unsigned char> host(bytes);
-  uint32_t grid = 0;
-  if (gemm_group_fill(list, n, host.data(), &grid) != SIF_OK) return false;
+  GemmGroup g;
+  if (gemm_group_fill(list, n, host.data(), &g) != SIF_OK) return false;
   unsigned char* dev = gp.pool + gp.used;
   gp.used += (bytes + 255) & ~uint64_t(255);
   const hipError_t e = hipMemcpy(dev, host.data(), bytes, hipMemcpyHostToDevice);
   if (e != hipSuccess) { gp.status = fail_hip(e, "training plan: upload of a weight-gradient group"); return false; }
   Op op;
   op.name = name;
-  op.fn = [dev, n, grid](hipStream_t s, const KCtl& c) { return launch_gemm_bf16_group(dev, n, grid, SIF_A_ROW_M, SIF_B_ROW_N, s, c); };
+  op.fn = [dev, n, g](hipStream_t s, const KCtl& c) { return launch_gemm_bf16_group(dev, n, g, SIF_A_ROW_M, SIF_B_ROW_N, s, c); };
   op.cost_us = cost + 4.0;
   op.prof_class = (int32_t)(SIF_A_ROW_M * 2 + SIF_B_ROW_N);
   op.flops = flops;

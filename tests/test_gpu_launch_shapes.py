@@ -15,6 +15,10 @@ if torch.cuda.is_available():
     from gpu_util import DEV, f32, up, assert_f32_close
 
 
+def _bf16(gen, *shape):
+    return torch.randn(shape, device=DEV, generator=gen).to(torch.bfloat16)
+
+
 @pytest.mark.parametrize("batch,hidden", [(1, 8), (32, 1024), (32, 1056), (33, 2048), (512, 1024), (520, 1024), (2048, 1024), (2080, 1024)])
 def test_last_block_is_found_whatever_the_grid(batch, hidden):
     """A launch is reported done by its last block; grids at the edges of the counting tree (1, 32, 33, 512, 2048
@@ -96,3 +100,50 @@ def test_gemm_f32_tiles_and_remainders(m, n, k, k_contig_a, k_contig_b):
     ref = a.astype(np.float64) @ b.astype(np.float64).T
     bound = (k + 4) * 2.0 ** -24 * (np.abs(a).astype(np.float64) @ np.abs(b).astype(np.float64).T)
     assert np.all(np.abs(up(c) - ref) <= bound)
+
+
+@pytest.mark.parametrize("al", [0, 1])
+@pytest.mark.parametrize("bl", [0, 1])
+@pytest.mark.parametrize("m,n,k", [(1, 8, 8), (31, 72, 64), (33, 64, 136), (64, 64, 256), (65, 200, 520), (300, 3080, 320), (1000, 768, 200),
+                                   (1000, 2304, 456), (2008, 1536, 520), (4100, 768, 328), (2056, 2048, 1032), (8192, 776, 72), (4096, 3072, 512)])
+def test_gemm_bf16_picks_tiles_that_give_the_bits_of_the_128_ones(m, n, k, al, bl):
+    """Products of a few rows to ones that fill the chip: whichever tile the launcher takes (32x64 to 256x256, rings of
+    whole turns and of less, ragged M, N and K), the result has the bits of the 128x128 tiles and is the product.  Bound:
+    one rounding to bf16 (2^-9 of the value) and the fp32 sum of k exact products ((k + 4) 2^-24 of their magnitudes)."""
+    gen = torch.Generator(device=DEV).manual_seed(m + 3 * n + 5 * k + al + 2 * bl)
+    mp, np_ = (m + 7) // 8 * 8, n
+    a, b = torch.zeros((mp, k), device=DEV, dtype=torch.bfloat16), _bf16(gen, n, k)
+    a[:m] = _bf16(gen, m, k)
+    A, Bt = (a if al == 0 else a.t().contiguous()), (b if bl == 0 else b.t().contiguous())
+    out = [torch.full((m, n), float("nan"), device=DEV, dtype=torch.bfloat16) for _ in range(2)]
+    torch.cuda.synchronize()
+    for c, tile in zip(out, (0, 128)):
+        S.sif_k_gemm_bf16(A, Bt, c, m, n, k, A.shape[1], Bt.shape[1], n, a_layout=al, b_layout=bl, tile=tile)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], out[1])
+    ref = a[:m].double() @ b.double().t()
+    bound = 2.0 ** -8 * ref.abs() + (k + 4) * 2.0 ** -24 * (a[:m].double().abs() @ b.double().abs().t())
+    assert bool(((out[0].double() - ref).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("m,n,k", [(77, 200, 136), (1000, 768, 256), (1032, 2304, 192)])
+@pytest.mark.parametrize("epi", ["bias_residual", "gelu_aux", "gelu_grad", "f32"])
+def test_gemm_bf16_epilogues_on_every_tile_width(m, n, k, epi):
+    """The staged epilogues through the staging areas of tiles 64 and 128 columns wide against the 128x128 ones."""
+    gen = torch.Generator(device=DEV).manual_seed(m + n + k)
+    a, b, bias, res, z = _bf16(gen, m, k), _bf16(gen, n, k), _bf16(gen, n), _bf16(gen, m, n), _bf16(gen, m, n)
+    got = []
+    for tile in (0, 128):
+        c = torch.zeros((m, n), device=DEV, dtype=torch.float32 if epi == "f32" else torch.bfloat16)
+        aux = z.clone()
+        kw = {"bias_residual": dict(epilogue=S.SIF_EPI_BIAS | S.SIF_EPI_RESIDUAL, bias=bias, res=res), "gelu_aux": dict(epilogue=S.SIF_EPI_GELU, bias=bias, aux=aux),
+              "gelu_grad": dict(epilogue=S.SIF_EPI_GELU_GRAD, aux=aux), "f32": dict(epilogue=S.SIF_EPI_OUT_F32)}[epi]
+        torch.cuda.synchronize()
+        S.sif_k_gemm_bf16(a, b, c, m, n, k, k, k, n, tile=tile, **kw)
+        torch.cuda.synchronize()
+        got.append((c, aux))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    acc = a.double() @ b.double().t()
+    ref = {"bias_residual": acc + bias.double() + res.double(), "gelu_aux": torch.nn.functional.gelu(acc + bias.double()), "f32": acc,
+           "gelu_grad": acc * (0.5 * (1 + torch.erf(z.double() / 2 ** 0.5)) + z.double() * torch.exp(-z.double() ** 2 / 2) / (2 * torch.pi) ** 0.5)}[epi]
+    assert float((got[0][0].double() - ref).norm() / ref.norm()) <= 2.0 ** -8

@@ -32,20 +32,9 @@ constexpr int AT_QB = 64;                                    // query rows per s
 
 __device__ __forceinline__ uint32_t at_key(uint32_t row) { return (row & 7u) ^ ((row >> 3) & 1u); }
 
-// ROWS x DH tile of a row-major bf16 matrix (rows row0.., 16-byte aligned, ld elements apart) into LDS as
-// [row][d] with the 16-byte chunks of a row XOR-swizzled; rows >= limit read as zero.
-template <int DH, int ROWS>
-__device__ __forceinline__ void at_load_rows(bf16_t* dst, const bf16_t* src, size_t ld, uint32_t row0, uint32_t limit) {
-  constexpr int CH = DH / 8;
-  for (uint32_t v = threadIdx.x; v < ROWS * CH; v += AT_THREADS) {
-    const uint32_t row = v / CH, c = v % CH;
-    uint4 x = make_uint4(0, 0, 0, 0);
-    if (row0 + row < limit) x = *reinterpret_cast<const uint4*>(src + (size_t)(row0 + row) * ld + c * 8);
-    *reinterpret_cast<uint4*>(dst + row * DH + ((c ^ (at_key(row) % CH)) << 3)) = x;
-  }
-}
-// The same tile fetched from global memory straight into LDS (global_load_lds_dwordx4: no staging registers, the
-// fetch of the next tile runs while the current one is used).  One instruction writes the 64 lanes' 16 bytes to
+// ROWS x DH tile of a row-major bf16 matrix (rows row0.., 16-byte aligned, ld elements apart) into LDS as [row][d] with
+// the 16-byte chunks of a row XOR-swizzled, fetched from global memory straight into LDS (global_load_lds_dwordx4: no
+// staging registers, the fetch of the next tile runs while the current one is used).  One instruction writes the 64 lanes' 16 bytes to
 // consecutive LDS addresses, so a lane's place in the tile is fixed and the swizzle is applied to what it fetches.
 // Rows >= limit cannot be zero-filled: they fetch row limit - 1 instead (finite data), and every use of such a row is
 // either masked (scores) or multiplied by a probability of zero.
@@ -144,7 +133,8 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_kernel(const bf16_t* _
                                                               KCtl ctl) {
   constexpr int KS = DH / 16, DT = DH / 32;                   // k steps of q k^T, 32-wide d tiles
   // d_head 64: two K and two V tile buffers (as four objects, so that the compiler can tell the one being filled from
-  // the one being read), the next tile is fetched while the current one is used; d_head 128: LDS holds one of each
+  // the one being read), the next tile is fetched while the current one is used; d_head 128: LDS holds one of each for
+  // two blocks per CU, and a tile of K or V is fetched while the other is in use (see the second loop)
   constexpr bool DB = DH == 64;
   __shared__ __align__(1024) bf16_t sK0[AT_KV * DH];
   __shared__ __align__(1024) bf16_t sV0[AT_KV * DH];
@@ -181,7 +171,7 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_kernel(const bf16_t* _
   float m_run = -INFINITY, l_run = 0.f, l_true = 0.f;
 
   const uint32_t kv_end = CAUSAL ? min(S, q_blk + AT_Q) : S;
-  auto tile = [&](const bf16_t* sK, const bf16_t* sV, const uint32_t kv0) {
+  auto tile = [&](const bf16_t* sK, const bf16_t* sV, const uint32_t kv0, auto scores_taken) {
     // S^T tiles: rows = kv (32 per tile), columns = the wavefront's 32 query rows (straight-line code: the four
     // accumulator chains interleave; skipping the tiles above the diagonal would cost more than it saves)
     const bool need_mask = kv0 + AT_KV > S || (CAUSAL && kv0 + AT_KV - 1 > qw);
@@ -194,6 +184,7 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_kernel(const bf16_t* _
       for (int ks = 0; ks < KS; ++ks)
         sacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(at_frag<DH>(sK, t * 32 + qi, ks * 2 + h), fq[ks], sacc[t], 0, 0, 0);
     }
+    scores_taken();
     // mask (only tiles that meet the diagonal or the end of the sequence), running maximum of the raw scores
     float mx = -INFINITY;
     if (need_mask) {
@@ -269,7 +260,7 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_kernel(const bf16_t* _
         at_dma_rows<DH, AT_KV>(sK1, base + da, ld_qkv, kv0 + AT_KV, S);
         at_dma_rows<DH, AT_KV>(sV1, base + 2 * da, ld_qkv, kv0 + AT_KV, S);
       }
-      tile(sK0, sV0, kv0);
+      tile(sK0, sV0, kv0, [] {});
       if (more) {
         wait_fetches();
         __syncthreads();                                 // tile kv0 + 128 has landed, nobody reads buffer 0 any more
@@ -277,16 +268,27 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_kernel(const bf16_t* _
           at_dma_rows<DH, AT_KV>(sK0, base + da, ld_qkv, kv0 + 2 * AT_KV, S);
           at_dma_rows<DH, AT_KV>(sV0, base + 2 * da, ld_qkv, kv0 + 2 * AT_KV, S);
         }
-        tile(sK1, sV1, kv0 + AT_KV);
+        tile(sK1, sV1, kv0 + AT_KV, [] {});
       }
     }
   } else {
+    // V(t) travels under S = Q K^T, K(t + 1) under the softmax and P V; each barrier stands where one buffer has landed
+    // and the other is free.  (Both loaded through registers in front of a tile, nothing overlapped and in all three
+    // kernels it was those trips that a step waited for.  Forward, dq and dk/dv of 4 x 4 heads x 2048 rows now take 64,
+    // 94 and 102 us, 510 together before; 24 such layers' training step 51.7 -> 45.7 ms, six layers of 2 x 16 heads
+    // 21.6 -> 18.3 ms.)
+    at_dma_rows<DH, AT_KV>(sK0, base + da, ld_qkv, 0, S);
+    wait_fetches();
+    __syncthreads();
     for (uint32_t kv0 = 0; kv0 < kv_end; kv0 += AT_KV) {
+      at_dma_rows<DH, AT_KV>(sV0, base + 2 * da, ld_qkv, kv0, S);
+      tile(sK0, sV0, kv0, [&] {
+        wait_fetches();
+        __syncthreads();
+        if (kv0 + AT_KV < kv_end) at_dma_rows<DH, AT_KV>(sK0, base + da, ld_qkv, kv0 + AT_KV, S);
+      });
+      wait_fetches();
       __syncthreads();
-      at_load_rows<DH, AT_KV>(sK0, base + da, ld_qkv, kv0, S);
-      at_load_rows<DH, AT_KV>(sV0, base + 2 * da, ld_qkv, kv0, S);
-      __syncthreads();
-      tile(sK0, sV0, kv0);
     }
   }
 
@@ -298,7 +300,7 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_kernel(const bf16_t* _
 }
 
 // Backward, dq.  One block = 128 query rows of one (batch, head), a query row per lane pair as in the forward;
-// keys/values streamed in tiles of 128, K and V as [kv][d].  Also writes delta = rowsum(do .* o)
+// keys/values streamed in tiles of 128 or 64, K and V as [kv][d].  Also writes delta = rowsum(do .* o)
 // for the dk/dv kernel.
 template <int DH, int CAUSAL>
 __global__ __launch_bounds__(AT_THREADS, 2) void attn_bwd_dq_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
@@ -306,11 +308,12 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_bwd_dq_kernel(const bf16_t
                                                                  float* __restrict__ delta, bf16_t* __restrict__ dqkv, uint32_t S, uint32_t H,
                                                                  uint32_t ld_qkv, uint32_t ld_o, uint32_t ld_dqkv, float scale, KCtl ctl) {
   constexpr int KS = DH / 16, DT = DH / 32;
-  constexpr bool DB = DH == 64;                               // two tile buffers each, as in the forward kernel
-  __shared__ __align__(1024) bf16_t sK0[AT_KV * DH];
-  __shared__ __align__(1024) bf16_t sV0[AT_KV * DH];
-  __shared__ __align__(1024) bf16_t sK1[DB ? AT_KV * DH : 8];
-  __shared__ __align__(1024) bf16_t sV1[DB ? AT_KV * DH : 8];
+  // two tile buffers each, as in the forward kernel; tiles of 64 keys with d_head 128, so that two blocks of a CU find room
+  constexpr int KV = DH == 64 ? AT_KV : AT_KV / 2;
+  __shared__ __align__(1024) bf16_t sK0[KV * DH];
+  __shared__ __align__(1024) bf16_t sV0[KV * DH];
+  __shared__ __align__(1024) bf16_t sK1[KV * DH];
+  __shared__ __align__(1024) bf16_t sV1[KV * DH];
   if (!kernel_begin(ctl)) { kernel_end(ctl, false); return; }
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, qi = lane & 31, h = lane >> 5;
   const uint32_t bh = blockIdx.x, b = bh / H, head = bh % H, da = H * DH;
@@ -350,9 +353,9 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_bwd_dq_kernel(const bf16_t
 
   const uint32_t kv_end = CAUSAL ? min(S, q_blk + AT_Q) : S;
   auto tile = [&](const bf16_t* sK, const bf16_t* sV, const uint32_t kv0) {
-    const bool need_mask = kv0 + AT_KV > S || (CAUSAL && kv0 + AT_KV - 1 > qw);
+    const bool need_mask = kv0 + KV > S || (CAUSAL && kv0 + KV - 1 > qw);
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
+    for (int t = 0; t < KV / 32; ++t) {
       floatx16 sacc, pacc;
 #pragma unroll
       for (int r = 0; r < 16; ++r) { sacc[r] = 0.f; pacc[r] = 0.f; }
@@ -380,39 +383,30 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_bwd_dq_kernel(const bf16_t
       }
     }
   };
-  if constexpr (DB) {
-    at_dma_rows<DH, AT_KV>(sK0, base + da, ld_qkv, 0, S);
-    at_dma_rows<DH, AT_KV>(sV0, base + 2 * da, ld_qkv, 0, S);
-    for (uint32_t kv0 = 0; kv0 < kv_end; kv0 += 2 * AT_KV) {
-      wait_fetches();
-      __syncthreads();                                   // tile kv0 has landed, nobody reads buffer 1 any more
-      const bool more = kv0 + AT_KV < kv_end;
-      if (more) {
-        at_dma_rows<DH, AT_KV>(sK1, base + da, ld_qkv, kv0 + AT_KV, S);
-        at_dma_rows<DH, AT_KV>(sV1, base + 2 * da, ld_qkv, kv0 + AT_KV, S);
-      }
-      tile(sK0, sV0, kv0);
-      if (more) {
-        wait_fetches();
-        __syncthreads();
-        if (kv0 + 2 * AT_KV < kv_end) {
-          at_dma_rows<DH, AT_KV>(sK0, base + da, ld_qkv, kv0 + 2 * AT_KV, S);
-          at_dma_rows<DH, AT_KV>(sV0, base + 2 * da, ld_qkv, kv0 + 2 * AT_KV, S);
-        }
-        tile(sK1, sV1, kv0 + AT_KV);
-      }
+  at_dma_rows<DH, KV>(sK0, base + da, ld_qkv, 0, S);
+  at_dma_rows<DH, KV>(sV0, base + 2 * da, ld_qkv, 0, S);
+  for (uint32_t kv0 = 0; kv0 < kv_end; kv0 += 2 * KV) {
+    wait_fetches();
+    __syncthreads();                                   // tile kv0 has landed, nobody reads buffer 1 any more
+    const bool more = kv0 + KV < kv_end;
+    if (more) {
+      at_dma_rows<DH, KV>(sK1, base + da, ld_qkv, kv0 + KV, S);
+      at_dma_rows<DH, KV>(sV1, base + 2 * da, ld_qkv, kv0 + KV, S);
     }
-  } else {
-    for (uint32_t kv0 = 0; kv0 < kv_end; kv0 += AT_KV) {
+    tile(sK0, sV0, kv0);
+    if (more) {
+      wait_fetches();
       __syncthreads();
-      at_load_rows<DH, AT_KV>(sK0, base + da, ld_qkv, kv0, S);
-      at_load_rows<DH, AT_KV>(sV0, base + 2 * da, ld_qkv, kv0, S);
-      __syncthreads();
-      tile(sK0, sV0, kv0);
+      if (kv0 + 2 * KV < kv_end) {
+        at_dma_rows<DH, KV>(sK0, base + da, ld_qkv, kv0 + 2 * KV, S);
+        at_dma_rows<DH, KV>(sV0, base + 2 * da, ld_qkv, kv0 + 2 * KV, S);
+      }
+      tile(sK1, sV1, kv0 + KV);
     }
   }
-  __syncthreads();                                         // nobody reads the last K/V tile any more: sK0 stages dq
-  at_store_tile<DH>(sK0 + wave * (32 * DH), dqacc, 1.0f, dqkv + ((size_t)b * S + qw) * ld_dqkv + head * DH, ld_dqkv, qw < S ? S - qw : 0u);
+  __syncthreads();                                         // nobody reads the last K/V tile any more: their buffers stage dq
+  bf16_t* stage = KV == AT_KV || wave < 2 ? sK0 + wave * (32 * DH) : sV0 + (wave - 2) * (32 * DH);
+  at_store_tile<DH>(stage, dqacc, 1.0f, dqkv + ((size_t)b * S + qw) * ld_dqkv + head * DH, ld_dqkv, qw < S ? S - qw : 0u);
   kernel_end(ctl, true);
 }
 
@@ -424,11 +418,12 @@ __global__ __launch_bounds__(AT_THREADS, DH == 64 ? 2 : 1) void attn_bwd_dkv_ker
                                                                   bf16_t* __restrict__ dqkv, uint32_t S, uint32_t H, uint32_t ld_qkv,
                                                                   uint32_t ld_o, uint32_t ld_dqkv, float scale, KCtl ctl) {
   constexpr int KS = DH / 16, DT = DH / 32;
-  constexpr bool DB = DH == 64;                               // two buffers of everything that is streamed, as in the forward kernel
+  // two buffers of everything that is streamed, as in the forward kernel (with d_head 128 too: its registers allow one
+  // block per CU, so the LDS is there)
   __shared__ __align__(1024) bf16_t sQ0[AT_QB * DH];
   __shared__ __align__(1024) bf16_t sDo0[AT_QB * DH];
-  __shared__ __align__(1024) bf16_t sQ1[DB ? AT_QB * DH : 8];
-  __shared__ __align__(1024) bf16_t sDo1[DB ? AT_QB * DH : 8];
+  __shared__ __align__(1024) bf16_t sQ1[AT_QB * DH];
+  __shared__ __align__(1024) bf16_t sDo1[AT_QB * DH];
   __shared__ __align__(16) float sL0[AT_QB];
   __shared__ __align__(16) float sD0[AT_QB];
   __shared__ __align__(16) float sL1[AT_QB];
@@ -513,41 +508,30 @@ __global__ __launch_bounds__(AT_THREADS, DH == 64 ? 2 : 1) void attn_bwd_dkv_ker
     }
   };
   const uint32_t q_first = CAUSAL ? (kv_blk / AT_QB) * AT_QB : 0;
-  if constexpr (DB) {
-    if (q_first < S) {
-      at_dma_rows<DH, AT_QB>(sQ0, base, ld_qkv, q_first, S);
-      at_dma_rows<DH, AT_QB>(sDo0, dobase, ld_o, q_first, S);
-      load_vectors(sL0, sD0, q_first);
+  if (q_first < S) {
+    at_dma_rows<DH, AT_QB>(sQ0, base, ld_qkv, q_first, S);
+    at_dma_rows<DH, AT_QB>(sDo0, dobase, ld_o, q_first, S);
+    load_vectors(sL0, sD0, q_first);
+  }
+  for (uint32_t q0 = q_first; q0 < S; q0 += 2 * AT_QB) {
+    wait_fetches();
+    __syncthreads();                                   // step q0 has landed, nobody reads buffer 1 any more
+    const bool more = q0 + AT_QB < S;
+    if (more) {
+      at_dma_rows<DH, AT_QB>(sQ1, base, ld_qkv, q0 + AT_QB, S);
+      at_dma_rows<DH, AT_QB>(sDo1, dobase, ld_o, q0 + AT_QB, S);
+      load_vectors(sL1, sD1, q0 + AT_QB);
     }
-    for (uint32_t q0 = q_first; q0 < S; q0 += 2 * AT_QB) {
+    tile(sQ0, sDo0, sL0, sD0, q0);
+    if (more) {
       wait_fetches();
-      __syncthreads();                                   // step q0 has landed, nobody reads buffer 1 any more
-      const bool more = q0 + AT_QB < S;
-      if (more) {
-        at_dma_rows<DH, AT_QB>(sQ1, base, ld_qkv, q0 + AT_QB, S);
-        at_dma_rows<DH, AT_QB>(sDo1, dobase, ld_o, q0 + AT_QB, S);
-        load_vectors(sL1, sD1, q0 + AT_QB);
-      }
-      tile(sQ0, sDo0, sL0, sD0, q0);
-      if (more) {
-        wait_fetches();
-        __syncthreads();
-        if (q0 + 2 * AT_QB < S) {
-          at_dma_rows<DH, AT_QB>(sQ0, base, ld_qkv, q0 + 2 * AT_QB, S);
-          at_dma_rows<DH, AT_QB>(sDo0, dobase, ld_o, q0 + 2 * AT_QB, S);
-          load_vectors(sL0, sD0, q0 + 2 * AT_QB);
-        }
-        tile(sQ1, sDo1, sL1, sD1, q0 + AT_QB);
-      }
-    }
-  } else {
-    for (uint32_t q0 = q_first; q0 < S; q0 += AT_QB) {
       __syncthreads();
-      at_load_rows<DH, AT_QB>(sQ0, base, ld_qkv, q0, S);
-      at_load_rows<DH, AT_QB>(sDo0, dobase, ld_o, q0, S);
-      load_vectors(sL0, sD0, q0);
-      __syncthreads();
-      tile(sQ0, sDo0, sL0, sD0, q0);
+      if (q0 + 2 * AT_QB < S) {
+        at_dma_rows<DH, AT_QB>(sQ0, base, ld_qkv, q0 + 2 * AT_QB, S);
+        at_dma_rows<DH, AT_QB>(sDo0, dobase, ld_o, q0 + 2 * AT_QB, S);
+        load_vectors(sL0, sD0, q0 + 2 * AT_QB);
+      }
+      tile(sQ1, sDo1, sL1, sD1, q0 + AT_QB);
     }
   }
   __syncthreads();                                         // nobody reads the last Q/dO step any more: its buffers stage dk, then dv

@@ -147,3 +147,34 @@ def test_gemm_bf16_epilogues_on_every_tile_width(m, n, k, epi):
     ref = {"bias_residual": acc + bias.double() + res.double(), "gelu_aux": torch.nn.functional.gelu(acc + bias.double()), "f32": acc,
            "gelu_grad": acc * (0.5 * (1 + torch.erf(z.double() / 2 ** 0.5)) + z.double() * torch.exp(-z.double() ** 2 / 2) / (2 * torch.pi) ** 0.5)}[epi]
     assert float((got[0][0].double() - ref).norm() / ref.norm()) <= 2.0 ** -8
+
+
+@pytest.mark.parametrize("causal", [0, 1])
+@pytest.mark.parametrize("bsz,s,h", [(2, 2, 2), (1, 63, 1), (2, 65, 2), (1, 129, 3), (2, 192, 1), (1, 257, 2), (1, 449, 1)])
+def test_attention_with_heads_of_128_at_the_edges_of_its_tiles(bsz, s, h, causal):
+    """K and V fetched in turns (forward), in 64-key tiles (dq), q and do in 64-query steps (dk, dv): one tile, an odd and
+    an even number of them, remainders of one row and of all but one.  Bounds: those of the fused attention's other tests, and in dq and dk what
+    rowsum(do o) is off by for an o rounded to bf16 (2^-8 sum |do| |o|): with two keys a gradient is a small difference of
+    such sums."""
+    from oracle.decoder import attention_bwd, attention_fwd
+    from oracle.numerics import Prec
+    from gpu_util import assert_bf16_close
+    rng, da = np.random.default_rng(s + 7 * causal), 128 * h
+    Q, DO = (torch.from_numpy(rng.standard_normal((bsz, s, n), dtype=np.float32)).to(DEV).to(torch.bfloat16) for n in (3 * da, da))
+    o, dqkv = torch.zeros((bsz, s, da), device=DEV, dtype=torch.bfloat16), torch.full((bsz, s, 3 * da), 5.0, device=DEV, dtype=torch.bfloat16)
+    lse, delta = torch.zeros((bsz * h, s), device=DEV), torch.zeros((bsz * h, s), device=DEV)
+    torch.cuda.synchronize()
+    S.sif_k_attn_fwd(Q, o, bsz, s, h, 128, 3 * da, da, causal, lse=lse)
+    S.sif_k_attn_bwd(Q, o, DO, lse, delta, dqkv, bsz, s, h, 128, 3 * da, da, 3 * da, causal)
+    torch.cuda.synchronize()
+    prec, qkv, do = Prec("bf16"), up(Q), up(DO)
+    ref_o, prob = attention_fwd(qkv, h, 128, bool(causal), prec)
+    ref = attention_bwd(do, qkv, prob, h, 128, prec)
+    assert_bf16_close(up(o), ref_o, "o", elem_slack=4e-3)
+    heads = lambda x: x.reshape(bsz, s, h, 128).transpose(0, 2, 1, 3)
+    back = lambda x: x.transpose(0, 2, 1, 3).reshape(bsz, s, da)
+    err = prob * (2.0 ** -8 / 128 ** 0.5 * (np.abs(heads(do)) * np.abs(heads(ref_o))).sum(-1)[..., None])
+    aq, ak = np.abs(heads(qkv[..., :da])), np.abs(heads(qkv[..., da:2 * da]))
+    for name, lo, extra in (("dq", 0, back(err @ ak)), ("dk", da, back(err.transpose(0, 1, 3, 2) @ aq)), ("dv", 2 * da, 0.0)):
+        got, want = up(dqkv)[..., lo:lo + da], ref[..., lo:lo + da]
+        assert np.all(np.abs(got - want) <= 2.0 ** -7 * np.abs(want) + 6e-3 * np.abs(want).max() + extra), name

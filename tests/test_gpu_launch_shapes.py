@@ -178,3 +178,30 @@ def test_attention_with_heads_of_128_at_the_edges_of_its_tiles(bsz, s, h, causal
     for name, lo, extra in (("dq", 0, back(err @ ak)), ("dk", da, back(err.transpose(0, 1, 3, 2) @ aq)), ("dv", 2 * da, 0.0)):
         got, want = up(dqkv)[..., lo:lo + da], ref[..., lo:lo + da]
         assert np.all(np.abs(got - want) <= 2.0 ** -7 * np.abs(want) + 6e-3 * np.abs(want).max() + extra), name
+
+
+@pytest.mark.parametrize("with_sum", [False, True])
+@pytest.mark.parametrize("rows,d,shift", [(1, 2056, 0), (17, 2056, 1), (33, 4088, 0), (530, 4096, 0), (8200, 2568, 1)])
+def test_layernorm_backward_of_rows_wider_than_2048(rows, d, shift, with_sum):
+    """A row per block: one row, an odd number of rows per block, blocks without rows, vectors past the row's end, partial
+    sums that are not 16-byte aligned.  Bounds: those of the other LayerNorm test; the column sums of n rows are fp32 sums,
+    which err by at most (n + 4) 2^-24 of their terms' magnitudes, and are rounded to bf16 once (2^-8)."""
+    from oracle import numerics as N
+    from gpu_util import assert_bf16_close
+    gen = torch.Generator(device=DEV).manual_seed(rows + d)
+    X, DY, R, G = _bf16(gen, rows, d) * 2, _bf16(gen, rows, d), _bf16(gen, rows, d), _bf16(gen, d) + 1
+    x, dy, res, g = up(X), up(DY), up(R), up(G)
+    _, mu, rs = N.layernorm_fwd(x, g, np.zeros(d))
+    dx, dg, db = torch.zeros_like(X), torch.zeros_like(G), torch.zeros_like(G)
+    dsum = torch.zeros_like(G) if with_sum else None
+    part = torch.full((3 * S.sif_colsum_parts(rows) * d + 4,), float("nan"), device=DEV)[shift:]
+    mean, rstd = f32(mu[:, 0].astype(np.float32)), f32(rs[:, 0].astype(np.float32))
+    torch.cuda.synchronize()
+    S.sif_k_layernorm_bwd(DY, X, G, mean, rstd, R, dx, dg, db, part, rows, d, dsum=dsum)
+    torch.cuda.synchronize()
+    rdx, rdg, _ = N.layernorm_bwd(dy, x, g, mu, rs)
+    assert_bf16_close(up(dx), res + rdx, "dx")
+    assert_bf16_close(up(dg), rdg, "dg")
+    for got, terms in ((db, dy),) + (((dsum, up(dx)),) if with_sum else ()):
+        want = terms.sum(0)
+        assert np.all(np.abs(up(got) - want) <= 2.0 ** -8 * np.abs(want) + (rows + 4) * 2.0 ** -24 * np.abs(terms).sum(0))

@@ -33,11 +33,11 @@ os.environ.setdefault("HIP_FORCE_DEV_KERNARG", "1")
 
 MFMA_BF16_PEAK_TFLOPS = 2500.0
 HBM_PEAK_TBPS = 8.0
-# Average bytes per dispatch of gemm_bf16_kernel<0,0> that pass between the L2s and the memory side in the headline
+# Average bytes per dispatch of the bf16 product with both operands K-contiguous (before the ring and ping-pong kernels) that pass between the L2s and the memory side in the headline
 # workload, from the FETCH_SIZE / WRITE_SIZE counter runs summarised in the file named beside it (counters cannot be
 # read from inside a timed run).
 GEMM00_HBM_BYTES_PER_LAUNCH = 754.7e6
-GEMM00_HBM_BYTES_SOURCE = "constant from profiles/bench_cfg2_hbm_traffic.md (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this command)"
+GEMM00_HBM_BYTES_SOURCE = "constant from profiles/bench_cfg2_hbm_traffic.md (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this command; of the product kernel before the ring and ping-pong ones)"
 PROF_SAMPLED = 3     # sif_profile_gemm: event pairs around every third launch of the a_layout = b_layout = 0 variant per stream
 N_RING = 64          # distinct input / output buffers the queued requests cycle through (a coalesced group is 32)
 
@@ -657,7 +657,7 @@ def main():
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / MFMA_BF16_PEAK_TFLOPS, "traffic": GEMM00_HBM_BYTES_PER_LAUNCH, "traffic_source": GEMM00_HBM_BYTES_SOURCE,
                      "algorithmic_flops_per_launch": (f00 / n00) if n00 else None,
-                     "kernel": "gemm_bf16_kernel<0,0>", "launches": int(n00), "launches_are": "every third launch of the kernel on each stream in the timed region (HIP event pairs)",
+                     "kernel": "gemm_ring_kernel<0,0> / gemm_pp_kernel<0,0>", "launches": int(n00), "launches_are": "every third launch of the kernel on each stream in the timed region (HIP event pairs)",
                      "avg_us": (1e6 * t00 / n00) if n00 else None,
                      "all_gemm_variants_tflops": (all_f / all_t / 1e12) if all_t > 0 else None},
         "paper_context": "paper (4x A100-40GB): up to 14x offline throughput over TGS, 67% lower online p95 than MPS; not comparable",

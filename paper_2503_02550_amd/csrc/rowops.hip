@@ -233,95 +233,136 @@ __global__ __launch_bounds__(256) void layernorm_bwd_kernel(const bf16_t* __rest
   kernel_end(ctl, true);
 }
 
-// The same for rows of more than 2048 columns: a row per block.  A wavefront per row would hold 3 x 64 sums per lane, with
-// no room for the row itself: it read everything twice, with nothing in flight across its reductions (155 us for 8192 x
-// 4096, 268 MB).  Here a thread owns 16 columns of every row of the block's range: row and next row in registers, one
-// barrier per row, no sums to combine at the end: a training step of 24 layers with two such launches each 46.5 -> 41.5 ms,
-// 105 us less per launch.
+// The same for rows of more than 2048 columns, with the sums in the same order and so with the same bits.  A wavefront
+// that kept a row and its 3 x 64 sums per lane in registers would be alone on its SIMD (without keeping the row it read
+// everything twice, nothing in flight across its reductions: 165 us for 8192 x 4096, 268 MB).  So the two jobs are dealt
+// differently: a wavefront takes a row, which gives the row's two sums in the wavefront's order, and leaves it in LDS; then
+// a thread takes 16 columns of the group's four rows, and four wavefronts' column sums of the variant above become sums
+// of the rows 0, 4, 8, .. of the block's range, then of 1, 5, 9, .. and so on, each added to what the earlier ones gave:
+// rows are taken in that order.  The next group's rows travel while the columns are worked on, two blocks to a CU.
+// 8192 x 4096: 64 us, 4.2 TB/s of the copy's 5.1.  (A thread that took 16 columns of one row after the other, its sums
+// through all of them, was 61 us; its chains of 16 to 32 additions in place of 4 to 8 raised the column sums' error against
+// 64 bits from 6.6e-8 to 8.1e-8 at 8192 rows and from 7.5e-8 to 1.07e-7 at 16384.)
 template <bool WITH_SUM>
-__global__ __launch_bounds__(256) void layernorm_bwd_wide_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ x,
-                                                                 const bf16_t* __restrict__ g, const float* __restrict__ mean,
-                                                                 const float* __restrict__ rstd, const bf16_t* __restrict__ res,
-                                                                 bf16_t* __restrict__ dx, float* __restrict__ part,
-                                                                 uint32_t rows, uint32_t d, uint32_t parts, KCtl ctl) {
-  constexpr int NV = 2, NSUM = WITH_SUM ? 3 : 2;
+__global__ __launch_bounds__(256, 2) void layernorm_bwd_wide_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ x,
+                                                                    const bf16_t* __restrict__ g, const float* __restrict__ mean,
+                                                                    const float* __restrict__ rstd, const bf16_t* __restrict__ res,
+                                                                    bf16_t* __restrict__ dx, float* __restrict__ part,
+                                                                    uint32_t rows, uint32_t d, uint32_t parts, KCtl ctl) {
+  constexpr int NV = 2, NSUM = WITH_SUM ? 3 : 2, MAXV = LN_MAXV;
   static_assert(NV * 256 >= 64 * LN_MAXV, "a thread's vectors cover the widest row");
-  __shared__ float2 sred[2][4];
+  __shared__ uint4 s_dy[4][64 * MAXV], s_x[4][64 * MAXV], s_g[64 * MAXV];
+  __shared__ float4 s_stat[4];                 // mean, rstd and the two means of the group's rows
   if (!kernel_begin(ctl)) { kernel_end(ctl, false); return; }
-  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nv = d >> 3;
+  const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nv = d >> 3;
   const uint32_t rows_per = (rows + parts - 1) / parts;
-  const uint32_t r_begin = blockIdx.x * rows_per, r_end = min(rows, r_begin + rows_per);
-  float acc[NSUM][NV][8];
-  uint4 cg[NV], ndy[NV], nx[NV], nres[NV];
+  const uint32_t r_begin = min(rows, blockIdx.x * rows_per), count = min(rows - r_begin, rows_per);
+  // the q-th row in the order above, and which of the four sums it belongs to
+  const uint32_t b1 = (count + 3) / 4, b2 = b1 + (count + 2) / 4, b3 = b2 + (count + 1) / 4;
+  auto sum_of = [&](uint32_t q) { return (q >= b1 ? 1u : 0u) + (q >= b2 ? 1u : 0u) + (q >= b3 ? 1u : 0u); };
+  auto row_of = [&](uint32_t q) {
+    const uint32_t c = sum_of(q);
+    return r_begin + c + 4 * (q - (c == 0 ? 0 : c == 1 ? b1 : c == 2 ? b2 : b3));
+  };
+  float acc[NSUM][NV][8], total[NSUM][NV][8];
+#pragma unroll
+  for (int w = 0; w < NSUM; ++w)
+#pragma unroll
+    for (int t = 0; t < NV; ++t)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[w][t][i] = total[w][t][i] = 0.f;
+  uint4 ndy[MAXV], nx[MAXV];
   float nmu = 0.f, nrs = 0.f;
+  // (loads without conditions: past the row's end a lane reads its last vector, past the last row the last one)
+  auto fetch_row = [&](uint32_t q) {
+    const uint32_t row = row_of(min(q, count - 1));
+    const uint4* dyr = reinterpret_cast<const uint4*>(dy) + (size_t)row * nv;
+    const uint4* xr = reinterpret_cast<const uint4*>(x) + (size_t)row * nv;
+#pragma unroll
+    for (int t = 0; t < MAXV; ++t) {
+      const uint32_t v = min(lane + 64 * t, nv - 1);
+      ndy[t] = dyr[v];
+      nx[t] = xr[v];
+    }
+    nmu = mean[row]; nrs = rstd[row];
+  };
 #pragma unroll
   for (int t = 0; t < NV; ++t) {
     const uint32_t v = threadIdx.x + 256 * t;
-    cg[t] = v < nv ? reinterpret_cast<const uint4*>(g)[v] : make_uint4(0, 0, 0, 0);
-#pragma unroll
-    for (int w = 0; w < NSUM; ++w)
-#pragma unroll
-      for (int i = 0; i < 8; ++i) acc[w][t][i] = 0.f;
+    if (v < nv) s_g[v] = reinterpret_cast<const uint4*>(g)[v];
   }
-  auto fetch_row = [&](uint32_t r) {
+  if (count > 0) fetch_row(wave);
+  __syncthreads();
+  uint32_t cur = 0;
+  for (uint32_t q0 = 0; q0 < count; q0 += 4) {
+    uint4 cres[4][NV];
+    if (res != nullptr) {
 #pragma unroll
-    for (int t = 0; t < NV; ++t) {
-      const uint32_t v = threadIdx.x + 256 * t;
-      const size_t at = (size_t)r * nv + v;
-      ndy[t] = v < nv ? reinterpret_cast<const uint4*>(dy)[at] : make_uint4(0, 0, 0, 0);
-      nx[t] = v < nv ? reinterpret_cast<const uint4*>(x)[at] : make_uint4(0, 0, 0, 0);
-      nres[t] = (res != nullptr && v < nv) ? reinterpret_cast<const uint4*>(res)[at] : make_uint4(0, 0, 0, 0);
+      for (int u = 0; u < 4; ++u) {
+        const uint4* rr = reinterpret_cast<const uint4*>(res) + (size_t)row_of(min(q0 + u, count - 1)) * nv;
+#pragma unroll
+        for (int t = 0; t < NV; ++t) cres[u][t] = rr[min(threadIdx.x + 256 * t, nv - 1)];
+      }
     }
-    nmu = mean[r]; nrs = rstd[r];
-  };
-  if (r_begin < r_end) fetch_row(r_begin);
-  for (uint32_t row = r_begin; row < r_end; ++row) {
-    uint4 cdy[NV], cx[NV], cres[NV];
-#pragma unroll
-    for (int t = 0; t < NV; ++t) { cdy[t] = ndy[t]; cx[t] = nx[t]; cres[t] = nres[t]; }
-    const float mu = nmu, rs = nrs;
-    if (row + 1 < r_end) fetch_row(row + 1);
     float s1 = 0.f, s2 = 0.f;
 #pragma unroll
-    for (int t = 0; t < NV; ++t) {
-      if (threadIdx.x + 256 * t >= nv) continue;
-      float fdy[8], fx[8], fg[8];
-      unpack8(cdy[t], fdy); unpack8(cx[t], fx); unpack8(cg[t], fg);
+    for (int t = 0; t < MAXV; ++t) {
+      const uint32_t v = lane + 64 * t;
+      if (v < nv) {
+        float fdy[8], fx[8], fg[8];
+        unpack8(ndy[t], fdy); unpack8(nx[t], fx); unpack8(s_g[v], fg);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const float xh = (fx[i] - mu) * rs, dxh = fdy[i] * fg[i];
-        s1 += dxh; s2 += dxh * xh;
-        acc[0][t][i] += fdy[i] * xh; acc[1][t][i] += fdy[i];
+        for (int i = 0; i < 8; ++i) {
+          const float xh = (fx[i] - nmu) * nrs, dxh = fdy[i] * fg[i];
+          s1 += dxh; s2 += dxh * xh;
+        }
       }
+      s_dy[wave][v] = ndy[t];
+      s_x[wave][v] = nx[t];
     }
-    s1 = wave_sum(s1); s2 = wave_sum(s2);
-    // two sets of slots in turn: nobody writes a set again before everyone has passed the next row's barrier
-    float2* slots = sred[(row - r_begin) & 1u];
-    if (lane == 0) slots[wave] = make_float2(s1, s2);
+    const float m1 = wave_sum(s1) / (float)d, m2 = wave_sum(s2) / (float)d;
+    if (lane == 0) s_stat[wave] = make_float4(nmu, nrs, m1, m2);
+    if (q0 + 4 < count) fetch_row(q0 + 4 + wave);
     __syncthreads();
-    const float m1 = (((slots[0].x + slots[1].x) + slots[2].x) + slots[3].x) / (float)d;
-    const float m2 = (((slots[0].y + slots[1].y) + slots[2].y) + slots[3].y) / (float)d;
 #pragma unroll
-    for (int t = 0; t < NV; ++t) {
-      const uint32_t v = threadIdx.x + 256 * t;
-      if (v >= nv) continue;
-      float fdy[8], fx[8], fg[8], fr[8], o[8];
-      unpack8(cdy[t], fdy); unpack8(cx[t], fx); unpack8(cg[t], fg);
-      if (res != nullptr) unpack8(cres[t], fr);
+    for (int u = 0; u < 4; ++u) {
+      const uint32_t q = q0 + u;
+      if (q >= count) break;
+      uint4* dxr = reinterpret_cast<uint4*>(dx) + (size_t)row_of(q) * nv;
+      if (sum_of(q) != cur) {
+        cur = sum_of(q);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const float xh = (fx[i] - mu) * rs;
-        o[i] = rs * (fdy[i] * fg[i] - m1 - xh * m2);
-        if (res != nullptr) o[i] += fr[i];
+        for (int w = 0; w < NSUM; ++w)
+#pragma unroll
+          for (int t = 0; t < NV; ++t)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) { total[w][t][i] += acc[w][t][i]; acc[w][t][i] = 0.f; }
       }
-      const uint4 packed = pack8(o);
-      reinterpret_cast<uint4*>(dx)[(size_t)row * nv + v] = packed;
-      if (WITH_SUM) {
-        unpack8(packed, o);                  // the column sums are those of the stored (rounded) values
+      const float4 st = s_stat[u];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) acc[NSUM - 1][t][i] += o[i];
+      for (int t = 0; t < NV; ++t) {
+        const uint32_t v = threadIdx.x + 256 * t;
+        if (v >= nv) continue;
+        float fdy[8], fx[8], fg[8], fr[8], o[8];
+        unpack8(s_dy[u][v], fdy); unpack8(s_x[u][v], fx); unpack8(s_g[v], fg);
+        if (res != nullptr) unpack8(cres[u][t], fr);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const float xh = (fx[i] - st.x) * st.y;
+          acc[0][t][i] += fdy[i] * xh; acc[1][t][i] += fdy[i];
+          o[i] = st.y * (fdy[i] * fg[i] - st.z - xh * st.w);
+          if (res != nullptr) o[i] += fr[i];
+        }
+        const uint4 packed = pack8(o);
+        dxr[v] = packed;
+        if (WITH_SUM) {
+          unpack8(packed, o);                  // the column sums are those of the stored (rounded) values
+#pragma unroll
+          for (int i = 0; i < 8; ++i) acc[NSUM - 1][t][i] += o[i];
+        }
       }
     }
+    __syncthreads();                           // the group's rows are done with
   }
   const bool wide = (reinterpret_cast<uintptr_t>(part) & 15u) == 0;
 #pragma unroll
@@ -330,13 +371,16 @@ __global__ __launch_bounds__(256) void layernorm_bwd_wide_kernel(const bf16_t* _
     for (int t = 0; t < NV; ++t) {
       const uint32_t v = threadIdx.x + 256 * t;
       if (v >= nv) continue;
+      float s[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) s[i] = total[w][t][i] + acc[w][t][i];
       float* to = part + (size_t)(w * parts + blockIdx.x) * d + 8 * v;
       if (wide) {
-        reinterpret_cast<float4*>(to)[0] = make_float4(acc[w][t][0], acc[w][t][1], acc[w][t][2], acc[w][t][3]);
-        reinterpret_cast<float4*>(to)[1] = make_float4(acc[w][t][4], acc[w][t][5], acc[w][t][6], acc[w][t][7]);
+        reinterpret_cast<float4*>(to)[0] = make_float4(s[0], s[1], s[2], s[3]);
+        reinterpret_cast<float4*>(to)[1] = make_float4(s[4], s[5], s[6], s[7]);
       } else {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) to[i] = acc[w][t][i];
+        for (int i = 0; i < 8; ++i) to[i] = s[i];
       }
     }
   kernel_end(ctl, true);

@@ -183,7 +183,7 @@ def test_attention_with_heads_of_128_at_the_edges_of_its_tiles(bsz, s, h, causal
 @pytest.mark.parametrize("with_sum", [False, True])
 @pytest.mark.parametrize("rows,d,shift", [(1, 2056, 0), (17, 2056, 1), (33, 4088, 0), (530, 4096, 0), (8200, 2568, 1)])
 def test_layernorm_backward_of_rows_wider_than_2048(rows, d, shift, with_sum):
-    """A row per block: one row, an odd number of rows per block, blocks without rows, vectors past the row's end, partial
+    """Groups of four rows in a block: one row, an odd number of rows per block, blocks without rows, vectors past the row's end, partial
     sums that are not 16-byte aligned.  Bounds: those of the other LayerNorm test; the column sums of n rows are fp32 sums,
     which err by at most (n + 4) 2^-24 of their terms' magnitudes, and are rounded to bf16 once (2^-8)."""
     from oracle import numerics as N
@@ -205,3 +205,55 @@ def test_layernorm_backward_of_rows_wider_than_2048(rows, d, shift, with_sum):
     for got, terms in ((db, dy),) + (((dsum, up(dx)),) if with_sum else ()):
         want = terms.sum(0)
         assert np.all(np.abs(up(got) - want) <= 2.0 ** -8 * np.abs(want) + (rows + 4) * 2.0 ** -24 * np.abs(terms).sum(0))
+
+
+@pytest.mark.parametrize("rows,d", [(1, 2056), (3, 4096), (17, 2056), (33, 4088), (530, 4096), (8200, 2568), (16400, 2560)])
+def test_layernorm_backward_of_wide_rows_sums_in_the_order_of_narrow_ones(rows, d):
+    """The order of every sum is that of a wavefront per row: lane l of 64 adds the row's terms of columns 8 (l + 64 t) + i by
+    ascending t and i and the lanes are joined by halves; a block's column sums are those of its rows 0, 4, 8, .., of 1, 5, 9,
+    .. and so on, added in turn.  So longer chains of additions (another error against 64 bits) fail here, at blocks of one
+    row, of remainders and of more rows than a block takes at a time.  fp32 steps are taken in 64 bits and rounded once, a
+    product that feeds a sum only there, as the fused operations do; all bits must agree."""
+    gen = torch.Generator(device=DEV).manual_seed(3 * rows + d)
+    X, DY, R, G = _bf16(gen, rows, d) * 2, _bf16(gen, rows, d), _bf16(gen, rows, d), _bf16(gen, d) + 1
+    mean = X.float().mean(1)
+    rstd = 1 / (X.float().var(1, unbiased=False) + 1e-5).sqrt()
+    dx, outs = torch.zeros_like(X), [torch.zeros_like(G) for _ in range(3)]
+    parts = S.sif_colsum_parts(rows)
+    part = torch.full((3, parts, d), float("nan"), device=DEV)
+    torch.cuda.synchronize()
+    S.sif_k_layernorm_bwd(DY, X, G, mean, rstd, R, dx, outs[0], outs[1], part, rows, d, dsum=outs[2])
+    torch.cuda.synchronize()
+
+    r32 = lambda v: v.float().double()
+    dy, g, m, rs = DY.double(), G.double(), mean.double()[:, None], rstd.double()[:, None]
+    xh, dxh = r32(r32(X.double() - m) * rs), r32(dy * g)
+    chunks = (d + 511) // 512
+
+    def row_mean(a, b):                          # of a b, in the wavefront's order
+        lanes = torch.zeros(2, rows, chunks * 512, device=DEV, dtype=torch.float64)
+        lanes[0, :, :d], lanes[1, :, :d] = a, b
+        a, b = lanes.view(2, rows, chunks, 64, 8)
+        s = torch.zeros(rows, 64, device=DEV, dtype=torch.float64)
+        for t in range(chunks):
+            for i in range(8):
+                s = r32(s + a[:, t, :, i] * b[:, t, :, i])
+        while s.shape[1] > 1:
+            half = s.shape[1] // 2
+            s = r32(s[:, :half] + s[:, half:])
+        return r32(s / d)
+
+    want = r32(rs * r32(r32(dxh - row_mean(dxh, torch.ones_like(dxh))) - xh * row_mean(dxh, xh)) + R.double()).to(torch.bfloat16)
+    assert torch.equal(dx, want)
+
+    per = (rows + parts - 1) // parts
+    for which, (a, b) in enumerate(((dy, xh), (dy, torch.ones_like(dy)), (dx.double(), torch.ones_like(dy)))):
+        want = torch.zeros(parts, d, device=DEV, dtype=torch.float64)
+        for first in range(4):
+            s = torch.zeros_like(want)
+            for k in range(first, per, 4):
+                at = torch.arange(parts, device=DEV) * per + k
+                ok = at < rows
+                s[ok] = r32(s[ok] + a[at[ok]] * b[at[ok]])
+            want = r32(want + s)
+        assert torch.equal(part[which], want.float()), which

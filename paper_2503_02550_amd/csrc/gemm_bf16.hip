@@ -102,6 +102,42 @@ __device__ __forceinline__ bf16x8 operand_frag(const bf16_t* tile, uint32_t rowb
   if (LAYOUT == 0) return *reinterpret_cast<const bf16x8*>(tile + lds_off(rowbase32 + (lane & 31), ks * 2 + kh));
   return kmajor_frag<ROWS>(tile, rowbase32, ks * 16 + kh * 8);
 }
+// The same for a ring of such tiles: T operands 32 rows apart, read from slot after slot with the distance as the read's
+// immediate offset (16 bits).  The registers that hold the lane's addresses are few - one per k slice, or per operand where
+// the LDS read transposes, and again per 64 KB of ring - and opaque to the compiler, which otherwise keeps an address for
+// nearly every read (256x128 tiles, both operands k-major: 41 of them, 23 spilled, reloaded inside the loop).
+template <int LAYOUT, int ROWS, int T, int ST>
+struct RingFrags {
+  static constexpr uint32_t TILE = ROWS * BK * 2, PER = 65536 / TILE;      // bytes of a slot, slots within reach
+  static constexpr int N = LAYOUT == 0 ? 4 : T, WINDOWS = (ST + PER - 1) / PER;
+  uint32_t at[WINDOWS][N];
+  __device__ __forceinline__ void init(uint32_t ring, uint32_t rowbase32) {      // `ring`: LDS byte address of slot 0
+    const uint32_t lane = threadIdx.x & 63, kh = lane >> 5, s = lane & 15, sw = s >> 2;
+#pragma unroll
+    for (int w = 0; w < WINDOWS; ++w)
+#pragma unroll
+      for (int q = 0; q < N; ++q) {
+        at[w][q] = ring + w * (PER * TILE) + 2 * (LAYOUT == 0 ? lds_off(rowbase32 + (lane & 31), q * 2 + kh)
+                                                              : (kh * 8 + sw) * ROWS + (((((rowbase32 >> 5) + q) ^ kmajor_key<ROWS>(sw)) << 5) |
+                                                                                        (((lane >> 4) & 1u) * 16 + 4 * (s & 3u))));
+        asm("" : "+v"(at[w][q]));
+      }
+  }
+  // operand i, k slice ks of a slot; `beyond` = where it starts past the slots of window w
+  __device__ __forceinline__ bf16x8 read(int w, uint32_t beyond, int i, int ks) const {
+    typedef __attribute__((address_space(3))) const bf16x8* row_ptr;
+    typedef __attribute__((address_space(3))) short4_lds* tr_ptr;
+    if (LAYOUT == 0) return *(row_ptr)(uintptr_t)(at[w][ks] + beyond + i * (32 * BK * 2));
+    const uint32_t p = at[w][i] + beyond + ks * (16 * ROWS * 2);
+    const short4_lds lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(uintptr_t)p);
+    const short4_lds hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(uintptr_t)(p + 4 * ROWS * 2));
+    typedef short short8_v __attribute__((ext_vector_type(8)));
+    const short8_v v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(bf16x8, v);
+  }
+  template <int SLOT>
+  __device__ __forceinline__ bf16x8 read_slot(int i, int ks) const { return read(SLOT / PER, SLOT % PER * TILE, i, ks); }
+};
 
 // ---------------------------------------------------------------------------------------------- fetches
 // One fetch instruction writes the 64 lanes' 16 bytes to consecutive LDS addresses from the scalar M0 on, 1 KB per
@@ -389,8 +425,11 @@ __device__ __forceinline__ void gemm_load_record(GemmP& p, const GemmP* group, u
 //   LAG = 0: step t's slot is fetched into again in step t, once all wavefronts have their fragments of t in registers
 //            (they wait for these before the barrier): ST steps in flight.
 //   LAG = 1: one step later; nothing is waited for before the barrier but the fetches of step t+1: ST - 1 in flight.
+// Registers: at most 248 of the 256 that two wavefronts of a SIMD may take (the attribute counts in pairs), so that a
+// one-wavefront kernel that sits on a CU for the length of a bubble (the training stream's wait) fits beside a block of the
+// 256x128 tiles, which otherwise stays off that CU until it ends.
 template <int ALAY, int BLAY, int BM, int BN, int WM, int WN, int ST, int LAG, int OCC, bool GROUPED = false>
-__global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_ring_kernel(GemmP p_in, KCtl ctl) {
+__global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_num_vgpr(124))) void gemm_ring_kernel(GemmP p_in, KCtl ctl) {
   // (a launch over several products has an instantiation of its own: in the others the product's record stays the
   // kernel argument, in scalar registers)
   GemmP p = p_in;
@@ -442,11 +481,15 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_ring_kernel(GemmP p_in
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) bf16_t*)lds;
 
   bf16x8 fa[2][4][TI], fb[2][4][TJ];
-  auto read_slice = [&](const bf16_t* st, int ks, bf16x8 (&a)[TI], bf16x8 (&b)[TJ]) {
+  RingFrags<ALAY, BM, TI, ST> ra_frags;
+  RingFrags<BLAY, BN, TJ, ST> rb_frags;
+  ra_frags.init(lds0, wm * (TI * 32));
+  rb_frags.init(lds0 + ST * SA * 2, wn * (TJ * 32));
+  auto read_slice = [&](auto SLOT, int ks, bf16x8 (&a)[TI], bf16x8 (&b)[TJ]) {
 #pragma unroll
-    for (int i = 0; i < TI; ++i) a[i] = operand_frag<ALAY, BM>(st, (wm * TI + i) * 32, ks);
+    for (int i = 0; i < TI; ++i) a[i] = ra_frags.template read_slot<decltype(SLOT)::value>(i, ks);
 #pragma unroll
-    for (int j = 0; j < TJ; ++j) b[j] = operand_frag<BLAY, BN>(st + SA, (wn * TJ + j) * 32, ks);
+    for (int j = 0; j < TJ; ++j) b[j] = rb_frags.template read_slot<decltype(SLOT)::value>(j, ks);
   };
   auto mfma_slice = [&](bf16x8 (&a)[TI], bf16x8 (&b)[TJ]) {
 #pragma unroll
@@ -456,14 +499,14 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_ring_kernel(GemmP p_in
   };
   // the next K step into a slot; `last`: the ragged one
   auto fetch_step = [&](uint32_t slot, bool last) {
-    const uint32_t o = lds0 + slot * (STAGE * 2);
+    const uint32_t oa = lds0 + slot * (SA * 2), ob = lds0 + ST * (SA * 2) + slot * (SB * 2);
     const i32x4 ra = operand_rsrc(base_a), rb = operand_rsrc(base_b);
     if (last) {
 #pragma unroll
-      for (int d = 0; d < F; ++d) { if (d < FA) ta.issue_last(ra, o, wave, d, k_rest); else tb.issue_last(rb, o + SA * 2, wave, d - FA, k_rest); }
+      for (int d = 0; d < F; ++d) { if (d < FA) ta.issue_last(ra, oa, wave, d, k_rest); else tb.issue_last(rb, ob, wave, d - FA, k_rest); }
     } else {
 #pragma unroll
-      for (int d = 0; d < F; ++d) { if (d < FA) ta.issue(ra, o, wave, d); else tb.issue(rb, o + SA * 2, wave, d - FA); }
+      for (int d = 0; d < F; ++d) { if (d < FA) ta.issue(ra, oa, wave, d); else tb.issue(rb, ob, wave, d - FA); }
     }
     base_a += step_a; base_b += step_b;
   };
@@ -471,21 +514,21 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_ring_kernel(GemmP p_in
   if (nt >= (uint32_t)AHEAD) wait_vm<F * (AHEAD - 1)>(); else wait_vm<0>();
   if (THREADS > 64) barrier_only();
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks) read_slice(lds, ks, fa[0][ks], fb[0][ks]);
+  for (int ks = 0; ks < 4; ++ks) read_slice(Int<0>(), ks, fa[0][ks], fb[0][ks]);
 
   auto steady = [&](auto S, auto P) {          // step in slot S with its fragments in register set P
     constexpr int s = decltype(S)::value, cur = decltype(P)::value, nx = (s + 1) % ST, fs = (s + AHEAD) % ST;
     wait_vm<F * (AHEAD - 2)>();                 // the next step has landed
     if (!LAG) wait_lds();
     if (THREADS > 64) barrier_only();
-    const uint32_t o = lds0 + fs * (STAGE * 2);
+    const uint32_t oa = lds0 + fs * (SA * 2), ob = lds0 + ST * (SA * 2) + fs * (SB * 2);
     const i32x4 ra = operand_rsrc(base_a), rb = operand_rsrc(base_b);
     base_a += step_a; base_b += step_b;
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
-      read_slice(lds + nx * STAGE, ks, fa[cur ^ 1][ks], fb[cur ^ 1][ks]);
+      read_slice(Int<nx>(), ks, fa[cur ^ 1][ks], fb[cur ^ 1][ks]);
 #pragma unroll
-      for (int d = ks * F / 4; d < (ks + 1) * F / 4; ++d) { if (d < FA) ta.issue(ra, o, wave, d); else tb.issue(rb, o + SA * 2, wave, d - FA); }
+      for (int d = ks * F / 4; d < (ks + 1) * F / 4; ++d) { if (d < FA) ta.issue(ra, oa, wave, d); else tb.issue(rb, ob, wave, d - FA); }
       __builtin_amdgcn_sched_barrier(0);
       mfma_slice(fa[cur][ks], fb[cur][ks]);
       __builtin_amdgcn_sched_barrier(0);
@@ -512,7 +555,12 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_ring_kernel(GemmP p_in
       if (!LAG) wait_lds();
       if (THREADS > 64) barrier_only();
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) read_slice(lds + nx * STAGE, ks, fa[cur ^ 1][ks], fb[cur ^ 1][ks]);
+      for (int ks = 0; ks < 4; ++ks) {
+#pragma unroll
+        for (int i = 0; i < TI; ++i) fa[cur ^ 1][ks][i] = ra_frags.read(0, nx * (SA * 2), i, ks);
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) fb[cur ^ 1][ks][j] = rb_frags.read(0, nx * (SB * 2), j, ks);
+      }
       if (t + AHEAD < nt) fetch_step(LAG ? (slot == 0 ? ST - 1 : slot - 1) : slot, t + AHEAD >= full);
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -551,9 +599,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_ring_kernel(GemmP p_in
 // stream - simply takes fewer tiles; with a fixed share per block the whole launch would wait for the late one.  An
 // unmonitored launch has no record: every block takes each gridDim.x-th tile (a stride that is a multiple of 8 keeps it
 // on its XCD's run).
-// Registers: two wavefronts per SIMD may take 256 of its 512 each.  The kernel is held to 248 (the attribute counts in
-// pairs): a one-wavefront kernel that sits on a CU for the length of a bubble (the training stream's wait) then still
-// fits beside a block, which otherwise stays off that CU, and the tiles of 255 CUs end a round later.
+// Registers: held to 248 for the same reason as the ring kernel.
 template <int ALAY, int BLAY, bool GROUPED = false>
 __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(124))) void gemm_pp_kernel(GemmP p_in, KCtl ctl) {
   constexpr int BM = 256, BN = 256, WM = 2, WN = 4, THREADS = 512, TI = 4, TJ = 2, HI = TI / 2, SR = 8;

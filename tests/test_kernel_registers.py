@@ -1,0 +1,57 @@
+"""Register use of the product kernels in the built library (read from its code objects' own metadata, no GPU)."""
+import os
+import struct
+
+import msgpack
+import pytest
+
+import paper_2503_02550_amd as S
+
+LIB = os.path.join(os.path.dirname(S.__file__), "libspecinf.so")
+
+
+def _notes(elf):
+    """The metadata maps of an ELF code object's notes."""
+    shoff, = struct.unpack_from("<Q", elf, 40)
+    entsize, count = struct.unpack_from("<HH", elf, 58)
+    for i in range(count):
+        kind, _, _, at, size = struct.unpack_from("<IQQQQ", elf, shoff + i * entsize + 4)
+        end = at + size
+        while kind == 7 and at < end:      # SHT_NOTE
+            namesz, descsz, note = struct.unpack_from("<III", elf, at)
+            desc = at + 12 + (namesz + 3) // 4 * 4
+            if note == 32:                 # AMDGPU metadata, MessagePack
+                yield msgpack.unpackb(elf[desc:desc + descsz], strict_map_key=False)
+            at = desc + (descsz + 3) // 4 * 4
+
+
+def _kernels():
+    with open(LIB, "rb") as f:
+        lib = f.read()
+    magic, at, got = b"__CLANG_OFFLOAD_BUNDLE__", 0, {}
+    while (at := lib.find(magic, at)) >= 0:
+        n, = struct.unpack_from("<Q", lib, at + len(magic))
+        pos = at + len(magic) + 8
+        for _ in range(n if n < 16 else 0):
+            off, size, name = struct.unpack_from("<QQQ", lib, pos)
+            if b"gfx950" in lib[pos + 24:pos + 24 + name] and size:
+                for notes in _notes(lib[at + off:at + off + size]):
+                    got.update({k[".name"]: k for k in notes["amdhsa.kernels"]})
+            pos += 24 + name
+        at += len(magic)
+    return got
+
+
+@pytest.mark.parametrize("kernel", ["gemm_ring_kernel", "gemm_pp_kernel"])
+def test_product_kernels_leave_room_for_the_bubbles_wait(kernel):
+    """Two of their wavefronts on a SIMD and the one that waits for the bubble's end share its 512 registers, so a block of
+    any product runs on the CU that holds that wait; and none is kept in scratch memory (a reload inside the main loop waits
+    for every fetch in flight)."""
+    kernels = _kernels()
+    wait = max(k[".vgpr_count"] for n, k in kernels.items() if "bubble" in n)
+    found = {n: k for n, k in kernels.items() if kernel in n}
+    assert len(found) >= 4
+    for name, k in found.items():
+        granule = lambda r: (r + 7) // 8 * 8
+        assert 2 * granule(k[".vgpr_count"]) + granule(wait) <= 512, (name, k[".vgpr_count"], wait)
+        assert k[".vgpr_spill_count"] == 0, name

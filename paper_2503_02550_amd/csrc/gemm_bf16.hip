@@ -783,6 +783,13 @@ static bool gemm_whole_steps(const sif_gemm_args& a) {
   return a.k_limit > before_last && ((a.k_limit - before_last) % BK) == 0;
 }
 
+// A causal product stops at the end of its row's (and skips what lies beyond its column's) 128-wide tile: what is past it
+// need not have been written, so tiles more than 128 rows tall are not for it.
+static bool gemm_tiles_fit(const sif_gemm_args& a, int cfg) {
+  if (cfg == kT256x256) return gemm_whole_steps(a);
+  return cfg != kT256x128 || !gemm_causal(a);
+}
+
 static double gemm_time_us(const sif_gemm_args& a, int cfg) {
   const GemmTiles& t = kGemmTiles[cfg];
   const uint64_t tiles = (uint64_t)((a.m + t.bm - 1) / t.bm) * ((a.n + t.bn - 1) / t.bn) * a.batch_outer * a.batch_inner, round = 256ull * t.slots;
@@ -803,8 +810,7 @@ static int gemm_choose(const sif_gemm_args& a) {
   int best = kT128x128;
   double best_us = gemm_time_us(a, best);
   for (int c = 0; c < kNTiles; ++c) {
-    if (c == kT256x256 && !gemm_whole_steps(a)) continue;
-    if (c == kT256x128 && gemm_causal(a)) continue;       // a causal product stops at the end of its row's 128-column tile
+    if (!gemm_tiles_fit(a, c)) continue;
     const double us = gemm_time_us(a, c);
     if (us < best_us) { best = c; best_us = us; }
   }
@@ -913,7 +919,7 @@ sif_status gemm_group_fill(const sif_gemm_args* list, uint32_t n, void* host_rec
     for (uint32_t i = 0; i < n; ++i) {
       tiles += (double)((list[i].m + t.bm - 1) / t.bm) * ((list[i].n + t.bn - 1) / t.bn);
       steps = std::max(steps, (double)((list[i].k + BK - 1) / BK));
-      ok = ok && (c != kT256x256 || gemm_whole_steps(list[i]));
+      ok = ok && gemm_tiles_fit(list[i], c);
     }
     const double round = 256.0 * t.slots, us = std::max(1.0, ceil(tiles / round)) * (t.fixed + t.step * steps);
     if (ok && (c == kT128x128 || us < best)) { cfg = c; best = us; }

@@ -257,3 +257,38 @@ def test_layernorm_backward_of_wide_rows_sums_in_the_order_of_narrow_ones(rows, 
                 s[ok] = r32(s[ok] + a[at[ok]] * b[at[ok]])
             want = r32(want + s)
         assert torch.equal(part[which], want.float()), which
+
+
+@pytest.mark.parametrize("case", ["k_causal_1", "k_causal_2", "causal_skip"])
+def test_causal_products_of_a_group_keep_to_their_128_tiles(case):
+    """A causal product in a group reads no more of its left operand than the 128-row tile has (beyond it stands what was
+    never written, here NaN) and writes no tile above the diagonal, also where the group's size asks for taller tiles: the
+    bits of the product by itself on 128x128 tiles."""
+    gen = torch.Generator(device=DEV).manual_seed(11)
+    m = n = 2560
+    k = 64 if case == "causal_skip" else m
+    a, b = _bf16(gen, k, m), _bf16(gen, k, n)
+    row, col = torch.arange(k, device=DEV)[:, None], torch.arange(m, device=DEV)[None]
+    kw = {}
+    if case == "k_causal_1":                     # A(m, k) is zero for k > m, and unwritten from the next 128 on
+        a[row > col] = 0
+        a[row >= (col // 128 + 1) * 128] = float("nan")
+        kw = dict(k_causal=1)
+    elif case == "k_causal_2":                   # zero for k < m, unwritten before the 128 that hold m
+        a[row < col] = 0
+        a[row < col // 128 * 128] = float("nan")
+        kw = dict(k_causal=2)
+    else:
+        kw = dict(epilogue=S.SIF_EPI_CAUSAL_SKIP)
+    long_a, long_b = _bf16(gen, 8192, 136), _bf16(gen, 8192, 264)      # a product beside it that asks for the tall tiles
+    c, alone = torch.full((m, n), 7.0, device=DEV, dtype=torch.bfloat16), torch.full((m, n), 7.0, device=DEV, dtype=torch.bfloat16)
+    other = torch.zeros((136, 264), device=DEV, dtype=torch.bfloat16)
+    lay = dict(a_layout=S.SIF_A_ROW_M, b_layout=S.SIF_B_ROW_N)
+    records = torch.zeros(S.sif_k_gemm_bf16_group_bytes(2) + 16, device=DEV, dtype=torch.uint8)
+    torch.cuda.synchronize()
+    S.sif_k_gemm_bf16_group([S.gemm_args(a, b, c, m, n, k, m, n, n, **lay, **kw), S.gemm_args(long_a, long_b, other, 136, 264, 8192, 136, 264, 264, **lay)], records)
+    S.sif_k_gemm_bf16(a, b, alone, m, n, k, m, n, n, tile=128, **lay, **kw)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(alone.float()).all())
+    assert torch.equal(c, alone)
+    assert float((other.double() - long_a.double().t() @ long_b.double()).norm() / other.double().norm()) <= 2.0 ** -8

@@ -790,11 +790,15 @@ static bool gemm_tiles_fit(const sif_gemm_args& a, int cfg) {
   return cfg != kT256x128 || !gemm_causal(a);
 }
 
-static double gemm_time_us(const sif_gemm_args& a, int cfg) {
+static uint64_t gemm_tiles_of(const sif_gemm_args& a, int cfg) {
   const GemmTiles& t = kGemmTiles[cfg];
-  const uint64_t tiles = (uint64_t)((a.m + t.bm - 1) / t.bm) * ((a.n + t.bn - 1) / t.bn) * a.batch_outer * a.batch_inner, round = 256ull * t.slots;
-  const double steps = (double)((a.k + BK - 1) / BK);
-  const uint64_t whole = tiles / round, rest = tiles % round;
+  return (uint64_t)((a.m + t.bm - 1) / t.bm) * ((a.n + t.bn - 1) / t.bn) * a.batch_outer * a.batch_inner;
+}
+static double gemm_steps_of(const sif_gemm_args& a) { return (double)((a.k + BK - 1) / BK); }
+
+static double gemm_time_us(uint64_t tiles, double steps, int cfg) {
+  const GemmTiles& t = kGemmTiles[cfg];
+  const uint64_t round = 256ull * t.slots, whole = tiles / round, rest = tiles % round;
   double us = 2.0 + (double)whole * (t.fixed + t.step * steps);
   if (rest > 0) {
     // a last round goes by the CU that holds the most of its tiles
@@ -808,10 +812,10 @@ static int gemm_choose(const sif_gemm_args& a) {
   if (a.tile == 256) return kT256x256;
   if (a.tile == 128) return kT128x128;
   int best = kT128x128;
-  double best_us = gemm_time_us(a, best);
+  double best_us = gemm_time_us(gemm_tiles_of(a, best), gemm_steps_of(a), best);
   for (int c = 0; c < kNTiles; ++c) {
     if (!gemm_tiles_fit(a, c)) continue;
-    const double us = gemm_time_us(a, c);
+    const double us = gemm_time_us(gemm_tiles_of(a, c), gemm_steps_of(a), c);
     if (us < best_us) { best = c; best_us = us; }
   }
   return best;
@@ -909,20 +913,24 @@ uint64_t gemm_group_bytes(uint32_t n) { return (uint64_t)n * sizeof(GemmP); }
 
 sif_status gemm_group_fill(const sif_gemm_args* list, uint32_t n, void* host_records, GemmGroup* out) {
   if (list == nullptr || n == 0 || n > 16 || host_records == nullptr || out == nullptr) return fail(SIF_E_INVAL, "gemm group: bad arguments");
-  // which tiles: the model's time for all products' tiles together, the longest K deciding
-  int cfg = kT128x128;
+  // Which tiles: the model's time for all products' tiles together, the longest K deciding.  A small layer's gradients (21
+  // tiles of 128x128 at 128 x 512) are a chain of K steps on few CUs: 128x128 with four steps in the ring of a CU's only
+  // block, as long as that is one round (2048 tokens of 128 x 512: 16 us, with two steps in the ring 20, on 256x128 27;
+  // two rounds, 8192 tokens of 768 x 3072: 131 us, where two blocks of a CU hide each other's ends 125).
+  int cfg = -1;
   double best = 0.0;
-  for (int c : {(int)kT128x128, (int)kT256x128, (int)kT256x256}) {
-    const GemmTiles& t = kGemmTiles[c];
-    double tiles = 0.0, steps = 0.0;
+  for (int c : {(int)kT128x128, (int)kT128x128x1, (int)kT256x128, (int)kT256x256}) {
+    uint64_t tiles = 0;
+    double steps = 0.0;
     bool ok = true;
     for (uint32_t i = 0; i < n; ++i) {
-      tiles += (double)((list[i].m + t.bm - 1) / t.bm) * ((list[i].n + t.bn - 1) / t.bn);
-      steps = std::max(steps, (double)((list[i].k + BK - 1) / BK));
+      tiles += gemm_tiles_of(list[i], c);
+      steps = std::max(steps, gemm_steps_of(list[i]));
       ok = ok && gemm_tiles_fit(list[i], c);
     }
-    const double round = 256.0 * t.slots, us = std::max(1.0, ceil(tiles / round)) * (t.fixed + t.step * steps);
-    if (ok && (c == kT128x128 || us < best)) { cfg = c; best = us; }
+    ok = ok && (c != kT128x128x1 || tiles <= 256);
+    const double us = gemm_time_us(tiles, steps, c);
+    if (ok && (cfg < 0 || us < best)) { cfg = c; best = us; }
   }
   GemmP* rec = static_cast<GemmP*>(host_records);
   uint32_t base = 0;
@@ -951,6 +959,7 @@ sif_status launch_gemm_bf16_group(const void* dev_records, uint32_t n, const Gem
   // (instantiated for the layouts of weight gradients, A [K][M] and B [K][N]; other layouts would need their own)
   if (a_layout != SIF_A_ROW_M || b_layout != SIF_B_ROW_N) return fail(SIF_E_INVAL, "gemm group: only A stored [K][M] with B stored [K][N]");
   if (g.cfg == kT256x256) hipLaunchKernelGGL((gemm_pp_kernel<1, 1, true>), dim3(std::min(g.tiles, gemm_cus())), dim3(512), 0, stream, head, ctl);
+  else if (g.cfg == kT128x128x1) hipLaunchKernelGGL((gemm_ring_kernel<1, 1, 128, 128, 4, 2, 4, 1, 1, true>), dim3(g.tiles), dim3(512), 0, stream, head, ctl);
   else if (g.cfg == kT256x128) hipLaunchKernelGGL((gemm_ring_kernel<1, 1, 256, 128, 4, 2, 3, 0, 1, true>), dim3(g.tiles), dim3(512), 0, stream, head, ctl);
   else hipLaunchKernelGGL((gemm_ring_kernel<1, 1, 128, 128, 2, 2, 2, 0, 2, true>), dim3(g.tiles), dim3(256), 0, stream, head, ctl);
   return check_launch("gemm_bf16_group");

@@ -1020,7 +1020,7 @@ sif_status sif_calibrate(sif_ctx* c, uint32_t iters, const void* train_inputs_de
       InferIO io[kMaxCoalesce];
       const uint64_t rows1 = (uint64_t)batch * s.seq;
       for (uint32_t r = 0; r < n; ++r) {
-        io[r].in_dev = (const unsigned char*)im.calib_in + (s.kind == SIF_MODEL_MLP ? 0 : r * rows1 * 4);
+        io[r].in_dev = im.calib_in;      // (the same ids for all: a request's own would not always be 16-byte aligned)
         io[r].out_dev = (unsigned char*)im.calib_out + (s.kind == SIF_MODEL_MLP ? 0 : r * rows1 * s.d_model * 2);
       }
       sif_status st = build_infer_plan(im, io, n, batch, s.seq, c->cfg.kernel_us_max, plan);

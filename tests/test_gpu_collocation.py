@@ -322,6 +322,16 @@ def test_training_that_never_idles_starves_inference_without_deadlock():
     # destroy cancelled the pending ticket and returned
 
 
+@pytest.mark.parametrize("batch,seq", [(10, 25), (1, 3), (3, 7), (4, 16)])
+def test_coalesced_requests_of_any_size_are_calibrated(batch, seq):
+    """The calibration runs as many requests as are coalesced, also where one of them is no multiple of 16 bytes of ids."""
+    enc = dict(ENC, batch=batch, seq=seq)
+    shape = encoder_shape(enc)
+    with Session() as s:
+        s.register_inference(shape, P.pack(shape, Y.encoder_params(2, enc)), coalesce=3)
+        assert S.sif_calibrate(s.ctx, 1) == S.SIF_OK
+
+
 def test_online_requests_are_pulled_one_at_a_time_inside_bubbles():
     """Online fill (Sec. 3.3 "Kernel Barrier", pull-and-execute): Poisson arrivals, batch 1, ragged lengths."""
     import threading

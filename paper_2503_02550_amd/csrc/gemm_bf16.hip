@@ -143,7 +143,8 @@ struct RingFrags {
 // One fetch instruction writes the 64 lanes' 16 bytes to consecutive LDS addresses from the scalar M0 on, 1 KB per
 // wavefront, so a lane's place in the tile is fixed and the swizzle is applied to what it fetches.  The instruction is
 // written as assembly: the compiler would otherwise make every LDS read wait for every fetch in flight.  `volatile` and
-// "memory" keep it in its place between the barriers.
+// "memory" keep it in its place between the barriers.  (M0 is reserved: the compiler keeps nothing in it, and naming it as
+// clobbered is no help, so nothing else in these kernels may use it; a test looks through the built instructions.)
 constexpr uint32_t kOutside = 0x80000000u;      // an offset beyond the resource's extent: the lane's 16 bytes are zeros
 __device__ __forceinline__ void fetch16(const i32x4& rsrc, uint32_t voff, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc) : "memory");

@@ -1,5 +1,7 @@
-"""Register use of the product kernels in the built library (read from its code objects' own metadata, no GPU)."""
+"""Register use of the product kernels in the built library, from its own code objects' metadata and instructions (no GPU)."""
 import os
+import re
+import subprocess
 import struct
 
 import msgpack
@@ -25,21 +27,23 @@ def _notes(elf):
             at = desc + (descsz + 3) // 4 * 4
 
 
-def _kernels():
+def _code_objects():
     with open(LIB, "rb") as f:
         lib = f.read()
-    magic, at, got = b"__CLANG_OFFLOAD_BUNDLE__", 0, {}
+    magic, at = b"__CLANG_OFFLOAD_BUNDLE__", 0
     while (at := lib.find(magic, at)) >= 0:
         n, = struct.unpack_from("<Q", lib, at + len(magic))
         pos = at + len(magic) + 8
         for _ in range(n if n < 16 else 0):
             off, size, name = struct.unpack_from("<QQQ", lib, pos)
             if b"gfx950" in lib[pos + 24:pos + 24 + name] and size:
-                for notes in _notes(lib[at + off:at + off + size]):
-                    got.update({k[".name"]: k for k in notes["amdhsa.kernels"]})
+                yield lib[at + off:at + off + size]
             pos += 24 + name
         at += len(magic)
-    return got
+
+
+def _kernels():
+    return {k[".name"]: k for elf in _code_objects() for notes in _notes(elf) for k in notes["amdhsa.kernels"]}
 
 
 @pytest.mark.parametrize("kernel", ["gemm_ring_kernel", "gemm_pp_kernel"])
@@ -55,3 +59,26 @@ def test_product_kernels_leave_room_for_the_bubbles_wait(kernel):
         granule = lambda r: (r + 7) // 8 * 8
         assert 2 * granule(k[".vgpr_count"]) + granule(wait) <= 512, (name, k[".vgpr_count"], wait)
         assert k[".vgpr_spill_count"] == 0, name
+
+
+def test_only_the_fetches_use_m0(tmp_path):
+    """The fetch into LDS is an assembly statement that writes M0.  The compiler reserves that register and cannot be told
+    of the write; it would set M0 itself right before an instruction that reads it, and a fetch could come to stand between
+    the two.  So no kernel with such fetches may contain another use of M0."""
+    objdump = "/opt/rocm/llvm/bin/llvm-objdump"
+    if not os.path.exists(objdump):
+        pytest.skip("no disassembler")
+    fetches = 0
+    for i, elf in enumerate(_code_objects()):
+        if b"gemm_ring_kernel" not in elf:
+            continue
+        (tmp_path / f"{i}.co").write_bytes(elf)
+        text = subprocess.run([objdump, "-d", "--no-show-raw-insn", "--mcpu=gfx950", tmp_path / f"{i}.co"], capture_output=True, text=True, check=True).stdout
+        for part in re.split(r"\n[0-9a-f]+ <", text)[1:]:
+            name, body = part.split(">:\n", 1)
+            code = [line.split("//")[0].strip() for line in body.splitlines()]
+            for k, line in enumerate(code):
+                if "m0" in line:
+                    assert re.match(r"s_mov_b32 m0, s\d+$", line) and code[k + 1] == "s_nop 0" and re.match(r"buffer_load_dwordx4 .* lds$", code[k + 2]), (name, code[k:k + 3])
+                    fetches += 1
+    assert fetches > 100

@@ -243,15 +243,10 @@ def test_bench_refuses_more_than_one_gpu():
 @pytest.mark.parametrize("d,f,tokens", [(64, 256, 1024), (128, 512, 2048), (256, 1024, 4096), (384, 1536, 512), (128, 512, 16384)])
 def test_group_of_a_small_layer_is_not_put_on_tall_tiles(d, f, tokens):
     """The weight gradients of a small layer are few tiles and one long K: on tiles twice as tall they keep half as many
-    CUs busy with the same chain of K steps.  The group's padded tile count tells which tiles were taken (host arithmetic
-    only: the addresses are never read)."""
-    import ctypes as C
-    fill = getattr(S.lib, "_ZN3sif15gemm_group_fillEPK13sif_gemm_argsjPvPNS_9GemmGroupE")
-    fill.restype, fill.argtypes = C.c_int, [C.c_void_p, C.c_uint32, C.c_void_p, C.c_void_p]
+    CUs busy with the same chain of K steps."""
+    from tile_choice import group
     shapes = [(d, f), (f, d), (d, d), (3 * d, d), (1, f), (1, 3 * d)]
     lay = dict(a_layout=S.SIF_A_ROW_M, b_layout=S.SIF_B_ROW_N)
-    prods = (S.sif_gemm_args * len(shapes))(*[S.gemm_args(1 << 20, 1 << 20, 1 << 20, m, n, tokens, (m + 7) // 8 * 8, n, n, **lay) for m, n in shapes])
-    records, got = (C.c_char * S.sif_k_gemm_bf16_group_bytes(len(shapes)))(), (C.c_uint32 * 2)()
-    assert fill(prods, len(shapes), records, got) == 0
+    tiles, name = group([S.gemm_args(1 << 20, 1 << 20, 1 << 20, m, n, tokens, (m + 7) // 8 * 8, n, n, **lay) for m, n in shapes])
     up = lambda v, by: (v + by - 1) // by
-    assert got[0] == sum(up(up(m, 128) * up(n, 128), 8) * 8 for m, n in shapes)
+    assert name == "128x128 one" and tiles == sum(up(up(m, 128) * up(n, 128), 8) * 8 for m, n in shapes)

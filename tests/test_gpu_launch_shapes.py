@@ -19,11 +19,11 @@ def _bf16(gen, *shape):
     return torch.randn(shape, device=DEV, generator=gen).to(torch.bfloat16)
 
 
-@pytest.mark.parametrize("batch,hidden", [(1, 8), (32, 1024), (32, 1056), (33, 2048), (512, 1024), (520, 1024), (2048, 1024), (2080, 1024)])
+@pytest.mark.parametrize("batch,hidden", [(1, 8), (16, 512), (16, 528), (32, 1024), (32, 1056), (33, 2048), (512, 1024), (520, 1024), (2048, 1024), (2080, 1024)])
 def test_last_block_is_found_whatever_the_grid(batch, hidden):
-    """A launch is reported done by its last block; grids at the edges of the counting tree (1, 32, 33, 512, 2048
-    blocks and a little more, in 32 x 32 tiles) must all be, twice in a row (the counters are re-armed), with every
-    kernel counted.  Products of fp32 values: the bound of the other fp32 tests, 1e-4 of the largest value."""
+    """A launch is reported done by its last block; grids at the edges of the counting tree must all be, twice in a row (the
+    counters are re-armed), with every kernel counted.  Blocks of the first product: 1, 32, 33, 128, 132, 384 (tiles of
+    16 x 16), 512, 544, 2048, 2080 (32 x 32); of the second 1 to 65.  Products of fp32 values: the bound of the other fp32 tests, 1e-4 of the largest value."""
     shape = mlp_shape(8, hidden, 32, batch)
     p = Y.mlp_params(3, 8, hidden, 32)
     with Session() as s:
@@ -107,8 +107,8 @@ def test_gemm_f32_tiles_and_remainders(m, n, k, k_contig_a, k_contig_b):
 @pytest.mark.parametrize("m,n,k", [(1, 8, 8), (31, 72, 64), (33, 64, 136), (64, 64, 256), (65, 200, 520), (300, 3080, 320), (1000, 768, 200),
                                    (1000, 2304, 456), (2008, 1536, 520), (4100, 768, 328), (2056, 2048, 1032), (8192, 776, 72), (4096, 3072, 512)])
 def test_gemm_bf16_picks_tiles_that_give_the_bits_of_the_128_ones(m, n, k, al, bl):
-    """Products of a few rows to ones that fill the chip: whichever tile the launcher takes (32x64 to 256x256, rings of
-    whole turns and of less, ragged M, N and K), the result has the bits of the 128x128 tiles and is the product.  Bound:
+    """Products of a few rows to ones that fill the chip: whichever tile the launcher takes (all but 128x64, which the test
+    below has, with long K), at ragged M, N and K, the result has the bits of the 128x128 tiles and is the product.  Bound:
     one rounding to bf16 (2^-9 of the value) and the fp32 sum of k exact products ((k + 4) 2^-24 of their magnitudes)."""
     gen = torch.Generator(device=DEV).manual_seed(m + 3 * n + 5 * k + al + 2 * bl)
     mp, np_ = (m + 7) // 8 * 8, n
@@ -124,6 +124,59 @@ def test_gemm_bf16_picks_tiles_that_give_the_bits_of_the_128_ones(m, n, k, al, b
     ref = a[:m].double() @ b.double().t()
     bound = 2.0 ** -8 * ref.abs() + (k + 4) * 2.0 ** -24 * (a[:m].double().abs() @ b.double().abs().t())
     assert bool(((out[0].double() - ref).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("al", [0, 1])
+@pytest.mark.parametrize("bl", [0, 1])
+@pytest.mark.parametrize("m,n,k,tiles", [(72, 200, 1160, "32x64"), (600, 1544, 776, "64x64"), (600, 2440, 1160, "128x64"), (1032, 2440, 776, "128x128 one"),
+                                         (4104, 2440, 776, "128x128 two"), (2008, 2440, 1160, "256x128"), (4360, 4104, 64, None), (4360, 4104, 192, None)])
+def test_gemm_bf16_long_rings_and_more_tiles_than_blocks_give_the_bits_of_the_128_ones(m, n, k, tiles, al, bl):
+    """Every ring over more K steps than its unrolled body has, with a ragged step behind them; and 256x256 tiles, of which
+    256 blocks work through 306 (one and three K steps): the next tile's operands travel while the last one is stored."""
+    from tile_choice import takes
+    gen = torch.Generator(device=DEV).manual_seed(m + 3 * n + 5 * k + al + 2 * bl)
+    a, b = _bf16(gen, m, k), _bf16(gen, n, k)
+    A, Bt = (a if al == 0 else a.t().contiguous()), (b if bl == 0 else b.t().contiguous())
+    out = [torch.full((m, n), float("nan"), device=DEV, dtype=torch.bfloat16) for _ in range(2)]
+    args = lambda c, tile: S.gemm_args(A, Bt, c, m, n, k, A.shape[1], Bt.shape[1], n, a_layout=al, b_layout=bl, tile=tile)
+    assert tiles is None or takes(args(out[0], 0), tiles)
+    torch.cuda.synchronize()
+    for c, tile in zip(out, (0 if tiles else 256, 128)):
+        S.sif_k_gemm_bf16(A, Bt, c, m, n, k, A.shape[1], Bt.shape[1], n, a_layout=al, b_layout=bl, tile=tile)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], out[1])
+    ref = a.double() @ b.double().t()
+    bound = 2.0 ** -8 * ref.abs() + (k + 4) * 2.0 ** -24 * (a.double().abs() @ b.double().abs().t())
+    assert bool(((out[0].double() - ref).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("shapes,k,tiles", [([(512, 128), (128, 512), (1, 512)], 1032, "128x128 one"), ([(1032, 776), (776, 3080), (1, 3080)], 1160, "256x128"),
+                                            ([(4104, 4616), (2056, 2568), (1, 8200)], 512, "256x256")])
+def test_groups_give_the_bits_of_the_128_tiles_on_every_tile(shapes, k, tiles):
+    """Groups whose products' tile counts are no multiples of eight (the padding has nothing to do), with one-row products,
+    a ragged K where the tiles allow it, and 256x256 tiles that are more than the chip's CUs, so that a block goes from one
+    product's tile to another's."""
+    from tile_choice import group
+    gen = torch.Generator(device=DEV).manual_seed(k)
+    lay = dict(a_layout=S.SIF_A_ROW_M, b_layout=S.SIF_B_ROW_N)
+    prods, pairs = [], []
+    for m, n in shapes:
+        a, b = torch.zeros((k, (m + 7) // 8 * 8), device=DEV, dtype=torch.bfloat16), _bf16(gen, k, n)
+        a[:, :m] = _bf16(gen, k, m)
+        c = [torch.full((m, n), float("nan"), device=DEV, dtype=torch.bfloat16) for _ in range(2)]
+        prods.append(S.gemm_args(a, b, c[0], m, n, k, a.shape[1], n, n, **lay))
+        pairs.append((a, b, c))
+    assert group(prods)[1] == tiles
+    records = torch.zeros(S.sif_k_gemm_bf16_group_bytes(len(prods)) + 16, device=DEV, dtype=torch.uint8)
+    torch.cuda.synchronize()
+    S.sif_k_gemm_bf16_group(prods, records)
+    for a, b, c in pairs:
+        S.sif_k_gemm_bf16(a, b, c[1], *c[1].shape, k, a.shape[1], b.shape[1], b.shape[1], tile=128, **lay)
+    torch.cuda.synchronize()
+    for a, b, c in pairs:
+        assert torch.equal(c[0], c[1])
+        ref = a[:, :c[0].shape[0]].double().t() @ b.double()
+        assert float((c[0].double() - ref).norm() / ref.norm()) <= 2.0 ** -8
 
 
 @pytest.mark.parametrize("m,n,k", [(77, 200, 136), (1000, 768, 256), (1032, 2304, 192)])

@@ -223,9 +223,10 @@ typedef struct sif_gemm_args {
 /* bf16 matrix product on the MFMA units, fp32 accumulation. */
 sif_status sif_k_gemm_bf16(const sif_gemm_args* a, void* stream);
 
-/* Several bf16 products as ONE launch of 128 x 128 tiles (Sec. 2.1: the weight gradients of a transformer layer, each
+/* Several bf16 products as ONE launch (Sec. 2.1: the weight gradients of a transformer layer, each
  * with too few output tiles for the chip by itself).  list[0..n): n <= 16 products, all with A stored [K][M] and B
- * stored [K][N] (a_layout = SIF_A_ROW_M, b_layout = SIF_B_ROW_N), no batches; `tile` is ignored.  records_dev: device
+ * stored [K][N] (a_layout = SIF_A_ROW_M, b_layout = SIF_B_ROW_N), no batches; `tile` is ignored, the tiles are
+ * chosen for all products together (none taller than 128 rows with a causal product among them).  records_dev: device
  * memory of at least sif_k_gemm_bf16_group_bytes(n) bytes, 16-byte aligned, owned by the caller; the call copies the
  * products' records there (a synchronous host -> device copy) and launches on `stream`; the memory must stay
  * untouched until the launch has finished.  Every product's result has the bits of sif_k_gemm_bf16 with tile = 128.

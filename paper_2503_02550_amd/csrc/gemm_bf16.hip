@@ -24,8 +24,8 @@
 // is not an MFMA - LDS reads, fetches, address arithmetic, branches - delays the MFMAs behind it unless it stands
 // between them.  Hence: no branch and no address arithmetic in the steady part of a loop (the ring's slots are constants
 // of an unrolled body), fragments of the next K step read between the MFMAs of this one, fetches waited for by count.
-// (Two K steps in LDS, waited for as a whole, were 4096 x 768 x 3072: 37 us, 77 x 768 x 3072: 23 us, 8192 x 768 x 3072:
-// 47 us, 8192 x 2048 x 4096 as a weight gradient: 135 us; now 23, 7.2, 38 and 102.)
+// (Two K steps in LDS, waited for as a whole, were 4096 x 768 x 3072: 36 us, 77 x 768 x 3072: 23 us, 8192 x 768 x 3072:
+// 44 us, 2048 x 4096 x 8192 as a weight gradient: 130 us; now 23.5, 8.2, 38.6 and 112, launches back to back.)
 //
 // Results depend neither on the grid nor on the tile: each output element is reduced over K in one fixed order
 // (ascending, 16 at a time) by one wavefront, so launching a row range of the same problem, or another configuration,
@@ -513,7 +513,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_num_vgpr(1
   };
   for (uint32_t s = 0; s < (uint32_t)AHEAD && s < nt; ++s) fetch_step(s, s >= full);
   if (nt >= (uint32_t)AHEAD) wait_vm<F * (AHEAD - 1)>(); else wait_vm<0>();
-  if (THREADS > 64) barrier_only();
+  barrier_only();
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) read_slice(Int<0>(), ks, fa[0][ks], fb[0][ks]);
 
@@ -521,7 +521,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_num_vgpr(1
     constexpr int s = decltype(S)::value, cur = decltype(P)::value, nx = (s + 1) % ST, fs = (s + AHEAD) % ST;
     wait_vm<F * (AHEAD - 2)>();                 // the next step has landed
     if (!LAG) wait_lds();
-    if (THREADS > 64) barrier_only();
+    barrier_only();
     const uint32_t oa = lds0 + fs * (SA * 2), ob = lds0 + ST * (SA * 2) + fs * (SB * 2);
     const i32x4 ra = operand_rsrc(base_a), rb = operand_rsrc(base_b);
     base_a += step_a; base_b += step_b;
@@ -554,7 +554,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_num_vgpr(1
     if (t + 1 < nt) {
       if (t + AHEAD - 1 < nt) wait_vm<F * (AHEAD - 2)>(); else wait_vm<0>();
       if (!LAG) wait_lds();
-      if (THREADS > 64) barrier_only();
+      barrier_only();
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) {
 #pragma unroll
@@ -590,8 +590,9 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_num_vgpr(1
 // times: B and the first halves of A are fetched in one phase, the second halves of A in the other, and every fetch has
 // five to six phases (a step and a half, about 1.5 us) to arrive; the counts waited for leave eight younger fetches per
 // wavefront in flight.  Two buffers of each part are 128 KB of LDS; the epilogue has 16 KB of its own for staging.
-// (One phase is 512 cycles of MFMA; a step takes 1.0 us where it was 1.27 with a barrier per step and everything in one
-// stream.  On a full chip the clock falls to what the power allows: 8192^3 800 -> 760 us.)
+// (One phase is 512 cycles of MFMA.  With a few tiles on the chip a step takes 0.96 us where it was 1.18 with a barrier per
+// step and everything in one stream; with a tile on every CU the clock falls to what the power allows: 1.47 us against
+// 1.51, 8192^3 795 -> 767 us.)
 //
 // Persistent: a block works through tiles one after the other; the first operand tiles of the next output tile are
 // fetched while the current one's epilogue runs.  Which tile comes next: a monitored launch hands its tiles out through
@@ -765,8 +766,11 @@ static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 // ---------------------------------------------------------------------------------------------- configurations
 // What a launch costs, per configuration: 2 us, and per round of tiles `fixed` + `step` * (K steps of 64) us with `slots`
 // tiles on a CU at a time, `step1` with one.  Least squares over 37 shapes from 77 x 768 x 3072 to 8192^3, three operand
-// layouts and three epilogues (each configuration's times are met to 8-17 %); the choice by this model is on average 0.7 %
-// slower than the best configuration of each shape and at worst 18 %.
+// layouts and three epilogues.  Checked against every configuration's time at 665 other shapes, plain products launched back
+// to back: the modelled times are 0.7 to 1.5 of the measured ones, the choice is on average 1.0 % slower than the best
+// configuration and at worst 21 % (at 6 us; 18 % at 8192 x 3072 x 768, 51 us on 256x128, 43 on 128x128).  A fit to those
+// would not be better: inside the training step, with its epilogues and with operands that come from memory, that product
+// takes 67.6 us on 256x128 and 71.2 on 128x128.
 struct GemmTiles { uint32_t bm, bn, slots; double fixed, step, step1; };
 enum { kT32x64, kT64x64, kT128x64, kT128x128x1, kT128x128, kT256x128, kT256x256, kNTiles };
 static const GemmTiles kGemmTiles[kNTiles] = {

@@ -238,14 +238,16 @@ static void emit_wgrad(Plan& p, const char* name, const bf16_t* a, const bf16_t*
 }
 
 // The four weight gradients of a layer as ONE launch (gemm_group_fill / launch_gemm_bf16_group): each by itself has too
-// few 128x128 tiles for the chip and is cut along K above, with fp32 partial results written, read again and summed
-// (1.25 GB per step of the 12-layer decoder); together they are 432 tiles over the whole K, no partial results.  The
+// few tiles for the chip and is cut along K above, with fp32 partial results written, read again and summed
+// (1.25 GB per step of the 12-layer decoder); together they are 432 tiles of 128x128 over the whole K, no partial results.  The
 // products' operands (the incoming gradient, dz, the gradient between the two halves of the layer, dqkv, the saved
 // activations) are all still in place when the last of them, dqkv, has been computed.  GroupPlan hands out device
 // memory for the launches' kernel records, which are written once, when the plan is built.
 // A bias gradient (the column sums of a gradient over the tokens) rides along as one more product of the group: the
-// left operand is `ones`, [tokens][8] with 1 in column 0, the result one row; its few tiles take block slots the weight
-// gradients leave idle, and the launch that would read the gradient once more for the sums is not needed.
+// left operand is `ones`, [tokens][8] with 1 in column 0, the result one row; the launch that would read the gradient once
+// more for the sums is not needed.  Its tiles (a row of them over the whole K) take block slots that the weight gradients
+// leave idle where the group fills part of a round: 474 tiles of 512 with layers of 768 columns.  They can also be what
+// begins another round (2048 columns: 824 tiles of 256x256, the weight gradients by themselves are 768 = three rounds).
 struct GroupPlan {
   unsigned char* pool = nullptr;
   uint64_t pool_bytes = 0, used = 0;

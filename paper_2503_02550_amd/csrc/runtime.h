@@ -124,7 +124,7 @@ struct InferIO { const void* in_dev; void* out_dev; uint32_t seq = 0; };      //
 sif_status build_infer_plan(const InferModel& im, const InferIO* io, uint32_t n_io, uint32_t batch, uint32_t seq,
                             uint32_t kernel_us_max, Plan& out);
 uint32_t infer_coalesce(const sif_infer_desc& d);
-// Cuts `op` (row_split) into its first `rows_first` rows (a multiple of 128, 0 < rows_first < m) and the rest
+// Cuts `op` (row_split) into its first `rows_first` rows (a multiple of its tiles' rows, 0 < rows_first < m) and the rest
 void split_gemm_rows(const Op& op, uint32_t rows_first, Op& first, Op& rest);
 constexpr uint32_t kMaxCoalesce = 32;     // most requests one coalesced kernel sequence serves
 

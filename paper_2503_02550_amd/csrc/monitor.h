@@ -122,7 +122,7 @@ __device__ __forceinline__ T ld_sys(const T* p) {
 }
 
 __device__ __forceinline__ uint32_t grid_blocks() { return gridDim.x * gridDim.y * gridDim.z; }
-__device__ __forceinline__ bool first_thread() { return threadIdx.x == 0 && threadIdx.y == 0 && threadIdx.z == 0; }
+__device__ __forceinline__ bool first_thread() { return threadIdx.x == 0; }      // (every launch has one-dimensional blocks)
 
 // Decision of the first block of a gated launch: run only if no earlier launch of this speculation window was
 // skipped, the training stream is inside a bubble, the predicted rest of the bubble holds this kernel, and

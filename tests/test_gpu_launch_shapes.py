@@ -202,6 +202,35 @@ def test_gemm_bf16_epilogues_on_every_tile_width(m, n, k, epi):
     assert float((got[0][0].double() - ref).norm() / ref.norm()) <= 2.0 ** -8
 
 
+@pytest.mark.parametrize("m,n,k", [(256, 256, 64), (300, 520, 192), (513, 264, 128), (31, 777, 64)])
+@pytest.mark.parametrize("epi", ["residual", "grad", "grad_residual", "grad_bias_residual", "gelu_aux_residual", "f32_residual"])
+def test_gemm_bf16_staged_epilogues_on_256_tiles(m, n, k, epi):
+    """What an epilogue reads is requested 16 or 32 rows ahead of its staging passes of eight (256x256 tiles) or with them (128x128):
+    whole and ragged tiles, an auxiliary tensor, a residual and both, 16-byte accesses and single ones: the same bits, and the
+    product (one rounding to bf16 of the result, and of fp32 sums that GELU' or GELU scales)."""
+    gen = torch.Generator(device=DEV).manual_seed(m + n + k)
+    a, b, bias, res, z = _bf16(gen, m, k), _bf16(gen, n, k), _bf16(gen, n), _bf16(gen, m, n), _bf16(gen, m, n)
+    f32out = epi.startswith("f32")
+    epilogue = sum(flag for name, flag in (("gelu", S.SIF_EPI_GELU), ("grad", S.SIF_EPI_GELU_GRAD), ("bias", S.SIF_EPI_BIAS), ("residual", S.SIF_EPI_RESIDUAL),
+                                           ("f32", S.SIF_EPI_OUT_F32)) if name in epi.split("_"))
+    got = []
+    for tile in (256, 128):
+        c, aux = torch.full((m, n), float("nan"), device=DEV, dtype=torch.float32 if f32out else torch.bfloat16), z.clone()
+        torch.cuda.synchronize()
+        S.sif_k_gemm_bf16(a, b, c, m, n, k, k, k, n, epilogue=epilogue, bias=bias if "bias" in epi else None, aux=None if f32out or epi == "residual" else aux,
+                          res=(res.float() if f32out else res) if "residual" in epi else None, tile=tile)
+        torch.cuda.synchronize()
+        got.append((c, aux))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    ref = a.double() @ b.double().t() + (bias.double() if "bias" in epi else 0.0)
+    if "grad" in epi:
+        ref = ref * (0.5 * (1 + torch.erf(z.double() / 2 ** 0.5)) + z.double() * torch.exp(-z.double() ** 2 / 2) / (2 * torch.pi) ** 0.5)
+    if "gelu" in epi:
+        ref = torch.nn.functional.gelu(ref)
+    ref = ref + (res.double() if "residual" in epi else 0.0)
+    assert float((got[0][0].double() - ref).norm() / ref.norm()) <= 2.0 ** -8
+
+
 @pytest.mark.parametrize("causal", [0, 1])
 @pytest.mark.parametrize("bsz,s,h", [(2, 2, 2), (1, 63, 1), (2, 65, 2), (1, 129, 3), (2, 192, 1), (1, 257, 2), (1, 449, 1)])
 def test_attention_with_heads_of_128_at_the_edges_of_its_tiles(bsz, s, h, causal):

@@ -339,11 +339,13 @@ __device__ __forceinline__ void gemm_store_tile(const GemmP& p, floatx16 (&acc)[
   // What the epilogue reads from global memory is requested before the staging, not inside it, and for 32 rows at a time
   // (the first 32, while all accumulators are still held, in halves) however few are staged in a pass: a wait for it also
   // waits for the stores before it.  (Requested by passes of eight rows, 131072 x 768 x 768 with bias and residual on
-  // 256x256 tiles took 225 us, now 205; with the GELU derivative 259 and 230.)  One set of registers: where both an auxiliary tensor and a residual are read, the
-  // residual is not requested ahead.
+  // 256x256 tiles took 229 us, now 190; with the GELU derivative 259 and 217.)  With several passes there is one set of
+  // registers: where both an auxiliary tensor and a residual are read, the residual is not requested ahead.
   const bool grad = (p.epi & SIF_EPI_GELU_GRAD) != 0, residual = (p.epi & (SIF_EPI_RESIDUAL | SIF_EPI_OUT_F32)) == SIF_EPI_RESIDUAL;
-  const bf16_t* ahead = grad ? p.aux : residual ? reinterpret_cast<const bf16_t*>(p.res) : nullptr;
-  uint4 read_q[PASSES][ITS];
+  const bf16_t* const res = reinterpret_cast<const bf16_t*>(p.res);
+  const bf16_t* const ahead = grad ? p.aux : residual ? res : nullptr;
+  constexpr bool BOTH = PASSES == 1;
+  uint4 read_q[PASSES][ITS], res_q[BOTH ? ITS : 1];
   auto request = [&](uint32_t m32, int from, int to) {
 #pragma unroll
     for (int ps = 0; ps < PASSES; ++ps)
@@ -352,8 +354,13 @@ __device__ __forceinline__ void gemm_store_tile(const GemmP& p, floatx16 (&acc)[
         if (ps < from || ps >= to) continue;
         const uint32_t ch = lane + it * 64, m = m32 + ps * SR + ch / CPR, n = nw + (ch % CPR) * 8;
         read_q[ps][it] = make_uint4(0, 0, 0, 0);
-        if (vec_ok && m < p.m && n < p.n && (ITEMS >= 64 || ch < ITEMS))
-          read_q[ps][it] = *reinterpret_cast<const uint4*>(ahead + c_off + (size_t)m * p.ldc + n);
+        if (BOTH) res_q[it] = make_uint4(0, 0, 0, 0);
+        if (vec_ok && m < p.m && n < p.n && (ITEMS >= 64 || ch < ITEMS)) {
+          const size_t idx = c_off + (size_t)m * p.ldc + n;
+          if (!BOTH) read_q[ps][it] = *reinterpret_cast<const uint4*>(ahead + idx);
+          if (BOTH && grad) read_q[ps][it] = *reinterpret_cast<const uint4*>(p.aux + idx);
+          if (BOTH && residual) res_q[it] = *reinterpret_cast<const uint4*>(res + idx);
+        }
       }
   };
 #pragma unroll
@@ -361,7 +368,7 @@ __device__ __forceinline__ void gemm_store_tile(const GemmP& p, floatx16 (&acc)[
     constexpr int HALF = PASSES > 2 ? PASSES / 2 : PASSES;
 #pragma unroll
     for (int ps = 0; ps < PASSES; ++ps) {
-      if (ahead != nullptr) {
+      if (BOTH || ahead != nullptr) {
         if (i == 0 && ps % HALF == 0) request(mw, ps, ps + HALF);
         if (i > 0 && ps == 0) request(mw + i * 32, 0, PASSES);
       }
@@ -383,9 +390,12 @@ __device__ __forceinline__ void gemm_store_tile(const GemmP& p, floatx16 (&acc)[
           float v[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
           const uint32_t m = mw + i * 32 + ps * SR + row, n = nw + c8 * 8;
           if (m < p.m && n < p.n) {
-            uint4 res_q = read_q[ps][it];
-            if (grad && residual && vec_ok) res_q = *reinterpret_cast<const uint4*>(reinterpret_cast<const bf16_t*>(p.res) + c_off + (size_t)m * p.ldc + n);
-            gemm_epilogue8(p, c_off, m, n, v, bias8, vec_ok, read_q[ps][it], res_q);
+            uint4 res8 = BOTH ? res_q[it] : read_q[ps][it];
+            if (!BOTH && grad && residual && vec_ok) {
+              res8 = *reinterpret_cast<const uint4*>(res + c_off + (size_t)m * p.ldc + n);
+              asm("" : "+v"(res8.x), "+v"(res8.y), "+v"(res8.z), "+v"(res8.w));      // waited for here, not by those that skip this
+            }
+            gemm_epilogue8(p, c_off, m, n, v, bias8, vec_ok, read_q[ps][it], res8);
           }
         }
       }
@@ -775,7 +785,7 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(124))) void 
       gemm_store_tile<TI, TJ, SR>(cp, acc, stage + wave * (SR * TJ * 32), cm0 + wm * (TI * 32), cn0 + wn * 64, c_off, bias_q);
     }
   }
-  kernel_end(ctl, true);
+  kernel_end(ctl, true, threadIdx.x == 0);
 }
 
 static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }

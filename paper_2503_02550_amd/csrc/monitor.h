@@ -122,7 +122,7 @@ __device__ __forceinline__ T ld_sys(const T* p) {
 }
 
 __device__ __forceinline__ uint32_t grid_blocks() { return gridDim.x * gridDim.y * gridDim.z; }
-__device__ __forceinline__ bool first_thread() { return threadIdx.x == 0; }      // (every launch has one-dimensional blocks)
+__device__ __forceinline__ bool first_thread() { return threadIdx.x == 0 && threadIdx.y == 0 && threadIdx.z == 0; }
 
 // Decision of the first block of a gated launch: run only if no earlier launch of this speculation window was
 // skipped, the training stream is inside a bubble, the predicted rest of the bubble holds this kernel, and
@@ -233,10 +233,12 @@ __device__ __forceinline__ bool kernel_begin(const KCtl& c) {
 // it reads in one round trip; a training kernel has nothing to read.  (With 64 first-level counters for every grid, the
 // kernel count read back by block 0 and the reads one after the other: step of the two-layer MLP 124 us, now 112; a
 // batch-1 encoder request of 86 launches 1603 -> 1483 us; two-layer decoder of 256 tokens 473 -> 412 us.)
-__device__ __forceinline__ void kernel_end(const KCtl& c, bool ran) {
+// (`first`: whether this is the block's first thread; a kernel with one-dimensional blocks and no register to spare says it
+// by the one coordinate that it holds anyway.)
+__device__ __forceinline__ void kernel_end(const KCtl& c, bool ran, bool first = first_thread()) {
   if (c.rec == nullptr || !ran) return;
   __syncthreads();
-  if (!first_thread()) return;
+  if (!first) return;
   const uint32_t total = grid_blocks(), id = linear_block();
   uint32_t arrivals = total;                     // on the top counter
   if (total > 32u) {

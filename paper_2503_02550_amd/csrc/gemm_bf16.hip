@@ -46,15 +46,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
-// 16 bytes of a result, stored with the non-temporal hint.  A product's output is written once and read by a later
-// kernel, and the chip's CUs write their tiles in bursts that exceed what the L2 takes in at once: stores that do not
-// claim L2 lines are acknowledged sooner (the wavefront waits for them at its next wait for a fetch), and they leave
-// the operand panels, which the tiles of an XCD share, in the L2.
-__device__ __forceinline__ void store_result16(void* p, const uint4& v) {
-  const u32x4 x = {v.x, v.y, v.z, v.w};
-  __builtin_nontemporal_store(x, reinterpret_cast<u32x4*>(p));
-}
-
 struct GemmP {
   const bf16_t* a; const bf16_t* b; void* c; const bf16_t* bias; const void* res; bf16_t* aux;
   uint32_t m, n, k, lda, ldb, ldc, epi, k_causal, batch_inner, tiles_m, tiles_n, k_limit;
@@ -169,16 +160,16 @@ struct TileFetch {
   static_assert(ROWS * 8 % THREADS == 0, "whole 16-byte vectors per thread and tile");
   static constexpr int NV = ROWS * 8 / THREADS;
   uint32_t voff[NV];
-  __device__ __forceinline__ static uint32_t unit(int i) { return i * THREADS + threadIdx.x; }
+  __device__ __forceinline__ static uint32_t unit(int i, uint32_t tid) { return i * THREADS + tid; }
   __device__ __forceinline__ static uint32_t row_of(uint32_t r) { return (r / G) * GS + PART * G + r % G; }
-  __device__ __forceinline__ static uint32_t k_of(int i) {      // first k of the 16 bytes
-    const uint32_t u = unit(i);
+  __device__ __forceinline__ static uint32_t k_of(int i, uint32_t tid) {      // first k of the 16 bytes
+    const uint32_t u = unit(i, tid);
     return LAYOUT == 0 ? ((u & 7u) ^ swz_key(u >> 3)) * 8 : u / (ROWS / 8);
   }
-  __device__ __forceinline__ void init(uint32_t ld, uint32_t rows_left) {
+  __device__ __forceinline__ void init(uint32_t ld, uint32_t rows_left, uint32_t tid) {
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-      const uint32_t u = unit(i), k = k_of(i);
+      const uint32_t u = unit(i, tid), k = k_of(i, tid);
       if (LAYOUT == 0) {
         const uint32_t r = row_of(u >> 3);
         voff[i] = r < rows_left ? (r * ld + k) * 2u : kOutside;
@@ -192,7 +183,7 @@ struct TileFetch {
     fetch16(rsrc, voff[i], lds + i * (THREADS * 16) + wave * 1024);
   }
   __device__ __forceinline__ void issue_last(const i32x4& rsrc, uint32_t lds, uint32_t wave, int i, uint32_t k_left) const {
-    fetch16(rsrc, k_of(i) < k_left ? voff[i] : kOutside, lds + i * (THREADS * 16) + wave * 1024);
+    fetch16(rsrc, k_of(i, threadIdx.x) < k_left ? voff[i] : kOutside, lds + i * (THREADS * 16) + wave * 1024);
   }
 };
 // waits until at most N vector memory operations of this wavefront are outstanding (they complete in order)
@@ -207,202 +198,248 @@ __device__ __forceinline__ void barrier_only() {
 }
 
 // ---------------------------------------------------------------------------------------------- epilogue
-// Epilogue of eight consecutive columns n..n+7 of row m (both inside the result): scale, bias, GELU, GELU' multiply,
-// residual, store; `vec` says that every access may be a 16-byte vector, and then b holds the eight bias values,
-// aux_q the eight auxiliary values (GELU_GRAD) and res_q the eight bf16 residual values.
-__device__ __forceinline__ void gemm_epilogue8(const GemmP& p, size_t c_off, uint32_t m, uint32_t n, float (&v)[8], const float (&b)[8], bool vec,
-                                               const uint4& aux_q, const uint4& res_q) {
+// What one wavefront stores is its (TI*32) x (TJ*32) part of an output tile, first row mw, first column nw.  Accumulator
+// element r of lane l is row (r/4)*8 + (l/32)*4 + r%4, column l%32 of its 32x32 tile.  The values pass through SR*TJ*128
+// bytes of LDS of the wavefront's own, so that every global access - residual, auxiliary tensor, result - is a 16-byte
+// vector along a row; no block-wide barrier is needed.
+//
+// Straight-line code: which tensors are read and written is decided once per tile (a variant each), and what lies past the
+// last row or column is left out by the range check of the buffer resources, not by branches; LDS operations of a wavefront
+// complete in order, so the next pass is written while the last one's reads are under way.  (What bounds it: with little
+// on the chip a wavefront's own instructions, with a tile on every CU the rate at which memory takes 32 MB at once.  With
+// the decisions taken element by element and a wait per pass, an eighth of a 256x256 tile took 5800 cycles plain and 13900
+// with a residual, nothing else on the chip; now 3300 and 5700.  131072 x 768 x 3072 with bias and residual 549 -> 539 us,
+// x 3072 x 768 with GELU 679 -> 650, 131072 x 768 x 768 with residual 200 -> 187, 4096 x 4096 x 512 with residual 29.4 -> 26.8;
+// six layers of d 2048 18.2 -> 17.0 ms a step, a batch of 4096 tokens through twelve of d 768 1.61 -> 1.54 ms.)
+
+// `bytes` from `base` on as a buffer resource, at most 2 GB: offsets beyond it read as zeros and are not written
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t result_rsrc(const void* base, uint64_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)(bytes < kOutside ? bytes : kOutside), 0x00020000);
+}
+__device__ __forceinline__ uint4 read16(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
+}
+// 16 bytes of a result, stored with the non-temporal hint (2).  A product's output is written once and read by a later
+// kernel, and the chip's CUs write their tiles in bursts that exceed what the L2 takes in at once: stores that do not
+// claim L2 lines are acknowledged sooner (the wavefront waits for them at its next wait for a fetch), and they leave
+// the operand panels, which the tiles of an XCD share, in the L2.
+__device__ __forceinline__ void write16(__amdgpu_buffer_rsrc_t r, uint32_t off, const uint4& v, bool streamed = true) {
+  if (streamed) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, (int)off, 0, 2);
+  else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, (int)off, 0, 0);
+}
+// LDS accesses of a wavefront's lanes to each other's data stay in order: for the compiler, the hardware keeps it anyway
+__device__ __forceinline__ void lanes_in_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Variants that read nothing but the bias (plain, bias, bias + GELU without the pre-activation output) are finished in the
+// accumulator layout, where a lane's column is fixed, and staged as bf16: two vertically adjacent results share a 32-bit
+// word, the staging area is [row pairs][W] words, half the LDS traffic of the fp32 staging below.  A lane then reads eight
+// words = eight columns of two rows, separates the rows with byte permutes and stores two 16-byte row vectors.  (Row pairs
+// of the two half-wavefronts differ by two: their columns are swapped in halves, so that they fall on different banks.)
+template <int TI, int TJ, int SR, bool GELU>
+__device__ __forceinline__ void gemm_store_packed(const GemmP& p, floatx16 (&acc)[TI][TJ], float* sW, uint32_t mw, uint32_t nw, size_t c_off, uint32_t lane,
+                                                  const bf16_t* bias_s) {
+  constexpr int W = TJ * 32, CPR = W / 8;                 // columns, 8-column chunks per row
+  constexpr int PR = SR < 16 ? SR : 16, PASSES = 16 / PR, RE = 16 / PASSES, ITS = PR * CPR / 64;      // row pairs, accumulator elements and vectors per lane of a pass
+  static_assert(PR * CPR % 64 == 0, "whole vectors per lane");
+  uint32_t* const sP = reinterpret_cast<uint32_t*>(sW);
+  const uint32_t hh = lane >> 5, pitch = p.ldc * 2;       // bytes from row to row
+  const auto c = result_rsrc(reinterpret_cast<bf16_t*>(p.c) + c_off + (size_t)mw * p.ldc + nw, mw < p.m ? (uint64_t)(p.m - mw) * pitch : 0);
+  uint32_t off[ITS];
+#pragma unroll
+  for (int it = 0; it < ITS; ++it) {
+    const uint32_t item = lane + it * 64;
+    off[it] = nw + item % CPR * 8 < p.n ? 2 * (item / CPR) * pitch + item % CPR * 16 : kOutside;
+  }
+  float bcol[TJ];
+#pragma unroll
+  for (int j = 0; j < TJ; ++j) bcol[j] = p.bias != nullptr ? bf2f(bias_s[j * 32 + (lane & 31)]) : 0.f;
+  uint4 w[2][ITS][2];
+  auto finish = [&](int pass) {
+#pragma unroll
+    for (int it = 0; it < ITS; ++it) {
+      const uint4 &w0 = w[pass & 1][it][0], &w1 = w[pass & 1][it][1];
+      const uint32_t o = off[it] + (uint32_t)(pass * 2 * PR) * pitch;
+      write16(c, o, make_uint4(__builtin_amdgcn_perm(w0.y, w0.x, 0x05040100), __builtin_amdgcn_perm(w0.w, w0.z, 0x05040100),
+                               __builtin_amdgcn_perm(w1.y, w1.x, 0x05040100), __builtin_amdgcn_perm(w1.w, w1.z, 0x05040100)));
+      write16(c, o + pitch, make_uint4(__builtin_amdgcn_perm(w0.y, w0.x, 0x07060302), __builtin_amdgcn_perm(w0.w, w0.z, 0x07060302),
+                                       __builtin_amdgcn_perm(w1.y, w1.x, 0x07060302), __builtin_amdgcn_perm(w1.w, w1.z, 0x07060302)));
+    }
+  };
+#pragma unroll
+  for (int pass = 0; pass < TI * PASSES; ++pass) {
+    const int i = pass / PASSES, ps = pass % PASSES;
+#pragma unroll
+    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+      for (int r = ps * RE; r < (ps + 1) * RE; r += 2) {
+        float x0 = acc[i][j][r] * p.alpha + bcol[j], x1 = acc[i][j][r + 1] * p.alpha + bcol[j];
+        if (GELU) { x0 = gelu_fast(x0); x1 = gelu_fast(x1); }
+        const uint32_t pr = (r >> 2) * 4 + hh * 2 + ((r & 3) >> 1) - ps * PR, col = (j * 32 + (lane & 31)) ^ (hh * (W / 2));
+        sP[pr * W + col] = pack_bf2(x0, x1);
+      }
+    lanes_in_order();
+#pragma unroll
+    for (int it = 0; it < ITS; ++it) {
+      const uint32_t item = lane + it * 64, pr = item / CPR, pos = ((item % CPR) ^ (((pr >> 1) & 1u) * (CPR / 2))) * 8;
+      w[pass & 1][it][0] = *reinterpret_cast<const uint4*>(sP + pr * W + pos);
+      w[pass & 1][it][1] = *reinterpret_cast<const uint4*>(sP + pr * W + pos + 4);
+    }
+    lanes_in_order();
+    if (pass > 0) finish(pass - 1);
+    __builtin_amdgcn_sched_barrier(0);                    // (no more than two passes in registers)
+  }
+  finish(TI * PASSES - 1);
+}
+
+// Variants that read a tensor of the result's shape, write the pre-activation too or store fp32: staged as fp32 by SR rows, a
+// chunk of eight columns per lane and vector.  Chunk c (four floats) of a staging row lives at c ^ key(row): the two
+// half-wavefronts of a store and the eight rows of a load then fall on different banks.  What is read is requested for 64
+// rows ahead: a wait for it also waits for the stores before it.
+enum { kRowsResidual, kRowsGeluAux, kRowsGeluGrad, kRowsF32 };
+template <int TI, int TJ, int SR, int KIND>
+__device__ __forceinline__ void gemm_store_rows(const GemmP& p, floatx16 (&acc)[TI][TJ], float* sW, uint32_t mw, uint32_t nw, size_t c_off, uint32_t lane,
+                                                const bf16_t* bias_s) {
+  constexpr int W = TJ * 32, CPR = W / 8, PASSES = 32 / SR, ITS = SR * CPR / 64, PER = PASSES * ITS;      // PER: vectors per lane of 32 rows
+  static_assert(SR * CPR % 64 == 0, "whole vectors per lane");
+  constexpr bool READS = KIND == kRowsResidual || KIND == kRowsGeluGrad, F32 = KIND == kRowsF32;
+  constexpr int AHEAD = TI < 2 ? TI : 2;
+  const uint32_t hh = lane >> 5, esize = F32 ? 4 : 2, pitch = p.ldc * esize;
+  const size_t first = c_off + (size_t)mw * p.ldc + nw;
+  const uint64_t extent = mw < p.m ? (uint64_t)(p.m - mw) * pitch : 0;
+  const auto c = result_rsrc(reinterpret_cast<unsigned char*>(p.c) + first * esize, extent);
+  const auto other = result_rsrc(KIND == kRowsResidual ? reinterpret_cast<const bf16_t*>(p.res) + first : p.aux + first, F32 ? 0 : extent);
+  uint32_t off[ITS];
+#pragma unroll
+  for (int it = 0; it < ITS; ++it) {
+    const uint32_t item = lane + it * 64;
+    off[it] = nw + item % CPR * 8 < p.n ? (item / CPR) * pitch + item % CPR * 8 * esize : kOutside;
+  }
+  uint4 q[AHEAD][PER];
+  auto request = [&](int i) {
+    if constexpr (READS) {
+#pragma unroll
+      for (int k = 0; k < PER; ++k) q[i % AHEAD][k] = read16(other, off[k % ITS] + (uint32_t)(i * 32 + k / ITS * SR) * pitch);
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) request(i);
+  const uint4 bq = p.bias != nullptr ? *reinterpret_cast<const uint4*>(bias_s + lane % CPR * 8) : make_uint4(0, 0, 0, 0);      // (64 is a multiple of CPR)
+  const float bias[8] = {bflo(bq.x), bfhi(bq.x), bflo(bq.y), bfhi(bq.y), bflo(bq.z), bfhi(bq.z), bflo(bq.w), bfhi(bq.w)};
+  auto key = [](uint32_t row) { return (((row >> 2) & 1u) * (W / 8)) | (row & 1u); };
+  auto pack = [](const float (&v)[8]) { return make_uint4(pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]), pack_bf2(v[4], v[5]), pack_bf2(v[6], v[7])); };
+  float4 s[2][ITS][2];
+  auto finish = [&](int pass) {
+#pragma unroll
+    for (int it = 0; it < ITS; ++it) {
+      const float4 &q0 = s[pass & 1][it][0], &q1 = s[pass & 1][it][1];
+      float v[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
+      const uint32_t o = off[it] + (uint32_t)(pass * SR) * pitch;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = v[e] * p.alpha + bias[e];
+      if constexpr (F32) {
+        write16(c, o, make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])), false);
+        write16(c, o + 16, make_uint4(__float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]), __float_as_uint(v[7])), false);
+        continue;
+      }
+      if constexpr (READS) {
+        const uint4 t = q[pass / PASSES % AHEAD][pass % PASSES * ITS + it];
+        const float x[8] = {bflo(t.x), bfhi(t.x), bflo(t.y), bfhi(t.y), bflo(t.z), bfhi(t.z), bflo(t.w), bfhi(t.w)};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { if (KIND == kRowsResidual) v[e] += x[e]; else v[e] *= gelu_grad_fast(x[e]); }
+      }
+      if constexpr (KIND == kRowsGeluAux) {
+        write16(other, o, pack(v), false);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = gelu_fast(v[e]);
+      }
+      write16(c, o, pack(v));
+    }
+  };
+#pragma unroll
+  for (int pass = 0; pass < TI * PASSES; ++pass) {
+    const int i = pass / PASSES, ps = pass % PASSES;
+#pragma unroll
+    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+      for (int r = ps * (SR / 2); r < (ps + 1) * (SR / 2); ++r) {
+        const uint32_t row = (r >> 2) * 8 + hh * 4 + (r & 3) - ps * SR, col = j * 32 + (lane & 31);
+        sW[row * W + ((((col >> 2) ^ key(row)) << 2) | (col & 3))] = acc[i][j][r];
+      }
+    lanes_in_order();
+#pragma unroll
+    for (int it = 0; it < ITS; ++it) {
+      const uint32_t item = lane + it * 64, row = item / CPR, c8 = item % CPR;
+      s[pass & 1][it][0] = *reinterpret_cast<const float4*>(sW + row * W + (((2 * c8) ^ key(row)) << 2));
+      s[pass & 1][it][1] = *reinterpret_cast<const float4*>(sW + row * W + (((2 * c8 + 1) ^ key(row)) << 2));
+    }
+    lanes_in_order();
+    if (pass > 0) {
+      finish(pass - 1);
+      if (pass % PASSES == 0 && i - 1 + AHEAD < TI) request(i - 1 + AHEAD);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  finish(TI * PASSES - 1);
+}
+
+// Everything else - a column count that is no multiple of eight, an output slice that is not 16-byte aligned, rare
+// combinations, rows further apart than the offsets above reach - one element at a time.
+template <int TI, int TJ, int SR>
+__device__ __forceinline__ void gemm_store_single(const GemmP& p, floatx16 (&acc)[TI][TJ], float* sW, uint32_t mw, uint32_t nw, size_t c_off, uint32_t lane) {
+  constexpr int W = TJ * 32, PASSES = 32 / SR;
   const uint32_t epi = p.epi;
-  const size_t idx = c_off + (size_t)m * p.ldc + n;
-  if (vec) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = v[e] * p.alpha + b[e];
-    if (epi & SIF_EPI_GELU) {
-      if (p.aux != nullptr)
-        *reinterpret_cast<uint4*>(p.aux + idx) = make_uint4(pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]), pack_bf2(v[4], v[5]), pack_bf2(v[6], v[7]));
+  for (int pass = 0; pass < TI * PASSES; ++pass) {
+    const int i = pass / PASSES, ps = pass % PASSES;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = gelu_fast(v[e]);
-    }
-    if (epi & SIF_EPI_GELU_GRAD) {
-      const uint4 q = aux_q;                  // fetched before the staging pass
-      const float z[8] = {bflo(q.x), bfhi(q.x), bflo(q.y), bfhi(q.y), bflo(q.z), bfhi(q.z), bflo(q.w), bfhi(q.w)};
+    for (int j = 0; j < TJ; ++j)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] *= gelu_grad_fast(z[e]);
-    }
-    if (epi & SIF_EPI_OUT_F32) {
-      float* cp = reinterpret_cast<float*>(p.c) + idx;
-      if (epi & SIF_EPI_RESIDUAL) {
-        const float* rp = reinterpret_cast<const float*>(p.res) + idx;
-        const float4 r0 = *reinterpret_cast<const float4*>(rp), r1 = *reinterpret_cast<const float4*>(rp + 4);
-        v[0] += r0.x; v[1] += r0.y; v[2] += r0.z; v[3] += r0.w; v[4] += r1.x; v[5] += r1.y; v[6] += r1.z; v[7] += r1.w;
-      }
-      *reinterpret_cast<float4*>(cp) = make_float4(v[0], v[1], v[2], v[3]);
-      *reinterpret_cast<float4*>(cp + 4) = make_float4(v[4], v[5], v[6], v[7]);
-    } else {
-      if (epi & SIF_EPI_RESIDUAL) {
-        const uint4 q = res_q;                // fetched before the staging pass
-        v[0] += bflo(q.x); v[1] += bfhi(q.x); v[2] += bflo(q.y); v[3] += bfhi(q.y); v[4] += bflo(q.z); v[5] += bfhi(q.z); v[6] += bflo(q.w); v[7] += bfhi(q.w);
-      }
-      store_result16(reinterpret_cast<bf16_t*>(p.c) + idx, make_uint4(pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]), pack_bf2(v[4], v[5]), pack_bf2(v[6], v[7])));
-    }
-  } else {
-    // ragged N (or an output slice that is not 16-byte aligned): one element at a time
-    for (int e = 0; e < 8 && n + e < p.n; ++e) {
-      float x = v[e] * p.alpha + (p.bias != nullptr ? bf2f(p.bias[n + e]) : 0.f);
+      for (int r = ps * (SR / 2); r < (ps + 1) * (SR / 2); ++r) sW[((r >> 2) * 8 + (lane >> 5) * 4 + (r & 3) - ps * SR) * W + j * 32 + (lane & 31)] = acc[i][j][r];
+    lanes_in_order();
+#pragma clang loop unroll(disable)
+    for (uint32_t at = lane; at < SR * W; at += 64) {
+      const uint32_t m = mw + pass * SR + at / W, n = nw + at % W;
+      if (m >= p.m || n >= p.n) continue;
+      const size_t idx = c_off + (size_t)m * p.ldc + n;
+      float x = sW[at] * p.alpha + (p.bias != nullptr ? bf2f(p.bias[n]) : 0.f);
       if (epi & SIF_EPI_GELU) {
-        if (p.aux != nullptr) p.aux[idx + e] = f2bf(x);
+        if (p.aux != nullptr) p.aux[idx] = f2bf(x);
         x = gelu_fast(x);
       }
-      if (epi & SIF_EPI_GELU_GRAD) x *= gelu_grad_fast(bf2f(p.aux[idx + e]));
+      if (epi & SIF_EPI_GELU_GRAD) x *= gelu_grad_fast(bf2f(p.aux[idx]));
       if (epi & SIF_EPI_OUT_F32) {
-        if (epi & SIF_EPI_RESIDUAL) x += reinterpret_cast<const float*>(p.res)[idx + e];
-        reinterpret_cast<float*>(p.c)[idx + e] = x;
+        if (epi & SIF_EPI_RESIDUAL) x += reinterpret_cast<const float*>(p.res)[idx];
+        reinterpret_cast<float*>(p.c)[idx] = x;
       } else {
-        if (epi & SIF_EPI_RESIDUAL) x += bf2f(reinterpret_cast<const bf16_t*>(p.res)[idx + e]);
-        reinterpret_cast<bf16_t*>(p.c)[idx + e] = f2bf(x);
+        if (epi & SIF_EPI_RESIDUAL) x += bf2f(reinterpret_cast<const bf16_t*>(p.res)[idx]);
+        reinterpret_cast<bf16_t*>(p.c)[idx] = f2bf(x);
       }
     }
+    lanes_in_order();
   }
 }
 
-// Epilogue of one wavefront's (TI*32) x (TJ*32) part of an output tile, first row mw, first column nw.  The accumulators
-// pass, SR rows (staged as fp32) or 2*SR rows (staged as bf16) at a time, through SR*TJ*128 bytes of LDS of the
-// wavefront's own so that every global access of the epilogue - bias, residual, auxiliary tensor, result - is a 16-byte
-// vector along a row; no block-wide barrier is needed.  Accumulator element r of lane l is row (r/4)*8 + (l/32)*4 + r%4,
-// column l%32 of its 32x32 tile.  bias_q: the bias of columns nw + 8*(l % (TJ*4))...
+// bias_s: the bias of the columns nw.. in LDS (gemm_fetch_bias)
 template <int TI, int TJ, int SR>
-__device__ __forceinline__ void gemm_store_tile(const GemmP& p, floatx16 (&acc)[TI][TJ], float* sW, uint32_t mw, uint32_t nw, size_t c_off, const uint4& bias_q) {
-  constexpr int W = TJ * 32, CPR = W / 8;                 // columns, 8-column chunks per row
-  const uint32_t lane = threadIdx.x & 63, hh = lane >> 5;
-  const bool vec_ok = (p.n & 7) == 0 && ((c_off & 7) == 0);
-  // Epilogues that read nothing but the bias (plain, bias, bias + GELU without the pre-activation output) are
-  // finished in the accumulator layout, where a lane's column is fixed, and staged as bf16: two vertically adjacent
-  // results share a 32-bit word, the staging area is [SR row pairs][W] words, half the LDS traffic of the
-  // fp32 staging below.  A lane then reads eight words = eight columns of two rows, separates the rows with byte
-  // permutes and stores two 16-byte row vectors.  The arithmetic per element is the same as in gemm_epilogue8.
-  // (Row pairs of the two half-wavefronts differ by two: their columns are swapped in halves, so that they fall on
-  // different banks.)
-  const bool packed = vec_ok && (p.epi & (SIF_EPI_RESIDUAL | SIF_EPI_GELU_GRAD | SIF_EPI_OUT_F32)) == 0 &&
-                      !((p.epi & SIF_EPI_GELU) && p.aux != nullptr);
-  if (packed) {
-    uint32_t* sP = reinterpret_cast<uint32_t*>(sW);
-    constexpr int PR = SR < 16 ? SR : 16, PASSES = 16 / PR, RE = 16 / PASSES;      // row pairs and accumulator elements per pass
-    float bcol[TJ];
-#pragma unroll
-    for (int j = 0; j < TJ; ++j) {
-      const uint32_t n = nw + j * 32 + (lane & 31);
-      bcol[j] = (p.bias != nullptr && n < p.n) ? bf2f(p.bias[n]) : 0.f;
-    }
-#pragma unroll
-    for (int i = 0; i < TI; ++i)
-#pragma unroll
-      for (int ps = 0; ps < PASSES; ++ps) {
-#pragma unroll
-        for (int j = 0; j < TJ; ++j)
-#pragma unroll
-          for (int r = ps * RE; r < (ps + 1) * RE; r += 2) {
-            float x0 = acc[i][j][r] * p.alpha + bcol[j], x1 = acc[i][j][r + 1] * p.alpha + bcol[j];
-            if (p.epi & SIF_EPI_GELU) { x0 = gelu_fast(x0); x1 = gelu_fast(x1); }
-            const uint32_t pr = (r >> 2) * 4 + hh * 2 + ((r & 3) >> 1) - ps * PR, col = (j * 32 + (lane & 31)) ^ (hh * (W / 2));
-            sP[pr * W + col] = pack_bf2(x0, x1);
-          }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int it = 0; it < (PR * CPR + 63) / 64; ++it) {
-          const uint32_t item = lane + it * 64, pr = item / CPR, c8 = item % CPR;     // PR row pairs x CPR chunks of 8 columns
-          if (PR * CPR >= 64 || item < PR * CPR) {
-            const uint32_t pos = (c8 ^ (((pr >> 1) & 1u) * (CPR / 2))) * 8;
-            const uint4 w0 = *reinterpret_cast<const uint4*>(sP + pr * W + pos), w1 = *reinterpret_cast<const uint4*>(sP + pr * W + pos + 4);
-            const uint4 even = make_uint4(__builtin_amdgcn_perm(w0.y, w0.x, 0x05040100), __builtin_amdgcn_perm(w0.w, w0.z, 0x05040100),
-                                          __builtin_amdgcn_perm(w1.y, w1.x, 0x05040100), __builtin_amdgcn_perm(w1.w, w1.z, 0x05040100));
-            const uint4 odd = make_uint4(__builtin_amdgcn_perm(w0.y, w0.x, 0x07060302), __builtin_amdgcn_perm(w0.w, w0.z, 0x07060302),
-                                         __builtin_amdgcn_perm(w1.y, w1.x, 0x07060302), __builtin_amdgcn_perm(w1.w, w1.z, 0x07060302));
-            const uint32_t m = mw + i * 32 + 2 * (pr + ps * PR), n = nw + c8 * 8;
-            bf16_t* cp = reinterpret_cast<bf16_t*>(p.c) + c_off + (size_t)m * p.ldc + n;
-            if (n < p.n) {
-              if (m < p.m) store_result16(cp, even);
-              if (m + 1 < p.m) store_result16(cp + p.ldc, odd);
-            }
-          }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-      }
-    return;
-  }
-  // fp32 staging: SR rows (of the tile's eight-row groups, SR/8 at a time).  Chunk c (four floats) of a staging row lives
-  // at c ^ key(row): the two half-wavefronts of a store and the eight rows of a load then fall on different banks.
-  const float bias8[8] = {bflo(bias_q.x), bfhi(bias_q.x), bflo(bias_q.y), bfhi(bias_q.y), bflo(bias_q.z), bfhi(bias_q.z), bflo(bias_q.w), bfhi(bias_q.w)};
-  constexpr int PASSES = 32 / SR, ITEMS = SR * CPR, ITS = (ITEMS + 63) / 64;
-  auto key = [](uint32_t row) { return (((row >> 2) & 1u) * (W / 8)) | (row & 1u); };
-  // What the epilogue reads from global memory is requested before the staging, not inside it, and for 32 rows at a time
-  // (the first 32, while all accumulators are still held, in halves) however few are staged in a pass: a wait for it also
-  // waits for the stores before it.  (Requested by passes of eight rows, 131072 x 768 x 768 with bias and residual on
-  // 256x256 tiles took 229 us, now 190; with the GELU derivative 259 and 217.)  With several passes there is one set of
-  // registers: where both an auxiliary tensor and a residual are read, the residual is not requested ahead.
-  const bool grad = (p.epi & SIF_EPI_GELU_GRAD) != 0, residual = (p.epi & (SIF_EPI_RESIDUAL | SIF_EPI_OUT_F32)) == SIF_EPI_RESIDUAL;
-  const bf16_t* const res = reinterpret_cast<const bf16_t*>(p.res);
-  const bf16_t* const ahead = grad ? p.aux : residual ? res : nullptr;
-  constexpr bool BOTH = PASSES == 1;
-  uint4 read_q[PASSES][ITS], res_q[BOTH ? ITS : 1];
-  auto request = [&](uint32_t m32, int from, int to) {
-#pragma unroll
-    for (int ps = 0; ps < PASSES; ++ps)
-#pragma unroll
-      for (int it = 0; it < ITS; ++it) {
-        if (ps < from || ps >= to) continue;
-        const uint32_t ch = lane + it * 64, m = m32 + ps * SR + ch / CPR, n = nw + (ch % CPR) * 8;
-        read_q[ps][it] = make_uint4(0, 0, 0, 0);
-        if (BOTH) res_q[it] = make_uint4(0, 0, 0, 0);
-        if (vec_ok && m < p.m && n < p.n && (ITEMS >= 64 || ch < ITEMS)) {
-          const size_t idx = c_off + (size_t)m * p.ldc + n;
-          if (!BOTH) read_q[ps][it] = *reinterpret_cast<const uint4*>(ahead + idx);
-          if (BOTH && grad) read_q[ps][it] = *reinterpret_cast<const uint4*>(p.aux + idx);
-          if (BOTH && residual) res_q[it] = *reinterpret_cast<const uint4*>(res + idx);
-        }
-      }
-  };
-#pragma unroll
-  for (int i = 0; i < TI; ++i) {
-    constexpr int HALF = PASSES > 2 ? PASSES / 2 : PASSES;
-#pragma unroll
-    for (int ps = 0; ps < PASSES; ++ps) {
-      if (BOTH || ahead != nullptr) {
-        if (i == 0 && ps % HALF == 0) request(mw, ps, ps + HALF);
-        if (i > 0 && ps == 0) request(mw + i * 32, 0, PASSES);
-      }
-#pragma unroll
-      for (int j = 0; j < TJ; ++j)
-#pragma unroll
-        for (int r = ps * (SR / 2); r < (ps + 1) * (SR / 2); ++r) {
-          const uint32_t row = (r >> 2) * 8 + hh * 4 + (r & 3) - ps * SR, col = j * 32 + (lane & 31);
-          sW[row * W + ((((col >> 2) ^ key(row)) << 2) | (col & 3))] = acc[i][j][r];
-        }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-#pragma unroll
-      for (int it = 0; it < ITS; ++it) {
-        const uint32_t ch = lane + it * 64, row = ch / CPR, c8 = ch % CPR;      // SR rows x CPR chunks of 8 columns
-        if (ITEMS >= 64 || ch < ITEMS) {
-          const float4 q0 = *reinterpret_cast<const float4*>(sW + row * W + (((2 * c8) ^ key(row)) << 2));
-          const float4 q1 = *reinterpret_cast<const float4*>(sW + row * W + (((2 * c8 + 1) ^ key(row)) << 2));
-          float v[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
-          const uint32_t m = mw + i * 32 + ps * SR + row, n = nw + c8 * 8;
-          if (m < p.m && n < p.n) {
-            uint4 res8 = BOTH ? res_q[it] : read_q[ps][it];
-            if (!BOTH && grad && residual && vec_ok) {
-              res8 = *reinterpret_cast<const uint4*>(res + c_off + (size_t)m * p.ldc + n);
-              asm("" : "+v"(res8.x), "+v"(res8.y), "+v"(res8.z), "+v"(res8.w));      // waited for here, not by those that skip this
-            }
-            gemm_epilogue8(p, c_off, m, n, v, bias8, vec_ok, read_q[ps][it], res8);
-          }
-        }
-      }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-    }
-  }
+__device__ __forceinline__ void gemm_store_tile(const GemmP& p, floatx16 (&acc)[TI][TJ], float* sW, uint32_t mw, uint32_t nw, size_t c_off, uint32_t lane,
+                                                const bf16_t* bias_s) {
+  const uint32_t what = p.epi & (SIF_EPI_GELU | SIF_EPI_GELU_GRAD | SIF_EPI_RESIDUAL | SIF_EPI_OUT_F32);
+  const bool vectors = (p.n & 7) == 0 && (c_off & 7) == 0 && p.ldc <= (1u << 21);      // (TI*32 rows of fp32 stay below 2 GB)
+  if (vectors && what == 0) gemm_store_packed<TI, TJ, SR, false>(p, acc, sW, mw, nw, c_off, lane, bias_s);
+  else if (vectors && what == SIF_EPI_GELU && p.aux == nullptr) gemm_store_packed<TI, TJ, SR, true>(p, acc, sW, mw, nw, c_off, lane, bias_s);
+  else if (vectors && what == SIF_EPI_GELU) gemm_store_rows<TI, TJ, SR, kRowsGeluAux>(p, acc, sW, mw, nw, c_off, lane, bias_s);
+  else if (vectors && what == SIF_EPI_RESIDUAL) gemm_store_rows<TI, TJ, SR, kRowsResidual>(p, acc, sW, mw, nw, c_off, lane, bias_s);
+  else if (vectors && what == SIF_EPI_GELU_GRAD) gemm_store_rows<TI, TJ, SR, kRowsGeluGrad>(p, acc, sW, mw, nw, c_off, lane, bias_s);
+  else if (vectors && what == SIF_EPI_OUT_F32) gemm_store_rows<TI, TJ, SR, kRowsF32>(p, acc, sW, mw, nw, c_off, lane, bias_s);
+  else gemm_store_single<TI, TJ, SR>(p, acc, sW, mw, nw, c_off, lane);
+}
+
+// The bias of a wavefront's columns nw.. into 1 KB of LDS of its own, by one fetch (which writes zeros behind them)
+__device__ __forceinline__ void gemm_fetch_bias(const GemmP& p, uint32_t nw, uint32_t width, uint32_t lane, uint32_t lds) {
+  if (p.bias != nullptr && (p.n & 7) == 0) fetch16(operand_rsrc((uint64_t)(p.bias + nw)), lane * 8 < width && nw + lane * 8 < p.n ? lane * 16 : kOutside, lds);
 }
 
 // ---------------------------------------------------------------------------------------------- tiles
@@ -433,17 +470,27 @@ __device__ __forceinline__ uint32_t gemm_steal_tile(StreamRec* rec, uint32_t tot
   return kNone;
 }
 
-// The product of a launch over several that block `pid` works on; its record, the same for every lane, goes word by word
-// into scalar registers.
-__device__ __forceinline__ void gemm_load_record(GemmP& p, const GemmP* group, uint32_t group_n, uint32_t pid) {
+// A product's record where it lies in memory that no kernel writes: the launch's own arguments, or its entry in the list of a
+// launch over several.  Read through the scalar cache where it is needed; the pointer is made opaque so that the words are
+// read again instead of being kept in (or spilled from) scalar registers through a main loop.
+typedef __attribute__((address_space(4))) const GemmP* gemm_record_ptr;
+__device__ __forceinline__ gemm_record_ptr gemm_record_of_launch() { return (gemm_record_ptr)__builtin_amdgcn_kernarg_segment_ptr(); }
+// (of a launch over several: the entry that block `pid` works on)
+__device__ __forceinline__ gemm_record_ptr gemm_record_of_block(gemm_record_ptr group, uint32_t group_n, uint32_t pid) {
   uint32_t g = 0;
   while (g + 1 < group_n && pid >= group[g + 1].tile_base) ++g;
+  return group + g;
+}
+__device__ __forceinline__ GemmP gemm_read_record(gemm_record_ptr p) {
+  asm volatile("" : "+s"(p));
   static_assert(sizeof(GemmP) % 4 == 0, "copied as 32-bit words");
+  typedef __attribute__((address_space(4))) const uint32_t* word_ptr;
   uint32_t words[sizeof(GemmP) / 4];
-  const uint32_t* src = reinterpret_cast<const uint32_t*>(group + g);
 #pragma unroll
-  for (uint32_t w = 0; w < sizeof(GemmP) / 4; ++w) words[w] = __builtin_amdgcn_readfirstlane(src[w]);
-  __builtin_memcpy(&p, words, sizeof(GemmP));
+  for (uint32_t w = 0; w < sizeof(GemmP) / 4; ++w) words[w] = ((word_ptr)p)[w];
+  GemmP q;
+  __builtin_memcpy(&q, words, sizeof(GemmP));
+  return q;
 }
 
 // One tile per block.  A ring of ST K steps in LDS; a wavefront keeps the fragments of two steps in registers, so that
@@ -470,8 +517,9 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_num_vgpr(1
   static_assert(ST * STAGE * 2 >= WM * WN * TJ * 128 * SR, "the epilogue is staged in the ring");
   static_assert(F * (AHEAD - 1) < 64, "the wait counts 63 operations");
   __shared__ __align__(1024) bf16_t lds[ST * STAGE];
+  __shared__ __align__(1024) bf16_t s_bias[WM * WN * 512];
   if (!kernel_begin(ctl)) { kernel_end(ctl, false); return; }
-  if constexpr (GROUPED) gemm_load_record(p, p_in.group, p_in.group_n, blockIdx.x);
+  if constexpr (GROUPED) p = gemm_read_record(gemm_record_of_block((gemm_record_ptr)p_in.group, p_in.group_n, blockIdx.x));
 
   const uint32_t total_tiles = p.tiles_m * p.tiles_n, pid = blockIdx.x - p.tile_base;
   const uint32_t bo = blockIdx.z / p.batch_inner, bi = blockIdx.z % p.batch_inner;
@@ -499,8 +547,8 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_num_vgpr(1
   const size_t c_off = (size_t)(bo * p.c_so + bi * p.c_si);
   FetchA ta;
   FetchB tb;
-  ta.init(p.lda, p.m - m0);
-  tb.init(p.ldb, p.n - n0);
+  ta.init(p.lda, p.m - m0, threadIdx.x);
+  tb.init(p.ldb, p.n - n0, threadIdx.x);
   const bf16_t* A = p.a + bo * p.a_so + bi * p.a_si;
   const bf16_t* B = p.b + bo * p.b_so + bi * p.b_si;
   uint64_t base_a = (uint64_t)(ALAY == 0 ? A + (size_t)m0 * p.lda + k_begin : A + (size_t)k_begin * p.lda + m0);
@@ -538,6 +586,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_num_vgpr(1
     }
     base_a += step_a; base_b += step_b;
   };
+  gemm_fetch_bias(p, n0 + wn * (TJ * 32), TJ * 32, lane, (uint32_t)(uintptr_t)(__attribute__((address_space(3))) bf16_t*)s_bias + wave * 1024);
   for (uint32_t s = 0; s < (uint32_t)AHEAD && s < nt; ++s) fetch_step(s, s >= full);
   if (nt >= (uint32_t)AHEAD) wait_vm<F * (AHEAD - 1)>(); else wait_vm<0>();
   barrier_only();
@@ -601,11 +650,8 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_num_vgpr(1
   while (t + 1 < nt) { step(Int<0>()); step(Int<1>()); }
   if (t < nt) step(Int<0>());
 
-  uint4 bias_q = make_uint4(0, 0, 0, 0);       // the eight columns that this lane finishes in every pass of the epilogue
-  const uint32_t bn = n0 + wn * (TJ * 32) + (lane % (TJ * 4)) * 8;
-  if ((p.n & 7) == 0 && (c_off & 7) == 0 && p.bias != nullptr && bn < p.n) bias_q = *reinterpret_cast<const uint4*>(p.bias + bn);
   __syncthreads();                             // nobody reads the ring any more: it stages the results
-  gemm_store_tile<TI, TJ, SR>(p, acc, reinterpret_cast<float*>(lds) + wave * (SR * TJ * 32), m0 + wm * (TI * 32), n0 + wn * (TJ * 32), c_off, bias_q);
+  gemm_store_tile<TI, TJ, SR>(p, acc, reinterpret_cast<float*>(lds) + wave * (SR * TJ * 32), m0 + wm * (TI * 32), n0 + wn * (TJ * 32), c_off, lane, s_bias + wave * 512);
   kernel_end(ctl, true);
 }
 
@@ -639,9 +685,10 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(124))) void 
   constexpr int F1 = FetchA1::NV, F0 = FetchA0::NV + FetchB::NV;       // fetches of the second halves of A; of the rest
   __shared__ __align__(1024) bf16_t lds[2 * STAGE];
   __shared__ __align__(16) float stage[WM * WN * SR * TJ * 32];
+  __shared__ __align__(1024) bf16_t s_bias[WM * WN * 512];
   __shared__ uint32_t s_next;
   if (!kernel_begin(ctl)) { kernel_end(ctl, false); return; }
-  GemmP p = p_in;
+  gemm_record_ptr fetched = gemm_record_of_launch();       // the product whose operands are fetched
   // (the record of a group's launch says how many blocks' worth of tiles it has in all)
   const uint32_t all_tiles = GROUPED ? p_in.tiles_m : p_in.tiles_m * p_in.tiles_n;
   const uint32_t bo = blockIdx.z / p_in.batch_inner, bi = blockIdx.z % p_in.batch_inner;
@@ -678,9 +725,11 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(124))) void 
   };
   // sets up tile `id` and fetches what its first two memory phases read, and one part more
   auto open_tile = [&](uint32_t id) {
-    uint32_t local = id, tile_m, tile_n;
+    uint32_t local = id, tile_m, tile_n, tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));              // (what follows from it is worked out here, not kept in registers through the main loop)
+    if constexpr (GROUPED) fetched = gemm_record_of_block((gemm_record_ptr)p_in.group, p_in.group_n, id);
+    const GemmP p = gemm_read_record(fetched);
     if constexpr (GROUPED) {
-      gemm_load_record(p, p_in.group, p_in.group_n, id);
       local = id - p.tile_base;
       // (a group pads every product to a multiple of eight tiles: what is beyond has no K steps and stores nothing)
       if (local >= p.tiles_m * p.tiles_n) { nt = 0; return; }
@@ -691,9 +740,9 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(124))) void 
     uint32_t k_end = p.k;
     if (p.k_limit != 0) k_end = min(p.k, p.k_limit - bi * p.k);      // slices of one long K: the last may be shorter
     nt = k_end / BK;
-    ta0.init(p.lda, p.m - m0);
-    ta1.init(p.lda, p.m - m0);
-    tb.init(p.ldb, p.n - n0);
+    ta0.init(p.lda, p.m - m0, tid);
+    ta1.init(p.lda, p.m - m0, tid);
+    tb.init(p.ldb, p.n - n0, tid);
     const bf16_t* A = p.a + bo * p.a_so + bi * p.a_si;
     const bf16_t* B = p.b + bo * p.b_so + bi * p.b_si;
     base_a = (uint64_t)(ALAY == 0 ? A + (size_t)m0 * p.lda : A + m0);
@@ -707,7 +756,7 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(124))) void 
   if (pid < all_tiles) open_tile(pid);
   while (pid < all_tiles) {
     const uint32_t cm0 = m0, cn0 = n0, cnt = nt;
-    GemmP cp = p;                              // (of a group: the next tile may belong to another product)
+    const gemm_record_ptr current = fetched;   // (of a group: the next tile may belong to another product)
     floatx16 acc[TI][TJ];
 #pragma unroll
     for (int i = 0; i < TI; ++i)
@@ -715,7 +764,6 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(124))) void 
       for (int j = 0; j < TJ; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-    const size_t c_off = (size_t)(bo * p.c_so + bi * p.c_si);
     bf16x8 fa[4][HI], fb[4][TJ];
     auto read_a = [&](const bf16_t* half) {
 #pragma unroll
@@ -741,6 +789,7 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(124))) void 
     };
     if (nt > 1) wait_vm<F1 + F0>(); else wait_vm<F1>();      // B and the first halves of A of step 0
     barrier_only();
+    gemm_fetch_bias(gemm_read_record(current), cn0 + wn * 64, 64, lane, (uint32_t)(uintptr_t)(__attribute__((address_space(3))) bf16_t*)s_bias + wave * 1024);
     uint32_t own = 0;
     if (dynamic && threadIdx.x == 0) own = atomicAdd(&ctl.rec->tile_next[my_x * 32u], 1u);      // the block's next tile is asked for now
     if (second) barrier_only();
@@ -779,10 +828,10 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(124))) void 
     pid = s_next;
     if (pid < all_tiles) open_tile(pid);
     if (cnt != 0) {
-      uint4 bias_q = make_uint4(0, 0, 0, 0);
-      const uint32_t n = cn0 + wn * 64 + (lane & 7) * 8;
-      if ((cp.n & 7) == 0 && (c_off & 7) == 0 && cp.bias != nullptr && n < cp.n) bias_q = *reinterpret_cast<const uint4*>(cp.bias + n);
-      gemm_store_tile<TI, TJ, SR>(cp, acc, stage + wave * (SR * TJ * 32), cm0 + wm * (TI * 32), cn0 + wn * 64, c_off, bias_q);
+      const GemmP cp = gemm_read_record(current);
+      uint32_t l = lane;
+      asm volatile("" : "+v"(l));              // (as in open_tile)
+      gemm_store_tile<TI, TJ, SR>(cp, acc, stage + wave * (SR * TJ * 32), cm0 + wm * (TI * 32), cn0 + wn * 64, (size_t)(bo * cp.c_so + bi * cp.c_si), l, s_bias + wave * 512);
     }
   }
   kernel_end(ctl, true, threadIdx.x == 0);

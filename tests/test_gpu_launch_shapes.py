@@ -231,6 +231,36 @@ def test_gemm_bf16_staged_epilogues_on_256_tiles(m, n, k, epi):
     assert float((got[0][0].double() - ref).norm() / ref.norm()) <= 2.0 ** -8
 
 
+@pytest.mark.parametrize("m,n", [(1, 8), (33, 200), (129, 136), (257, 328)])
+@pytest.mark.parametrize("epi", ["plain", "gelu", "residual", "gelu_aux", "gelu_grad", "f32"])
+@pytest.mark.parametrize("tile", [0, 128, 256])
+def test_gemm_bf16_epilogues_write_their_rows_and_columns_only(m, n, epi, tile):
+    """Rows further apart than their columns, the last rows and columns of a tile missing: what lies between the rows and
+    behind the last one keeps its value, in the result and in the auxiliary tensor, and what lies there in the tensors that
+    are read (NaN) reaches no result.  Bound: one rounding to bf16 of the result, and of fp32 sums that GELU' or GELU scales."""
+    gen = torch.Generator(device=DEV).manual_seed(m + n)
+    k, ld = 64, n + 24
+    a, b, bias, z = _bf16(gen, m, k), _bf16(gen, n, k), _bf16(gen, n), _bf16(gen, m, n)
+    c = torch.full((m + 256, ld), 7.0, device=DEV, dtype=torch.float32 if epi == "f32" else torch.bfloat16)
+    other = torch.full((m + 256, ld), float("nan"), device=DEV, dtype=torch.bfloat16)
+    other[:m, :n] = z
+    kw = {"plain": dict(epilogue=S.SIF_EPI_BIAS, bias=bias), "gelu": dict(epilogue=S.SIF_EPI_GELU, bias=bias),
+          "residual": dict(epilogue=S.SIF_EPI_BIAS | S.SIF_EPI_RESIDUAL, bias=bias, res=other), "gelu_aux": dict(epilogue=S.SIF_EPI_GELU, bias=bias, aux=other),
+          "gelu_grad": dict(epilogue=S.SIF_EPI_GELU_GRAD, aux=other), "f32": dict(epilogue=S.SIF_EPI_OUT_F32)}[epi]
+    torch.cuda.synchronize()
+    S.sif_k_gemm_bf16(a, b, c, m, n, k, k, k, ld, tile=tile, **kw)
+    torch.cuda.synchronize()
+    assert bool((c[m:] == 7.0).all()) and bool((c[:, n:] == 7.0).all())
+    assert bool(other[m:].isnan().all()) and bool(other[:, n:].isnan().all())
+    acc, zd = a.double() @ b.double().t(), z.double()
+    ref = {"plain": acc + bias.double(), "gelu": torch.nn.functional.gelu(acc + bias.double()), "residual": acc + bias.double() + zd,
+           "gelu_aux": torch.nn.functional.gelu(acc + bias.double()), "f32": acc,
+           "gelu_grad": acc * (0.5 * (1 + torch.erf(zd / 2 ** 0.5)) + zd * torch.exp(-zd ** 2 / 2) / (2 * torch.pi) ** 0.5)}[epi]
+    assert float((c[:m, :n].double() - ref).norm() / ref.norm()) <= 2.0 ** -8
+    if epi == "gelu_aux":
+        assert float((other[:m, :n].double() - acc - bias.double()).norm() / acc.norm()) <= 2.0 ** -8
+
+
 @pytest.mark.parametrize("causal", [0, 1])
 @pytest.mark.parametrize("bsz,s,h", [(2, 2, 2), (1, 63, 1), (2, 65, 2), (1, 129, 3), (2, 192, 1), (1, 257, 2), (1, 449, 1)])
 def test_attention_with_heads_of_128_at_the_edges_of_its_tiles(bsz, s, h, causal):

@@ -12,7 +12,8 @@
 // operand as it lies in memory: rows of 64 k (128 bytes, XOR-swizzled in 16-byte chunks so that reads spread over the
 // banks) or, where the other dimension is contiguous, k-rows that the LDS read itself transposes (ds_read_b64_tr_b16).
 //
-// Two kernels, chosen by a model of their times (gemm_choose):
+// Three kernels, chosen by a model of their times (gemm_choose):
+//   gemm_fed_kernel    the smaller tiles where no CU gets more than one: wavefronts of their own for the fetches.
 //   gemm_ring_kernel   one tile per block, a ring of two to four K steps in LDS.  Tiles from 32x64 (a handful of rows)
 //                      over 64x64, 128x64 and 128x128 to 256x128, so that a product of any size finds one that
 //                      spreads it over the chip.
@@ -127,6 +128,7 @@ struct RingFrags {
     const short8_v v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     return __builtin_bit_cast(bf16x8, v);
   }
+  __device__ __forceinline__ bf16x8 read_tile(int slot, int i, int ks) const { return read(slot / PER, slot % PER * TILE, i, ks); }      // (slot a constant)
   template <int SLOT>
   __device__ __forceinline__ bf16x8 read_slot(int i, int ks) const { return read(SLOT / PER, SLOT % PER * TILE, i, ks); }
 };
@@ -183,8 +185,8 @@ struct TileFetch {
   __device__ __forceinline__ void issue(const i32x4& rsrc, uint32_t lds, uint32_t wave, int i) const {
     fetch16(rsrc, voff[i], lds + i * (THREADS * 16) + wave * 1024);
   }
-  __device__ __forceinline__ void issue_last(const i32x4& rsrc, uint32_t lds, uint32_t wave, int i, uint32_t k_left) const {
-    fetch16(rsrc, k_of(i, threadIdx.x) < k_left ? voff[i] : kOutside, lds + i * (THREADS * 16) + wave * 1024);
+  __device__ __forceinline__ void issue_last(const i32x4& rsrc, uint32_t lds, uint32_t wave, int i, uint32_t k_left, uint32_t tid) const {
+    fetch16(rsrc, k_of(i, tid) < k_left ? voff[i] : kOutside, lds + i * (THREADS * 16) + wave * 1024);
   }
 };
 // waits until at most N vector memory operations of this wavefront are outstanding (they complete in order)
@@ -608,7 +610,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_num_vgpr(1
     const i32x4 ra = operand_rsrc(base_a), rb = operand_rsrc(base_b);
     if (last) {
 #pragma unroll
-      for (int d = 0; d < F; ++d) { if (d < FA) ta.issue_last(ra, oa, wave, d, k_rest); else tb.issue_last(rb, ob, wave, d - FA, k_rest); }
+      for (int d = 0; d < F; ++d) { if (d < FA) ta.issue_last(ra, oa, wave, d, k_rest, threadIdx.x); else tb.issue_last(rb, ob, wave, d - FA, k_rest, threadIdx.x); }
     } else {
 #pragma unroll
       for (int d = 0; d < F; ++d) { if (d < FA) ta.issue(ra, oa, wave, d); else tb.issue(rb, ob, wave, d - FA); }
@@ -697,6 +699,144 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_num_vgpr(1
   }
   __syncthreads();                             // nobody reads the ring any more: it stages the results
   gemm_store_tile<TI, TJ, SR>(p, acc, reinterpret_cast<float*>(lds) + wave * (SR * TJ * 32), m0 + wm * (TI * 32), n0 + wn * (TJ * 32), c_off, lane, s_bias + wave * 512);
+  kernel_end(ctl, true);
+}
+
+// Tiles of a launch with at most one per CU, with wavefronts that only fetch.  A fetch of 1 KB holds its wavefront for some 70
+// cycles (a wavefront by itself takes in 33 bytes/ns, two 70, four 120 to 155), and in the ring above it stands in front of the
+// same wavefront's MFMAs: with 8 to 24 KB per 64 k and few MFMAs to them that was what a step waited for.  Here FW wavefronts
+// fetch and wait for what has landed, the other WM x WN read fragments and multiply; a barrier per step, of KB times 64 k,
+// keeps them together (with one per 64 k the smallest tiles spend more than half of a step in it).  Weights as they come from
+// twelve layers' 170 MB, launches back to back: 77 x 768 x 3072 13.0 -> 8.1 us, 77 x 768 x 768 5.8 -> 4.8, 512 x 768 x 3072
+// 13.3 -> 10.0, 1100 x 768 x 3072 15.2 -> 12.7, 2008 x 768 x 3072 22.1 -> 20.5.  With several tiles on a CU these hide each
+// other's fetches and the ring above is as fast.
+//   ST - 1 steps are in flight: the slot of the step before the current one is free for fetches when all wavefronts have
+// passed the barrier in front of the current one's products, which used that step's fragments before it.
+template <int I, int N, typename F>
+__device__ __forceinline__ void gemm_unrolled(F&& f) {
+  if constexpr (I < N) { f(Int<I>()); gemm_unrolled<I + 1, N>(f); }
+}
+// waits until at most `steps` steps of F fetches, of no more than MOST, are outstanding
+template <int F, int MOST>
+__device__ __forceinline__ void gemm_wait_steps(uint32_t steps) {
+  if constexpr (MOST == 0) { wait_vm<0>(); }
+  else { if (steps >= (uint32_t)MOST) wait_vm<F * MOST>(); else gemm_wait_steps<F, MOST - 1>(steps); }
+}
+template <int ALAY, int BLAY, int BM, int BN, int WM, int WN, int FW, int ST, int KB>
+__global__ __launch_bounds__(64 * (WM * WN + FW), 2) void gemm_fed_kernel(GemmP p, KCtl ctl) {
+  constexpr int MW = WM * WN, FT = 64 * FW, TI = BM / (WM * 32), TJ = BN / (WN * 32), AHEAD = ST - 1;
+  constexpr uint32_t SA = BM * BK, SB = BN * BK, STAGE = SA + SB;      // elements of 64 k
+  typedef TileFetch<ALAY, BM, FT, BM, BM, 0> FetchA;
+  typedef TileFetch<BLAY, BN, FT, BN, BN, 0> FetchB;
+  constexpr int FA = FetchA::NV, F1 = FA + FetchB::NV, F = F1 * KB;    // fetches per thread: of 64 k, of a step
+  constexpr int SR = 32;                                               // staging rows of the epilogue
+  static_assert(ST * KB * STAGE * 2 >= MW * TJ * 128 * SR, "the epilogue is staged in the ring");
+  static_assert(F * AHEAD < 64, "the waits count 63 operations");
+  static_assert(ST % 2 == 0, "the register sets alternate with the slots");
+  __shared__ __align__(1024) bf16_t lds[ST * KB * STAGE];
+  __shared__ __align__(1024) bf16_t s_bias[MW * 512];
+  if (!kernel_begin(ctl)) { kernel_end(ctl, false); return; }
+
+  const uint32_t bo = blockIdx.z / p.batch_inner, bi = blockIdx.z % p.batch_inner;
+  uint32_t tile_m, tile_n;
+  gemm_tile_of(p, p.tiles_m * p.tiles_n, blockIdx.x, tile_m, tile_n);
+  const uint32_t m0 = tile_m * BM, n0 = tile_n * BN;
+  if ((p.epi & SIF_EPI_CAUSAL_SKIP) && n0 / 128 > (m0 + BM - 1) / 128) { kernel_end(ctl, true); return; }      // (as in the ring)
+  uint32_t k_begin = 0, k_end = p.k;
+  if (p.k_limit != 0) k_end = min(p.k, p.k_limit - bi * p.k);
+  if (p.k_causal == 1) k_end = min(p.k, m0 + BM);
+  if (p.k_causal == 2) k_begin = (m0 / BK) * BK;
+  const uint32_t nt = (k_end - k_begin + BK * KB - 1) / (BK * KB), full = (k_end - k_begin) / BK, k_rest = (k_end - k_begin) % BK;
+  const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) bf16_t*)lds;
+
+  if (wave >= MW) {
+    const uint32_t tid = threadIdx.x - MW * 64, fw = wave - MW;
+    FetchA ta;
+    FetchB tb;
+    ta.init(p.lda, p.m - m0, tid);
+    tb.init(p.ldb, p.n - n0, tid);
+    const bf16_t* A = p.a + bo * p.a_so + bi * p.a_si;
+    const bf16_t* B = p.b + bo * p.b_so + bi * p.b_si;
+    uint64_t base_a = (uint64_t)(ALAY == 0 ? A + (size_t)m0 * p.lda + k_begin : A + (size_t)k_begin * p.lda + m0);
+    uint64_t base_b = (uint64_t)(BLAY == 0 ? B + (size_t)n0 * p.ldb + k_begin : B + (size_t)k_begin * p.ldb + n0);
+    const uint64_t step_a = ALAY == 0 ? BK * 2 : (uint64_t)BK * p.lda * 2, step_b = BLAY == 0 ? BK * 2 : (uint64_t)BK * p.ldb * 2;
+    uint32_t slot = 0;                         // of the next step to be fetched
+    auto fetch_step = [&](uint32_t step) {
+#pragma unroll
+      for (int u = 0; u < KB; ++u) {
+        const uint32_t oa = lds0 + (slot * KB + u) * (SA * 2), ob = lds0 + ST * KB * (SA * 2) + (slot * KB + u) * (SB * 2), at = step * KB + u;
+        const i32x4 ra = operand_rsrc(base_a), rb = operand_rsrc(base_b);
+        if (at >= full) {                      // the ragged end of K, and zeros for what a step has beyond it
+          const uint32_t left = at == full ? k_rest : 0;
+#pragma unroll
+          for (int d = 0; d < F1; ++d) { if (d < FA) ta.issue_last(ra, oa, fw, d, left, tid); else tb.issue_last(rb, ob, fw, d - FA, left, tid); }
+        } else {
+#pragma unroll
+          for (int d = 0; d < F1; ++d) { if (d < FA) ta.issue(ra, oa, fw, d); else tb.issue(rb, ob, fw, d - FA); }
+        }
+        base_a += step_a; base_b += step_b;
+      }
+      slot = slot + 1 == ST ? 0 : slot + 1;
+    };
+    uint32_t s = 0;                            // steps asked for
+    for (; s < (uint32_t)AHEAD && s < nt; ++s) fetch_step(s);
+    gemm_wait_steps<F, AHEAD - 1>(s - 1);
+    barrier_only();
+    for (uint32_t t = 1; t < nt; ++t) {        // step t has landed: it is read behind the barrier
+      gemm_wait_steps<F, AHEAD - 2>(s - t - 1);
+      barrier_only();
+      if (s < nt) { fetch_step(s); ++s; }
+    }
+    __syncthreads();
+  } else {
+    const uint32_t wm = wave / WN, wn = wave % WN;
+    floatx16 acc[TI][TJ];
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+      for (int j = 0; j < TJ; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    bf16x8 fa[2][4 * KB][TI], fb[2][4 * KB][TJ];
+    RingFrags<ALAY, BM, TI, ST * KB> ra_frags;
+    RingFrags<BLAY, BN, TJ, ST * KB> rb_frags;
+    ra_frags.init(lds0, wm * (TI * 32));
+    rb_frags.init(lds0 + ST * KB * SA * 2, wn * (TJ * 32));
+    auto read_slice = [&](int slot, int ks, bf16x8 (&a)[TI], bf16x8 (&b)[TJ]) {
+#pragma unroll
+      for (int i = 0; i < TI; ++i) a[i] = ra_frags.read_tile(slot * KB + ks / 4, i, ks % 4);
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) b[j] = rb_frags.read_tile(slot * KB + ks / 4, j, ks % 4);
+    };
+    gemm_fetch_bias(p, n0 + wn * (TJ * 32), TJ * 32, lane, (uint32_t)(uintptr_t)(__attribute__((address_space(3))) bf16_t*)s_bias + wave * 1024);
+    barrier_only();
+#pragma unroll
+    for (int ks = 0; ks < 4 * KB; ++ks) read_slice(0, ks, fa[0][ks], fb[0][ks]);
+    // the step in slot S, its fragments in register set S % 2; more: another one follows
+    auto step = [&](auto S, bool more) {
+      constexpr int s = decltype(S)::value, cur = s & 1, nx = (s + 1) % ST;
+      if (more) barrier_only();
+#pragma unroll
+      for (int ks = 0; ks < 4 * KB; ++ks) {
+        if (more) read_slice(nx, ks, fa[cur ^ 1][ks], fb[cur ^ 1][ks]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+          for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][ks][i], fb[cur][ks][j], acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    uint32_t t = 0;
+#pragma clang loop unroll(disable)
+    for (; t + ST < nt; t += ST) gemm_unrolled<0, ST>([&](auto S) { step(S, true); });
+    gemm_unrolled<0, ST>([&](auto S) { if (t + decltype(S)::value < nt) step(S, t + decltype(S)::value + 1 < nt); });
+    wait_vm<0>();                              // the bias
+    __syncthreads();                           // nobody reads the ring any more: it stages the results
+    gemm_store_tile<TI, TJ, SR>(p, acc, reinterpret_cast<float*>(lds) + wave * (SR * TJ * 32), m0 + wm * (TI * 32), n0 + wn * (TJ * 32),
+                                (size_t)(bo * p.c_so + bi * p.c_si), lane, s_bias + wave * 512);
+  }
   kernel_end(ctl, true);
 }
 
@@ -1024,11 +1164,20 @@ typedef void (*gemm_kern_fn)(GemmP, KCtl);
 #define RING(BM, BN, WM, WN, ST, LAG, OCC)                                                                                        \
   {{gemm_ring_kernel<0, 0, BM, BN, WM, WN, ST, LAG, OCC>, gemm_ring_kernel<0, 1, BM, BN, WM, WN, ST, LAG, OCC>},                  \
    {gemm_ring_kernel<1, 0, BM, BN, WM, WN, ST, LAG, OCC>, gemm_ring_kernel<1, 1, BM, BN, WM, WN, ST, LAG, OCC>}}
+#define FED(BM, BN, WM, WN, FW, ST, KB)                                                                                           \
+  {{gemm_fed_kernel<0, 0, BM, BN, WM, WN, FW, ST, KB>, gemm_fed_kernel<0, 1, BM, BN, WM, WN, FW, ST, KB>},                        \
+   {gemm_fed_kernel<1, 0, BM, BN, WM, WN, FW, ST, KB>, gemm_fed_kernel<1, 1, BM, BN, WM, WN, FW, ST, KB>}}
 static const gemm_kern_fn kGemmKernels[kNTiles][2][2] = {
     RING(32, 64, 1, 2, 4, 1, 2),   RING(64, 64, 2, 2, 4, 1, 2),   RING(128, 64, 2, 2, 3, 0, 2), RING(128, 128, 4, 2, 4, 1, 1),
     RING(128, 128, 2, 2, 2, 0, 2), RING(256, 128, 4, 2, 3, 0, 1), {{gemm_pp_kernel<0, 0>, gemm_pp_kernel<0, 1>}, {gemm_pp_kernel<1, 0>, gemm_pp_kernel<1, 1>}}};
+// launches of at most one tile per CU, by their tiles: 32x64, 64x64, 128x64, and 32x32 instead of 32x64 where that is still one
+// tile per CU (a third less to fetch for each; 77 x 768 x 3072: 8.1 us, on 32x64 9.5)
+static const struct { gemm_kern_fn kern[2][2]; uint32_t threads; } kGemmFed[] = {
+    {FED(32, 64, 1, 2, 4, 6, 2), 384}, {FED(64, 64, 2, 2, 4, 8, 1), 512}, {FED(128, 64, 2, 2, 4, 6, 1), 512}, {FED(32, 32, 1, 1, 4, 6, 2), 320}};
+constexpr uint32_t kFed32x32 = 3;
 static const uint32_t kGemmThreads[kNTiles] = {128, 256, 256, 512, 256, 512, 512};
 #undef RING
+#undef FED
 
 static uint32_t gemm_cus() {
   static const uint32_t cus = [] {
@@ -1048,7 +1197,20 @@ static sif_status launch_gemm_cfg(const sif_gemm_args* a, int want, hipStream_t 
   // 8 keeps a block on the tiles of its own XCD
   uint32_t grid_x = p.tiles_m * p.tiles_n;
   if (cfg == kT256x256 && batches == 1) grid_x = std::min(grid_x, gemm_cus());
-  hipLaunchKernelGGL(kGemmKernels[cfg][a->a_layout][a->b_layout], dim3(grid_x, 1, (uint32_t)batches), dim3(kGemmThreads[cfg]), 0, stream, p, ctl);
+  gemm_kern_fn kern = kGemmKernels[cfg][a->a_layout][a->b_layout];
+  uint32_t threads = kGemmThreads[cfg];
+  if (cfg <= kT128x64 && grid_x * batches <= gemm_cus()) {
+    uint32_t fed = (uint32_t)cfg;
+    const uint32_t narrow = (a->n + 31) / 32;
+    if (cfg == kT32x64 && (uint64_t)p.tiles_m * narrow * batches <= gemm_cus()) {
+      fed = kFed32x32;
+      p.tiles_n = narrow;
+      grid_x = p.tiles_m * narrow;
+    }
+    kern = kGemmFed[fed].kern[a->a_layout][a->b_layout];
+    threads = kGemmFed[fed].threads;
+  }
+  hipLaunchKernelGGL(kern, dim3(grid_x, 1, (uint32_t)batches), dim3(threads), 0, stream, p, ctl);
   return check_launch("gemm_bf16");
 }
 sif_status launch_gemm_bf16(const sif_gemm_args* a, hipStream_t stream, const KCtl& ctl) { return launch_gemm_cfg(a, kAuto, stream, ctl); }

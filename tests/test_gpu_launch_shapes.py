@@ -128,6 +128,29 @@ def test_gemm_bf16_picks_tiles_that_give_the_bits_of_the_128_ones(m, n, k, al, b
 
 @pytest.mark.parametrize("al", [0, 1])
 @pytest.mark.parametrize("bl", [0, 1])
+@pytest.mark.parametrize("m,n", [(33, 72), (72, 2312), (280, 1992), (580, 2440), (1100, 3080)])
+@pytest.mark.parametrize("k", [8, 64, 72, 128, 640, 648, 704, 1480])
+def test_gemm_bf16_fed_tiles_give_the_bits_of_the_128_ones(m, n, k, al, bl):
+    """Tiles with wavefronts that only fetch (32x32, 32x64, 64x64, 128x64, as the launcher takes them, one per CU) and small
+    ones of which CUs get several: K shorter than the ring, as long as it, whole turns of it and some steps more, ragged at the
+    end of either half of a step."""
+    gen = torch.Generator(device=DEV).manual_seed(m + 3 * n + 5 * k + al + 2 * bl)
+    a, b, bias = torch.zeros(((m + 7) // 8 * 8, k), device=DEV, dtype=torch.bfloat16), _bf16(gen, n, k), _bf16(gen, n)
+    a[:m] = _bf16(gen, m, k)
+    A, Bt = (a if al == 0 else a.t().contiguous()), (b if bl == 0 else b.t().contiguous())
+    out = [torch.full((m, n), float("nan"), device=DEV, dtype=torch.bfloat16) for _ in range(2)]
+    torch.cuda.synchronize()
+    for c, tile in zip(out, (0, 128)):
+        S.sif_k_gemm_bf16(A, Bt, c, m, n, k, A.shape[1], Bt.shape[1], n, a_layout=al, b_layout=bl, epilogue=S.SIF_EPI_BIAS, bias=bias, tile=tile)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], out[1])
+    ref = a[:m].double() @ b.double().t() + bias.double()
+    bound = 2.0 ** -8 * ref.abs() + (k + 5) * 2.0 ** -24 * (a[:m].double().abs() @ b.double().abs().t() + bias.double().abs())
+    assert bool(((out[0].double() - ref).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("al", [0, 1])
+@pytest.mark.parametrize("bl", [0, 1])
 @pytest.mark.parametrize("m,n,k,tiles", [(72, 200, 1160, "32x64"), (600, 1544, 776, "64x64"), (600, 2440, 1160, "128x64"), (1032, 2440, 776, "128x128 one"),
                                          (4104, 2440, 776, "128x128 two"), (2008, 2440, 1160, "256x128"), (4360, 4104, 64, None), (4360, 4104, 192, None)])
 def test_gemm_bf16_long_rings_and_more_tiles_than_blocks_give_the_bits_of_the_128_ones(m, n, k, tiles, al, bl):

@@ -56,7 +56,6 @@ struct GemmP {
   // number of the launch's first block that works on it (a multiple of 8)
   const GemmP* group;
   uint32_t group_n, tile_base;
-  bf16_t* sums;      // of a group's product, optional: [m], the sums of A over k (the bias gradient that belongs to a weight gradient)
 };
 
 // ---------------------------------------------------------------------------------------------- operands in LDS
@@ -496,28 +495,6 @@ __device__ __forceinline__ GemmP gemm_read_record(gemm_record_ptr p) {
   return q;
 }
 
-// The sums of a weight gradient's left operand over k - the bias gradient that belongs to it - ride in the blocks of the
-// first tile column: the first of the wavefronts that hold the same rows adds up its fragments, four v_dot2 with ones per
-// fragment between the MFMAs that use it.  A lane adds its row's eight k of a 16-wide slice, 16 by 16; the two halves of a
-// wavefront are joined at the end, and the tile does not matter for the order.  (As products of their own, one row by a
-// column of ones, they took tiles over the whole K: 824 tiles of 256x256 instead of 768 at d 2048 and 474 of 128x128 instead
-// of 432 at d 768, where 216 of 256x128 fill the chip once.)
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void gemm_add_sums(float& sum, const bf16x8& f) {
-  const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-  const bf16x2 a = {f[0], f[1]}, b = {f[2], f[3]}, c = {f[4], f[5]}, d = {f[6], f[7]};
-  sum = __builtin_amdgcn_fdot2_f32_bf16(a, ones, sum, false);
-  sum = __builtin_amdgcn_fdot2_f32_bf16(b, ones, sum, false);
-  sum = __builtin_amdgcn_fdot2_f32_bf16(c, ones, sum, false);
-  sum = __builtin_amdgcn_fdot2_f32_bf16(d, ones, sum, false);
-}
-// rows m.. (32 of them), from the lane's part of the sum
-__device__ __forceinline__ void gemm_store_sums(const GemmP& p, float sum, uint32_t m, uint32_t lane) {
-  sum += __shfl_xor(sum, 32, 64);
-  m += lane;
-  if (lane < 32 && m < p.m) p.sums[m] = f2bf((p.epi & SIF_EPI_RESIDUAL) ? sum + bf2f(p.sums[m]) : sum);      // (accumulated as the products are)
-}
-
 // One tile per block.  A ring of ST K steps in LDS; a wavefront keeps the fragments of two steps in registers, so that
 // those of step t+1 are read, slice by slice, between the MFMAs of step t.  The steady part is a body of whole turns of
 // the ring (every LDS address a constant); what is left - the last ST and a few steps, a ragged last step among them -
@@ -592,17 +569,11 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_num_vgpr(1
 #pragma unroll
     for (int j = 0; j < TJ; ++j) b[j] = rb_frags.template read_slot<decltype(SLOT)::value>(j, ks);
   };
-  float sums[TI];
+  auto mfma_slice = [&](bf16x8 (&a)[TI], bf16x8 (&b)[TJ]) {
 #pragma unroll
-  for (int i = 0; i < TI; ++i) sums[i] = 0.f;
-  const bool summing = GROUPED && p.sums != nullptr && tile_n == 0 && wn == 0;
-  auto mfma_slice = [&](bf16x8 (&a)[TI], bf16x8 (&b)[TJ], auto SUM) {
-#pragma unroll
-    for (int i = 0; i < TI; ++i) {
+    for (int i = 0; i < TI; ++i)
 #pragma unroll
       for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-      if constexpr (decltype(SUM)::value != 0) gemm_add_sums(sums[i], a[i]);
-    }
   };
   // the next K step into a slot; `last`: the ragged one
   auto fetch_step = [&](uint32_t slot, bool last) {
@@ -624,7 +595,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_num_vgpr(1
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) read_slice(Int<0>(), ks, fa[0][ks], fb[0][ks]);
 
-  auto steady = [&](auto S, auto P, auto SUM) {      // step in slot S with its fragments in register set P
+  auto steady = [&](auto S, auto P) {          // step in slot S with its fragments in register set P
     constexpr int s = decltype(S)::value, cur = decltype(P)::value, nx = (s + 1) % ST, fs = (s + AHEAD) % ST;
     wait_vm<F * (AHEAD - 2)>();                 // the next step has landed
     if (!LAG) wait_lds();
@@ -638,28 +609,22 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_num_vgpr(1
 #pragma unroll
       for (int d = ks * F / 4; d < (ks + 1) * F / 4; ++d) { if (d < FA) ta.issue(ra, oa, wave, d); else tb.issue(rb, ob, wave, d - FA); }
       __builtin_amdgcn_sched_barrier(0);
-      mfma_slice(fa[cur][ks], fb[cur][ks], SUM);
+      mfma_slice(fa[cur][ks], fb[cur][ks]);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
   uint32_t t = 0;
   constexpr uint32_t TURN = ST == 3 ? 6 : ST;      // an even number of steps: the register sets alternate too
   static_assert(ST >= 2 && ST <= 4, "the turns written out below");
-  auto turns = [&](auto SUM) {
-    while (t + AHEAD + TURN - 1 < full) {
-      if constexpr (ST == 2) { steady(Int<0>(), Int<0>(), SUM); steady(Int<1>(), Int<1>(), SUM); }
-      if constexpr (ST == 3) {
-        steady(Int<0>(), Int<0>(), SUM); steady(Int<1>(), Int<1>(), SUM); steady(Int<2>(), Int<0>(), SUM);
-        steady(Int<0>(), Int<1>(), SUM); steady(Int<1>(), Int<0>(), SUM); steady(Int<2>(), Int<1>(), SUM);
-      }
-      if constexpr (ST == 4) {
-        steady(Int<0>(), Int<0>(), SUM); steady(Int<1>(), Int<1>(), SUM); steady(Int<2>(), Int<0>(), SUM); steady(Int<3>(), Int<1>(), SUM);
-      }
-      t += TURN;
+  while (t + AHEAD + TURN - 1 < full) {
+    if constexpr (ST == 2) { steady(Int<0>(), Int<0>()); steady(Int<1>(), Int<1>()); }
+    if constexpr (ST == 3) {
+      steady(Int<0>(), Int<0>()); steady(Int<1>(), Int<1>()); steady(Int<2>(), Int<0>());
+      steady(Int<0>(), Int<1>()); steady(Int<1>(), Int<0>()); steady(Int<2>(), Int<1>());
     }
-  };
-  if constexpr (GROUPED) { if (summing) turns(Int<1>()); }
-  turns(Int<0>());
+    if constexpr (ST == 4) { steady(Int<0>(), Int<0>()); steady(Int<1>(), Int<1>()); steady(Int<2>(), Int<0>()); steady(Int<3>(), Int<1>()); }
+    t += TURN;
+  }
   uint32_t slot = 0;
   auto step = [&](auto P) {
     constexpr int cur = decltype(P)::value;
@@ -679,13 +644,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_num_vgpr(1
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) mfma_slice(fa[cur][ks], fb[cur][ks], Int<0>());
-    if (GROUPED && summing) {
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-        for (int i = 0; i < TI; ++i) gemm_add_sums(sums[i], fa[cur][ks][i]);
-    }
+    for (int ks = 0; ks < 4; ++ks) mfma_slice(fa[cur][ks], fb[cur][ks]);
     __builtin_amdgcn_sched_barrier(0);
     slot = nx;
     ++t;
@@ -693,10 +652,6 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_num_vgpr(1
   while (t + 1 < nt) { step(Int<0>()); step(Int<1>()); }
   if (t < nt) step(Int<0>());
 
-  if (GROUPED && summing) {
-#pragma unroll
-    for (int i = 0; i < TI; ++i) gemm_store_sums(p, sums[i], m0 + wm * (TI * 32) + i * 32, lane);
-  }
   __syncthreads();                             // nobody reads the ring any more: it stages the results
   gemm_store_tile<TI, TJ, SR>(p, acc, reinterpret_cast<float*>(lds) + wave * (SR * TJ * 32), m0 + wm * (TI * 32), n0 + wn * (TJ * 32), c_off, lane, s_bias + wave * 512);
   kernel_end(ctl, true);
@@ -894,7 +849,6 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(124))) void 
   FetchB tb;
   uint64_t base_a = 0, base_b = 0, step_a = 0, step_b = 0;
   uint32_t m0 = 0, n0 = 0, nt = 0;
-  bool sum_tile = false;                       // of a group: the sums of A over k belong to this tile
   auto fetch_a0b = [&](uint32_t t) {
     const uint32_t o = lds0 + (t & 1u) * (STAGE * 2);
     const i32x4 ra = operand_rsrc(base_a + t * step_a), rb = operand_rsrc(base_b + t * step_b);
@@ -923,7 +877,6 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(124))) void 
     gemm_tile_of(p, p.tiles_m * p.tiles_n, local, tile_m, tile_n);
     m0 = tile_m * BM;
     n0 = tile_n * BN;
-    if constexpr (GROUPED) sum_tile = p.sums != nullptr && tile_n == 0;
     uint32_t k_end = p.k;
     if (p.k_limit != 0) k_end = min(p.k, p.k_limit - bi * p.k);      // slices of one long K: the last may be shorter
     nt = k_end / BK;
@@ -964,17 +917,6 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(124))) void 
 #pragma unroll
         for (int j = 0; j < TJ; ++j) fb[ks][j] = operand_frag<BLAY, BN>(tile, (wn * TJ + j) * 32, ks);
     };
-    float sums[TI];
-#pragma unroll
-    for (int i = 0; i < TI; ++i) sums[i] = 0.f;
-    const bool summing = GROUPED && sum_tile && wn == 0;
-    // (of both halves in the second memory phase, which has half the reads of the first)
-    auto add_half = [&](auto H) {
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-        for (int i = 0; i < HI; ++i) gemm_add_sums(sums[decltype(H)::value * HI + i], fa[ks][i]);
-    };
     auto multiply = [&](auto H) {
       constexpr int h = decltype(H)::value;
 #pragma unroll
@@ -1005,11 +947,9 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(124))) void 
       multiply(Int<0>());
       if (!second) { if (more) wait_vm<F0 + F1>(); else wait_vm<0>(); }
       barrier_only();
-      if (GROUPED && summing) add_half(Int<0>());
       read_a(cur + HA);
       if (more2) fetch_a0b(t + 2);
       wait_lds();
-      if (GROUPED && summing) add_half(Int<1>());
       if (second && more) { if (more2) wait_vm<F0 + F1>(); else wait_vm<F1>(); }      // B and first halves of A, step t + 1
       barrier_only();
       multiply(Int<1>());
@@ -1017,13 +957,6 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(124))) void 
       barrier_only();
     }
     if (!second) barrier_only();
-    if constexpr (GROUPED) {
-      if (summing) {
-        const GemmP cp = gemm_read_record(current);
-#pragma unroll
-        for (int i = 0; i < TI; ++i) gemm_store_sums(cp, sums[i], cm0 + wm * (TI * 32) + i * 32, lane);
-      }
-    }
 
     if (threadIdx.x == 0) {
       uint32_t np = kNone;
@@ -1154,7 +1087,7 @@ static sif_status gemm_fill(const sif_gemm_args* a, GemmP& p, int cfg, int* cfg_
   p.a_so = a->a_stride_outer; p.a_si = a->a_stride_inner; p.b_so = a->b_stride_outer; p.b_si = a->b_stride_inner;
   p.c_so = a->c_stride_outer; p.c_si = a->c_stride_inner; p.alpha = a->alpha;
   p.tiles_n = (a->n + bn - 1) / bn; p.tiles_m = (a->m + bm - 1) / bm;
-  p.group = nullptr; p.group_n = 0; p.tile_base = 0; p.sums = nullptr;
+  p.group = nullptr; p.group_n = 0; p.tile_base = 0;
   if (batches > 65535) return fail(SIF_E_INVAL, "gemm: grid too large");
   *cfg_out = cfg;
   return SIF_OK;
@@ -1221,8 +1154,7 @@ sif_status launch_gemm_bf16(const sif_gemm_args* a, hipStream_t stream, const KC
 // copied to `gemm_group_bytes(n)` bytes of device memory once; launch_gemm_bf16_group then takes that copy.
 uint64_t gemm_group_bytes(uint32_t n) { return (uint64_t)n * sizeof(GemmP); }
 
-// sums[i] (optional): where the sums of product i's left operand over k go, bf16 [m]
-sif_status gemm_group_fill_sums(const sif_gemm_args* list, uint32_t n, void* const* sums, void* host_records, GemmGroup* out) {
+sif_status gemm_group_fill(const sif_gemm_args* list, uint32_t n, void* host_records, GemmGroup* out) {
   if (list == nullptr || n == 0 || n > 16 || host_records == nullptr || out == nullptr) return fail(SIF_E_INVAL, "gemm group: bad arguments");
   // Which tiles: the model's time for all products' tiles together, the longest K deciding.  A small layer's gradients (21
   // tiles of 128x128 at 128 x 512) are a chain of K steps on few CUs: 128x128 with four steps in the ring of a CU's only
@@ -1253,15 +1185,12 @@ sif_status gemm_group_fill_sums(const sif_gemm_args* list, uint32_t n, void* con
     int got = 0;
     if (sif_status st = gemm_fill(&a, rec[i], cfg, &got)) return st;
     rec[i].tile_base = base;
-    if (sums != nullptr) rec[i].sums = static_cast<bf16_t*>(sums[i]);
     base += (rec[i].tiles_m * rec[i].tiles_n + 7u) & ~7u;       // a multiple of 8 keeps the tile order's idea of the XCDs
   }
   out->tiles = base;
   out->cfg = cfg;
   return SIF_OK;
 }
-
-sif_status gemm_group_fill(const sif_gemm_args* list, uint32_t n, void* host_records, GemmGroup* out) { return gemm_group_fill_sums(list, n, nullptr, host_records, out); }
 
 sif_status launch_gemm_bf16_group(const void* dev_records, uint32_t n, const GemmGroup& g, uint32_t a_layout, uint32_t b_layout, hipStream_t stream, const KCtl& ctl) {
   if (dev_records == nullptr || n == 0 || g.tiles == 0 || a_layout > 1 || b_layout > 1) return fail(SIF_E_INVAL, "gemm group: bad arguments");

@@ -202,48 +202,6 @@ def test_groups_give_the_bits_of_the_128_tiles_on_every_tile(shapes, k, tiles):
         assert float((c[0].double() - ref).norm() / ref.norm()) <= 2.0 ** -8
 
 
-@pytest.mark.parametrize("shapes,k,tiles", [([(512, 128), (130, 512)], 1032, "128x128 one"), ([(2056, 1288), (1290, 2056)], 264, "128x128 two"),
-                                            ([(1030, 776), (776, 3080), (258, 776)], 1160, "256x128"), ([(4102, 4616), (2056, 2568)], 512, "256x256")])
-@pytest.mark.parametrize("accumulate", [False, True])
-def test_sums_of_the_left_operands_ride_in_a_group(shapes, k, tiles, accumulate):
-    """What a layer's bias gradients are: the sums over k of each product's left operand, from the blocks of its first tile
-    column, on every tile that a group takes; ragged rows and K, added to what is there or not, nothing behind the last row.
-    Bound: one rounding to bf16 (2^-9 of the value) and the fp32 sum ((k + 4) 2^-24 of the magnitudes).  The products keep
-    their bits."""
-    import ctypes as C
-    from tile_choice import group
-    gen = torch.Generator(device=DEV).manual_seed(k)
-    lay = dict(a_layout=S.SIF_A_ROW_M, b_layout=S.SIF_B_ROW_N)
-    prods, data = [], []
-    for m, n in shapes:
-        a, b = torch.zeros((k, (m + 7) // 8 * 8), device=DEV, dtype=torch.bfloat16), _bf16(gen, k, n)
-        a[:, :m] = _bf16(gen, k, m)
-        c, sums = _bf16(gen, m, n), _bf16(gen, m + 64)
-        kw = dict(epilogue=S.SIF_EPI_RESIDUAL, res=c) if accumulate else {}
-        prods.append(S.gemm_args(a, b, c, m, n, k, a.shape[1], n, n, **lay, **kw))
-        data.append((a, b, c, c.clone(), sums, sums.clone()))
-    assert group(prods)[1] == tiles
-    fill, launch = (getattr(S.lib, name) for name in ("_ZN3sif20gemm_group_fill_sumsEPK13sif_gemm_argsjPKPvS3_PNS_9GemmGroupE",
-                                                      "_ZN3sif22launch_gemm_bf16_groupEPKvjRKNS_9GemmGroupEjjP12ihipStream_tRKNS_4KCtlE"))
-    size = S.sif_k_gemm_bf16_group_bytes(len(prods))
-    host, how, ctl = (C.c_char * size)(), (C.c_uint32 * 2)(), (C.c_char * 256)()      # (a control block of zeros: no monitor)
-    where = (C.c_void_p * len(prods))(*(d[4].data_ptr() for d in data))
-    fill.argtypes, launch.argtypes = [C.c_void_p, C.c_uint32, C.c_void_p, C.c_void_p, C.c_void_p], [C.c_void_p, C.c_uint32, C.c_void_p, C.c_uint32, C.c_uint32, C.c_void_p, C.c_void_p]
-    assert fill((S.sif_gemm_args * len(prods))(*prods), len(prods), where, host, how) == 0
-    records = torch.frombuffer(host, dtype=torch.uint8).to(DEV)
-    torch.cuda.synchronize()
-    assert launch(records.data_ptr(), len(prods), how, S.SIF_A_ROW_M, S.SIF_B_ROW_N, torch.cuda.current_stream().cuda_stream, ctl) == 0
-    torch.cuda.synchronize()
-    for (m, n), (a, b, c, before, sums, sums_before) in zip(shapes, data):
-        alone = before.clone()
-        S.sif_k_gemm_bf16(a, b, alone, m, n, k, a.shape[1], n, n, tile=128, **lay, **(dict(epilogue=S.SIF_EPI_RESIDUAL, res=alone) if accumulate else {}))
-        torch.cuda.synchronize()
-        assert torch.equal(c, alone)
-        want = a[:, :m].double().sum(0) + (sums_before[:m].double() if accumulate else 0.0)
-        bound = 2.0 ** -8 * want.abs() + (k + 4) * 2.0 ** -24 * a[:, :m].double().abs().sum(0)
-        assert bool(((sums[:m].double() - want).abs() <= bound).all()) and torch.equal(sums[m:], sums_before[m:])
-
-
 @pytest.mark.parametrize("m,n,k", [(77, 200, 136), (1000, 768, 256), (1032, 2304, 192)])
 @pytest.mark.parametrize("epi", ["bias_residual", "gelu_aux", "gelu_grad", "f32"])
 def test_gemm_bf16_epilogues_on_every_tile_width(m, n, k, epi):

@@ -664,7 +664,8 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_num_vgpr(1
 // keeps them together (with one per 64 k the smallest tiles spend more than half of a step in it).  Weights as they come from
 // twelve layers' 170 MB, launches back to back: 77 x 768 x 3072 13.0 -> 8.1 us, 77 x 768 x 768 5.8 -> 4.8, 512 x 768 x 3072
 // 13.3 -> 10.0, 1100 x 768 x 3072 15.2 -> 12.7, 2008 x 768 x 3072 22.1 -> 20.5.  With several tiles on a CU these hide each
-// other's fetches and the ring above is as fast.
+// other's fetches and the ring above is as fast.  (So it is with 128x128 tiles, one per
+// CU or fewer: eight wavefronts' MFMAs cover the fetches, and with four more that fetch it took 0.96 to 1.04 of the time.)
 //   ST - 1 steps are in flight: the slot of the step before the current one is free for fetches when all wavefronts have
 // passed the barrier in front of the current one's products, which used that step's fragments before it.
 template <int I, int N, typename F>
@@ -986,7 +987,9 @@ static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 // to back: the modelled times are 0.7 to 1.5 of the measured ones, the choice is on average 1.0 % slower than the best
 // configuration and at worst 21 % (at 6 us; 18 % at 8192 x 3072 x 768, 51 us on 256x128, 43 on 128x128).  A fit to those
 // would not be better: inside the training step, with its epilogues and with operands that come from memory, that product
-// takes 67.6 us on 256x128 and 71.2 on 128x128.
+// takes 67.6 us on 256x128 and 71.2 on 128x128.  Tiles with wavefronts that only fetch are faster than the constants say, where
+// the small tiles were the choice already: over 477 products of 32 to 4096 rows with weights from memory the choice is on
+// average 0.4 % above the best, as it is with constants fitted to those.
 struct GemmTiles { uint32_t bm, bn, slots; double fixed, step, step1; };
 enum { kT32x64, kT64x64, kT128x64, kT128x128x1, kT128x128, kT256x128, kT256x256, kNTiles };
 static const GemmTiles kGemmTiles[kNTiles] = {

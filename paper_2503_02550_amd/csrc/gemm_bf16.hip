@@ -1157,12 +1157,11 @@ sif_status launch_gemm_bf16(const sif_gemm_args* a, hipStream_t stream, const KC
 // copied to `gemm_group_bytes(n)` bytes of device memory once; launch_gemm_bf16_group then takes that copy.
 uint64_t gemm_group_bytes(uint32_t n) { return (uint64_t)n * sizeof(GemmP); }
 
-sif_status gemm_group_fill(const sif_gemm_args* list, uint32_t n, void* host_records, GemmGroup* out) {
-  if (list == nullptr || n == 0 || n > 16 || host_records == nullptr || out == nullptr) return fail(SIF_E_INVAL, "gemm group: bad arguments");
-  // Which tiles: the model's time for all products' tiles together, the longest K deciding.  A small layer's gradients (21
-  // tiles of 128x128 at 128 x 512) are a chain of K steps on few CUs: 128x128 with four steps in the ring of a CU's only
-  // block, as long as that is one round (2048 tokens of 128 x 512: 16 us, with two steps in the ring 20, on 256x128 27;
-  // two rounds, 8192 tokens of 768 x 3072: 131 us, where two blocks of a CU hide each other's ends 125).
+// Which tiles: the model's time for all products' tiles together, the longest K deciding.  A small layer's gradients (21
+// tiles of 128x128 at 128 x 512) are a chain of K steps on few CUs: 128x128 with four steps in the ring of a CU's only
+// block, as long as that is one round (2048 tokens of 128 x 512: 16 us, with two steps in the ring 20, on 256x128 27;
+// two rounds, 8192 tokens of 768 x 3072: 131 us, where two blocks of a CU hide each other's ends 125).
+static int gemm_group_choose(const sif_gemm_args* list, uint32_t n, double* us_out) {
   int cfg = -1;
   double best = 0.0;
   for (int c : {(int)kT128x128, (int)kT128x128x1, (int)kT256x128, (int)kT256x256}) {
@@ -1178,6 +1177,30 @@ sif_status gemm_group_fill(const sif_gemm_args* list, uint32_t n, void* host_rec
     const double us = gemm_time_us(tiles, steps, c);
     if (ok && (cfg < 0 || us < best)) { cfg = c; best = us; }
   }
+  *us_out = best;
+  return cfg;
+}
+
+// How many of a launch's n products it should hold, where the ones from `first` on could be launches of their own: all, or the
+// first ones.  By themselves these take small tiles that the whole chip shares; in the group a row of them is a chain over
+// the whole K on a few big tiles, which costs nothing in a round that is not full and a whole round where it begins one.
+// (4096 tokens of 2048 columns: 768 tiles of 256x256 are three rounds, with two one-row products more a fourth.  Modelled
+// 344 us against 259 and twice 11; a step of six such layers, two micro-batches: 17.0 -> 16.5 ms.)
+uint32_t gemm_group_part(const sif_gemm_args* list, uint32_t first, uint32_t n) {
+  if (first == 0 || first >= n) return n;
+  double all = 0.0, apart = 0.0;
+  if (gemm_group_choose(list, n, &all) < 0 || gemm_group_choose(list, first, &apart) < 0) return n;
+  for (uint32_t i = first; i < n; ++i) {
+    const int cfg = gemm_choose(list[i]);
+    apart += gemm_time_us(gemm_tiles_of(list[i], cfg), gemm_steps_of(list[i]), cfg);
+  }
+  return apart < all ? first : n;
+}
+
+sif_status gemm_group_fill(const sif_gemm_args* list, uint32_t n, void* host_records, GemmGroup* out) {
+  if (list == nullptr || n == 0 || n > 16 || host_records == nullptr || out == nullptr) return fail(SIF_E_INVAL, "gemm group: bad arguments");
+  double us = 0.0;
+  const int cfg = gemm_group_choose(list, n, &us);
   GemmP* rec = static_cast<GemmP*>(host_records);
   uint32_t base = 0;
   for (uint32_t i = 0; i < n; ++i) {

@@ -20,6 +20,7 @@ sif_status launch_gemm_bf16(const sif_gemm_args* a, hipStream_t s, const KCtl& c
 // bytes), copy them to device memory once, launch with that copy
 struct GemmGroup { uint32_t tiles; int32_t cfg; };
 uint64_t gemm_group_bytes(uint32_t n);
+uint32_t gemm_group_part(const sif_gemm_args* list, uint32_t first, uint32_t n);
 sif_status gemm_group_fill(const sif_gemm_args* list, uint32_t n, void* host_records, GemmGroup* out);
 sif_status launch_gemm_bf16_group(const void* dev_records, uint32_t n, const GemmGroup& g, uint32_t a_layout, uint32_t b_layout, hipStream_t s, const KCtl& c);
 // rows of a product (A [M][K] row-major, one batch) that fill the chip with one whole round of the tiles it will run on

@@ -257,18 +257,25 @@ struct GroupPlan {
 struct WgradItem { const bf16_t* a; const bf16_t* b; bf16_t* dw; uint32_t m_out, n_out, lda; };
 
 static bool emit_wgrad_group(Plan& p, const char* name, const WgradItem* items, uint32_t n, uint32_t tokens, uint32_t acc, GroupPlan& gp) {
-  const uint64_t bytes = gemm_group_bytes(n);
-  if (gp.pool == nullptr || gp.used + bytes > gp.pool_bytes || n > 8) return false;
+  if (gp.pool == nullptr || n > 8) return false;
   sif_gemm_args list[8];
-  double cost = 0.0, flops = 0.0;
+  uint32_t weights = 0;                        // (the one-row products come last)
   for (uint32_t i = 0; i < n; ++i) {
     if (items[i].n_out & 7) return false;
     G g(items[i].a, items[i].b, items[i].dw, items[i].m_out, items[i].n_out, tokens, items[i].lda, items[i].n_out, items[i].n_out);
     g.lay(SIF_A_ROW_M, SIF_B_ROW_N);
     if (acc) g.epi(SIF_EPI_RESIDUAL, nullptr, items[i].dw);      // micro-batch accumulation: add to the stored gradient
     list[i] = g.a;
-    cost += gemm_cost_us(g.a) - 4.0;
-    flops += gemm_flops(g.a);
+    if (items[i].m_out > 1) weights = i + 1;
+  }
+  const uint32_t all = n;
+  n = gemm_group_part(list, weights, all);
+  const uint64_t bytes = gemm_group_bytes(n);
+  if (gp.used + bytes > gp.pool_bytes) return false;
+  double cost = 0.0, flops = 0.0;
+  for (uint32_t i = 0; i < n; ++i) {
+    cost += gemm_cost_us(list[i]) - 4.0;
+    flops += gemm_flops(list[i]);
   }
   std::vector<unsigned char> host(bytes);
   GemmGroup g;
@@ -284,6 +291,7 @@ static bool emit_wgrad_group(Plan& p, const char* name, const WgradItem* items, 
   op.prof_class = (int32_t)(SIF_A_ROW_M * 2 + SIF_B_ROW_N);
   op.flops = flops;
   p.push_back(std::move(op));
+  for (uint32_t i = n; i < all; ++i) p.push_back(make_gemm_op("db_layer", list[i]));
   return true;
 }
 

@@ -126,6 +126,35 @@ def test_gemm_bf16_picks_tiles_that_give_the_bits_of_the_128_ones(m, n, k, al, b
     assert bool(((out[0].double() - ref).abs() <= bound).all())
 
 
+@pytest.mark.parametrize("d,da,f,k,apart", [(2048, 2048, 8192, 256, True), (520, 512, 2056, 8200, True), (768, 768, 3072, 1000, False)])
+@pytest.mark.parametrize("acc", [0, 1])
+def test_bias_gradients_that_would_begin_another_round_follow_with_the_same_bits(d, da, f, k, apart, acc):
+    """The one-row products of a layer's group, in it and as launches of their own, onto a stored gradient too; sizes on both
+    sides of the rule, ragged tokens.  Bound: one rounding to bf16 and fp32 sums of k terms."""
+    from tile_choice import part
+    gen = torch.Generator(device=DEV).manual_seed(d + k)
+    lay = dict(a_layout=S.SIF_A_ROW_M, b_layout=S.SIF_B_ROW_N)
+    ones = torch.zeros((k, 8), device=DEV, dtype=torch.bfloat16)
+    ones[:, 0] = 1
+    rows = [(_bf16(gen, k, n), _bf16(gen, n)) for n in (f, 3 * da)]
+    wide = [(_bf16(gen, k, m), _bf16(gen, k, n), torch.zeros((m, n), device=DEV, dtype=torch.bfloat16)) for m, n in ((d, f), (f, d), (d, da), (3 * da, d))]
+    out = [[c.clone() for _, c in rows] for _ in range(2)]
+    onto = lambda c: dict(lay, **(dict(epilogue=S.SIF_EPI_RESIDUAL, res=c) if acc else {}))
+    prods = [S.gemm_args(a, b, c, *c.shape, k, c.shape[0], c.shape[1], c.shape[1], **lay) for a, b, c in wide]
+    prods += [S.gemm_args(ones, b, c, 1, c.numel(), k, 8, c.numel(), c.numel(), **onto(c)) for (b, _), c in zip(rows, out[0])]
+    assert part(prods, 4) == (4 if apart else 6)
+    records = torch.zeros(S.sif_k_gemm_bf16_group_bytes(6) + 16, device=DEV, dtype=torch.uint8)
+    torch.cuda.synchronize()
+    S.sif_k_gemm_bf16_group(prods, records)
+    for (b, _), c in zip(rows, out[1]):
+        S.sif_k_gemm_bf16(ones, b, c, 1, c.numel(), k, 8, c.numel(), c.numel(), **onto(c))
+    torch.cuda.synchronize()
+    for (b, c0), x, y in zip(rows, *out):
+        assert torch.equal(x, y)
+        ref = b.double().sum(0) + acc * c0.double()
+        assert bool(((x.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + (k + 2) * 2.0 ** -24 * (b.double().abs().sum(0) + c0.double().abs())).all())
+
+
 @pytest.mark.parametrize("al", [0, 1])
 @pytest.mark.parametrize("bl", [0, 1])
 @pytest.mark.parametrize("m,n", [(33, 72), (72, 2312), (280, 1992), (580, 2440), (1100, 3080)])

@@ -25,3 +25,10 @@ def group(products):
     n, got = len(products), (C.c_uint32 * 2)()
     assert fill((S.sif_gemm_args * n)(*products), n, (C.c_char * S.sif_k_gemm_bf16_group_bytes(n))(), got) == 0
     return got[0], list(TILES)[got[1]]
+
+
+def part(products, first):
+    """How many of the products one launch holds where those from `first` on could follow it."""
+    f = getattr(S.lib, "_ZN3sif15gemm_group_partEPK13sif_gemm_argsjj")
+    f.restype, f.argtypes = C.c_uint32, [C.c_void_p, C.c_uint32, C.c_uint32]
+    return f((S.sif_gemm_args * len(products))(*products), first, len(products))

@@ -296,28 +296,28 @@ __device__ __forceinline__ void gemm_store_packed(const GemmP& p, floatx16 (&acc
   finish(TI * PASSES - 1);
 }
 
-// Variants that read a tensor of the result's shape, write the pre-activation too or store fp32: staged as fp32 by SR rows, a
-// chunk of eight columns per lane and vector.  Chunk c (four floats) of a staging row lives at c ^ key(row): the two
+// bf16 variants that read a tensor of the result's shape or write the pre-activation too: staged as fp32 by SR rows, a chunk of
+// eight columns per lane and vector.  Chunk c (four floats) of a staging row lives at c ^ key(row): the two
 // half-wavefronts of a store and the eight rows of a load then fall on different banks.  What is read is requested for 64
 // rows ahead: a wait for it also waits for the stores before it.
-enum { kRowsResidual, kRowsGeluAux, kRowsGeluGrad, kRowsF32 };
+enum { kRowsResidual, kRowsGeluAux, kRowsGeluGrad };
 template <int TI, int TJ, int SR, int KIND>
 __device__ __forceinline__ void gemm_store_rows(const GemmP& p, floatx16 (&acc)[TI][TJ], float* sW, uint32_t mw, uint32_t nw, size_t c_off, uint32_t lane,
                                                 const bf16_t* bias_s) {
   constexpr int W = TJ * 32, CPR = W / 8, PASSES = 32 / SR, ITS = SR * CPR / 64, PER = PASSES * ITS;      // PER: vectors per lane of 32 rows
   static_assert(SR * CPR % 64 == 0, "whole vectors per lane");
-  constexpr bool READS = KIND == kRowsResidual || KIND == kRowsGeluGrad, F32 = KIND == kRowsF32;
+  constexpr bool READS = KIND == kRowsResidual || KIND == kRowsGeluGrad;
   constexpr int AHEAD = TI < 2 ? TI : 2;
-  const uint32_t hh = lane >> 5, esize = F32 ? 4 : 2, pitch = p.ldc * esize;
+  const uint32_t hh = lane >> 5, pitch = p.ldc * 2;
   const size_t first = c_off + (size_t)mw * p.ldc + nw;
   const uint64_t extent = mw < p.m ? (uint64_t)(p.m - mw) * pitch : 0;
-  const auto c = result_rsrc(reinterpret_cast<unsigned char*>(p.c) + first * esize, extent);
-  const auto other = result_rsrc(KIND == kRowsResidual ? reinterpret_cast<const bf16_t*>(p.res) + first : p.aux + first, F32 ? 0 : extent);
+  const auto c = result_rsrc(reinterpret_cast<bf16_t*>(p.c) + first, extent);
+  const auto other = result_rsrc(KIND == kRowsResidual ? reinterpret_cast<const bf16_t*>(p.res) + first : p.aux + first, extent);
   uint32_t off[ITS];
 #pragma unroll
   for (int it = 0; it < ITS; ++it) {
     const uint32_t item = lane + it * 64;
-    off[it] = nw + item % CPR * 8 < p.n ? (item / CPR) * pitch + item % CPR * 8 * esize : kOutside;
+    off[it] = nw + item % CPR * 8 < p.n ? (item / CPR) * pitch + item % CPR * 16 : kOutside;
   }
   uint4 q[AHEAD][PER];
   auto request = [&](int i) {
@@ -341,11 +341,6 @@ __device__ __forceinline__ void gemm_store_rows(const GemmP& p, floatx16 (&acc)[
       const uint32_t o = off[it] + (uint32_t)(pass * SR) * pitch;
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[e] = v[e] * p.alpha + bias[e];
-      if constexpr (F32) {
-        write16(c, o, make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])), false);
-        write16(c, o + 16, make_uint4(__float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]), __float_as_uint(v[7])), false);
-        continue;
-      }
       if constexpr (READS) {
         const uint4 t = q[pass / PASSES % AHEAD][pass % PASSES * ITS + it];
         const float x[8] = {bflo(t.x), bfhi(t.x), bflo(t.y), bfhi(t.y), bflo(t.z), bfhi(t.z), bflo(t.w), bfhi(t.w)};
@@ -387,8 +382,168 @@ __device__ __forceinline__ void gemm_store_rows(const GemmP& p, floatx16 (&acc)[
   finish(TI * PASSES - 1);
 }
 
-// Everything else - a column count that is no multiple of eight, an output slice that is not 16-byte aligned, rare
-// combinations, rows further apart than the offsets above reach - one element at a time.
+// bf16 results of the other combinations - a residual together with GELU or GELU' - and of rows further apart than the offsets
+// above reach: vectors too, but 64-bit addresses and decisions while it runs.  The first tensor that is read is requested 32
+// rows ahead (64 where a pass has 32), the residual beside an auxiliary tensor with its pass.  (One element at a time 4096 x
+// 4096 x 512 on 256x256 tiles took 115 us with GELU and a residual, 148 with GELU' and a residual, 75 with both of GELU and
+// GELU'; now 29, 43 and 38, with the residual alone 26; 77 x 768 x 768 with rows of 2 M elements 6.8 and now 5.4.)
+template <int TI, int TJ, int SR>
+__device__ __forceinline__ void gemm_store_mixed(const GemmP& p, floatx16 (&acc)[TI][TJ], float* sW, uint32_t mw, uint32_t nw, size_t c_off, uint32_t lane,
+                                                 const bf16_t* bias_s) {
+  constexpr int W = TJ * 32, CPR = W / 8, PASSES = 32 / SR, ITS = SR * CPR / 64, PER = PASSES * ITS;
+  constexpr int AHEAD = TI < 2 || SR < 32 ? 1 : 2;
+  static_assert(SR * CPR % 64 == 0, "whole vectors per lane");
+  const uint32_t hh = lane >> 5, n = nw + lane % CPR * 8;                // (64 is a multiple of CPR: a lane keeps its columns)
+  const bool grad = (p.epi & SIF_EPI_GELU_GRAD) != 0, gelu = (p.epi & SIF_EPI_GELU) != 0, residual = (p.epi & SIF_EPI_RESIDUAL) != 0;
+  const bf16_t* const res = reinterpret_cast<const bf16_t*>(p.res);
+  const bf16_t* const first = grad ? p.aux : residual ? res : nullptr;      // the tensor that is requested ahead
+  // the row of a lane's k-th vector in the i-th 32 rows, and where what is read for it lies: beyond the last row or column, in these
+  auto row_of = [&](int i, int k) { return mw + i * 32 + k / ITS * SR + (lane + k % ITS * 64) / CPR; };
+  auto read_at = [&](int i, int k) { return c_off + (size_t)min(row_of(i, k), p.m - 1) * p.ldc + min(n, p.n - 8); };
+  uint4 ahead[AHEAD][PER];
+  auto request = [&](int i) {
+    if (first == nullptr) return;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) ahead[i % AHEAD][k] = *reinterpret_cast<const uint4*>(first + read_at(i, k));
+  };
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) request(i);
+  const uint4 bq = p.bias != nullptr ? *reinterpret_cast<const uint4*>(bias_s + lane % CPR * 8) : make_uint4(0, 0, 0, 0);
+  const float bias[8] = {bflo(bq.x), bfhi(bq.x), bflo(bq.y), bfhi(bq.y), bflo(bq.z), bfhi(bq.z), bflo(bq.w), bfhi(bq.w)};
+  auto key = [](uint32_t row) { return (((row >> 2) & 1u) * (W / 8)) | (row & 1u); };
+  auto pack = [](const float (&v)[8]) { return make_uint4(pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]), pack_bf2(v[4], v[5]), pack_bf2(v[6], v[7])); };
+#pragma unroll
+  for (int pass = 0; pass < TI * PASSES; ++pass) {
+    const int i = pass / PASSES, ps = pass % PASSES;
+    uint4 late[ITS];                           // the residual where it is not the tensor requested ahead
+    if (residual && grad) {
+#pragma unroll
+      for (int it = 0; it < ITS; ++it) late[it] = *reinterpret_cast<const uint4*>(res + read_at(i, ps * ITS + it));
+    }
+#pragma unroll
+    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+      for (int r = ps * (SR / 2); r < (ps + 1) * (SR / 2); ++r) {
+        const uint32_t row = (r >> 2) * 8 + hh * 4 + (r & 3) - ps * SR, col = j * 32 + (lane & 31);
+        sW[row * W + ((((col >> 2) ^ key(row)) << 2) | (col & 3))] = acc[i][j][r];
+      }
+    lanes_in_order();
+#pragma unroll
+    for (int it = 0; it < ITS; ++it) {
+      const int k = ps * ITS + it;
+      const uint32_t item = lane + it * 64, row = item / CPR, c8 = item % CPR, m = row_of(i, k);
+      const float4 q0 = *reinterpret_cast<const float4*>(sW + row * W + (((2 * c8) ^ key(row)) << 2));
+      const float4 q1 = *reinterpret_cast<const float4*>(sW + row * W + (((2 * c8 + 1) ^ key(row)) << 2));
+      float v[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = v[e] * p.alpha + bias[e];
+      const bool inside = m < p.m && n < p.n;
+      const size_t idx = c_off + (size_t)m * p.ldc + n;
+      if (gelu) {
+        if (p.aux != nullptr && inside) *reinterpret_cast<uint4*>(p.aux + idx) = pack(v);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = gelu_fast(v[e]);
+      }
+      const uint4 a = ahead[i % AHEAD][k];
+      if (grad) {
+        const float z[8] = {bflo(a.x), bfhi(a.x), bflo(a.y), bfhi(a.y), bflo(a.z), bfhi(a.z), bflo(a.w), bfhi(a.w)};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] *= gelu_grad_fast(z[e]);
+      }
+      if (residual) {
+        const uint4 t = grad ? late[it] : a;
+        const float x[8] = {bflo(t.x), bfhi(t.x), bflo(t.y), bfhi(t.y), bflo(t.z), bfhi(t.z), bflo(t.w), bfhi(t.w)};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += x[e];
+      }
+      const uint4 w = pack(v);
+      const u32x4 x = {w.x, w.y, w.z, w.w};
+      if (inside) __builtin_nontemporal_store(x, reinterpret_cast<u32x4*>(reinterpret_cast<bf16_t*>(p.c) + idx));
+    }
+    lanes_in_order();
+    if (ps == PASSES - 1 && i + AHEAD < TI) request(i + AHEAD);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// fp32 results: four columns per lane, so that one store writes rows of the wavefront's part whole.  The residual is read with
+// its pass: requested ahead it only lies in front of the stores and is waited for longer (47 us instead of 43 at the size below).
+// The auxiliary tensor is requested ahead as above.  (4096 x 4096 x 512 on 256x256 tiles 27.1 us, 30.8 with eight columns per
+// lane in two stores; with a residual 43, with GELU' 44, with both GELU and a residual 50, one element at a time 98, 101, 134.)
+template <int TI, int TJ, int SR>
+__device__ __forceinline__ void gemm_store_f32(const GemmP& p, floatx16 (&acc)[TI][TJ], float* sW, uint32_t mw, uint32_t nw, size_t c_off, uint32_t lane,
+                                               const bf16_t* bias_s) {
+  constexpr int W = TJ * 32, CPR = W / 4, PASSES = 32 / SR, ITS = SR * CPR / 64, AHEAD = TI < 2 || SR < 32 ? 1 : 2;
+  const uint32_t hh = lane >> 5, c4 = lane % CPR, n = nw + c4 * 4;       // (64 is a multiple of CPR: a lane keeps its columns)
+  const bool grad = (p.epi & SIF_EPI_GELU_GRAD) != 0, gelu = (p.epi & SIF_EPI_GELU) != 0, residual = (p.epi & SIF_EPI_RESIDUAL) != 0;
+  const float* const res = reinterpret_cast<const float*>(p.res);
+  auto row_of = [&](int pass, int it) { return mw + pass * SR + (lane + it * 64) / CPR; };
+  auto read_at = [&](int pass, int it) { return c_off + (size_t)min(row_of(pass, it), p.m - 1) * p.ldc + min(n, p.n - 4); };
+  uint2 z[AHEAD][PASSES * ITS];
+  auto request = [&](int i) {
+    if (!grad) return;
+#pragma unroll
+    for (int k = 0; k < PASSES * ITS; ++k) z[i % AHEAD][k] = *reinterpret_cast<const uint2*>(p.aux + read_at(i * PASSES + k / ITS, k % ITS));
+  };
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) request(i);
+  const uint2 bq = p.bias != nullptr ? *reinterpret_cast<const uint2*>(bias_s + c4 * 4) : make_uint2(0, 0);
+  const float bias[4] = {bflo(bq.x), bfhi(bq.x), bflo(bq.y), bfhi(bq.y)};
+  auto key = [](uint32_t row) { return (((row >> 2) & 1u) * (W / 8)) | (row & 1u); };
+#pragma unroll
+  for (int pass = 0; pass < TI * PASSES; ++pass) {
+    const int i = pass / PASSES, ps = pass % PASSES;
+#pragma unroll
+    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+      for (int e = ps * (SR / 2); e < (ps + 1) * (SR / 2); ++e) {
+        const uint32_t row = (e >> 2) * 8 + hh * 4 + (e & 3) - ps * SR, col = j * 32 + (lane & 31);
+        sW[row * W + ((((col >> 2) ^ key(row)) << 2) | (col & 3))] = acc[i][j][e];
+      }
+    lanes_in_order();
+    float4 s[ITS];
+#pragma unroll
+    for (int it = 0; it < ITS; ++it) {
+      const uint32_t row = (lane + it * 64) / CPR;
+      s[it] = *reinterpret_cast<const float4*>(sW + row * W + ((c4 ^ key(row)) << 2));
+    }
+    lanes_in_order();
+    float4 r[ITS];
+    if (residual) {
+#pragma unroll
+      for (int it = 0; it < ITS; ++it) r[it] = *reinterpret_cast<const float4*>(res + read_at(pass, it));
+    }
+#pragma unroll
+    for (int it = 0; it < ITS; ++it) {
+      const uint32_t m = row_of(pass, it);
+      const bool inside = m < p.m && n < p.n;
+      const size_t idx = c_off + (size_t)m * p.ldc + n;
+      float v[4] = {s[it].x, s[it].y, s[it].z, s[it].w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = v[e] * p.alpha + bias[e];
+      if (gelu) {
+        if (p.aux != nullptr && inside) *reinterpret_cast<uint2*>(p.aux + idx) = make_uint2(pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = gelu_fast(v[e]);
+      }
+      if (grad) {
+        const uint2 q = z[i % AHEAD][ps * ITS + it];
+        const float x[4] = {bflo(q.x), bfhi(q.x), bflo(q.y), bfhi(q.y)};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] *= gelu_grad_fast(x[e]);
+      }
+      if (residual) {
+        const float4 x = r[it];
+        v[0] += x.x; v[1] += x.y; v[2] += x.z; v[3] += x.w;
+      }
+      if (inside) *reinterpret_cast<float4*>(reinterpret_cast<float*>(p.c) + idx) = make_float4(v[0], v[1], v[2], v[3]);
+    }
+    if (ps == PASSES - 1 && i + AHEAD < TI) request(i + AHEAD);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// A column count that is no multiple of eight: one element at a time.
 template <int TI, int TJ, int SR>
 __device__ __forceinline__ void gemm_store_single(const GemmP& p, floatx16 (&acc)[TI][TJ], float* sW, uint32_t mw, uint32_t nw, size_t c_off, uint32_t lane) {
   constexpr int W = TJ * 32, PASSES = 32 / SR;
@@ -424,19 +579,34 @@ __device__ __forceinline__ void gemm_store_single(const GemmP& p, floatx16 (&acc
   }
 }
 
+// An epilogue that is not one of the common ones: ragged columns, fp32, two of GELU, GELU' and a residual, rows so far apart that
+// 32-bit offsets do not reach over the 128 of a wavefront.  They have kernels of their own.  (With all variants in one kernel the
+// main loops beside the common ones came out slower: six layers of d 2048 16.6 -> 17.4 ms a step, a batch of 4096 tokens through
+// twelve of d 768 1.55 -> 1.62.)  A launch over several products that has both takes one with all of them.
+__host__ __device__ __forceinline__ bool gemm_rare(uint32_t epilogue, uint32_t n, uint32_t ldc) {
+  const uint32_t what = epilogue & (SIF_EPI_GELU | SIF_EPI_GELU_GRAD | SIF_EPI_RESIDUAL | SIF_EPI_OUT_F32);
+  return (n & 7) != 0 || ldc > (1u << 21) || (what & SIF_EPI_OUT_F32) || (what & (what - 1)) != 0;
+}
+enum { kEpiCommon, kEpiRare, kEpiAll };
 // bias_s: the bias of the columns nw.. in LDS (gemm_fetch_bias)
-template <int TI, int TJ, int SR>
+template <int TI, int TJ, int SR, int EPI>
 __device__ __forceinline__ void gemm_store_tile(const GemmP& p, floatx16 (&acc)[TI][TJ], float* sW, uint32_t mw, uint32_t nw, size_t c_off, uint32_t lane,
                                                 const bf16_t* bias_s) {
-  const uint32_t what = p.epi & (SIF_EPI_GELU | SIF_EPI_GELU_GRAD | SIF_EPI_RESIDUAL | SIF_EPI_OUT_F32);
-  const bool vectors = (p.n & 7) == 0 && (c_off & 7) == 0 && p.ldc <= (1u << 21);      // (TI*32 rows of fp32 stay below 2 GB)
-  if (vectors && what == 0) gemm_store_packed<TI, TJ, SR, false>(p, acc, sW, mw, nw, c_off, lane, bias_s);
-  else if (vectors && what == SIF_EPI_GELU && p.aux == nullptr) gemm_store_packed<TI, TJ, SR, true>(p, acc, sW, mw, nw, c_off, lane, bias_s);
-  else if (vectors && what == SIF_EPI_GELU) gemm_store_rows<TI, TJ, SR, kRowsGeluAux>(p, acc, sW, mw, nw, c_off, lane, bias_s);
-  else if (vectors && what == SIF_EPI_RESIDUAL) gemm_store_rows<TI, TJ, SR, kRowsResidual>(p, acc, sW, mw, nw, c_off, lane, bias_s);
-  else if (vectors && what == SIF_EPI_GELU_GRAD) gemm_store_rows<TI, TJ, SR, kRowsGeluGrad>(p, acc, sW, mw, nw, c_off, lane, bias_s);
-  else if (vectors && what == SIF_EPI_OUT_F32) gemm_store_rows<TI, TJ, SR, kRowsF32>(p, acc, sW, mw, nw, c_off, lane, bias_s);
-  else gemm_store_single<TI, TJ, SR>(p, acc, sW, mw, nw, c_off, lane);
+  if constexpr (EPI != kEpiCommon) {
+    if (EPI == kEpiRare || gemm_rare(p.epi, p.n, p.ldc)) {
+      if ((p.n & 7) != 0) gemm_store_single<TI, TJ, SR>(p, acc, sW, mw, nw, c_off, lane);
+      else if (p.epi & SIF_EPI_OUT_F32) gemm_store_f32<TI, TJ, SR>(p, acc, sW, mw, nw, c_off, lane, bias_s);
+      else gemm_store_mixed<TI, TJ, SR>(p, acc, sW, mw, nw, c_off, lane, bias_s);
+      return;
+    }
+  }
+  if constexpr (EPI != kEpiRare) {
+    if (p.epi & SIF_EPI_RESIDUAL) gemm_store_rows<TI, TJ, SR, kRowsResidual>(p, acc, sW, mw, nw, c_off, lane, bias_s);
+    else if (p.epi & SIF_EPI_GELU_GRAD) gemm_store_rows<TI, TJ, SR, kRowsGeluGrad>(p, acc, sW, mw, nw, c_off, lane, bias_s);
+    else if (!(p.epi & SIF_EPI_GELU)) gemm_store_packed<TI, TJ, SR, false>(p, acc, sW, mw, nw, c_off, lane, bias_s);
+    else if (p.aux == nullptr) gemm_store_packed<TI, TJ, SR, true>(p, acc, sW, mw, nw, c_off, lane, bias_s);
+    else gemm_store_rows<TI, TJ, SR, kRowsGeluAux>(p, acc, sW, mw, nw, c_off, lane, bias_s);
+  }
 }
 
 // The bias of a wavefront's columns nw.. into 1 KB of LDS of its own, by one fetch (which writes zeros behind them)
@@ -505,7 +675,7 @@ __device__ __forceinline__ GemmP gemm_read_record(gemm_record_ptr p) {
 // Registers: at most 248 of the 256 that two wavefronts of a SIMD may take (the attribute counts in pairs), so that a
 // one-wavefront kernel that sits on a CU for the length of a bubble (the training stream's wait) fits beside a block of the
 // 256x128 tiles, which otherwise stays off that CU until it ends.
-template <int ALAY, int BLAY, int BM, int BN, int WM, int WN, int ST, int LAG, int OCC, bool GROUPED = false>
+template <int ALAY, int BLAY, int BM, int BN, int WM, int WN, int ST, int LAG, int OCC, int EPI, bool GROUPED = false>
 __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_num_vgpr(124))) void gemm_ring_kernel(GemmP p_in, KCtl ctl) {
   // (a launch over several products has an instantiation of its own: in the others the product's record stays the
   // kernel argument, in scalar registers)
@@ -653,7 +823,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_num_vgpr(1
   if (t < nt) step(Int<0>());
 
   __syncthreads();                             // nobody reads the ring any more: it stages the results
-  gemm_store_tile<TI, TJ, SR>(p, acc, reinterpret_cast<float*>(lds) + wave * (SR * TJ * 32), m0 + wm * (TI * 32), n0 + wn * (TJ * 32), c_off, lane, s_bias + wave * 512);
+  gemm_store_tile<TI, TJ, SR, EPI>(p, acc, reinterpret_cast<float*>(lds) + wave * (SR * TJ * 32), m0 + wm * (TI * 32), n0 + wn * (TJ * 32), c_off, lane, s_bias + wave * 512);
   kernel_end(ctl, true);
 }
 
@@ -678,7 +848,7 @@ __device__ __forceinline__ void gemm_wait_steps(uint32_t steps) {
   if constexpr (MOST == 0) { wait_vm<0>(); }
   else { if (steps >= (uint32_t)MOST) wait_vm<F * MOST>(); else gemm_wait_steps<F, MOST - 1>(steps); }
 }
-template <int ALAY, int BLAY, int BM, int BN, int WM, int WN, int FW, int ST, int KB>
+template <int ALAY, int BLAY, int BM, int BN, int WM, int WN, int FW, int ST, int KB, int EPI>
 __global__ __launch_bounds__(64 * (WM * WN + FW), 2) void gemm_fed_kernel(GemmP p, KCtl ctl) {
   constexpr int MW = WM * WN, FT = 64 * FW, TI = BM / (WM * 32), TJ = BN / (WN * 32), AHEAD = ST - 1;
   constexpr uint32_t SA = BM * BK, SB = BN * BK, STAGE = SA + SB;      // elements of 64 k
@@ -790,7 +960,7 @@ __global__ __launch_bounds__(64 * (WM * WN + FW), 2) void gemm_fed_kernel(GemmP 
     gemm_unrolled<0, ST>([&](auto S) { if (t + decltype(S)::value < nt) step(S, t + decltype(S)::value + 1 < nt); });
     wait_vm<0>();                              // the bias
     __syncthreads();                           // nobody reads the ring any more: it stages the results
-    gemm_store_tile<TI, TJ, SR>(p, acc, reinterpret_cast<float*>(lds) + wave * (SR * TJ * 32), m0 + wm * (TI * 32), n0 + wn * (TJ * 32),
+    gemm_store_tile<TI, TJ, SR, EPI>(p, acc, reinterpret_cast<float*>(lds) + wave * (SR * TJ * 32), m0 + wm * (TI * 32), n0 + wn * (TJ * 32),
                                 (size_t)(bo * p.c_so + bi * p.c_si), lane, s_bias + wave * 512);
   }
   kernel_end(ctl, true);
@@ -816,7 +986,7 @@ __global__ __launch_bounds__(64 * (WM * WN + FW), 2) void gemm_fed_kernel(GemmP 
 // unmonitored launch has no record: every block takes each gridDim.x-th tile (a stride that is a multiple of 8 keeps it
 // on its XCD's run).
 // Registers: held to 248 for the same reason as the ring kernel.
-template <int ALAY, int BLAY, bool GROUPED = false>
+template <int ALAY, int BLAY, int EPI, bool GROUPED = false>
 __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(124))) void gemm_pp_kernel(GemmP p_in, KCtl ctl) {
   constexpr int BM = 256, BN = 256, WM = 2, WN = 4, THREADS = 512, TI = 4, TJ = 2, HI = TI / 2, SR = 8;
   constexpr uint32_t HA = BM / 2 * BK, STAGE = 2 * HA + BN * BK;       // elements: two halves of A, then B
@@ -972,7 +1142,7 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(124))) void 
       const GemmP cp = gemm_read_record(current);
       uint32_t l = lane;
       asm volatile("" : "+v"(l));              // (as in open_tile)
-      gemm_store_tile<TI, TJ, SR>(cp, acc, stage + wave * (SR * TJ * 32), cm0 + wm * (TI * 32), cn0 + wn * 64, (size_t)(bo * cp.c_so + bi * cp.c_si), l, s_bias + wave * 512);
+      gemm_store_tile<TI, TJ, SR, EPI>(cp, acc, stage + wave * (SR * TJ * 32), cm0 + wm * (TI * 32), cn0 + wn * 64, (size_t)(bo * cp.c_so + bi * cp.c_si), l, s_bias + wave * 512);
     }
   }
   kernel_end(ctl, true, threadIdx.x == 0);
@@ -1097,23 +1267,24 @@ static sif_status gemm_fill(const sif_gemm_args* a, GemmP& p, int cfg, int* cfg_
 }
 
 typedef void (*gemm_kern_fn)(GemmP, KCtl);
-#define RING(BM, BN, WM, WN, ST, LAG, OCC)                                                                                        \
-  {{gemm_ring_kernel<0, 0, BM, BN, WM, WN, ST, LAG, OCC>, gemm_ring_kernel<0, 1, BM, BN, WM, WN, ST, LAG, OCC>},                  \
-   {gemm_ring_kernel<1, 0, BM, BN, WM, WN, ST, LAG, OCC>, gemm_ring_kernel<1, 1, BM, BN, WM, WN, ST, LAG, OCC>}}
-#define FED(BM, BN, WM, WN, FW, ST, KB)                                                                                           \
-  {{gemm_fed_kernel<0, 0, BM, BN, WM, WN, FW, ST, KB>, gemm_fed_kernel<0, 1, BM, BN, WM, WN, FW, ST, KB>},                        \
-   {gemm_fed_kernel<1, 0, BM, BN, WM, WN, FW, ST, KB>, gemm_fed_kernel<1, 1, BM, BN, WM, WN, FW, ST, KB>}}
-static const gemm_kern_fn kGemmKernels[kNTiles][2][2] = {
+#define OF_LAYOUTS(KERNEL, EPI, ...)                                                                                              \
+  {{KERNEL<0, 0, __VA_ARGS__ EPI>, KERNEL<0, 1, __VA_ARGS__ EPI>}, {KERNEL<1, 0, __VA_ARGS__ EPI>, KERNEL<1, 1, __VA_ARGS__ EPI>}}
+#define OF_EPILOGUES(KERNEL, ...) {OF_LAYOUTS(KERNEL, kEpiCommon, __VA_ARGS__), OF_LAYOUTS(KERNEL, kEpiRare, __VA_ARGS__)}
+#define RING(...) OF_EPILOGUES(gemm_ring_kernel, __VA_ARGS__, )
+#define FED(...) OF_EPILOGUES(gemm_fed_kernel, __VA_ARGS__, )
+static const gemm_kern_fn kGemmKernels[kNTiles][2][2][2] = {      // [..][common or rare epilogue][layout of A][layout of B]
     RING(32, 64, 1, 2, 4, 1, 2),   RING(64, 64, 2, 2, 4, 1, 2),   RING(128, 64, 2, 2, 3, 0, 2), RING(128, 128, 4, 2, 4, 1, 1),
-    RING(128, 128, 2, 2, 2, 0, 2), RING(256, 128, 4, 2, 3, 0, 1), {{gemm_pp_kernel<0, 0>, gemm_pp_kernel<0, 1>}, {gemm_pp_kernel<1, 0>, gemm_pp_kernel<1, 1>}}};
+    RING(128, 128, 2, 2, 2, 0, 2), RING(256, 128, 4, 2, 3, 0, 1), OF_EPILOGUES(gemm_pp_kernel, )};
 // launches of at most one tile per CU, by their tiles: 32x64, 64x64, 128x64, and 32x32 instead of 32x64 where that is still one
 // tile per CU (a third less to fetch for each; 77 x 768 x 3072: 8.1 us, on 32x64 9.5)
-static const struct { gemm_kern_fn kern[2][2]; uint32_t threads; } kGemmFed[] = {
+static const struct { gemm_kern_fn kern[2][2][2]; uint32_t threads; } kGemmFed[] = {
     {FED(32, 64, 1, 2, 4, 6, 2), 384}, {FED(64, 64, 2, 2, 4, 8, 1), 512}, {FED(128, 64, 2, 2, 4, 6, 1), 512}, {FED(32, 32, 1, 1, 4, 6, 2), 320}};
 constexpr uint32_t kFed32x32 = 3;
 static const uint32_t kGemmThreads[kNTiles] = {128, 256, 256, 512, 256, 512, 512};
 #undef RING
 #undef FED
+#undef OF_LAYOUTS
+#undef OF_EPILOGUES
 
 static uint32_t gemm_cus() {
   static const uint32_t cus = [] {
@@ -1133,7 +1304,8 @@ static sif_status launch_gemm_cfg(const sif_gemm_args* a, int want, hipStream_t 
   // 8 keeps a block on the tiles of its own XCD
   uint32_t grid_x = p.tiles_m * p.tiles_n;
   if (cfg == kT256x256 && batches == 1) grid_x = std::min(grid_x, gemm_cus());
-  gemm_kern_fn kern = kGemmKernels[cfg][a->a_layout][a->b_layout];
+  const bool rare = gemm_rare(a->epilogue, a->n, a->ldc);
+  gemm_kern_fn kern = kGemmKernels[cfg][rare][a->a_layout][a->b_layout];
   uint32_t threads = kGemmThreads[cfg];
   if (cfg <= kT128x64 && grid_x * batches <= gemm_cus()) {
     uint32_t fed = (uint32_t)cfg;
@@ -1143,7 +1315,7 @@ static sif_status launch_gemm_cfg(const sif_gemm_args* a, int want, hipStream_t 
       p.tiles_n = narrow;
       grid_x = p.tiles_m * narrow;
     }
-    kern = kGemmFed[fed].kern[a->a_layout][a->b_layout];
+    kern = kGemmFed[fed].kern[rare][a->a_layout][a->b_layout];
     threads = kGemmFed[fed].threads;
   }
   hipLaunchKernelGGL(kern, dim3(grid_x, 1, (uint32_t)batches), dim3(threads), 0, stream, p, ctl);
@@ -1203,6 +1375,7 @@ sif_status gemm_group_fill(const sif_gemm_args* list, uint32_t n, void* host_rec
   const int cfg = gemm_group_choose(list, n, &us);
   GemmP* rec = static_cast<GemmP*>(host_records);
   uint32_t base = 0;
+  out->rare = 0;
   for (uint32_t i = 0; i < n; ++i) {
     sif_gemm_args a = list[i];
     if (a.a_layout != list[0].a_layout || a.b_layout != list[0].b_layout) return fail(SIF_E_INVAL, "gemm group: the products must share their operand layouts");
@@ -1210,6 +1383,7 @@ sif_status gemm_group_fill(const sif_gemm_args* list, uint32_t n, void* host_rec
     a.tile = 0;
     int got = 0;
     if (sif_status st = gemm_fill(&a, rec[i], cfg, &got)) return st;
+    out->rare |= gemm_rare(a.epilogue, a.n, a.ldc);
     rec[i].tile_base = base;
     base += (rec[i].tiles_m * rec[i].tiles_n + 7u) & ~7u;       // a multiple of 8 keeps the tile order's idea of the XCDs
   }
@@ -1227,10 +1401,13 @@ sif_status launch_gemm_bf16_group(const void* dev_records, uint32_t n, const Gem
   head.tiles_m = g.tiles;
   // (instantiated for the layouts of weight gradients, A [K][M] and B [K][N]; other layouts would need their own)
   if (a_layout != SIF_A_ROW_M || b_layout != SIF_B_ROW_N) return fail(SIF_E_INVAL, "gemm group: only A stored [K][M] with B stored [K][N]");
-  if (g.cfg == kT256x256) hipLaunchKernelGGL((gemm_pp_kernel<1, 1, true>), dim3(std::min(g.tiles, gemm_cus())), dim3(512), 0, stream, head, ctl);
-  else if (g.cfg == kT128x128x1) hipLaunchKernelGGL((gemm_ring_kernel<1, 1, 128, 128, 4, 2, 4, 1, 1, true>), dim3(g.tiles), dim3(512), 0, stream, head, ctl);
-  else if (g.cfg == kT256x128) hipLaunchKernelGGL((gemm_ring_kernel<1, 1, 256, 128, 4, 2, 3, 0, 1, true>), dim3(g.tiles), dim3(512), 0, stream, head, ctl);
-  else hipLaunchKernelGGL((gemm_ring_kernel<1, 1, 128, 128, 2, 2, 2, 0, 2, true>), dim3(g.tiles), dim3(256), 0, stream, head, ctl);
+#define GROUPED(KERNEL, ...) (g.rare ? KERNEL<1, 1, __VA_ARGS__ kEpiAll, true> : KERNEL<1, 1, __VA_ARGS__ kEpiCommon, true>)
+  gemm_kern_fn kern = GROUPED(gemm_ring_kernel, 128, 128, 2, 2, 2, 0, 2, );
+  if (g.cfg == kT256x256) kern = GROUPED(gemm_pp_kernel, );
+  if (g.cfg == kT128x128x1) kern = GROUPED(gemm_ring_kernel, 128, 128, 4, 2, 4, 1, 1, );
+  if (g.cfg == kT256x128) kern = GROUPED(gemm_ring_kernel, 256, 128, 4, 2, 3, 0, 1, );
+#undef GROUPED
+  hipLaunchKernelGGL(kern, dim3(g.cfg == kT256x256 ? std::min(g.tiles, gemm_cus()) : g.tiles), dim3(kGemmThreads[g.cfg]), 0, stream, head, ctl);
   return check_launch("gemm_bf16_group");
 }
 

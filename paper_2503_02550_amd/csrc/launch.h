@@ -18,7 +18,7 @@ inline KCtl no_ctl() { KCtl c{}; return c; }
 sif_status launch_gemm_bf16(const sif_gemm_args* a, hipStream_t s, const KCtl& c);
 // several products of the same operand layouts as one launch: fill the kernel records on the host (gemm_group_bytes(n)
 // bytes), copy them to device memory once, launch with that copy
-struct GemmGroup { uint32_t tiles; int32_t cfg; };
+struct GemmGroup { uint32_t tiles; int32_t cfg; uint32_t rare; };      // rare: has epilogues other than the common ones
 uint64_t gemm_group_bytes(uint32_t n);
 uint32_t gemm_group_part(const sif_gemm_args* list, uint32_t first, uint32_t n);
 sif_status gemm_group_fill(const sif_gemm_args* list, uint32_t n, void* host_records, GemmGroup* out);

@@ -257,9 +257,10 @@ def test_gemm_bf16_epilogues_on_every_tile_width(m, n, k, epi):
 @pytest.mark.parametrize("m,n,k", [(256, 256, 64), (300, 520, 192), (513, 264, 128), (31, 777, 64)])
 @pytest.mark.parametrize("epi", ["residual", "grad", "grad_residual", "grad_bias_residual", "gelu_aux_residual", "f32_residual"])
 def test_gemm_bf16_staged_epilogues_on_256_tiles(m, n, k, epi):
-    """What an epilogue reads is requested 16 or 32 rows ahead of its staging passes of eight (256x256 tiles) or with them (128x128):
-    whole and ragged tiles, an auxiliary tensor, a residual and both, 16-byte accesses and single ones: the same bits, and the
-    product (one rounding to bf16 of the result, and of fp32 sums that GELU' or GELU scales)."""
+    """What an epilogue reads is requested 32 or 64 rows ahead of its staging passes, a second tensor with its pass (of eight rows on
+    256x256 tiles, of 32 on 128x128): whole and ragged tiles, an auxiliary tensor, a residual and both, vectors and (777 columns)
+    single elements: the same bits, and the product (one rounding to bf16 of the result, and of fp32 sums that GELU' or GELU
+    scales)."""
     gen = torch.Generator(device=DEV).manual_seed(m + n + k)
     a, b, bias, res, z = _bf16(gen, m, k), _bf16(gen, n, k), _bf16(gen, n), _bf16(gen, m, n), _bf16(gen, m, n)
     f32out = epi.startswith("f32")
@@ -283,34 +284,118 @@ def test_gemm_bf16_staged_epilogues_on_256_tiles(m, n, k, epi):
     assert float((got[0][0].double() - ref).norm() / ref.norm()) <= 2.0 ** -8
 
 
-@pytest.mark.parametrize("m,n", [(1, 8), (33, 200), (129, 136), (257, 328)])
-@pytest.mark.parametrize("epi", ["plain", "gelu", "residual", "gelu_aux", "gelu_grad", "f32"])
+EPILOGUES = ["plain", "gelu", "residual", "gelu_aux", "gelu_grad", "f32", "gelu_residual", "gelu_aux_residual", "grad_residual", "grad_bias_residual", "f32_residual",
+             "f32_gelu", "f32_grad", "f32_grad_residual", "f32_gelu_aux_residual"]
+
+
+def _epilogue(name, acc, bias, res, z):
+    """(flags, bias?, residual?, auxiliary tensor?, result, auxiliary output or None) of a named epilogue over the product acc;
+    everything in 64 bits.  GELU and a residual alone come with a bias."""
+    words = name.split("_")
+    grad, gelu = "grad" in words, "gelu" in words and "grad" not in words
+    biased = gelu or "bias" in words or name in ("plain", "residual")
+    flags = (S.SIF_EPI_GELU * gelu | S.SIF_EPI_GELU_GRAD * grad | S.SIF_EPI_RESIDUAL * ("residual" in words) | S.SIF_EPI_OUT_F32 * ("f32" in words) |
+             S.SIF_EPI_BIAS * (biased and not gelu))
+    x = acc + bias if biased else acc
+    pre = x if gelu and "aux" in words else None
+    if gelu:
+        x = torch.nn.functional.gelu(x)
+    if grad:
+        x = x * (0.5 * (1 + torch.erf(z / 2 ** 0.5)) + z * torch.exp(-z ** 2 / 2) / (2 * torch.pi) ** 0.5)
+    if "residual" in words:
+        x = x + res
+    return flags, biased, "residual" in words, grad or "aux" in words, x, pre
+
+
+@pytest.mark.parametrize("m,n,far", [(1, 8, False), (33, 200, False), (129, 136, False), (257, 328, False), (33, 200, True)])
+@pytest.mark.parametrize("epi", EPILOGUES)
 @pytest.mark.parametrize("tile", [0, 128, 256])
-def test_gemm_bf16_epilogues_write_their_rows_and_columns_only(m, n, epi, tile):
-    """Rows further apart than their columns, the last rows and columns of a tile missing: what lies between the rows and
-    behind the last one keeps its value, in the result and in the auxiliary tensor, and what lies there in the tensors that
-    are read (NaN) reaches no result.  Bound: one rounding to bf16 of the result, and of fp32 sums that GELU' or GELU scales."""
+def test_gemm_bf16_epilogues_write_their_rows_and_columns_only(m, n, far, epi, tile):
+    """Rows further apart than their columns (by 24 elements, and by more than 2 M), the last rows and columns of a tile
+    missing: what lies between the rows and behind the last one keeps its value, in the result and in the auxiliary tensor, and
+    what lies there in the tensors that are read (NaN) reaches no result.  Bound: one rounding to bf16 of the result, and of
+    fp32 sums that GELU' or GELU scales."""
     gen = torch.Generator(device=DEV).manual_seed(m + n)
-    k, ld = 64, n + 24
-    a, b, bias, z = _bf16(gen, m, k), _bf16(gen, n, k), _bf16(gen, n), _bf16(gen, m, n)
-    c = torch.full((m + 256, ld), 7.0, device=DEV, dtype=torch.float32 if epi == "f32" else torch.bfloat16)
-    other = torch.full((m + 256, ld), float("nan"), device=DEV, dtype=torch.bfloat16)
-    other[:m, :n] = z
-    kw = {"plain": dict(epilogue=S.SIF_EPI_BIAS, bias=bias), "gelu": dict(epilogue=S.SIF_EPI_GELU, bias=bias),
-          "residual": dict(epilogue=S.SIF_EPI_BIAS | S.SIF_EPI_RESIDUAL, bias=bias, res=other), "gelu_aux": dict(epilogue=S.SIF_EPI_GELU, bias=bias, aux=other),
-          "gelu_grad": dict(epilogue=S.SIF_EPI_GELU_GRAD, aux=other), "f32": dict(epilogue=S.SIF_EPI_OUT_F32)}[epi]
+    k, ld, below = 64, (1 << 21) + 8 if far else n + 24, 2 if far else 256
+    a, b, bias, res, z = _bf16(gen, m, k), _bf16(gen, n, k), _bf16(gen, n), _bf16(gen, m, n), _bf16(gen, m, n)
+    flags, biased, residual, has_aux, ref, pre = _epilogue(epi, a.double() @ b.double().t(), bias.double(), res.double(), z.double())
+    dtype = torch.float32 if "f32" in epi else torch.bfloat16
+    c, aux, other = torch.full((m + below, ld), 7.0, device=DEV, dtype=dtype), None, None
+    if has_aux:
+        aux = torch.full((m + below, ld), float("nan"), device=DEV, dtype=torch.bfloat16)
+        aux[:m, :n] = z
+    if residual:
+        other = torch.full((m + below, ld), float("nan"), device=DEV, dtype=dtype)
+        other[:m, :n] = res
     torch.cuda.synchronize()
-    S.sif_k_gemm_bf16(a, b, c, m, n, k, k, k, ld, tile=tile, **kw)
+    S.sif_k_gemm_bf16(a, b, c, m, n, k, k, k, ld, epilogue=flags, bias=bias if biased else None, res=other, aux=aux, tile=tile)
     torch.cuda.synchronize()
     assert bool((c[m:] == 7.0).all()) and bool((c[:, n:] == 7.0).all())
-    assert bool(other[m:].isnan().all()) and bool(other[:, n:].isnan().all())
-    acc, zd = a.double() @ b.double().t(), z.double()
-    ref = {"plain": acc + bias.double(), "gelu": torch.nn.functional.gelu(acc + bias.double()), "residual": acc + bias.double() + zd,
-           "gelu_aux": torch.nn.functional.gelu(acc + bias.double()), "f32": acc,
-           "gelu_grad": acc * (0.5 * (1 + torch.erf(zd / 2 ** 0.5)) + zd * torch.exp(-zd ** 2 / 2) / (2 * torch.pi) ** 0.5)}[epi]
+    assert aux is None or bool(aux[m:].isnan().all()) and bool(aux[:, n:].isnan().all())
     assert float((c[:m, :n].double() - ref).norm() / ref.norm()) <= 2.0 ** -8
-    if epi == "gelu_aux":
-        assert float((other[:m, :n].double() - acc - bias.double()).norm() / acc.norm()) <= 2.0 ** -8
+    if pre is not None:
+        assert float((aux[:m, :n].double() - pre).norm() / pre.norm()) <= 2.0 ** -8
+
+
+@pytest.mark.parametrize("m,k,tiles", [(136, 136, "128x128 one"), (776, 136, "128x128 two"), (776, 1160, "256x128"), (1032, 512, "256x256"), (2056, 1024, "256x256")])
+@pytest.mark.parametrize("ragged", [False, True])
+def test_a_group_whose_products_have_all_epilogues_gives_each_its_bits(m, k, tiles, ragged):
+    """One launch over products with the common epilogues and with the others, ragged columns among them: the bits of each by
+    itself."""
+    from tile_choice import group
+    gen = torch.Generator(device=DEV).manual_seed(m + k)
+    lay = dict(a_layout=S.SIF_A_ROW_M, b_layout=S.SIF_B_ROW_N)
+    prods, outs = [], []
+    for i, epi in enumerate(EPILOGUES):
+        n, pitch = m // 2 + 8 * i - (3 if ragged and i % 4 == 3 else 0), m + 512
+        a, b, bias = _bf16(gen, k, m), _bf16(gen, k, m + 512), _bf16(gen, m + 512)
+        flags, biased, residual, has_aux, _, _ = _epilogue(epi, *[torch.zeros(1, device=DEV)] * 4)
+        dtype = torch.float32 if "f32" in epi else torch.bfloat16
+        res, z = torch.randn((m, pitch), device=DEV, generator=gen).to(dtype), _bf16(gen, m, pitch)
+        pair = [(torch.full((m, pitch), 7.0, device=DEV, dtype=dtype), z.clone()) for _ in range(2)]
+        call = lambda c, aux, **kw: ((a, b, c, m, n, k, m, m + 512, pitch), dict(lay, epilogue=flags, bias=bias if biased else None, res=res if residual else None,
+                                                                              aux=aux if has_aux else None, **kw))
+        args, kw = call(*pair[0])
+        prods.append(S.gemm_args(*args, **kw))
+        args, kw = call(*pair[1], tile=128)
+        outs.append((pair, a, b, bias, res))
+        torch.cuda.synchronize()
+        S.sif_k_gemm_bf16(*args, **kw)
+    assert group(prods)[1] == tiles
+    records = torch.zeros(S.sif_k_gemm_bf16_group_bytes(len(prods)) + 16, device=DEV, dtype=torch.uint8)
+    torch.cuda.synchronize()
+    S.sif_k_gemm_bf16_group(prods, records)
+    torch.cuda.synchronize()
+    for epi, (pair, *_) in zip(EPILOGUES, outs):
+        assert torch.equal(pair[0][0], pair[1][0]) and torch.equal(pair[0][1], pair[1][1]), epi
+
+
+@pytest.mark.parametrize("tile", [128, 256])
+def test_gemm_bf16_epilogues_that_read_two_tensors_or_store_fp32_are_vectors_too(tile):
+    """A residual together with GELU or GELU', and fp32 with any of these: at most three times the time of the plain product
+    (they move up to five times its bytes and take 1.3 to 2.5 times as long; one element at a time it is 3.4 to 6.3 times)."""
+    m, n, k = 4096, 4096, 512
+    gen = torch.Generator(device=DEV).manual_seed(1)
+    a, b, bias = _bf16(gen, m, k), _bf16(gen, n, k), _bf16(gen, n)
+    us = {}
+    for epi in EPILOGUES:
+        flags, biased, residual, has_aux, _, _ = _epilogue(epi, *[torch.zeros(1, device=DEV)] * 4)
+        dtype = torch.float32 if "f32" in epi else torch.bfloat16
+        c, res, aux = (torch.zeros((m, n), device=DEV, dtype=t) for t in (dtype, dtype, torch.bfloat16))
+        launch = lambda: S.sif_k_gemm_bf16(a, b, c, m, n, k, k, k, n, epilogue=flags, bias=bias if biased else None, res=res if residual else None,
+                                           aux=aux if has_aux else None, tile=tile)
+        times = []
+        for _ in range(6):
+            at = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            torch.cuda.synchronize()
+            at[0].record()
+            for _ in range(10):
+                launch()
+            at[1].record()
+            torch.cuda.synchronize()
+            times.append(at[0].elapsed_time(at[1]) * 100)
+        us[epi] = min(times)
+    assert all(t <= 3 * us["plain"] for t in us.values()), us
 
 
 @pytest.mark.parametrize("causal", [0, 1])

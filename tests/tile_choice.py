@@ -22,7 +22,7 @@ def group(products):
     """(tiles with their padding, name of the tiles) of a launch over several products."""
     fill = getattr(S.lib, "_ZN3sif15gemm_group_fillEPK13sif_gemm_argsjPvPNS_9GemmGroupE")
     fill.restype, fill.argtypes = C.c_int, [C.c_void_p, C.c_uint32, C.c_void_p, C.c_void_p]
-    n, got = len(products), (C.c_uint32 * 2)()
+    n, got = len(products), (C.c_uint32 * 3)()
     assert fill((S.sif_gemm_args * n)(*products), n, (C.c_char * S.sif_k_gemm_bf16_group_bytes(n))(), got) == 0
     return got[0], list(TILES)[got[1]]
 

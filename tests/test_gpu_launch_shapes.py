@@ -307,7 +307,8 @@ def _epilogue(name, acc, bias, res, z):
     return flags, biased, "residual" in words, grad or "aux" in words, x, pre
 
 
-@pytest.mark.parametrize("m,n,far", [(1, 8, False), (33, 200, False), (129, 136, False), (257, 328, False), (33, 200, True)])
+@pytest.mark.parametrize("m,n,far", [(1, 8, False), (33, 200, False), (129, 136, False), (257, 328, False), (33, 200, True),
+                                     (33, 77, False), (257, 333, False), (33, 77, True)])
 @pytest.mark.parametrize("epi", EPILOGUES)
 @pytest.mark.parametrize("tile", [0, 128, 256])
 def test_gemm_bf16_epilogues_write_their_rows_and_columns_only(m, n, far, epi, tile):
@@ -370,11 +371,14 @@ def test_a_group_whose_products_have_all_epilogues_gives_each_its_bits(m, k, til
         assert torch.equal(pair[0][0], pair[1][0]) and torch.equal(pair[0][1], pair[1][1]), epi
 
 
+@pytest.mark.parametrize("n,most", [(4096, 3.0), (4093, 2.2)])
 @pytest.mark.parametrize("tile", [128, 256])
-def test_gemm_bf16_epilogues_that_read_two_tensors_or_store_fp32_are_vectors_too(tile):
-    """A residual together with GELU or GELU', and fp32 with any of these: at most three times the time of the plain product
-    (they move up to five times its bytes and take 1.3 to 2.5 times as long; one element at a time it is 3.4 to 6.3 times)."""
-    m, n, k = 4096, 4096, 512
+def test_gemm_bf16_epilogues_do_not_wait_for_every_element(n, most, tile):
+    """A residual together with GELU or GELU', and fp32 with any of these, are vectors where the columns are a multiple of eight:
+    at most three times the plain product's time (they move up to five times its bytes and take 1.2 to 2.1 times as long, one
+    element at a time up to 6.3 times).  Ragged columns: what is read for several elements is waited for once (1.0 to 1.7 times
+    the plain product's time, with a wait for each element up to 2.8)."""
+    m, k = 4096, 512
     gen = torch.Generator(device=DEV).manual_seed(1)
     a, b, bias = _bf16(gen, m, k), _bf16(gen, n, k), _bf16(gen, n)
     us = {}
@@ -395,7 +399,7 @@ def test_gemm_bf16_epilogues_that_read_two_tensors_or_store_fp32_are_vectors_too
             torch.cuda.synchronize()
             times.append(at[0].elapsed_time(at[1]) * 100)
         us[epi] = min(times)
-    assert all(t <= 3 * us["plain"] for t in us.values()), us
+    assert all(t <= most * us["plain"] for t in us.values()), us
 
 
 @pytest.mark.parametrize("causal", [0, 1])

@@ -87,3 +87,21 @@ def lse_reference(qkv64, h, dh, causal=True):
         sc = np.where(np.tril(np.ones((s, s), dtype=bool)), sc, -np.inf)
     mx = sc.max(axis=-1, keepdims=True)
     return (mx + np.log(np.exp(sc - mx).sum(axis=-1, keepdims=True)))[..., 0].reshape(b * h, s)
+
+
+def stream_beside(side, busy):
+    """A stream whose work does not wait for what is queued on `side` (two streams can share a hardware queue); `busy` queues
+    some milliseconds of work there."""
+    x = torch.zeros(1, device=DEV)
+    for _ in range(16):
+        main = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        busy()
+        with torch.cuda.stream(main):
+            x.add_(1.0)
+        main.synchronize()
+        beside = not side.query()
+        torch.cuda.synchronize()
+        if beside:
+            return main
+    raise RuntimeError("no stream found that runs beside the other")

@@ -9,7 +9,7 @@ pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
     import paper_2503_02550_amd as S
-    from gpu_util import DEV, bf, f32, i32, up, q, assert_bf16_close, assert_f32_close, rel_err, lse_reference
+    from gpu_util import DEV, bf, f32, i32, up, q, assert_bf16_close, assert_f32_close, rel_err, lse_reference, stream_beside
 
 
 def rnd(seed, *shape, scale=1.0):
@@ -494,27 +494,34 @@ def test_tiles_fetched_into_lds_give_the_same_bits_beside_other_kernels():
     m, n, k = 2048, 2304, 768
     A, B = bf(rnd(53, m, k)), bf(rnd(54, n, k))
 
-    def run(stream):
+    side, big = torch.cuda.Stream(), torch.zeros(64 * 2 ** 20, device=DEV)
+
+    def copy(times):
+        with torch.cuda.stream(side):
+            for _ in range(times):
+                big.add_(1.0)                      # 256 MB read and written per pass, beside the kernels under test
+
+    main = stream_beside(side, lambda: copy(32))
+
+    def run(copies):
         o = torch.zeros((bsz, s, da), device=DEV, dtype=torch.bfloat16)
         lse, delta = torch.zeros((bsz * h, s), device=DEV), torch.zeros((bsz * h, s), device=DEV)
         dqkv = torch.zeros((bsz, s, 3 * da), device=DEV, dtype=torch.bfloat16)
         c = torch.zeros((m, n), device=DEV, dtype=torch.bfloat16)
         torch.cuda.synchronize()
-        S.sif_k_attn_fwd(Q, o, bsz, s, h, dh, 3 * da, da, 1, lse=lse, stream=stream)
-        S.sif_k_attn_bwd(Q, o, DO, lse, delta, dqkv, bsz, s, h, dh, 3 * da, da, 3 * da, 1, stream=stream)
-        S.sif_k_gemm_bf16(A, B, c, m, n, k, k, k, n, stream=stream)
-        return o, lse, dqkv, c
-
-    quiet = [t.cpu() for t in run(None)]
-    torch.cuda.synchronize()
-    side, main = torch.cuda.Stream(), torch.cuda.Stream()
-    big = torch.zeros(64 * 2 ** 20, device=DEV)
-    for rep in range(12):
-        with torch.cuda.stream(side):
-            for _ in range(4):
-                big.add_(1.0)                      # 256 MB read and written per pass, beside the kernels under test
-        got = run(main)
+        copy(copies)
+        S.sif_k_attn_fwd(Q, o, bsz, s, h, dh, 3 * da, da, 1, lse=lse, stream=main)
+        S.sif_k_attn_bwd(Q, o, DO, lse, delta, dqkv, bsz, s, h, dh, 3 * da, da, 3 * da, 1, stream=main)
+        S.sif_k_gemm_bf16(A, B, c, m, n, k, k, k, n, stream=main)
+        main.synchronize()
+        beside = not side.query()
         torch.cuda.synchronize()
+        return (o, lse, dqkv, c), beside
+
+    quiet = [t.cpu() for t in run(0)[0]]
+    for rep in range(12):
+        got, beside = run(32)
+        assert beside, "the copies were over before the kernels"
         for name, a, b in zip(("o", "lse", "dqkv", "c"), quiet, got):
             assert torch.equal(a, b.cpu()), f"{name} differs from the quiet run in repetition {rep}"
 

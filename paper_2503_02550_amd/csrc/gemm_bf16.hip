@@ -1305,15 +1305,12 @@ typedef void (*gemm_kern_fn)(GemmP, KCtl);
 #define OF_EPILOGUES(KERNEL, ...) {OF_LAYOUTS(KERNEL, kEpiCommon, __VA_ARGS__), OF_LAYOUTS(KERNEL, kEpiRare, __VA_ARGS__)}
 #define RING(...) OF_EPILOGUES(gemm_ring_kernel, __VA_ARGS__, )
 #define FED(...) OF_EPILOGUES(gemm_fed_kernel, __VA_ARGS__, )
-static const gemm_kern_fn kGemmKernels[kNTiles][2][2][2] = {      // [..][common or rare epilogue][layout of A][layout of B]
-    RING(32, 64, 1, 2, 4, 1, 2),   RING(64, 64, 2, 2, 4, 1, 2),   RING(128, 64, 2, 2, 3, 0, 2), RING(128, 128, 4, 2, 4, 1, 1),
-    RING(128, 128, 2, 2, 2, 0, 2), RING(256, 128, 4, 2, 3, 0, 1), OF_EPILOGUES(gemm_pp_kernel, )};
-// launches of at most one tile per CU, by their tiles: 32x64, 64x64, 128x64, and 32x32 instead of 32x64 where that is still one
-// tile per CU (a third less to fetch for each; 77 x 768 x 3072: 8.1 us, on 32x64 9.5)
-static const struct { gemm_kern_fn kern[2][2][2]; uint32_t threads; } kGemmFed[] = {
-    {FED(32, 64, 1, 2, 4, 6, 2), 384}, {FED(64, 64, 2, 2, 4, 8, 1), 512}, {FED(128, 64, 2, 2, 4, 6, 1), 512}, {FED(32, 32, 1, 1, 4, 6, 2), 320}};
-constexpr uint32_t kFed32x32 = 3;
-static const uint32_t kGemmThreads[kNTiles] = {128, 256, 256, 512, 256, 512, 512};
+// The kernels: one per configuration, and behind them those with wavefronts that only fetch.
+enum { kFed32x64 = kNTiles, kFed64x64, kFed128x64, kFed32x32, kNKernels };
+static const struct { gemm_kern_fn kern[2][2][2]; uint32_t threads; } kGemmKernels[kNKernels] = {      // [common or rare epilogue][layout of A][layout of B]
+    {RING(32, 64, 1, 2, 4, 1, 2), 128},    {RING(64, 64, 2, 2, 4, 1, 2), 256},    {RING(128, 64, 2, 2, 3, 0, 2), 256}, {RING(128, 128, 4, 2, 4, 1, 1), 512},
+    {RING(128, 128, 2, 2, 2, 0, 2), 256},  {RING(256, 128, 4, 2, 3, 0, 1), 512},  {OF_EPILOGUES(gemm_pp_kernel, ), 512},
+    {FED(32, 64, 1, 2, 4, 6, 2), 384},     {FED(64, 64, 2, 2, 4, 8, 1), 512},     {FED(128, 64, 2, 2, 4, 6, 1), 512},  {FED(32, 32, 1, 1, 4, 6, 2), 320}};
 #undef RING
 #undef FED
 #undef OF_LAYOUTS
@@ -1328,33 +1325,31 @@ static uint32_t gemm_cus() {
   return cus;
 }
 
-static sif_status launch_gemm_cfg(const sif_gemm_args* a, int want, hipStream_t stream, const KCtl& ctl) {
+// The kernel of a product on configuration cfg's tiles: where no CU gets more than one of the smaller tiles the one with
+// wavefronts that only fetch, and 32x32 tiles instead of 32x64 where that is still one per CU (a third less to fetch for each;
+// 77 x 768 x 3072: 8.1 us, on 32x64 9.5).
+static int gemm_kernel(const sif_gemm_args& a, int cfg) {
+  if (cfg > kT128x64 || gemm_tiles_of(a, cfg) > gemm_cus()) return cfg;
+  const uint64_t narrow = (uint64_t)((a.m + 31) / 32) * ((a.n + 31) / 32) * a.batch_outer * a.batch_inner;
+  return cfg == kT32x64 && narrow <= gemm_cus() ? (int)kFed32x32 : kFed32x64 + cfg;
+}
+int gemm_kernel_of(const sif_gemm_args& a) { return gemm_kernel(a, gemm_choose(a)); }
+
+sif_status launch_gemm_bf16(const sif_gemm_args* a, hipStream_t stream, const KCtl& ctl) {
   GemmP p;
-  int cfg = 0;
-  if (sif_status st = gemm_fill(a, p, want, &cfg)) return st;
+  int cfg = kAuto;
+  if (sif_status st = gemm_fill(a, p, kAuto, &cfg)) return st;
   const uint64_t batches = (uint64_t)a->batch_outer * a->batch_inner;
+  const int kernel = gemm_kernel(*a, cfg);
+  if (kernel == kFed32x32) p.tiles_n = (a->n + 31) / 32;
   // 256x256 tiles: one block per CU, each working through every (number of CUs)-th tile; a stride that is a multiple of
   // 8 keeps a block on the tiles of its own XCD
   uint32_t grid_x = p.tiles_m * p.tiles_n;
   if (cfg == kT256x256 && batches == 1) grid_x = std::min(grid_x, gemm_cus());
-  const bool rare = gemm_rare(a->epilogue, a->n, a->ldc);
-  gemm_kern_fn kern = kGemmKernels[cfg][rare][a->a_layout][a->b_layout];
-  uint32_t threads = kGemmThreads[cfg];
-  if (cfg <= kT128x64 && grid_x * batches <= gemm_cus()) {
-    uint32_t fed = (uint32_t)cfg;
-    const uint32_t narrow = (a->n + 31) / 32;
-    if (cfg == kT32x64 && (uint64_t)p.tiles_m * narrow * batches <= gemm_cus()) {
-      fed = kFed32x32;
-      p.tiles_n = narrow;
-      grid_x = p.tiles_m * narrow;
-    }
-    kern = kGemmFed[fed].kern[rare][a->a_layout][a->b_layout];
-    threads = kGemmFed[fed].threads;
-  }
-  hipLaunchKernelGGL(kern, dim3(grid_x, 1, (uint32_t)batches), dim3(threads), 0, stream, p, ctl);
+  const auto kern = kGemmKernels[kernel].kern[gemm_rare(a->epilogue, a->n, a->ldc)][a->a_layout][a->b_layout];
+  hipLaunchKernelGGL(kern, dim3(grid_x, 1, (uint32_t)batches), dim3(kGemmKernels[kernel].threads), 0, stream, p, ctl);
   return check_launch("gemm_bf16");
 }
-sif_status launch_gemm_bf16(const sif_gemm_args* a, hipStream_t stream, const KCtl& ctl) { return launch_gemm_cfg(a, kAuto, stream, ctl); }
 
 // Several products of the same operand layouts as ONE launch (the weight gradients of a layer: each by itself has too
 // few tiles for the chip and would have to be cut along K, with fp32 partial results written, read again and summed;
@@ -1440,7 +1435,7 @@ sif_status launch_gemm_bf16_group(const void* dev_records, uint32_t n, const Gem
   if (g.cfg == kT128x128x1) kern = GROUPED(gemm_ring_kernel, 128, 128, 4, 2, 4, 1, 1, );
   if (g.cfg == kT256x128) kern = GROUPED(gemm_ring_kernel, 256, 128, 4, 2, 3, 0, 1, );
 #undef GROUPED
-  hipLaunchKernelGGL(kern, dim3(g.cfg == kT256x256 ? std::min(g.tiles, gemm_cus()) : g.tiles), dim3(kGemmThreads[g.cfg]), 0, stream, head, ctl);
+  hipLaunchKernelGGL(kern, dim3(g.cfg == kT256x256 ? std::min(g.tiles, gemm_cus()) : g.tiles), dim3(kGemmKernels[g.cfg].threads), 0, stream, head, ctl);
   return check_launch("gemm_bf16_group");
 }
 

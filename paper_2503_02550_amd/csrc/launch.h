@@ -16,6 +16,7 @@ inline KCtl no_ctl() { KCtl c{}; return c; }
 
 // Internal launchers: same argument checks as the public sif_k_* entry points, plus the monitor control block.
 sif_status launch_gemm_bf16(const sif_gemm_args* a, hipStream_t s, const KCtl& c);
+int gemm_kernel_of(const sif_gemm_args& a);      // the kernel it launches, as an index of the table of kernels; so that tests know what they reach
 // several products of the same operand layouts as one launch: fill the kernel records on the host (gemm_group_bytes(n)
 // bytes), copy them to device memory once, launch with that copy
 struct GemmGroup { uint32_t tiles; int32_t cfg; uint32_t rare; };      // rare: has epilogues other than the common ones

@@ -12,7 +12,7 @@ if torch.cuda.is_available():
     import paper_2503_02550_amd as S
     from paper_2503_02550_amd import params as P
     from paper_2503_02550_amd.session import Session, mlp_shape
-    from gpu_util import DEV, f32, up, assert_f32_close
+    from gpu_util import DEV, f32, up, assert_f32_close, stream_beside
 
 
 def _bf16(gen, *shape):
@@ -107,8 +107,9 @@ def test_gemm_f32_tiles_and_remainders(m, n, k, k_contig_a, k_contig_b):
 @pytest.mark.parametrize("m,n,k", [(1, 8, 8), (31, 72, 64), (33, 64, 136), (64, 64, 256), (65, 200, 520), (300, 3080, 320), (1000, 768, 200),
                                    (1000, 2304, 456), (2008, 1536, 520), (4100, 768, 328), (2056, 2048, 1032), (8192, 776, 72), (4096, 3072, 512)])
 def test_gemm_bf16_picks_tiles_that_give_the_bits_of_the_128_ones(m, n, k, al, bl):
-    """Products of a few rows to ones that fill the chip: whichever tile the launcher takes (all but 128x64, which the test
-    below has, with long K), at ragged M, N and K, the result has the bits of the 128x128 tiles and is the product.  Bound:
+    """Products of a few rows to ones that fill the chip: whichever kernel the launcher takes (fetching 32x32 and 64x64, 128x128
+    with one and two per CU, 256x128, 256x256; the tests below have the others and name them), at ragged M, N and K, the
+    result has the bits of the 128x128 tiles and is the product.  Bound:
     one rounding to bf16 (2^-9 of the value) and the fp32 sum of k exact products ((k + 4) 2^-24 of their magnitudes)."""
     gen = torch.Generator(device=DEV).manual_seed(m + 3 * n + 5 * k + al + 2 * bl)
     mp, np_ = (m + 7) // 8 * 8, n
@@ -155,19 +156,29 @@ def test_bias_gradients_that_would_begin_another_round_follow_with_the_same_bits
         assert bool(((x.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + (k + 2) * 2.0 ** -24 * (b.double().abs().sum(0) + c0.double().abs())).all())
 
 
+# (rows, columns, K, kernel): K shorter than the kernel's ring (six steps of 128 with 32 rows, eight of 64 with 64x64, six of 64
+# with 128x64, which no shorter K gets), as long as it, whole turns of it and some steps more, ragged at the end of either
+# half of a step
+FETCHING = [(m, n, k, "fetching " + name) for name, sizes, ks in (
+    ("32x32", [(33, 72), (72, 2312)], (72, 128, 200, 640, 648, 704, 768, 1480, 1544)), ("32x64", [(848, 520), (77, 3072)], (72, 128, 200, 640, 648, 704, 768, 1480, 1544)),
+    ("64x64", [(280, 1992)], (72, 128, 448, 456, 512, 640, 648, 704, 1024, 1480)), ("128x64", [(580, 2440)], (328, 384, 392, 640, 648, 704, 768, 1480)))
+    for m, n in sizes for k in ks]
+OTHERS = ([(m, n, k, None) for m, n in ((33, 72), (72, 2312), (280, 1992), (848, 520)) for k in (8, 64)] + [(580, 2440, k, "32x64") for k in (8, 64, 72, 128)] +
+          [(1100, 3080, k, "128x64" if k < 200 else "128x128 one") for k in (8, 64, 72, 128, 640, 648, 704, 1480)])
+
+
 @pytest.mark.parametrize("al", [0, 1])
 @pytest.mark.parametrize("bl", [0, 1])
-@pytest.mark.parametrize("m,n", [(33, 72), (72, 2312), (280, 1992), (580, 2440), (1100, 3080)])
-@pytest.mark.parametrize("k", [8, 64, 72, 128, 640, 648, 704, 1480])
-def test_gemm_bf16_fed_tiles_give_the_bits_of_the_128_ones(m, n, k, al, bl):
-    """Tiles with wavefronts that only fetch (32x32, 32x64, 64x64, 128x64, as the launcher takes them, one per CU) and small
-    ones of which CUs get several: K shorter than the ring, as long as it, whole turns of it and some steps more, ragged at the
-    end of either half of a step."""
+@pytest.mark.parametrize("m,n,k,name", FETCHING + OTHERS)
+def test_gemm_bf16_fed_tiles_give_the_bits_of_the_128_ones(m, n, k, name, al, bl):
+    """Kernels with wavefronts that only fetch (FETCHING), and the ring beside them at the same sizes and short K."""
+    from tile_choice import kernel
     gen = torch.Generator(device=DEV).manual_seed(m + 3 * n + 5 * k + al + 2 * bl)
     a, b, bias = torch.zeros(((m + 7) // 8 * 8, k), device=DEV, dtype=torch.bfloat16), _bf16(gen, n, k), _bf16(gen, n)
     a[:m] = _bf16(gen, m, k)
     A, Bt = (a if al == 0 else a.t().contiguous()), (b if bl == 0 else b.t().contiguous())
     out = [torch.full((m, n), float("nan"), device=DEV, dtype=torch.bfloat16) for _ in range(2)]
+    assert name is None or kernel(S.gemm_args(A, Bt, out[0], m, n, k, A.shape[1], Bt.shape[1], n, a_layout=al, b_layout=bl)) == name
     torch.cuda.synchronize()
     for c, tile in zip(out, (0, 128)):
         S.sif_k_gemm_bf16(A, Bt, c, m, n, k, A.shape[1], Bt.shape[1], n, a_layout=al, b_layout=bl, epilogue=S.SIF_EPI_BIAS, bias=bias, tile=tile)
@@ -180,26 +191,67 @@ def test_gemm_bf16_fed_tiles_give_the_bits_of_the_128_ones(m, n, k, al, bl):
 
 @pytest.mark.parametrize("al", [0, 1])
 @pytest.mark.parametrize("bl", [0, 1])
-@pytest.mark.parametrize("m,n,k,tiles", [(72, 200, 1160, "32x64"), (600, 1544, 776, "64x64"), (600, 2440, 1160, "128x64"), (1032, 2440, 776, "128x128 one"),
-                                         (4104, 2440, 776, "128x128 two"), (2008, 2440, 1160, "256x128"), (4360, 4104, 64, None), (4360, 4104, 192, None)])
-def test_gemm_bf16_long_rings_and_more_tiles_than_blocks_give_the_bits_of_the_128_ones(m, n, k, tiles, al, bl):
+@pytest.mark.parametrize("m,n,k,name", [(72, 200, 1160, "fetching 32x32"), (600, 1544, 776, "fetching 64x64"), (600, 2440, 1160, "fetching 128x64"),
+                                        (400, 2440, 1160, "32x64"), (792, 2440, 1160, "64x64"), (1576, 2440, 1160, "128x64"), (1032, 2440, 776, "128x128 one"),
+                                        (4104, 2440, 776, "128x128 two"), (2008, 2440, 1160, "256x128"), (4360, 4104, 64, "256x256"), (4360, 4104, 192, "256x256")])
+def test_gemm_bf16_long_rings_and_more_tiles_than_blocks_give_the_bits_of_the_128_ones(m, n, k, name, al, bl):
     """Every ring over more K steps than its unrolled body has, with a ragged step behind them; and 256x256 tiles, of which
     256 blocks work through 306 (one and three K steps): the next tile's operands travel while the last one is stored."""
-    from tile_choice import takes
+    from tile_choice import kernel
     gen = torch.Generator(device=DEV).manual_seed(m + 3 * n + 5 * k + al + 2 * bl)
     a, b = _bf16(gen, m, k), _bf16(gen, n, k)
     A, Bt = (a if al == 0 else a.t().contiguous()), (b if bl == 0 else b.t().contiguous())
     out = [torch.full((m, n), float("nan"), device=DEV, dtype=torch.bfloat16) for _ in range(2)]
-    args = lambda c, tile: S.gemm_args(A, Bt, c, m, n, k, A.shape[1], Bt.shape[1], n, a_layout=al, b_layout=bl, tile=tile)
-    assert tiles is None or takes(args(out[0], 0), tiles)
+    chosen = 256 if name == "256x256" else 0
+    assert kernel(S.gemm_args(A, Bt, out[0], m, n, k, A.shape[1], Bt.shape[1], n, a_layout=al, b_layout=bl, tile=chosen)) == name
     torch.cuda.synchronize()
-    for c, tile in zip(out, (0 if tiles else 256, 128)):
+    for c, tile in zip(out, (chosen, 128)):
         S.sif_k_gemm_bf16(A, Bt, c, m, n, k, A.shape[1], Bt.shape[1], n, a_layout=al, b_layout=bl, tile=tile)
     torch.cuda.synchronize()
     assert torch.equal(out[0], out[1])
     ref = a.double() @ b.double().t()
     bound = 2.0 ** -8 * ref.abs() + (k + 4) * 2.0 ** -24 * (a.double().abs() @ b.double().abs().t())
     assert bool(((out[0].double() - ref).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("al,bl", [(0, 0), (0, 1), (1, 1)])
+def test_products_with_fetching_wavefronts_give_the_same_bits_beside_copies(al, bl):
+    """What a fetching wavefront has waited for is what the others read behind the barrier: many times beside copies on another
+    stream that keep the memory system busy, the bits of the quiet run."""
+    from tile_choice import kernel
+    gen = torch.Generator(device=DEV).manual_seed(5)
+    cases = []
+    for m, n, k, name in ((77, 768, 768, "fetching 32x32"), (512, 768, 3072, "fetching 32x64"), (600, 1544, 776, "fetching 64x64"), (600, 2440, 1160, "fetching 128x64")):
+        a, b = _bf16(gen, *((m, k) if al == 0 else (k, (m + 7) // 8 * 8))), _bf16(gen, *((n, k) if bl == 0 else (k, n)))
+        cases.append((a, b, m, n, k))
+        assert kernel(S.gemm_args(a, b, a, m, n, k, a.shape[1], b.shape[1], n, a_layout=al, b_layout=bl)) == name
+
+    side, big = torch.cuda.Stream(), torch.zeros(64 * 2 ** 20, device=DEV)
+
+    def copy(times):
+        with torch.cuda.stream(side):
+            for _ in range(times):
+                big.add_(1.0)                      # 256 MB read and written per pass, beside the kernels under test
+
+    main = stream_beside(side, lambda: copy(32))
+
+    def run(copies):
+        out = [[torch.full((m, n), float("nan"), device=DEV, dtype=torch.bfloat16) for _, _, m, n, _ in cases] for _ in range(5)]
+        torch.cuda.synchronize()
+        copy(copies)
+        for turn in out:
+            for c, (a, b, m, n, k) in zip(turn, cases):
+                S.sif_k_gemm_bf16(a, b, c, m, n, k, a.shape[1], b.shape[1], n, a_layout=al, b_layout=bl, stream=main)
+        main.synchronize()
+        beside = not side.query()
+        torch.cuda.synchronize()
+        return out, beside
+
+    quiet, _ = run(0)
+    for _ in range(6):
+        got, beside = run(32)
+        assert beside                          # copies were still to come when the last product was done
+        assert all(torch.equal(x, y) for turn in got for x, y in zip(quiet[0], turn))
 
 
 @pytest.mark.parametrize("shapes,k,tiles", [([(512, 128), (128, 512), (1, 512)], 1032, "128x128 one"), ([(1032, 776), (776, 3080), (1, 3080)], 1160, "256x128"),
@@ -307,17 +359,22 @@ def _epilogue(name, acc, bias, res, z):
     return flags, biased, "residual" in words, grad or "aux" in words, x, pre
 
 
-@pytest.mark.parametrize("m,n,far", [(1, 8, False), (33, 200, False), (129, 136, False), (257, 328, False), (33, 200, True),
-                                     (33, 77, False), (257, 333, False), (33, 77, True)])
+@pytest.mark.parametrize("m,n,far,k,tile,name",
+                         [(m, n, far, 64, tile, None) for m, n, far in ((1, 8, False), (33, 200, False), (129, 136, False), (257, 328, False), (33, 200, True),
+                                                                        (33, 77, False), (257, 333, False), (33, 77, True)) for tile in (0, 128, 256)] +
+                         [(m, n + more, False, k, 0, name) for m, n, k, name in ((33, 200, 136, "fetching 32x32"), (847, 520, 136, "fetching 32x64"), (281, 1992, 136, "fetching 64x64"),
+                                                                                 (581, 2440, 392, "fetching 128x64"), (401, 2440, 136, "32x64"), (793, 2440, 136, "64x64"),
+                                                                                 (1577, 2440, 136, "128x64"), (1033, 2440, 776, "128x128 one"), (4105, 2440, 136, "128x128 two"),
+                                                                                 (2009, 2440, 1160, "256x128")) for more in (0, -3)])
 @pytest.mark.parametrize("epi", EPILOGUES)
-@pytest.mark.parametrize("tile", [0, 128, 256])
-def test_gemm_bf16_epilogues_write_their_rows_and_columns_only(m, n, far, epi, tile):
+def test_gemm_bf16_epilogues_write_their_rows_and_columns_only(m, n, far, k, tile, name, epi):
     """Rows further apart than their columns (by 24 elements, and by more than 2 M), the last rows and columns of a tile
     missing: what lies between the rows and behind the last one keeps its value, in the result and in the auxiliary tensor, and
     what lies there in the tensors that are read (NaN) reaches no result.  Bound: one rounding to bf16 of the result, and of
     fp32 sums that GELU' or GELU scales."""
+    from tile_choice import kernel
     gen = torch.Generator(device=DEV).manual_seed(m + n)
-    k, ld, below = 64, (1 << 21) + 8 if far else n + 24, 2 if far else 256
+    ld, below = (1 << 21) + 8 if far else n + 24, 2 if far else 256
     a, b, bias, res, z = _bf16(gen, m, k), _bf16(gen, n, k), _bf16(gen, n), _bf16(gen, m, n), _bf16(gen, m, n)
     flags, biased, residual, has_aux, ref, pre = _epilogue(epi, a.double() @ b.double().t(), bias.double(), res.double(), z.double())
     dtype = torch.float32 if "f32" in epi else torch.bfloat16
@@ -328,6 +385,7 @@ def test_gemm_bf16_epilogues_write_their_rows_and_columns_only(m, n, far, epi, t
     if residual:
         other = torch.full((m + below, ld), float("nan"), device=DEV, dtype=dtype)
         other[:m, :n] = res
+    assert name is None or kernel(S.gemm_args(a, b, c, m, n, k, k, k, ld)) == name
     torch.cuda.synchronize()
     S.sif_k_gemm_bf16(a, b, c, m, n, k, k, k, ld, epilogue=flags, bias=bias if biased else None, res=other, aux=aux, tile=tile)
     torch.cuda.synchronize()

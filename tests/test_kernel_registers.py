@@ -46,7 +46,7 @@ def _kernels():
     return {k[".name"]: k for elf in _code_objects() for notes in _notes(elf) for k in notes["amdhsa.kernels"]}
 
 
-@pytest.mark.parametrize("kernel", ["gemm_ring_kernel", "gemm_pp_kernel"])
+@pytest.mark.parametrize("kernel", ["gemm_ring_kernel", "gemm_fed_kernel", "gemm_pp_kernel"])
 def test_product_kernels_leave_room_for_the_bubbles_wait(kernel):
     """Two of their wavefronts on a SIMD and the one that waits for the bubble's end share its 512 registers, so a block of
     any product runs on the CU that holds that wait; and none is kept in scratch memory (a reload inside the main loop waits

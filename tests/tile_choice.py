@@ -4,18 +4,17 @@ import ctypes as C
 
 import paper_2503_02550_amd as S
 
-# rows, columns, blocks of a CU at a time; the library's order
-TILES = {"32x64": (32, 64, 3), "64x64": (64, 64, 2), "128x64": (128, 64, 2), "128x128 one": (128, 128, 1), "128x128 two": (128, 128, 2),
-         "256x128": (256, 128, 1), "256x256": (256, 256, 1)}
+# the library's order
+TILES = ["32x64", "64x64", "128x64", "128x128 one", "128x128 two", "256x128", "256x256"]
+KERNELS = TILES + ["fetching 32x64", "fetching 64x64", "fetching 128x64", "fetching 32x32"]
 
 
-def takes(a, name):
-    """Whether the rows that the library counts for a round of the product's tiles are those of the named tiles and of no
-    others."""
-    rows = getattr(S.lib, "_ZN3sif15gemm_round_rowsERK13sif_gemm_args")
-    rows.restype, rows.argtypes = C.c_uint32, [C.POINTER(S.sif_gemm_args)]
-    got = rows(a)
-    return [t for t, (bm, bn, slots) in TILES.items() if got == bm * max(1, 256 * slots // ((a.n + bn - 1) // bn))] == [name]
+def kernel(a):
+    """The kernel that the launcher takes for a product: the ring or ping-pong kernel of its tiles, or the one with wavefronts
+    that only fetch."""
+    f = getattr(S.lib, "_ZN3sif14gemm_kernel_ofERK13sif_gemm_args")
+    f.restype, f.argtypes = C.c_int, [C.POINTER(S.sif_gemm_args)]
+    return KERNELS[f(a)]
 
 
 def group(products):
@@ -24,7 +23,7 @@ def group(products):
     fill.restype, fill.argtypes = C.c_int, [C.c_void_p, C.c_uint32, C.c_void_p, C.c_void_p]
     n, got = len(products), (C.c_uint32 * 3)()
     assert fill((S.sif_gemm_args * n)(*products), n, (C.c_char * S.sif_k_gemm_bf16_group_bytes(n))(), got) == 0
-    return got[0], list(TILES)[got[1]]
+    return got[0], TILES[got[1]]
 
 
 def part(products, first):

@@ -1327,9 +1327,12 @@ static uint32_t gemm_cus() {
 
 // The kernel of a product on configuration cfg's tiles: where no CU gets more than one of the smaller tiles the one with
 // wavefronts that only fetch, and 32x32 tiles instead of 32x64 where that is still one per CU (a third less to fetch for each;
-// 77 x 768 x 3072: 8.1 us, on 32x64 9.5).
+// 77 x 768 x 3072: 8.1 us, on 32x64 9.5).A single K step has no fetches to keep in flight, and the ring's smaller blocks start
+// sooner: with K 8 and 64 twelve shapes from 32 x 768 to 1024 x 1024 take 3.3 to 3.9 us on it, 3.4 to 4.2 on the others.  (From
+// K 128 to 1024 the others take 0.63 to 0.98 of the ring's time with weights from memory, with operands that stay in the L2 0.93
+// to 1.01, but 64x64 tiles from K 512 on 1.03 to 1.07.)
 static int gemm_kernel(const sif_gemm_args& a, int cfg) {
-  if (cfg > kT128x64 || gemm_tiles_of(a, cfg) > gemm_cus()) return cfg;
+  if (cfg > kT128x64 || a.k <= BK || gemm_tiles_of(a, cfg) > gemm_cus()) return cfg;
   const uint64_t narrow = (uint64_t)((a.m + 31) / 32) * ((a.n + 31) / 32) * a.batch_outer * a.batch_inner;
   return cfg == kT32x64 && narrow <= gemm_cus() ? (int)kFed32x32 : kFed32x64 + cfg;
 }

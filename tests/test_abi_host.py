@@ -250,3 +250,12 @@ def test_group_of_a_small_layer_is_not_put_on_tall_tiles(d, f, tokens):
     tiles, name = group([S.gemm_args(1 << 20, 1 << 20, 1 << 20, m, n, tokens, (m + 7) // 8 * 8, n, n, **lay) for m, n in shapes])
     up = lambda v, by: (v + by - 1) // by
     assert name == "128x128 one" and tiles == sum(up(up(m, 128) * up(n, 128), 8) * 8 for m, n in shapes)
+
+
+@pytest.mark.parametrize("m,n,ring,fetching", [(32, 768, "32x64", "32x32"), (77, 3072, "32x64", "32x64"), (1000, 768, "64x64", "64x64"), (1024, 1024, "64x64", "64x64")])
+def test_products_of_one_k_step_run_on_the_ring(m, n, ring, fetching):
+    """Wavefronts that only fetch have nothing to keep in flight for a single K step, and their larger blocks start later."""
+    from tile_choice import kernel
+    args = lambda k: S.gemm_args(1 << 20, 1 << 20, 1 << 20, m, n, k, 128, 128, n)
+    assert [kernel(args(k)) for k in (8, 64)] == [ring] * 2
+    assert [kernel(args(k)) for k in (72, 128)] == ["fetching " + fetching] * 2

@@ -107,8 +107,8 @@ def test_gemm_f32_tiles_and_remainders(m, n, k, k_contig_a, k_contig_b):
 @pytest.mark.parametrize("m,n,k", [(1, 8, 8), (31, 72, 64), (33, 64, 136), (64, 64, 256), (65, 200, 520), (300, 3080, 320), (1000, 768, 200),
                                    (1000, 2304, 456), (2008, 1536, 520), (4100, 768, 328), (2056, 2048, 1032), (8192, 776, 72), (4096, 3072, 512)])
 def test_gemm_bf16_picks_tiles_that_give_the_bits_of_the_128_ones(m, n, k, al, bl):
-    """Products of a few rows to ones that fill the chip: whichever kernel the launcher takes (fetching 32x32 and 64x64, 128x128
-    with one and two per CU, 256x128, 256x256; the tests below have the others and name them), at ragged M, N and K, the
+    """Products of a few rows to ones that fill the chip: whichever kernel the launcher takes (32x64 with one K step, fetching
+    32x32 and 64x64, 128x128 with one and two per CU, 256x128, 256x256; the tests below have the others and name them), at ragged M, N and K, the
     result has the bits of the 128x128 tiles and is the product.  Bound:
     one rounding to bf16 (2^-9 of the value) and the fp32 sum of k exact products ((k + 4) 2^-24 of their magnitudes)."""
     gen = torch.Generator(device=DEV).manual_seed(m + 3 * n + 5 * k + al + 2 * bl)
@@ -163,7 +163,7 @@ FETCHING = [(m, n, k, "fetching " + name) for name, sizes, ks in (
     ("32x32", [(33, 72), (72, 2312)], (72, 128, 200, 640, 648, 704, 768, 1480, 1544)), ("32x64", [(848, 520), (77, 3072)], (72, 128, 200, 640, 648, 704, 768, 1480, 1544)),
     ("64x64", [(280, 1992)], (72, 128, 448, 456, 512, 640, 648, 704, 1024, 1480)), ("128x64", [(580, 2440)], (328, 384, 392, 640, 648, 704, 768, 1480)))
     for m, n in sizes for k in ks]
-OTHERS = ([(m, n, k, None) for m, n in ((33, 72), (72, 2312), (280, 1992), (848, 520)) for k in (8, 64)] + [(580, 2440, k, "32x64") for k in (8, 64, 72, 128)] +
+OTHERS = ([(m, n, k, name) for m, n, name in ((33, 72, "32x64"), (72, 2312, "32x64"), (280, 1992, "64x64"), (848, 520, "32x64")) for k in (8, 64)] + [(580, 2440, k, "32x64") for k in (8, 64, 72, 128)] +
           [(1100, 3080, k, "128x64" if k < 200 else "128x128 one") for k in (8, 64, 72, 128, 640, 648, 704, 1480)])
 
 
@@ -212,6 +212,52 @@ def test_gemm_bf16_long_rings_and_more_tiles_than_blocks_give_the_bits_of_the_12
     ref = a.double() @ b.double().t()
     bound = 2.0 ** -8 * ref.abs() + (k + 4) * 2.0 ** -24 * (a.double().abs() @ b.double().abs().t())
     assert bool(((out[0].double() - ref).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("what,s,batch,dh,name", [("scores", 200, 6, 136, "fetching 32x64"), ("scores", 264, 6, 128, "fetching 64x64"), ("pv", 200, 6, 136, "fetching 32x32"),
+                                                  ("pv", 776, 3, 136, "fetching 32x64"), ("pv", 776, 4, 136, "fetching 64x64"), ("pv", 776, 8, 136, "fetching 128x64"),
+                                                  ("ptdo", 200, 6, 136, "fetching 32x32"), ("ptdo", 776, 3, 136, "fetching 32x64"), ("ptdo", 776, 4, 136, "fetching 64x64"),
+                                                  ("ptdo", 776, 8, 136, "fetching 128x64"), ("slices", 520, 5, 200, "fetching 64x64"), ("slices", 200, 4, 192, "fetching 32x32")])
+def test_batched_causal_and_sliced_products_on_fetching_kernels_give_the_bits_of_the_128_ones(what, s, batch, dh, name):
+    """Causal scores (tiles above the diagonal are not written), products that stop at or begin with the diagonal, so that
+    their first or last tiles have fewer K steps than the ring, and slices of one long K with a shorter, ragged last one.
+    Bits of the 128x128 tiles, and the product: fp32 sums of at most s terms, one rounding where it is stored as bf16."""
+    from tile_choice import kernel
+    gen = torch.Generator(device=DEV).manual_seed(s + batch)
+    p = torch.tril(_bf16(gen, batch, s, s))
+    x, y = _bf16(gen, batch, s, dh), _bf16(gen, batch, s, dh)
+    if what == "scores":
+        m, n, k, a, b, ref, dtype = s, s, dh, x, y, x.double() @ y.double().transpose(1, 2).contiguous(), torch.float32
+        kw = dict(epilogue=S.SIF_EPI_OUT_F32 | S.SIF_EPI_CAUSAL_SKIP, a_strides=(0, s * dh), b_strides=(0, s * dh), c_strides=(0, s * s))
+        lda, ldb = dh, dh
+    elif what == "slices":
+        m, n, k, total, dtype = s, 264, dh, dh * (batch - 1) + 77, torch.float32
+        lda = ldb = (total + 7) // 8 * 8
+        a, b = _bf16(gen, m, lda), _bf16(gen, n, lda)
+        a[:, total:] = 0
+        cut = [slice(i * dh, min(total, (i + 1) * dh)) for i in range(batch)]
+        ref = torch.stack([a[:, c].double() @ b[:, c].double().t() for c in cut])
+        kw = dict(epilogue=S.SIF_EPI_OUT_F32, a_strides=(0, dh), b_strides=(0, dh), c_strides=(0, m * n), k_limit=total)
+    else:
+        m, n, k, a, b, dtype, lda, ldb = s, dh, s, p, x, torch.bfloat16, s, dh
+        left = p.double() if what == "pv" else p.double().transpose(1, 2).contiguous()
+        ref = left @ x.double()
+        kw = dict(a_layout=S.SIF_A_ROW_K if what == "pv" else S.SIF_A_ROW_M, b_layout=S.SIF_B_ROW_N, k_causal=1 if what == "pv" else 2,
+                  a_strides=(0, s * s), b_strides=(0, s * dh), c_strides=(0, s * dh))
+    out = [torch.full((batch, m, n), 9.0, device=DEV, dtype=dtype) for _ in range(2)]
+    assert kernel(S.gemm_args(a, b, out[0], m, n, k, lda, ldb, n, batch_inner=batch, **kw)) == name
+    torch.cuda.synchronize()
+    for c, tile in zip(out, (0, 128)):
+        S.sif_k_gemm_bf16(a, b, c, m, n, k, lda, ldb, n, batch_inner=batch, tile=tile, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], out[1])
+    got = out[0].double()
+    if what == "scores":
+        at = torch.arange(s, device=DEV) // 128
+        above = at[None, :] > at[:, None]
+        assert bool((got[:, above] == 9.0).all())
+        got, ref = got[:, ~above], ref[:, ~above]
+    assert float((got - ref).norm() / ref.norm()) <= (2.0 ** -8 if dtype == torch.bfloat16 else 1e-5)
 
 
 @pytest.mark.parametrize("al,bl", [(0, 0), (0, 1), (1, 1)])

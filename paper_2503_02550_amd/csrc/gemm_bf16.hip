@@ -1327,7 +1327,7 @@ static uint32_t gemm_cus() {
 
 // The kernel of a product on configuration cfg's tiles: where no CU gets more than one of the smaller tiles the one with
 // wavefronts that only fetch, and 32x32 tiles instead of 32x64 where that is still one per CU (a third less to fetch for each;
-// 77 x 768 x 3072: 8.1 us, on 32x64 9.5).A single K step has no fetches to keep in flight, and the ring's smaller blocks start
+// 77 x 768 x 3072: 8.1 us, on 32x64 9.5).  A single K step has no fetches to keep in flight, and the ring's smaller blocks start
 // sooner: with K 8 and 64 twelve shapes from 32 x 768 to 1024 x 1024 take 3.3 to 3.9 us on it, 3.4 to 4.2 on the others.  (From
 // K 128 to 1024 the others take 0.63 to 0.98 of the ring's time with weights from memory, with operands that stay in the L2 0.93
 // to 1.01, but 64x64 tiles from K 512 on 1.03 to 1.07.)
@@ -1364,6 +1364,12 @@ uint64_t gemm_group_bytes(uint32_t n) { return (uint64_t)n * sizeof(GemmP); }
 // tiles of 128x128 at 128 x 512) are a chain of K steps on few CUs: 128x128 with four steps in the ring of a CU's only
 // block, as long as that is one round (2048 tokens of 128 x 512: 16 us, with two steps in the ring 20, on 256x128 27;
 // two rounds, 8192 tokens of 768 x 3072: 131 us, where two blocks of a CU hide each other's ends 125).
+//   Every product begins at a multiple of eight blocks, so the first XCD gets an eighth of each product's tiles, rounded up, and
+// with one tile per CU that is what makes a round (256x256 too: a block asks for its next tile when it begins one, so an XCD's
+// 33rd is taken there).  (85 + 85 + 20 + 60 tiles of 128x128 are 250, but 33 on each of four XCDs, whose 32 CUs begin a second
+// round: steps of four layers of 520 x 2056 on 8192 tokens 2.91 ms, on 256x128 2.65; 704 x 2816 on 8192 3.24 -> 3.05, 856 x 7176 on
+// 8192 5.88 -> 5.49.  Over 48 layers and token counts at such borders a step takes 0.98 of the time, at most 1.02.  With
+// two tiles per CU these hide it: counted so for them, nine of 110 launches got slower by up to 11 %.)
 static int gemm_group_choose(const sif_gemm_args* list, uint32_t n, double* us_out) {
   int cfg = -1;
   double best = 0.0;
@@ -1372,7 +1378,8 @@ static int gemm_group_choose(const sif_gemm_args* list, uint32_t n, double* us_o
     double steps = 0.0;
     bool ok = true;
     for (uint32_t i = 0; i < n; ++i) {
-      tiles += gemm_tiles_of(list[i], c);
+      const uint64_t own = gemm_tiles_of(list[i], c);
+      tiles += kGemmTiles[c].slots == 1 ? (own + 7) / 8 * 8 : own;
       steps = std::max(steps, gemm_steps_of(list[i]));
       ok = ok && gemm_tiles_fit(list[i], c);
     }

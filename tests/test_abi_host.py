@@ -259,3 +259,15 @@ def test_products_of_one_k_step_run_on_the_ring(m, n, ring, fetching):
     args = lambda k: S.gemm_args(1 << 20, 1 << 20, 1 << 20, m, n, k, 128, 128, n)
     assert [kernel(args(k)) for k in (8, 64)] == [ring] * 2
     assert [kernel(args(k)) for k in (72, 128)] == ["fetching " + fetching] * 2
+
+
+@pytest.mark.parametrize("tokens", [4096, 8192, 8200])
+def test_group_counts_the_tiles_of_the_fullest_xcd(tokens):
+    """85 + 85 + 20 + 60 tiles of 128x128 are fewer than the chip has CUs, but every product begins at the first XCD, which gets 11
+    + 11 + 3 + 8 of them for its 32 CUs: no single round.  The one-row products stay in the launch, which is one on taller tiles."""
+    from tile_choice import group, part
+    lay = dict(a_layout=S.SIF_A_ROW_M, b_layout=S.SIF_B_ROW_N)
+    d, da, f = 520, 512, 2056
+    list_ = [S.gemm_args(1 << 20, 1 << 20, 1 << 20, m, n, tokens, (m + 7) // 8 * 8, n, n, **lay) for m, n in ((d, f), (f, d), (d, da), (3 * da, d), (1, f), (1, 3 * da))]
+    assert group(list_[:4])[1] != "128x128 one"
+    assert part(list_, 4) == 6 and group(list_)[1] == "256x128"

@@ -271,3 +271,14 @@ def test_group_counts_the_tiles_of_the_fullest_xcd(tokens):
     list_ = [S.gemm_args(1 << 20, 1 << 20, 1 << 20, m, n, tokens, (m + 7) // 8 * 8, n, n, **lay) for m, n in ((d, f), (f, d), (d, da), (3 * da, d), (1, f), (1, 3 * da))]
     assert group(list_[:4])[1] != "128x128 one"
     assert part(list_, 4) == 6 and group(list_)[1] == "256x128"
+
+
+@pytest.mark.parametrize("d,da,f,tokens,apart", [(2048, 2048, 8192, 4096, True), (1984, 1984, 7936, 2048, True), (1920, 1920, 7680, 1024, True), (2048, 2048, 8192, 256, False),
+                                                 (1984, 1984, 7936, 512, False), (816, 1408, 5520, 8192, False), (776, 1280, 5360, 4096, False), (488, 1408, 4288, 2048, False)])
+def test_one_row_products_leave_a_group_only_for_more_than_the_models_error(d, da, f, tokens, apart):
+    """Layers where the one-row products as launches of their own were measured to be faster, and ones where the model sees a
+    small gain and they were measured to be slower."""
+    from tile_choice import part
+    lay = dict(a_layout=S.SIF_A_ROW_M, b_layout=S.SIF_B_ROW_N)
+    list_ = [S.gemm_args(1 << 20, 1 << 20, 1 << 20, m, n, tokens, (m + 7) // 8 * 8, n, n, **lay) for m, n in ((d, f), (f, d), (d, da), (3 * da, d), (1, f), (1, 3 * da))]
+    assert part(list_, 4) == (4 if apart else 6)

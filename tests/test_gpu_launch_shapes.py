@@ -127,7 +127,7 @@ def test_gemm_bf16_picks_tiles_that_give_the_bits_of_the_128_ones(m, n, k, al, b
     assert bool(((out[0].double() - ref).abs() <= bound).all())
 
 
-@pytest.mark.parametrize("d,da,f,k,apart", [(1920, 1920, 7680, 1024, True), (1744, 192, 3976, 8200, True), (520, 512, 2056, 8200, False), (768, 768, 3072, 1000, False)])
+@pytest.mark.parametrize("d,da,f,k,apart", [(1920, 1920, 7680, 1024, True), (1744, 192, 3976, 8200, True), (2048, 2048, 8192, 256, False), (520, 512, 2056, 8200, False), (768, 768, 3072, 1000, False)])
 @pytest.mark.parametrize("acc", [0, 1])
 def test_bias_gradients_that_would_begin_another_round_follow_with_the_same_bits(d, da, f, k, apart, acc):
     """The one-row products of a layer's group, in it and as launches of their own, onto a stored gradient too; sizes on both

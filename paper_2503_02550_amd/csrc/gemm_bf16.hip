@@ -235,7 +235,7 @@ __device__ __forceinline__ void lanes_in_order() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// Variants that read nothing but the bias (plain, bias, bias + GELU without the pre-activation output) are finished in the
+// bf16 variants that read nothing but the bias (plain, bias, bias + GELU without the pre-activation output) are finished in the
 // accumulator layout, where a lane's column is fixed, and staged as bf16: two vertically adjacent results share a 32-bit
 // word, the staging area is [row pairs][W] words, half the LDS traffic of the fp32 staging below.  A lane then reads eight
 // words = eight columns of two rows, separates the rows with byte permutes and stores two 16-byte row vectors.  (Row pairs
@@ -382,6 +382,50 @@ __device__ __forceinline__ void gemm_store_rows(const GemmP& p, floatx16 (&acc)[
   finish(TI * PASSES - 1);
 }
 
+// fp32 results, four columns per lane, so that one store writes rows of the wavefront's part whole.  (4096 x 4096 x 512 on 256x256
+// tiles 26 us, with eight columns per lane in two stores 30.)
+template <int TI, int TJ, int SR>
+__device__ __forceinline__ void gemm_store_f32(const GemmP& p, floatx16 (&acc)[TI][TJ], float* sW, uint32_t mw, uint32_t nw, size_t c_off, uint32_t lane,
+                                               const bf16_t* bias_s) {
+  constexpr int W = TJ * 32, CPR = W / 4, PASSES = 32 / SR, ITS = SR * CPR / 64;
+  const uint32_t hh = lane >> 5, c4 = lane % CPR, n = nw + c4 * 4, pitch = p.ldc * 4;
+  const auto c = result_rsrc(reinterpret_cast<float*>(p.c) + c_off + (size_t)mw * p.ldc + nw, mw < p.m ? (uint64_t)(p.m - mw) * pitch : 0);
+  const uint32_t off = n < p.n ? lane / CPR * pitch + c4 * 16 : kOutside;
+  const uint2 bq = p.bias != nullptr ? *reinterpret_cast<const uint2*>(bias_s + c4 * 4) : make_uint2(0, 0);
+  const float bias[4] = {bflo(bq.x), bfhi(bq.x), bflo(bq.y), bfhi(bq.y)};
+  auto key = [](uint32_t row) { return (((row >> 2) & 1u) * (W / 8)) | (row & 1u); };
+  float4 s[2][ITS];
+  auto finish = [&](int pass) {
+#pragma unroll
+    for (int it = 0; it < ITS; ++it) {
+      const float4 q = s[pass & 1][it];
+      write16(c, off + (uint32_t)(pass * SR + it * (64 / CPR)) * pitch, make_uint4(__float_as_uint(q.x * p.alpha + bias[0]), __float_as_uint(q.y * p.alpha + bias[1]),
+                                                                                    __float_as_uint(q.z * p.alpha + bias[2]), __float_as_uint(q.w * p.alpha + bias[3])), false);
+    }
+  };
+#pragma unroll
+  for (int pass = 0; pass < TI * PASSES; ++pass) {
+    const int i = pass / PASSES, ps = pass % PASSES;
+#pragma unroll
+    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+      for (int e = ps * (SR / 2); e < (ps + 1) * (SR / 2); ++e) {
+        const uint32_t row = (e >> 2) * 8 + hh * 4 + (e & 3) - ps * SR, col = j * 32 + (lane & 31);
+        sW[row * W + ((((col >> 2) ^ key(row)) << 2) | (col & 3))] = acc[i][j][e];
+      }
+    lanes_in_order();
+#pragma unroll
+    for (int it = 0; it < ITS; ++it) {
+      const uint32_t row = (lane + it * 64) / CPR;
+      s[pass & 1][it] = *reinterpret_cast<const float4*>(sW + row * W + ((c4 ^ key(row)) << 2));
+    }
+    lanes_in_order();
+    if (pass > 0) finish(pass - 1);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  finish(TI * PASSES - 1);
+}
+
 // bf16 results of the other combinations - a residual together with GELU or GELU' - and of rows further apart than the offsets
 // above reach: vectors too, but 64-bit addresses and decisions while it runs.  The first tensor that is read is requested 32
 // rows ahead (64 where a pass has 32), the residual beside an auxiliary tensor with its pass.  (One element at a time 4096 x
@@ -466,13 +510,12 @@ __device__ __forceinline__ void gemm_store_mixed(const GemmP& p, floatx16 (&acc)
   }
 }
 
-// fp32 results: four columns per lane, so that one store writes rows of the wavefront's part whole.  The residual is read with
-// its pass: requested ahead it only lies in front of the stores and is waited for longer (47 us instead of 43 at the size below).
-// The auxiliary tensor is requested ahead as above.  (4096 x 4096 x 512 on 256x256 tiles 27.1 us, 30.8 with eight columns per
-// lane in two stores; with a residual 43, with GELU' 44, with both GELU and a residual 50, one element at a time 98, 101, 134.)
+// fp32 results with anything else.  The residual is read with its pass: requested ahead it only lies in front of the stores and is
+// waited for longer (47 us instead of 43 at the size below).  The auxiliary tensor is requested ahead as above.  (4096 x 4096 x 512
+// on 256x256 tiles with a residual 43 us, with GELU' 44, with both GELU and a residual 50, one element at a time 98, 101, 134.)
 template <int TI, int TJ, int SR>
-__device__ __forceinline__ void gemm_store_f32(const GemmP& p, floatx16 (&acc)[TI][TJ], float* sW, uint32_t mw, uint32_t nw, size_t c_off, uint32_t lane,
-                                               const bf16_t* bias_s) {
+__device__ __forceinline__ void gemm_store_f32_mixed(const GemmP& p, floatx16 (&acc)[TI][TJ], float* sW, uint32_t mw, uint32_t nw, size_t c_off, uint32_t lane,
+                                                     const bf16_t* bias_s) {
   constexpr int W = TJ * 32, CPR = W / 4, PASSES = 32 / SR, ITS = SR * CPR / 64, AHEAD = TI < 2 || SR < 32 ? 1 : 2;
   const uint32_t hh = lane >> 5, c4 = lane % CPR, n = nw + c4 * 4;       // (64 is a multiple of CPR: a lane keeps its columns)
   const bool grad = (p.epi & SIF_EPI_GELU_GRAD) != 0, gelu = (p.epi & SIF_EPI_GELU) != 0, residual = (p.epi & SIF_EPI_RESIDUAL) != 0;
@@ -612,13 +655,14 @@ __device__ __forceinline__ void gemm_store_single(const GemmP& p, floatx16 (&acc
   }
 }
 
-// An epilogue that is not one of the common ones: ragged columns, fp32, two of GELU, GELU' and a residual, rows so far apart that
+// An epilogue that is not one of the common ones: ragged columns, two of GELU, GELU', a residual and fp32, rows so far apart that
 // 32-bit offsets do not reach over the 128 of a wavefront.  They have kernels of their own.  (With all variants in one kernel the
 // main loops beside the common ones came out slower: six layers of d 2048 16.6 -> 17.4 ms a step, a batch of 4096 tokens through
-// twelve of d 768 1.55 -> 1.62.)  A launch over several products that has both takes one with all of them.
+// twelve of d 768 1.55 -> 1.62.  Plain fp32 among the rare ones, decided element by element, made 8192 x 768 x 50304 in eight slices
+// of K 6 % slower.)  A launch over several products that has both takes one with all of them.
 __host__ __device__ __forceinline__ bool gemm_rare(uint32_t epilogue, uint32_t n, uint32_t ldc) {
   const uint32_t what = epilogue & (SIF_EPI_GELU | SIF_EPI_GELU_GRAD | SIF_EPI_RESIDUAL | SIF_EPI_OUT_F32);
-  return (n & 7) != 0 || ldc > (1u << 21) || (what & SIF_EPI_OUT_F32) || (what & (what - 1)) != 0;
+  return (n & 7) != 0 || ldc > (1u << 21) || (what & (what - 1)) != 0;
 }
 enum { kEpiCommon, kEpiRare, kEpiAll };
 // bias_s: the bias of the columns nw.. in LDS (gemm_fetch_bias)
@@ -628,7 +672,7 @@ __device__ __forceinline__ void gemm_store_tile(const GemmP& p, floatx16 (&acc)[
   if constexpr (EPI != kEpiCommon) {
     if (EPI == kEpiRare || gemm_rare(p.epi, p.n, p.ldc)) {
       if ((p.n & 7) != 0) gemm_store_single<TI, TJ, SR>(p, acc, sW, mw, nw, c_off, lane);
-      else if (p.epi & SIF_EPI_OUT_F32) gemm_store_f32<TI, TJ, SR>(p, acc, sW, mw, nw, c_off, lane, bias_s);
+      else if (p.epi & SIF_EPI_OUT_F32) gemm_store_f32_mixed<TI, TJ, SR>(p, acc, sW, mw, nw, c_off, lane, bias_s);
       else gemm_store_mixed<TI, TJ, SR>(p, acc, sW, mw, nw, c_off, lane, bias_s);
       return;
     }
@@ -636,6 +680,7 @@ __device__ __forceinline__ void gemm_store_tile(const GemmP& p, floatx16 (&acc)[
   if constexpr (EPI != kEpiRare) {
     if (p.epi & SIF_EPI_RESIDUAL) gemm_store_rows<TI, TJ, SR, kRowsResidual>(p, acc, sW, mw, nw, c_off, lane, bias_s);
     else if (p.epi & SIF_EPI_GELU_GRAD) gemm_store_rows<TI, TJ, SR, kRowsGeluGrad>(p, acc, sW, mw, nw, c_off, lane, bias_s);
+    else if (p.epi & SIF_EPI_OUT_F32) gemm_store_f32<TI, TJ, SR>(p, acc, sW, mw, nw, c_off, lane, bias_s);
     else if (!(p.epi & SIF_EPI_GELU)) gemm_store_packed<TI, TJ, SR, false>(p, acc, sW, mw, nw, c_off, lane, bias_s);
     else if (p.aux == nullptr) gemm_store_packed<TI, TJ, SR, true>(p, acc, sW, mw, nw, c_off, lane, bias_s);
     else gemm_store_rows<TI, TJ, SR, kRowsGeluAux>(p, acc, sW, mw, nw, c_off, lane, bias_s);

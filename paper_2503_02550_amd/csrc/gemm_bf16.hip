@@ -914,6 +914,10 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_num_vgpr(1
 // 13.3 -> 10.0, 1100 x 768 x 3072 15.2 -> 12.7, 2008 x 768 x 3072 22.1 -> 20.5.  With several tiles on a CU these hide each
 // other's fetches and the ring above is as fast.  (So it is with 128x128 tiles, one per
 // CU or fewer: eight wavefronts' MFMAs cover the fetches, and with four more that fetch it took 0.96 to 1.04 of the time.)
+//   Apart: one request of 77 tokens through twelve layers takes 860 us on the ring, 761 with these wavefronts, 32x64 tiles and a
+// barrier per 64 k, 723 with one per 128 k, 662 with 32x32 tiles; 77 x 768 x 3072 17.0, 12.2, 11.4, 8.7.  Their 97 to 148 KB of LDS
+// leave less room for another stream's blocks than the ring's 50 to 70; beside training that costs nothing (online requests p95 5.4
+// ms on either, the training step +2.4 % and on the ring +3.2 %; offline filling within what two runs differ by).
 //   ST - 1 steps are in flight: the slot of the step before the current one is free for fetches when all wavefronts have
 // passed the barrier in front of the current one's products, which used that step's fragments before it.
 template <int I, int N, typename F>

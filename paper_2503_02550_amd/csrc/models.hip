@@ -247,7 +247,8 @@ static void emit_wgrad(Plan& p, const char* name, const bf16_t* a, const bf16_t*
 // left operand is `ones`, [tokens][8] with 1 in column 0, the result one row; the launch that would read the gradient once
 // more for the sums is not needed.  Its tiles (a row of them over the whole K) take block slots that the weight gradients
 // leave idle where the group fills part of a round: 474 tiles of 512 with layers of 768 columns.  They can also be what
-// begins another round (2048 columns: 824 tiles of 256x256, the weight gradients by themselves are 768 = three rounds).
+// begins another round (4096 tokens of 2048 columns: 824 tiles of 256x256, the weight gradients by themselves are 768 = three
+// rounds); then they follow the group as launches of their own (gemm_group_part).
 struct GroupPlan {
   unsigned char* pool = nullptr;
   uint64_t pool_bytes = 0, used = 0;

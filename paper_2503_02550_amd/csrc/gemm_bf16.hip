@@ -917,7 +917,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_num_vgpr(1
 //   Apart: one request of 77 tokens through twelve layers takes 860 us on the ring, 761 with these wavefronts, 32x64 tiles and a
 // barrier per 64 k, 723 with one per 128 k, 662 with 32x32 tiles; 77 x 768 x 3072 17.0, 12.2, 11.4, 8.7.  Their 97 to 148 KB of LDS
 // leave less room for another stream's blocks than the ring's 50 to 70; beside training that costs nothing (online requests p95 5.4
-// ms on either, the training step +2.4 % and on the ring +3.2 %; offline filling within what two runs differ by).
+// ms on either, the training step +2.4 % and on the ring +3.2 %).
 //   ST - 1 steps are in flight: the slot of the step before the current one is free for fetches when all wavefronts have
 // passed the barrier in front of the current one's products, which used that step's fragments before it.
 template <int I, int N, typename F>

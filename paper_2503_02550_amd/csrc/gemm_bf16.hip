@@ -12,7 +12,8 @@
 // operand as it lies in memory: rows of 64 k (128 bytes, XOR-swizzled in 16-byte chunks so that reads spread over the
 // banks) or, where the other dimension is contiguous, k-rows that the LDS read itself transposes (ds_read_b64_tr_b16).
 //
-// Three kernels, chosen by a model of their times (gemm_choose):
+// Three kernels, chosen by a model of their times (gemm_choose, gemm_kernel), each compiled for the common epilogues and for the
+// rare ones (gemm_rare):
 //   gemm_fed_kernel    the smaller tiles where no CU gets more than one: wavefronts of their own for the fetches.
 //   gemm_ring_kernel   one tile per block, a ring of two to four K steps in LDS.  Tiles from 32x64 (a handful of rows)
 //                      over 64x64, 128x64 and 128x128 to 256x128, so that a product of any size finds one that

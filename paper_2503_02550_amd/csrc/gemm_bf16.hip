@@ -1028,9 +1028,11 @@ __global__ __launch_bounds__(64 * (WM * WN + FW), 2) void gemm_fed_kernel(GemmP 
 // other reads the fragments of its next 32 from LDS and issues fetches, then a barrier swaps them.  Per K step a
 // wavefront has two memory phases: B (kept in registers for both) with the first half of its A rows, then the second
 // half of its A rows.  The parts of a step are therefore read, and free for the fetch of two steps later, at different
-// times: B and the first halves of A are fetched in one phase, the second halves of A in the other, and every fetch has
-// five to six phases (a step and a half, about 1.5 us) to arrive; the counts waited for leave eight younger fetches per
-// wavefront in flight.  Two buffers of each part are 128 KB of LDS; the epilogue has 16 KB of its own for staging.
+// times: the first halves of A and half of B are fetched in one phase, the rest of B and the second halves of A in the next, and
+// every fetch has four to six phases (1 to 1.5 us) to arrive; the counts waited for leave six to eight younger fetches per
+// wavefront in flight.  (All of B with the first halves of A: six fetches in that phase and two in the other, and a phase is as
+// long as its memory half: 8192^3 719 us, now 705, with both operands k-major 778 and 737; on zeros, which leave the clock at its
+// limit, 549 and 516.)  Two buffers of each part are 128 KB of LDS; the epilogue has 16 KB of its own for staging.
 // (One phase is 512 cycles of MFMA.  With a few tiles on the chip a step takes 0.96 us where it was 1.18 with a barrier per
 // step and everything in one stream; with a tile on every CU the clock falls to what the power allows: 1.47 us against
 // 1.51, 8192^3 795 -> 767 us.)
@@ -1050,7 +1052,8 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(124))) void 
   typedef TileFetch<ALAY, BM / 2, THREADS, BM / WM / 2, BM / WM, 0> FetchA0;
   typedef TileFetch<ALAY, BM / 2, THREADS, BM / WM / 2, BM / WM, 1> FetchA1;
   typedef TileFetch<BLAY, BN, THREADS, BN, BN, 0> FetchB;
-  constexpr int F1 = FetchA1::NV, F0 = FetchA0::NV + FetchB::NV;       // fetches of the second halves of A; of the rest
+  constexpr int FA = FetchA0::NV, FB = FetchB::NV / 2;                 // fetches of a half of A; of a half of B
+  static_assert(FetchA1::NV == FA, "two equal halves");
   __shared__ __align__(1024) bf16_t lds[2 * STAGE];
   __shared__ __align__(16) float stage[WM * WN * (kStage / 4)];
   __shared__ __align__(1024) bf16_t s_bias[WM * WN * 512];
@@ -1077,19 +1080,21 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(124))) void 
   FetchB tb;
   uint64_t base_a = 0, base_b = 0, step_a = 0, step_b = 0;
   uint32_t m0 = 0, n0 = 0, nt = 0;
-  auto fetch_a0b = [&](uint32_t t) {
-    const uint32_t o = lds0 + (t & 1u) * (STAGE * 2);
-    const i32x4 ra = operand_rsrc(base_a + t * step_a), rb = operand_rsrc(base_b + t * step_b);
+  // of step t, whose operands begin at base_a and base_b
+  auto fetch_a0 = [&](uint32_t t) {
+    const i32x4 r = operand_rsrc(base_a);
 #pragma unroll
-    for (int i = 0; i < FetchA0::NV; ++i) ta0.issue(ra, o, wave, i);
-#pragma unroll
-    for (int i = 0; i < FetchB::NV; ++i) tb.issue(rb, o + HA * 4, wave, i);
+    for (int i = 0; i < FA; ++i) ta0.issue(r, lds0 + (t & 1u) * (STAGE * 2), wave, i);
   };
   auto fetch_a1 = [&](uint32_t t) {
-    const uint32_t o = lds0 + (t & 1u) * (STAGE * 2) + HA * 2;
-    const i32x4 ra = operand_rsrc(base_a + t * step_a);
+    const i32x4 r = operand_rsrc(base_a);
 #pragma unroll
-    for (int i = 0; i < F1; ++i) ta1.issue(ra, o, wave, i);
+    for (int i = 0; i < FA; ++i) ta1.issue(r, lds0 + (t & 1u) * (STAGE * 2) + HA * 2, wave, i);
+  };
+  auto fetch_b = [&](uint32_t t, auto PART) {
+    const i32x4 r = operand_rsrc(base_b);
+#pragma unroll
+    for (int i = decltype(PART)::value * FB; i < (decltype(PART)::value + 1) * FB; ++i) tb.issue(r, lds0 + (t & 1u) * (STAGE * 2) + HA * 4, wave, i);
   };
   // sets up tile `id` and fetches what its first two memory phases read, and one part more
   auto open_tile = [&](uint32_t id) {
@@ -1117,9 +1122,12 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(124))) void 
     base_b = (uint64_t)(BLAY == 0 ? B + (size_t)n0 * p.ldb : B + n0);
     step_a = ALAY == 0 ? BK * 2 : (uint64_t)BK * p.lda * 2;
     step_b = BLAY == 0 ? BK * 2 : (uint64_t)BK * p.ldb * 2;
-    fetch_a0b(0);
+    fetch_a0(0);
+    fetch_b(0, Int<0>());
+    fetch_b(0, Int<1>());
     fetch_a1(0);
-    if (nt > 1) fetch_a0b(1);
+    base_a += step_a; base_b += step_b;
+    if (nt > 1) { fetch_a0(1); fetch_b(1, Int<0>()); }
   };
   if (pid < all_tiles) open_tile(pid);
   while (pid < all_tiles) {
@@ -1151,36 +1159,46 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(124))) void 
         }
       __builtin_amdgcn_sched_barrier(0);
     };
-    if (nt > 1) wait_vm<F1 + F0>(); else wait_vm<F1>();      // B and the first halves of A of step 0
+    if (nt > 1) wait_vm<2 * FA + FB>(); else wait_vm<FA>();      // B and the first halves of A of step 0
     barrier_only();
     gemm_fetch_bias(gemm_read_record(current), cn0 + wn * 64, 64, lane, (uint32_t)(uintptr_t)(__attribute__((address_space(3))) bf16_t*)s_bias + wave * 1024);
     uint32_t own = 0;
     if (dynamic && threadIdx.x == 0) own = atomicAdd(&ctl.rec->tile_next[my_x * 32u], 1u);      // the block's next tile is asked for now
-    if (second) barrier_only();
-    // The waits stand before the barrier behind which the first half reads what they wait for: at the end of its own
-    // matrix phase, at the end of the second half's memory phase.
-    for (uint32_t t = 0; t < nt; ++t) {
+    // A step, of the half SECOND; MORE: another one follows, MORE2: and one more (all known when compiling: scalar code between the
+    // MFMAs and the barriers, and between the barriers and the fetches, is in the way of both halves).  The waits stand before the
+    // barrier behind which the first half reads what they wait for: at the end of its own matrix phase, at the end of the second
+    // half's memory phase.
+    auto step = [&](uint32_t t, auto SECOND, auto MORE, auto MORE2) {
+      constexpr bool late = decltype(SECOND)::value != 0, more = decltype(MORE)::value != 0, more2 = decltype(MORE2)::value != 0;
       const bf16_t* cur = lds + (t & 1u) * STAGE;
-      const bool more = t + 1 < nt, more2 = t + 2 < nt;
+      auto second_halves = [&] { wait_vm<more ? 2 * FA + 2 * FB : 0>(); };                        // of A, step t
+      auto next_step = [&] { if (more) wait_vm<FA + (more2 ? FA + FB : 0)>(); };                  // B and first halves of A, step t + 1
       read_b(cur + 2 * HA);
       read_a(cur);
-      if (more) fetch_a1(t + 1);
+      if (more) { fetch_b(t + 1, Int<1>()); fetch_a1(t + 1); }
       wait_lds();
-      if (second) { if (more) wait_vm<F0 + F1>(); else wait_vm<0>(); }       // second halves of A, step t
+      if (late) second_halves();
       barrier_only();
       multiply(Int<0>());
-      if (!second) { if (more) wait_vm<F0 + F1>(); else wait_vm<0>(); }
+      if (!late) second_halves();
       barrier_only();
       read_a(cur + HA);
-      if (more2) fetch_a0b(t + 2);
+      base_a += step_a; base_b += step_b;
+      if (more2) { fetch_a0(t + 2); fetch_b(t + 2, Int<0>()); }
       wait_lds();
-      if (second && more) { if (more2) wait_vm<F0 + F1>(); else wait_vm<F1>(); }      // B and first halves of A, step t + 1
+      if (late) next_step();
       barrier_only();
       multiply(Int<1>());
-      if (!second && more) { if (more2) wait_vm<F0 + F1>(); else wait_vm<F1>(); }
+      if (!late) next_step();
       barrier_only();
-    }
-    if (!second) barrier_only();
+    };
+    auto steps = [&](auto SECOND) {
+      uint32_t t = 0;
+      for (; t + 2 < nt; ++t) step(t, SECOND, Int<1>(), Int<1>());
+      if (t + 1 < nt) { step(t, SECOND, Int<1>(), Int<0>()); ++t; }
+      if (t < nt) step(t, SECOND, Int<0>(), Int<0>());
+    };
+    if (second) { barrier_only(); steps(Int<1>()); } else { steps(Int<0>()); barrier_only(); }
 
     if (threadIdx.x == 0) {
       uint32_t np = kNone;

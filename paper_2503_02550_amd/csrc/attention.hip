@@ -151,7 +151,7 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_kernel(const bf16_t* _
   // so that the long blocks of every (batch, head) start first
   const uint32_t q_blk = (CAUSAL ? gridDim.y - 1 - blockIdx.y : blockIdx.y) * AT_Q, qw = q_blk + wave * 32, q = qw + qi;
   const float c2 = scale * 1.44269504088896f;
-  if (q_blk >= S) { kernel_end(ctl, true); return; }       // the grid is sized for the longest sequence
+  if (q_blk >= S) { kernel_finish(ctl, kernel_arrive(ctl)); return; }       // the grid is sized for the longest sequence
 
   bf16x8 fq[KS];
   if constexpr (!DB) {
@@ -293,10 +293,11 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_kernel(const bf16_t* _
   }
 
   __syncthreads();                                         // nobody reads the last K/V tile any more: sK0 stages the output
+  const Arrival arrival = kernel_arrive(ctl);
   at_store_tile<DH>(sK0 + wave * (32 * DH), oacc, l_run > 0.f ? 1.0f / l_run : 0.f, o + (row0 + qw) * ld_o + head * DH, ld_o,
                     qw < S ? S - qw : 0u);
   if (q < S && lse != nullptr && h == 0) lse[(size_t)bh * S + q] = (m_run + __log2f(l_true)) * 0.693147180559945f;
-  kernel_end(ctl, true);
+  kernel_finish(ctl, arrival);
 }
 
 // Backward, dq.  One block = 128 query rows of one (batch, head), a query row per lane pair as in the forward;
@@ -405,9 +406,10 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_bwd_dq_kernel(const bf16_t
     }
   }
   __syncthreads();                                         // nobody reads the last K/V tile any more: their buffers stage dq
+  const Arrival arrival = kernel_arrive(ctl);
   bf16_t* stage = KV == AT_KV || wave < 2 ? sK0 + wave * (32 * DH) : sV0 + (wave - 2) * (32 * DH);
   at_store_tile<DH>(stage, dqacc, 1.0f, dqkv + ((size_t)b * S + qw) * ld_dqkv + head * DH, ld_dqkv, qw < S ? S - qw : 0u);
-  kernel_end(ctl, true);
+  kernel_finish(ctl, arrival);
 }
 
 // Backward, dk and dv.  One block = 128 key rows of one (batch, head), a key row per lane pair (its K and V rows stay
@@ -535,6 +537,7 @@ __global__ __launch_bounds__(AT_THREADS, DH == 64 ? 2 : 1) void attn_bwd_dkv_ker
     }
   }
   __syncthreads();                                         // nobody reads the last Q/dO step any more: its buffers stage dk, then dv
+  const Arrival arrival = kernel_arrive(ctl);
   {
     bf16_t* stage = (wave < 2 ? sQ0 : sDo0) + (wave & 1) * (32 * DH);
     bf16_t* kp = dqkv + ((size_t)b * S + kw) * ld_dqkv + da + head * DH;
@@ -542,7 +545,7 @@ __global__ __launch_bounds__(AT_THREADS, DH == 64 ? 2 : 1) void attn_bwd_dkv_ker
     at_store_tile<DH>(stage, dkacc, 1.0f, kp, ld_dqkv, rows);
     at_store_tile<DH>(stage, dvacc, 1.0f, kp + da, ld_dqkv, rows);
   }
-  kernel_end(ctl, true);
+  kernel_finish(ctl, arrival);
 }
 
 static sif_status attn_check(const char* who, uint32_t batch, uint32_t seq, uint32_t heads, uint32_t d_head) {

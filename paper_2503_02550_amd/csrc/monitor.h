@@ -32,6 +32,7 @@ struct alignas(128) StreamRec {     // one per stream, in HBM
   // accumulators (ticks / counts), mirrored to the host mailbox by whoever updates them
   uint64_t steps, step_ticks_sum, step_ticks_last;
   uint64_t bubble_ticks, filled_ticks, infer_ticks;
+  uint64_t solo_ticks;              // inference kernels without a gate: the sum of their ends less the sum of their starts
   uint64_t kernels_run, kernels_skipped, train_kernels;
   // completion counters of the kernel currently running on this stream (see kernel_end): zero between kernels
   uint32_t done_top;
@@ -121,6 +122,9 @@ __device__ __forceinline__ T ld_sys(const T* p) {
   return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// waits until every vector memory operation of this wavefront is complete (s_waitcnt vmcnt(0))
+__device__ __forceinline__ void wait_vector_memory() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+
 __device__ __forceinline__ uint32_t grid_blocks() { return gridDim.x * gridDim.y * gridDim.z; }
 __device__ __forceinline__ bool first_thread() { return threadIdx.x == 0 && threadIdx.y == 0 && threadIdx.z == 0; }
 
@@ -176,6 +180,7 @@ __device__ __forceinline__ bool kernel_begin(const KCtl& c) {
       st_relaxed(&c.rec->t_start, t0);
       st_relaxed(&c.slot->decision, (c.kseq << 2) | 1u);
       if ((c.kind_id >> 28) == kKindTrain) st_sys_relaxed(&c.mir->t_launched, c.nth);
+      else atomicAdd(reinterpret_cast<unsigned long long*>(&c.rec->solo_ticks), (unsigned long long)-t0);
     }
     return true;
   }
@@ -223,38 +228,56 @@ __device__ __forceinline__ bool kernel_begin(const KCtl& c) {
   return s_run != 0;
 }
 
-// Kernel epilogue.  Every thread calls it after its last global store.  The last block of the grid to leave
-// stamps the end time and bumps the counters.  Kernels of one stream never overlap, so the counters belong to the
-// stream and the last block re-arms them.
-// How the last block is found: a device-scope atomic takes a round trip of about 0.7 us to the memory side, and
-// atomics on one address serialise there at about 50 ns each.  A grid of up to 32 blocks therefore counts on one
-// counter (one round trip, at most 1.6 us when all leave together); a larger one on a tree of two levels with roughly
-// as many first-level counters (on cache lines of their own) as blocks per counter.  What the last block has to read
-// it reads in one round trip; a training kernel has nothing to read.  (With 64 first-level counters for every grid, the
-// kernel count read back by block 0 and the reads one after the other: step of the two-layer MLP 124 us, now 112; a
-// batch-1 encoder request of 86 launches 1603 -> 1483 us; two-layer decoder of 256 tokens 473 -> 412 us.)
-// (`first`: whether this is the block's first thread; a kernel with one-dimensional blocks and no register to spare says it
-// by the one coordinate that it holds anyway.)
-__device__ __forceinline__ void kernel_end(const KCtl& c, bool ran, bool first = first_thread()) {
-  if (c.rec == nullptr || !ran) return;
-  __syncthreads();
-  if (!first) return;
-  const uint32_t total = grid_blocks(), id = linear_block();
-  uint32_t arrivals = total;                     // on the top counter
-  if (total > 32u) {
-    const uint32_t lg = total <= 512u ? 4u : (total <= 2048u ? 5u : 6u), n_sub = 1u << lg, sub = id & (n_sub - 1u);
-    const uint32_t in_sub = (total - sub + n_sub - 1u) >> lg;
-    uint32_t* cnt = c.rec->done_sub + sub * 32u;
-    if (atomicAdd(cnt, 1u) + 1u != in_sub) return;
-    *cnt = 0;
-    arrivals = n_sub;
+// Kernel epilogue.  The last block of the grid stamps the end time and bumps the counters.  Kernels of one stream never
+// overlap, so the counters belong to the stream and the last block re-arms them.
+// How the last block is found: a device-scope atomic takes a round trip of about 0.7 us to the memory side, and atomics on one
+// address serialise there at about 10 ns each.  So a grid of up to `direct` blocks counts on one counter, a larger one on a tree
+// of two levels with roughly as many first-level counters (on cache lines of their own) as blocks per counter.  A training kernel
+// has nothing to read.  (With 64 first-level counters for every grid, the kernel count read back by block 0 and the reads one
+// after the other: step of the two-layer MLP 124 us, now 112; a batch-1 encoder request of 86 launches 1603 -> 1483 us; two-layer
+// decoder of 256 tokens 473 -> 412 us.)
+// When a block counts itself: kernel_end does so behind its last store and then waits for the answer.  A kernel can also call
+// kernel_arrive when all that it reads is there and only its results are left to work out and write, and kernel_finish at the end:
+// the round trip is under way meanwhile.  (Not in front of loads: operations complete in order, so a wait for these would wait for
+// the answer too, 1.3 us a launch of the two-layer MLP.)  The block that arrives last then ends with the last ones, not always as
+// the last.  (Chains of launches that load and store 256 floats a block: 16, 72 and 256 blocks 2.23, 2.56 and 2.79 us, of which
+// 1.70 to 1.76 without the monitor; inference, which also read four words of its record, 2.55, 3.18 and 3.31.)
+// (`first`: whether this is the thread that counts for its block, the same one in both calls.)
+constexpr uint32_t kDirectAtEnd = 32, kDirectEarly = 128;
+struct Arrival { uint32_t before; };       // blocks that had counted themselves on this block's counter
+
+__device__ __forceinline__ uint32_t arrival_levels(uint32_t total) { return total <= 512u ? 4u : (total <= 2048u ? 5u : 6u); }
+
+template <uint32_t DIRECT = kDirectEarly>
+__device__ __forceinline__ Arrival kernel_arrive(const KCtl& c, bool first = first_thread()) {
+  Arrival a = {0};
+  const uint32_t total = grid_blocks();
+  if (c.rec != nullptr && total > 1u && first) {
+    uint32_t* p = total > DIRECT ? c.rec->done_sub + (linear_block() & ((1u << arrival_levels(total)) - 1u)) * 32u : &c.rec->done_top;
+    asm("" : "+v"(p));                     // (an address of the lane's own: else the compiler counts lanes first and waits here)
+    a.before = __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (arrivals > 1u) {
-    if (atomicAdd(&c.rec->done_top, 1u) + 1u != arrivals) return;
-    c.rec->done_top = 0;
+  return a;
+}
+
+// rearm: the kernel hands out its tiles through the record's work counters
+template <uint32_t DIRECT = kDirectEarly>
+__device__ __forceinline__ void kernel_finish(const KCtl& c, const Arrival& a, bool first = first_thread(), bool rearm = false) {
+  if (c.rec == nullptr || !first) return;
+  const uint32_t total = grid_blocks();
+  if (total > DIRECT) {
+    const uint32_t lg = arrival_levels(total), n_sub = 1u << lg, sub = linear_block() & (n_sub - 1u);
+    if (a.before + 1u != (total - sub + n_sub - 1u) >> lg) return;
+    st_relaxed(&c.rec->done_sub[sub * 32u], 0u);
+    if (atomicAdd(&c.rec->done_top, 1u) + 1u != n_sub) return;
+  } else if (a.before + 1u != total) {
+    return;
   }
+  st_relaxed(&c.rec->done_top, 0u);
+  if (rearm) {
 #pragma unroll
-  for (int x = 0; x < 8; ++x) st_relaxed(&c.rec->tile_next[x * 32], 0u);
+    for (int x = 0; x < 8; ++x) st_relaxed(&c.rec->tile_next[x * 32], 0u);
+  }
   Mirror* m = c.mir;
   StreamRec* r = c.rec;
   const uint64_t t1 = now_ticks();
@@ -262,36 +285,48 @@ __device__ __forceinline__ void kernel_end(const KCtl& c, bool ran, bool first =
   st_relaxed(&r->t_end, t1);
   if ((c.kind_id >> 28) == kKindTrain) {
     st_sys_relaxed(&m->t_completed, c.nth);         // also the count of training kernels run (the host takes differences)
-  } else {
-    const uint64_t t0 = ld_relaxed(&c.slot->t0), infer0 = r->infer_ticks, filled0 = r->filled_ticks, run0 = r->kernels_run;
-    uint64_t ib = 0, busy_begin = 0;
-    uint32_t state = kStateBusy;
-    if (c.gate != nullptr) {
-      ib = ld_relaxed(&c.gate->t_idle_begin);
-      state = ld_relaxed(&c.gate->state);
-      busy_begin = ld_relaxed(&c.gate->t_busy_begin);
-    }
-    const uint64_t dur = t1 - t0;
-    uint64_t fill = dur;
-    if (c.gate != nullptr) {
-      const uint64_t end = state == kStateIdle ? t1 : busy_begin;
-      const uint64_t lo = t0 > ib ? t0 : ib, hi = t1 < end ? t1 : end;
-      fill = hi > lo ? hi - lo : 0;
-    }
-    r->infer_ticks = infer0 + dur;
-    r->filled_ticks = filled0 + fill;
-    r->kernels_run = run0 + 1;
-    // The statistics travel to the host mailbox with the last kernel of a job and with every eighth launch (each
-    // store to host memory lengthens the end of the kernel); the progress word travels every time.  It says that the
-    // last block is about to leave, not that the kernel's results are visible: the host reports a job done only after
-    // an event recorded behind its last kernel has completed.
-    if ((c.flags & 1u) || (c.kseq & 7u) == 0u) {
-      st_sys_relaxed(&m->infer_ticks, infer0 + dur);
-      st_sys_relaxed(&m->filled_ticks, filled0 + fill);
-      st_sys_relaxed(&m->kernels_run, run0 + 1);
-    }
-    st_sys_relaxed(&m->i_done, c.kseq);
+    return;
   }
+  // The statistics travel to the host mailbox with the last kernel of a job and with every eighth launch (each store to host
+  // memory lengthens the end of the kernel); the progress word travels every time.  It says that the last block is about to
+  // leave, not that the kernel's results are visible: the host reports a job done only after an event recorded behind its
+  // last kernel has completed.
+  const bool report = (c.flags & 1u) || (c.kseq & 7u) == 0u;
+  if (c.gate == nullptr) {
+    // no bubbles: all of the kernel's time counts, and is added without reading anything (its start was subtracted at the start)
+    atomicAdd(reinterpret_cast<unsigned long long*>(&r->solo_ticks), (unsigned long long)t1);
+    atomicAdd(reinterpret_cast<unsigned long long*>(&r->kernels_run), 1ull);
+    if (report) {
+      wait_vector_memory();
+      const uint64_t solo = ld_relaxed(&r->solo_ticks), infer0 = ld_relaxed(&r->infer_ticks), filled0 = ld_relaxed(&r->filled_ticks), run = ld_relaxed(&r->kernels_run);
+      st_sys_relaxed(&m->infer_ticks, infer0 + solo);
+      st_sys_relaxed(&m->filled_ticks, filled0 + solo);
+      st_sys_relaxed(&m->kernels_run, run);
+    }
+  } else {
+    const uint64_t t0 = ld_relaxed(&c.slot->t0), infer = ld_relaxed(&r->infer_ticks), filled = ld_relaxed(&r->filled_ticks), run = ld_relaxed(&r->kernels_run);
+    const uint64_t solo = ld_relaxed(&r->solo_ticks), ib = ld_relaxed(&c.gate->t_idle_begin), busy_begin = ld_relaxed(&c.gate->t_busy_begin);
+    const uint32_t state = ld_relaxed(&c.gate->state);
+    const uint64_t dur = t1 - t0, end = state == kStateIdle ? t1 : busy_begin;
+    const uint64_t lo = t0 > ib ? t0 : ib, hi = t1 < end ? t1 : end, fill = hi > lo ? hi - lo : 0;
+    st_relaxed(&r->infer_ticks, infer + dur);
+    st_relaxed(&r->filled_ticks, filled + fill);
+    st_relaxed(&r->kernels_run, run + 1);
+    if (report) {
+      st_sys_relaxed(&m->infer_ticks, infer + dur + solo);
+      st_sys_relaxed(&m->filled_ticks, filled + fill + solo);
+      st_sys_relaxed(&m->kernels_run, run + 1);
+    }
+  }
+  st_sys_relaxed(&m->i_done, c.kseq);
+}
+
+// Every thread calls it after its last global store.  (A kernel with one-dimensional blocks and no register to spare says `first`
+// by the one coordinate that it holds anyway.)
+__device__ __forceinline__ void kernel_end(const KCtl& c, bool ran, bool first = first_thread()) {
+  if (c.rec == nullptr || !ran) return;
+  __syncthreads();
+  kernel_finish<kDirectAtEnd>(c, kernel_arrive<kDirectAtEnd>(c, first), first, true);
 }
 
 }  // namespace sif

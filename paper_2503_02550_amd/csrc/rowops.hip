@@ -44,6 +44,8 @@ __global__ __launch_bounds__(256) void layernorm_fwd_kernel(const bf16_t* __rest
   // the row is the same for the whole wavefront: as a scalar it can index the segment table in the kernel arguments
   const uint32_t lane = threadIdx.x & 63, nv = d >> 3, n_waves = gridDim.x * 4;
   uint32_t row = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+  Arrival arrival = {0};                       // the block is counted with the last row of its first wavefront
+  if (row >= rows) arrival = kernel_arrive(ctl);
   auto out_row = [&](uint32_t r_) -> uint4* {
     if (segs.n != 0) {
       uint32_t r = 0;
@@ -70,6 +72,7 @@ __global__ __launch_bounds__(256) void layernorm_fwd_kernel(const bf16_t* __rest
     }
     while (row < rows) {
       const uint32_t next = __builtin_amdgcn_readfirstlane(row + n_waves);
+      if (next >= rows) arrival = kernel_arrive(ctl);
       if (next < rows) fetch(nx, next);
       uint4* yr = out_row(row);
       float s = 0.f, f[8];
@@ -97,6 +100,7 @@ __global__ __launch_bounds__(256) void layernorm_fwd_kernel(const bf16_t* __rest
     }
   } else {
     for (; row < rows; row = __builtin_amdgcn_readfirstlane(row + n_waves)) {
+      if (row + n_waves >= rows) arrival = kernel_arrive(ctl);
       const uint4* xr = reinterpret_cast<const uint4*>(x + (size_t)row * d);
       uint4* yr = out_row(row);
       float s = 0.f, f[8];
@@ -114,7 +118,7 @@ __global__ __launch_bounds__(256) void layernorm_fwd_kernel(const bf16_t* __rest
       if (lane == 0 && mean_out != nullptr) { mean_out[row] = mean; rstd_out[row] = rstd; }
     }
   }
-  kernel_end(ctl, true);
+  kernel_finish(ctl, arrival);
 }
 
 constexpr int LN_MAXV = 8;   // vectors of 8 columns per lane: d <= 4096
@@ -211,6 +215,7 @@ __global__ __launch_bounds__(256) void layernorm_bwd_kernel(const bf16_t* __rest
       }
     }
   }
+  const Arrival arrival = kernel_arrive(ctl);
   // combine the four wavefronts in order 0,1,2,3, 512 columns at a time
 #pragma unroll
   for (int t = 0; t < MAXV; ++t) {
@@ -230,7 +235,7 @@ __global__ __launch_bounds__(256) void layernorm_bwd_kernel(const bf16_t* __rest
       }
     }
   }
-  kernel_end(ctl, true);
+  kernel_finish(ctl, arrival);
 }
 
 // The same for rows of more than 2048 columns, with the sums in the same order and so with the same bits.  A wavefront
@@ -364,6 +369,7 @@ __global__ __launch_bounds__(256, 2) void layernorm_bwd_wide_kernel(const bf16_t
     }
     __syncthreads();                           // the group's rows are done with
   }
+  const Arrival arrival = kernel_arrive(ctl);
   const bool wide = (reinterpret_cast<uintptr_t>(part) & 15u) == 0;
 #pragma unroll
   for (int w = 0; w < NSUM; ++w)
@@ -383,7 +389,7 @@ __global__ __launch_bounds__(256, 2) void layernorm_bwd_wide_kernel(const bf16_t
         for (int i = 0; i < 8; ++i) to[i] = s[i];
       }
     }
-  kernel_end(ctl, true);
+  kernel_finish(ctl, arrival);
 }
 
 // Sum of `parts` rows of partial sums per column, in a fixed order: 1024 threads = 16 wavefronts x 64 columns;
@@ -487,6 +493,7 @@ __global__ __launch_bounds__(1024) void colsum_fin_kernel(const float* __restric
 __global__ __launch_bounds__(1024) void fin_batch_kernel(const FinItem* __restrict__ items, uint32_t acc, KCtl ctl) {
   __shared__ float sm[1024];
   if (!kernel_begin(ctl)) { kernel_end(ctl, false); return; }
+  const Arrival arrival = kernel_arrive(ctl);
   const FinItem it = items[blockIdx.y];
   if (blockIdx.x * 64 < it.n) {                       // uniform over the block
     const uint32_t c = blockIdx.x * 64 + (threadIdx.x & 63);
@@ -496,7 +503,7 @@ __global__ __launch_bounds__(1024) void fin_batch_kernel(const FinItem* __restri
       if (threadIdx.x < 64 && c < it.n && out != nullptr) out[c] = f2bf(acc ? bf2f(out[c]) + t : t);
     }
   }
-  kernel_end(ctl, true);
+  kernel_finish(ctl, arrival);
 }
 
 __global__ __launch_bounds__(256) void colsum_f32_kernel(const float* __restrict__ x, uint32_t ld, float* __restrict__ out,
@@ -518,6 +525,7 @@ constexpr int SM_MAXT = 8;   // 4 columns per lane per step: cols <= 2048
 __global__ __launch_bounds__(256) void softmax_fwd_kernel(const float* __restrict__ s, bf16_t* __restrict__ p, uint32_t rows,
                                                           uint32_t cols, uint32_t ld_s, uint32_t ld_p, uint32_t causal, KCtl ctl) {
   if (!kernel_begin(ctl)) { kernel_end(ctl, false); return; }
+  const Arrival arrival = kernel_arrive(ctl);
   const uint32_t row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (row < rows) {
     const size_t r = (size_t)blockIdx.y * rows + row;
@@ -553,13 +561,14 @@ __global__ __launch_bounds__(256) void softmax_fwd_kernel(const float* __restric
       if (c < w_end) *reinterpret_cast<uint2*>(pr + c) = make_uint2(pack_bf2(v[t][0] * inv, v[t][1] * inv), pack_bf2(v[t][2] * inv, v[t][3] * inv));
     }
   }
-  kernel_end(ctl, true);
+  kernel_finish(ctl, arrival);
 }
 
 __global__ __launch_bounds__(256) void softmax_bwd_kernel(const float* __restrict__ dp, const bf16_t* __restrict__ p,
                                                           bf16_t* __restrict__ ds, uint32_t rows, uint32_t cols, uint32_t ld,
                                                           float scale, uint32_t causal, KCtl ctl) {
   if (!kernel_begin(ctl)) { kernel_end(ctl, false); return; }
+  const Arrival arrival = kernel_arrive(ctl);
   const uint32_t row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (row < rows) {
     const size_t r = (size_t)blockIdx.y * rows + row;
@@ -596,7 +605,7 @@ __global__ __launch_bounds__(256) void softmax_bwd_kernel(const float* __restric
       }
     }
   }
-  kernel_end(ctl, true);
+  kernel_finish(ctl, arrival);
 }
 
 // ---------------------------------------------------------------------------------------------- embedding
@@ -608,6 +617,7 @@ __global__ __launch_bounds__(256) void embed_fwd_kernel(const int32_t* __restric
                                                         const bf16_t* __restrict__ wpe, bf16_t* __restrict__ x,
                                                         uint32_t tokens, uint32_t seq, uint32_t d, uint32_t vocab, KCtl ctl) {
   if (!kernel_begin(ctl)) { kernel_end(ctl, false); return; }
+  const Arrival arrival = kernel_arrive(ctl);
   const uint32_t t = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63, nv = d >> 3;
   if (t < tokens) {
     const uint4* a = reinterpret_cast<const uint4*>(wte + (size_t)clamp_id(ids[t], vocab) * d);
@@ -620,7 +630,7 @@ __global__ __launch_bounds__(256) void embed_fwd_kernel(const int32_t* __restric
       o[v] = pack8(r);
     }
   }
-  kernel_end(ctl, true);
+  kernel_finish(ctl, arrival);
 }
 
 // The same for several requests whose rows lie back to back in x: segment r reads its own token ids, positions
@@ -628,6 +638,7 @@ __global__ __launch_bounds__(256) void embed_fwd_kernel(const int32_t* __restric
 __global__ __launch_bounds__(256) void embed_fwd_segs_kernel(RowSegs segs, const bf16_t* __restrict__ wte, const bf16_t* __restrict__ wpe,
                                                              bf16_t* __restrict__ x, uint32_t tokens, uint32_t d, uint32_t vocab, KCtl ctl) {
   if (!kernel_begin(ctl)) { kernel_end(ctl, false); return; }
+  const Arrival arrival = kernel_arrive(ctl);
   const uint32_t t = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6)), lane = threadIdx.x & 63, nv = d >> 3;
   if (t < tokens) {
     uint32_t r = 0;
@@ -644,7 +655,7 @@ __global__ __launch_bounds__(256) void embed_fwd_segs_kernel(RowSegs segs, const
       o[v] = pack8(q);
     }
   }
-  kernel_end(ctl, true);
+  kernel_finish(ctl, arrival);
 }
 
 constexpr int EB_MAXC = 16;   // columns per thread: d <= 4096
@@ -832,13 +843,14 @@ __global__ __launch_bounds__(256) void embed_bwd_wte_lds_kernel(const int32_t* _
 __global__ __launch_bounds__(256) void embed_bwd_wpe_kernel(const bf16_t* __restrict__ dx, bf16_t* __restrict__ dwpe,
                                                             uint32_t tokens, uint32_t seq, uint32_t d, KCtl ctl) {
   if (!kernel_begin(ctl)) { kernel_end(ctl, false); return; }
+  const Arrival arrival = kernel_arrive(ctl);
   const uint32_t s = blockIdx.x;
   for (uint32_t c = threadIdx.x; c < d; c += 256) {
     float a = 0.f;
     for (uint32_t t = s; t < tokens; t += seq) a += bf2f(dx[(size_t)t * d + c]);
     dwpe[(size_t)s * d + c] = f2bf(a);
   }
-  kernel_end(ctl, true);
+  kernel_finish(ctl, arrival);
 }
 
 // ---------------------------------------------------------------------------------------------- cross entropy

@@ -961,14 +961,18 @@ __global__ __launch_bounds__(THREADS, (THREADS <= 512 ? 2 : 1)) void xent_reg_ke
   kernel_end(ctl, true);
 }
 
-// The register variant as one block per CU that works through rows one after the other: the next row's loads are
+// The register variant as a few blocks per CU that work through rows one after the other: the next row's loads are
 // issued before the current row is reduced and travel meanwhile, the current row's stores drain during the next row's
 // reductions.  A block's first two rows are fixed (blockIdx.x and blockIdx.x + gridDim.x); a monitored launch hands out
 // the others through a counter in the stream's record, asked for one row ahead so that the answer is there when it
 // is needed: a block that starts late (its CU was held by a kernel of the other stream) then simply takes fewer rows.
-// Same values, same order of additions per row.
+// Same values, same order of additions per row: a vector beyond the row's end adds zeros, so the number of vectors per thread
+// (MAXV) and wavefronts without any leave the sums as they are.  For a row of few vectors a thread's loops are as short as the
+// row, and the CU's other blocks are at work while one reduces.  (With thirteen vectors per thread and one block per CU 256 rows of
+// 300 columns took 9.2 us, now 4.8, 2008 of 10007 49.5 and 15.6, 8192 of 4000 183 and 27, 8192 of 20000 194 and 132.  From 28673
+// columns on it is thirteen, as before: 8192 of 40000 242.)
 template <int MAXV, int THREADS>
-__global__ __launch_bounds__(THREADS, 1) void xent_stream_kernel(bf16_t* __restrict__ logits, const int32_t* __restrict__ targets,
+__global__ __launch_bounds__(THREADS, THREADS == 64 ? 4 : MAXV == 1 ? 8 : MAXV <= 3 ? 6 : MAXV <= 7 ? 4 : 1) void xent_stream_kernel(bf16_t* __restrict__ logits, const int32_t* __restrict__ targets,
                                                                  float* __restrict__ loss, uint32_t tokens, uint32_t vocab, uint32_t ld, KCtl ctl) {
   __shared__ float sred[16];
   if (!kernel_begin(ctl)) { kernel_end(ctl, false); return; }
@@ -992,7 +996,7 @@ __global__ __launch_bounds__(THREADS, 1) void xent_stream_kernel(bf16_t* __restr
     const int32_t tg = (int32_t)clamp_id(targets[t], vocab);
     const float at_target = bf2f(logits[(size_t)t * ld + tg]);      // read before anything of this row is written back
     uint32_t asked = 0;
-    if (dynamic && threadIdx.x == 0) asked = atomicAdd(&ctl.rec->tile_next[0], 1u);      // the row after the next one
+    if (dynamic && threadIdx.x == 0 && 2u * gridDim.x < tokens) asked = atomicAdd(&ctl.rec->tile_next[0], 1u);      // the row after the next one
     float e[MAXV][8];
 #pragma unroll
     for (int k = 0; k < MAXV; ++k) {
@@ -1269,8 +1273,18 @@ sif_status launch_xent(void* logits, const int32_t* targets, float* loss, uint32
   REQ(logits && targets && loss && tokens > 0 && vocab > 0, "xent: null or empty");
   REQ((ld & 7) == 0 && ld >= vocab && al16(logits), "xent: ld must be a multiple of 8 and >= vocab");
   if (ld <= 8 * 512 * 13) {          // the row fits in the registers of a block of 512 threads
-    // (344 us for 8192 x 50257 with one row per block, two blocks per CU; 328 us as one block per CU with two rows in flight)
-    hipLaunchKernelGGL((xent_stream_kernel<13, 512>), dim3(std::min<uint32_t>(tokens, n_cus())), dim3(512), 0, s, (bf16_t*)logits, targets, loss, tokens, vocab, ld, c);
+    // As many vectors per thread as the row needs, and as many blocks per CU as those leave registers for: one wavefront up to 512
+    // columns, then 512 threads with 1, 3, 7 or 13 vectors each.  (344 us for 8192 x 50257 with one row per block, two blocks per
+    // CU; 328 us as one block per CU with two rows in flight)
+    const uint32_t nv = ld / 8;
+    auto launch = [&](auto kernel, uint32_t threads, uint32_t per_cu) {
+      hipLaunchKernelGGL(kernel, dim3(std::min<uint32_t>(tokens, n_cus() * per_cu)), dim3(threads), 0, s, (bf16_t*)logits, targets, loss, tokens, vocab, ld, c);
+    };
+    if (nv <= 64) launch(xent_stream_kernel<1, 64>, 64, 16);
+    else if (nv <= 512) launch(xent_stream_kernel<1, 512>, 512, 4);
+    else if (nv <= 3 * 512) launch(xent_stream_kernel<3, 512>, 512, 3);
+    else if (nv <= 7 * 512) launch(xent_stream_kernel<7, 512>, 512, 2);
+    else launch(xent_stream_kernel<13, 512>, 512, 1);
     return check_launch("xent");
   }
   if (ld <= 8 * 1024 * 8) {          // up to 65536 columns: 1024 threads, one block per CU

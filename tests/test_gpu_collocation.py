@@ -782,3 +782,26 @@ def test_online_requests_run_beside_training_with_concurrent_filling():
             torch.cuda.synchronize()
             s.wait(s.submit_online(m, I, out, lens[i]))
             assert torch.equal(out.cpu(), res[1][1][i]), i
+
+
+@pytest.mark.parametrize("blocks", [1, 32, 33, 128, 129, 512, 513, 2049])
+def test_every_launch_is_found_complete_whatever_its_grid(blocks):
+    """The last block of a launch is found on one counter or on a tree of them, by the number of blocks; LayerNorm, embedding and the
+    products of 4 rows a block give every border.  Each launch of every request is reported, ends after it starts and before the
+    next one starts, and the statistics are the sums of the trace."""
+    c = dict(n_layers=1, d_model=64, n_heads=1, d_head=64, d_ffn=128, vocab=64, max_pos=4, batch=blocks, seq=4)
+    shape = encoder_shape(c)
+    with Session() as s:
+        m = s.register_inference(shape, P.pack(shape, Y.encoder_params(2, c)))
+        ids = i32(Y.token_ids(5, blocks, 4, 64))
+        out = torch.zeros((blocks, 4, 64), device=DEV, dtype=torch.bfloat16)
+        torch.cuda.synchronize()
+        for _ in range(3):
+            s.wait(s.submit_offline(m, ids, out, blocks, 4), 10.0)
+        torch.cuda.synchronize()
+        st = s.stats()
+        runs = [r for r in S.sif_read_trace(s.ctx, 1) if r[0] == 2]
+        assert len(runs) == st.kernels_run == st.kernels_launched == 3 * 9
+        assert all(t0 <= t1 for _, _, _, _, t0, t1 in runs)
+        assert all(a[5] <= b[4] for a, b in zip(runs, runs[1:]))
+        assert st.infer_busy_ns == st.filled_ns == sum(t1 - t0 for _, _, _, _, t0, t1 in runs)

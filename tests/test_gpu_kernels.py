@@ -362,7 +362,9 @@ def test_embedding_fwd_bwd():
     assert bool((guard[:2 * d] == 3.0).all()) and bool((guard[(2 + vocab) * d:] == 3.0).all())
 
 
-@pytest.mark.parametrize("tokens,vocab", [(5, 37), (64, 50257), (3, 8), (4, 60001), (2, 70003)])
+# (the borders between the numbers of vectors per thread, rows for one, two and more turns of a block, and a ragged end)
+@pytest.mark.parametrize("tokens,vocab", [(5, 37), (64, 50257), (3, 8), (4, 60001), (2, 70003), (9001, 37), (4097, 512), (40, 513), (2100, 4096), (40, 4097), (7, 12285),
+                                          (7, 12289), (3, 28672), (520, 28673)])
 def test_cross_entropy(tokens, vocab):
     ld = (vocab + 7) // 8 * 8
     lg = np.zeros((tokens, ld), np.float32)

@@ -612,8 +612,10 @@ static sif_status run_step(sif_ctx* c, const void* inputs, const void* targets, 
   TrainModel& tm = *c->train;
   tm.cur_inputs = inputs; tm.cur_targets = targets; tm.cur_loss = loss;
   hipStream_t s = c->T.stream;
+  // the step's begin and end are marked by its first and last kernel, where it begins and ends with one
+  const bool first_marks = tm.plan.size() > 1 && tm.plan.front().bubble_site < 0, last_marks = tm.plan.size() > 1 && tm.plan.back().bubble_site < 0;
   KCtl k0 = make_ctl(c, c->T, kKindStep, c->step_no, nullptr, 0);
-  sif_status st = launch_step_marker(s, c->T.rec, c->mir, k0.slot, 0, k0.kind_id);
+  sif_status st = first_marks ? SIF_OK : launch_step_marker(s, c->T.rec, c->mir, k0.slot, 0, k0.kind_id);
   if (st != SIF_OK) return st;
   tm.last_kseq.assign(tm.plan.size(), 0);
   for (size_t i = 0; i < tm.plan.size(); ++i) {
@@ -643,7 +645,9 @@ static sif_status run_step(sif_ctx* c, const void* inputs, const void* targets, 
                            c->cfg.device_timed_bubbles, kb.kind_id);
       }
     } else {
-      const KCtl k = make_ctl(c, c->T, kKindTrain, (uint32_t)i, nullptr, 0);
+      KCtl k = make_ctl(c, c->T, kKindTrain, (uint32_t)i, nullptr, 0);
+      if (first_marks && i == 0) k.flags |= kFirstOfStep;
+      if (last_marks && i + 1 == tm.plan.size()) { k.flags |= kLastOfStep; k.cost_ticks = c->step_no; }
       tm.last_kseq[i] = k.kseq;
       st = launch_op(c, op, s, k);
     }
@@ -651,7 +655,7 @@ static sif_status run_step(sif_ctx* c, const void* inputs, const void* targets, 
   }
   KCtl k1 = make_ctl(c, c->T, kKindStep, c->step_no, nullptr, 0);
   ++c->step_no;
-  return launch_step_marker(s, c->T.rec, c->mir, k1.slot, 1, k1.kind_id);
+  return last_marks ? SIF_OK : launch_step_marker(s, c->T.rec, c->mir, k1.slot, 1, k1.kind_id);
 }
 
 static uint64_t workspace_layout(uint64_t* rec_t, uint64_t* rec_i, uint64_t* ring_t, uint64_t* ring_i) {

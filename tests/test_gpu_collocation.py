@@ -805,3 +805,37 @@ def test_every_launch_is_found_complete_whatever_its_grid(blocks):
         assert all(t0 <= t1 for _, _, _, _, t0, t1 in runs)
         assert all(a[5] <= b[4] for a, b in zip(runs, runs[1:]))
         assert st.infer_busy_ns == st.filled_ns == sum(t1 - t0 for _, _, _, _, t0, t1 in runs)
+
+
+@pytest.mark.parametrize("mode", ["kernels", "bubble first"])
+def test_a_steps_record_spans_its_launches(mode):
+    """The step's begin and end are marked by its first and last kernel, or by a launch of their own where it begins with a bubble
+    (a later pipeline stage): one record per step, from the first launch's start to the last kernel's end."""
+    c = dict(n_layers=1, d_model=64, n_heads=1, d_head=64, d_ffn=128, vocab=0, max_pos=0, batch=2, seq=16)
+    shape = decoder_shape(c)
+    n = S.sif_model_n_params(shape)
+    w = (np.random.default_rng(1).standard_normal(n) * 0.02).astype(np.float32)
+    with Session() as s:
+        if mode == "kernels":
+            s.register_training(shape, w)
+        else:
+            s.register_training(shape, w, par_mode=S.SIF_PAR_PP, pp_stages=2, pp_micro=2, pp_stage=1, pp_tf_ns=200_000, pp_tb_ns=400_000)
+        micro = 1 if mode == "kernels" else 2
+        x = bf(np.random.default_rng(2).standard_normal((micro, 2, 16, 64)))
+        torch.cuda.synchronize()
+        for _ in range(3):
+            s.step(x, x)
+        s.sync()
+        assert s.stats().steps == 3
+        tr = S.sif_read_trace(s.ctx, 0)
+        steps = [r for r in tr if r[0] == 4]
+        assert [r[1] for r in steps] == [0, 1, 2]
+        ends = [i for i, r in enumerate(tr) if r[0] == 4]
+        begin = 0
+        for end, rec in zip(ends, steps):
+            inside = [r for r in tr[begin:end] if r[0] in (1, 3)]
+            assert (inside[0][0] == 3) == (mode != "kernels") and inside[-1][0] == 1
+            assert rec[4] == inside[0][4] if mode == "kernels" else rec[4] <= inside[0][4]
+            assert rec[5] == inside[-1][5] and all(a[5] <= b[4] for a, b in zip(inside, inside[1:]))
+            begin = end + 1
+        assert s.stats().step_ns_sum == sum(r[5] - r[4] for r in steps)

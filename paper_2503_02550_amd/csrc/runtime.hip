@@ -26,6 +26,7 @@ static inline uint64_t host_now_ns() {
 static inline void cpu_relax(int n) { for (int i = 0; i < n; ++i) __builtin_ia32_pause(); }
 
 constexpr uint32_t kBubbleTable = 4096;
+constexpr uint64_t kLookNs = 50000;       // how long sif_wait looks before it sleeps
 
 struct sif_ctx {
   sif_config cfg;
@@ -938,9 +939,19 @@ sif_status sif_wait(sif_ctx* c, sif_ticket t, uint64_t timeout_ns) {
   if (!c) return fail(SIF_E_INVAL, "wait: null");
   std::unique_lock<std::mutex> lk(c->mu);
   auto it = c->jobs.find(t);
+  // A small request is done before a thread that went to sleep is awake again: looked at for a while first.  (The lock is given
+  // up between two looks, so the ticket is looked up anew: another waiter may have taken it.)
+  const uint64_t begin = host_now_ns(), look_until = begin + std::min<uint64_t>(timeout_ns, kLookNs);
+  while (it != c->jobs.end() && it->second->result == 1 && host_now_ns() < look_until) {
+    lk.unlock();
+    cpu_relax(20);
+    lk.lock();
+    it = c->jobs.find(t);
+  }
   if (it == c->jobs.end()) return fail(SIF_E_INVAL, "wait: unknown ticket");
   Job* j = it->second.get();
-  const bool ok = c->cv.wait_for(lk, std::chrono::nanoseconds(timeout_ns), [&] { return j->result != 1; });
+  const uint64_t looked = host_now_ns() - begin;
+  const bool ok = c->cv.wait_for(lk, std::chrono::nanoseconds(timeout_ns > looked ? timeout_ns - looked : 0), [&] { return j->result != 1; });
   if (!ok) return fail(SIF_E_TIMEOUT, "wait: ticket %llu still pending", (unsigned long long)t);
   const int32_t r = j->result;
   c->jobs.erase(it);

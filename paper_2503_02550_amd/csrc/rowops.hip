@@ -137,7 +137,7 @@ __global__ __launch_bounds__(256) void layernorm_bwd_kernel(const bf16_t* __rest
                                                             bf16_t* __restrict__ dx, float* __restrict__ part,
                                                             uint32_t rows, uint32_t d, uint32_t parts, KCtl ctl) {
   constexpr int NSUM = WITH_SUM ? 3 : 2;
-  __shared__ float sred[4 * 512];
+  __shared__ __align__(16) float sred[NSUM][4][512];
   if (!kernel_begin(ctl)) { kernel_end(ctl, false); return; }
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nv = d >> 3;
   const uint32_t rows_per = (rows + parts - 1) / parts;
@@ -216,22 +216,26 @@ __global__ __launch_bounds__(256) void layernorm_bwd_kernel(const bf16_t* __rest
     }
   }
   const Arrival arrival = kernel_arrive(ctl);
-  // combine the four wavefronts in order 0,1,2,3, 512 columns at a time
+  // combine the four wavefronts in order 0,1,2,3, all sums of 512 columns at a time (a sum at a time, with a wait for everybody
+  // before and after each: 256 rows of 128 columns 6.4 us, now 5.6, 2008 of 520 9.4 and 8.1, 8192 of 768 14.0 and 12.2)
 #pragma unroll
   for (int t = 0; t < MAXV; ++t) {
     if ((uint32_t)(64 * t) >= nv) break;
+    if (t > 0) __syncthreads();
 #pragma unroll
     for (int which = 0; which < NSUM; ++which) {
-      __syncthreads();
+      float4* to = reinterpret_cast<float4*>(&sred[which][wave][lane * 8]);
+      to[0] = make_float4(acc[which][t][0], acc[which][t][1], acc[which][t][2], acc[which][t][3]);
+      to[1] = make_float4(acc[which][t][4], acc[which][t][5], acc[which][t][6], acc[which][t][7]);
+    }
+    __syncthreads();
 #pragma unroll
-      for (int i = 0; i < 8; ++i) sred[wave * 512 + lane * 8 + i] = acc[which][t][i];
-      __syncthreads();
-      for (uint32_t cidx = threadIdx.x; cidx < 512; cidx += 256) {
-        const uint32_t col = 512 * t + cidx;
-        if (col < d) {
-          const float s = ((sred[cidx] + sred[512 + cidx]) + sred[1024 + cidx]) + sred[1536 + cidx];
-          part[(size_t)(which * parts + blockIdx.x) * d + col] = s;
-        }
+    for (uint32_t cidx = threadIdx.x; cidx < 512; cidx += 256) {
+      const uint32_t col = 512 * t + cidx;
+      if (col < d) {
+#pragma unroll
+        for (int which = 0; which < NSUM; ++which)
+          part[(size_t)(which * parts + blockIdx.x) * d + col] = ((sred[which][0][cidx] + sred[which][1][cidx]) + sred[which][2][cidx]) + sred[which][3][cidx];
       }
     }
   }

@@ -303,11 +303,15 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_kernel(const bf16_t* _
 // Backward, dq.  One block = 128 query rows of one (batch, head), a query row per lane pair as in the forward;
 // keys/values streamed in tiles of 128 or 64, K and V as [kv][d].  Also writes delta = rowsum(do .* o)
 // for the dk/dv kernel.
+// With a causal mask a (batch, head)'s blocks differ in length.  The grid's slow index counts them from the longest, which start
+// first.  Where all of a launch's blocks find room at once, two per CU, that puts long ones together: from `fold` on, where the CUs'
+// second blocks begin, the shortest come first instead.  (2 x 16 heads of 128, 2048 rows, 512 blocks: 101.7 us, now 97.2; the
+// forward kernel takes 66 either way.)
 template <int DH, int CAUSAL>
 __global__ __launch_bounds__(AT_THREADS, 2) void attn_bwd_dq_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
                                                                  const bf16_t* __restrict__ d_o, const float* __restrict__ lse,
                                                                  float* __restrict__ delta, bf16_t* __restrict__ dqkv, uint32_t S, uint32_t H,
-                                                                 uint32_t ld_qkv, uint32_t ld_o, uint32_t ld_dqkv, float scale, KCtl ctl) {
+                                                                 uint32_t ld_qkv, uint32_t ld_o, uint32_t ld_dqkv, float scale, uint32_t fold, KCtl ctl) {
   constexpr int KS = DH / 16, DT = DH / 32;
   // two tile buffers each, as in the forward kernel; tiles of 64 keys with d_head 128, so that two blocks of a CU find room
   constexpr int KV = DH == 64 ? AT_KV : AT_KV / 2;
@@ -319,7 +323,7 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_bwd_dq_kernel(const bf16_t
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, qi = lane & 31, h = lane >> 5;
   const uint32_t bh = blockIdx.x, b = bh / H, head = bh % H, da = H * DH;
   const bf16_t* base = qkv + (size_t)b * S * ld_qkv + head * DH;
-  const uint32_t q_blk = (CAUSAL ? gridDim.y - 1 - blockIdx.y : blockIdx.y) * AT_Q, qw = q_blk + wave * 32, q = qw + qi;
+  const uint32_t q_blk = (CAUSAL ? (blockIdx.y < fold ? gridDim.y - 1 - blockIdx.y : blockIdx.y - fold) : blockIdx.y) * AT_Q, qw = q_blk + wave * 32, q = qw + qi;
   const bool q_ok = q < S;
   const float c2 = scale * 1.44269504088896f;
 
@@ -611,6 +615,17 @@ static sif_status attn_bwd_check(const char* who, const void* qkv, const void* o
   return SIF_OK;
 }
 
+// The row of the grid at which the order turns round (see the kernel): where the blocks fit on the chip at once and the first ones of
+// all CUs are whole rows of the grid; otherwise nowhere.
+static uint32_t attn_fold(const dim3& grid, uint32_t causal) {
+  static const uint32_t cus = [] {
+    int dev = 0, n = 0;
+    return hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0 ? (uint32_t)n : 256u;
+  }();
+  const bool folds = causal && cus % grid.x == 0 && (uint64_t)grid.x * grid.y <= 2ull * cus;
+  return folds ? std::min(cus / grid.x, grid.y) : grid.y;
+}
+
 sif_status launch_attn_bwd_dq(const void* qkv, const void* o, const void* d_o, const float* lse, float* delta, void* dqkv, uint32_t batch,
                               uint32_t seq, uint32_t heads, uint32_t d_head, uint32_t ld_qkv, uint32_t ld_o, uint32_t ld_dqkv, uint32_t causal,
                               hipStream_t s, const KCtl& c) {
@@ -618,7 +633,7 @@ sif_status launch_attn_bwd_dq(const void* qkv, const void* o, const void* d_o, c
   const float scale = 1.0f / sqrtf((float)d_head);
   dim3 grid(batch * heads, (seq + AT_Q - 1) / AT_Q);
 #define AT_LAUNCH(DH, C) hipLaunchKernelGGL((attn_bwd_dq_kernel<DH, C>), grid, dim3(AT_THREADS), 0, s, (const bf16_t*)qkv, (const bf16_t*)o, \
-                                            (const bf16_t*)d_o, lse, delta, (bf16_t*)dqkv, seq, heads, ld_qkv, ld_o, ld_dqkv, scale, c)
+                                            (const bf16_t*)d_o, lse, delta, (bf16_t*)dqkv, seq, heads, ld_qkv, ld_o, ld_dqkv, scale, attn_fold(grid, causal), c)
   if (d_head == 64) { if (causal) AT_LAUNCH(64, 1); else AT_LAUNCH(64, 0); }
   else { if (causal) AT_LAUNCH(128, 1); else AT_LAUNCH(128, 0); }
 #undef AT_LAUNCH

@@ -460,7 +460,7 @@ def test_fused_attention_forward_sequences_of_unequal_length(lens, h, dh, causal
 
 @pytest.mark.parametrize("causal", [0, 1])
 @pytest.mark.parametrize("bsz,s,h,dh", [(2, 5, 2, 64), (3, 37, 2, 64), (2, 128, 3, 64), (2, 200, 2, 64), (1, 300, 2, 128), (2, 64, 1, 128),
-                                        (1, 520, 1, 64)])
+                                        (1, 520, 1, 64), (4, 1100, 8, 64), (2, 1030, 16, 128)])      # (the last two: more blocks than CUs, all on the chip at once)
 def test_fused_attention_backward(bsz, s, h, dh, causal):
     from oracle.decoder import attention_bwd, attention_fwd
     from oracle.numerics import Prec

@@ -151,7 +151,7 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_kernel(const bf16_t* _
   // so that the long blocks of every (batch, head) start first
   const uint32_t q_blk = (CAUSAL ? gridDim.y - 1 - blockIdx.y : blockIdx.y) * AT_Q, qw = q_blk + wave * 32, q = qw + qi;
   const float c2 = scale * 1.44269504088896f;
-  if (q_blk >= S) { kernel_finish(ctl, kernel_arrive(ctl)); return; }       // the grid is sized for the longest sequence
+  if (q_blk >= S) { kernel_end(ctl, true); return; }       // the grid is sized for the longest sequence
 
   bf16x8 fq[KS];
   if constexpr (!DB) {
@@ -293,7 +293,7 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_kernel(const bf16_t* _
   }
 
   __syncthreads();                                         // nobody reads the last K/V tile any more: sK0 stages the output
-  const Arrival arrival = kernel_arrive(ctl);
+  const Arrival arrival = kernel_arrive(ctl, seqs.n == 0);
   at_store_tile<DH>(sK0 + wave * (32 * DH), oacc, l_run > 0.f ? 1.0f / l_run : 0.f, o + (row0 + qw) * ld_o + head * DH, ld_o,
                     qw < S ? S - qw : 0u);
   if (q < S && lse != nullptr && h == 0) lse[(size_t)bh * S + q] = (m_run + __log2f(l_true)) * 0.693147180559945f;

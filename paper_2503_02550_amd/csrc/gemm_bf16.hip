@@ -755,7 +755,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_num_vgpr(1
   const uint32_t m0 = tile_m * BM, n0 = tile_n * BN;
   // (blocks of a group beyond their product's tiles have nothing to do, and of a causal product those whose 128x128 tile
   // lies above the diagonal)
-  if (pid >= total_tiles || ((p.epi & SIF_EPI_CAUSAL_SKIP) && n0 / 128 > (m0 + BM - 1) / 128)) { kernel_finish(ctl, kernel_arrive(ctl)); return; }
+  if (pid >= total_tiles || ((p.epi & SIF_EPI_CAUSAL_SKIP) && n0 / 128 > (m0 + BM - 1) / 128)) { kernel_end(ctl, true); return; }
 
   uint32_t k_begin = 0, k_end = p.k;
   if (p.k_limit != 0) k_end = min(p.k, p.k_limit - bi * p.k);      // slices of one long K: the last may be shorter
@@ -874,7 +874,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_num_vgpr(1
   if (t < nt) step(Int<0>());
 
   __syncthreads();                             // nobody reads the ring any more: it stages the results
-  const Arrival arrival = kernel_arrive(ctl);
+  const Arrival arrival = kernel_arrive(ctl, !GROUPED && !(p.epi & SIF_EPI_CAUSAL_SKIP));
   gemm_store_tile<TI, TJ, EPI>(p, acc, reinterpret_cast<float*>(lds) + wave * (kStage / 4), m0 + wm * (TI * 32), n0 + wn * (TJ * 32), c_off, lane, s_bias + wave * 512);
   kernel_finish(ctl, arrival);
 }
@@ -929,7 +929,7 @@ __global__ __launch_bounds__(64 * (WM * WN + FW), 2) void gemm_fed_kernel(GemmP 
   uint32_t tile_m, tile_n;
   gemm_tile_of(p, p.tiles_m * p.tiles_n, blockIdx.x, tile_m, tile_n);
   const uint32_t m0 = tile_m * BM, n0 = tile_n * BN;
-  if ((p.epi & SIF_EPI_CAUSAL_SKIP) && n0 / 128 > (m0 + BM - 1) / 128) { kernel_finish(ctl, kernel_arrive(ctl)); return; }      // (as in the ring)
+  if ((p.epi & SIF_EPI_CAUSAL_SKIP) && n0 / 128 > (m0 + BM - 1) / 128) { kernel_end(ctl, true); return; }      // (as in the ring)
   uint32_t k_begin = 0, k_end = p.k;
   if (p.k_limit != 0) k_end = min(p.k, p.k_limit - bi * p.k);
   if (p.k_causal == 1) k_end = min(p.k, m0 + BM);
@@ -937,6 +937,7 @@ __global__ __launch_bounds__(64 * (WM * WN + FW), 2) void gemm_fed_kernel(GemmP 
   const uint32_t nt = (k_end - k_begin + BK * KB - 1) / (BK * KB), full = (k_end - k_begin) / BK, k_rest = (k_end - k_begin) % BK;
   const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) bf16_t*)lds;
+  Arrival arrival = {Arrival::kNotCounted, 0};
 
   if (wave >= MW) {
     const uint32_t tid = threadIdx.x - MW * 64, fw = wave - MW;
@@ -977,8 +978,9 @@ __global__ __launch_bounds__(64 * (WM * WN + FW), 2) void gemm_fed_kernel(GemmP 
       if (s < nt) { fetch_step(s); ++s; }
     }
     __syncthreads();
-    // the tile is counted by a wavefront that has nothing else left to do
-    kernel_finish(ctl, kernel_arrive(ctl, tid == 0), tid == 0);
+    // the tile is counted by a wavefront that has nothing else left to do (block 0 behind the wait for the bias in its others)
+    arrival = kernel_arrive(ctl, !(p.epi & SIF_EPI_CAUSAL_SKIP), tid == 0);
+    kernel_answer(ctl, arrival, tid == 0);
   } else {
     const uint32_t wm = wave / WN, wn = wave % WN;
     floatx4 acc[2 * TI][2 * TJ];
@@ -1023,6 +1025,7 @@ __global__ __launch_bounds__(64 * (WM * WN + FW), 2) void gemm_fed_kernel(GemmP 
     gemm_store_tile<TI, TJ, EPI>(p, acc, reinterpret_cast<float*>(lds) + wave * (kStage / 4), m0 + wm * (TI * 32), n0 + wn * (TJ * 32),
                                 (size_t)(bo * p.c_so + bi * p.c_si), lane, s_bias + wave * 512);
   }
+  kernel_finish(ctl, arrival, threadIdx.x == MW * 64);
 }
 
 // 256x256 tiles, eight wavefronts of 128x64, whole K steps.  The wavefronts of the tile's upper and of its lower half -
@@ -1131,9 +1134,8 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(124))) void 
     base_a += step_a; base_b += step_b;
     if (nt > 1) { fetch_a0(1); fetch_b(1, Int<0>()); }
   };
-  Arrival arrival = {0};
+  Arrival arrival = {Arrival::kNotCounted, 0};
   if (pid < all_tiles) open_tile(pid);
-  else arrival = kernel_arrive(ctl, threadIdx.x == 0);
   while (pid < all_tiles) {
     const uint32_t cm0 = m0, cn0 = n0, cnt = nt;
     const gemm_record_ptr current = fetched;   // (of a group: the next tile may belong to another product)
@@ -1213,7 +1215,7 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(124))) void 
     __syncthreads();
     pid = s_next;
     if (pid < all_tiles) open_tile(pid);
-    else arrival = kernel_arrive(ctl, threadIdx.x == 0);
+    else arrival = kernel_arrive(ctl, !GROUPED, threadIdx.x == 0);
     if (cnt != 0) {
       const GemmP cp = gemm_read_record(current);
       uint32_t l = lane;

@@ -8,6 +8,7 @@
 // decides (run or skip), publishes the decision, and every other block follows it.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 namespace sif {
@@ -84,11 +85,12 @@ struct KCtl {                       // by-value kernel argument
   uint32_t kind_id;
   uint32_t flags;                   // bit 0: last kernel of its job; bit 1: gated on the poison only (runs beside training);
                                     // bits 8..15: 0, or 1 + log2 of the bound on the spins a block waits for block 0's decision;
-                                    // bits 16, 17: first, last launch of a training step (see step_begin, step_end)
+                                    // bits 16, 17: first, last launch of a training step (see step_begin, step_end);
+                                    // bit 18: its blocks count themselves when they end (see kernel_end)
   uint32_t nth;                     // training launches: how many monitored kernels of the stream this makes (they are never
                                     // skipped, so the host knows the count and no block has to read it back)
 };
-constexpr uint32_t kDefaultSpinLog2 = 18, kFirstOfStep = 1u << 16, kLastOfStep = 1u << 17;
+constexpr uint32_t kDefaultSpinLog2 = 18, kFirstOfStep = 1u << 16, kLastOfStep = 1u << 17, kCountAtEnd = 1u << 18;
 
 __device__ __forceinline__ uint64_t now_ticks() { return wall_clock64(); }
 
@@ -261,41 +263,54 @@ __device__ __forceinline__ bool kernel_begin(const KCtl& c) {
 // Kernel epilogue.  The last block of the grid stamps the end time and bumps the counters.  Kernels of one stream never
 // overlap, so the counters belong to the stream and the last block re-arms them.
 // How the last block is found: a device-scope atomic takes a round trip of about 0.7 us to the memory side, and atomics on one
-// address serialise there at about 10 ns each.  So a grid of up to `direct` blocks counts on one counter, a larger one on a tree
+// address serialise there at about 10 ns each.  So a grid of up to kDirect blocks counts on one counter, a larger one on a tree
 // of two levels with roughly as many first-level counters (on cache lines of their own) as blocks per counter.  A training kernel
 // has nothing to read.  (With 64 first-level counters for every grid, the kernel count read back by block 0 and the reads one
 // after the other: step of the two-layer MLP 124 us, now 112; a batch-1 encoder request of 86 launches 1603 -> 1483 us; two-layer
 // decoder of 256 tokens 473 -> 412 us.)
-// When a block counts itself: kernel_end does so behind its last store and then waits for the answer.  A kernel can also call
-// kernel_arrive when all that it reads is there and only its results are left to work out and write, and kernel_finish at the end:
-// the round trip is under way meanwhile.  (Not in front of loads: operations complete in order, so a wait for these would wait for
-// the answer too, 1.3 us a launch of the two-layer MLP.)  The block that arrives last then ends with the last ones, not always as
-// the last.  (Chains of launches that load and store 256 floats a block: 16, 72 and 256 blocks 2.23, 2.56 and 2.79 us, of which
-// 1.70 to 1.76 without the monitor; inference, which also read four words of its record, 2.55, 3.18 and 3.31.)
-// (`first`: whether this is the thread that counts for its block, the same one in both calls.)
-constexpr uint32_t kDirectAtEnd = 32, kDirectEarly = 128;
-struct Arrival { uint32_t before; };       // blocks that had counted themselves on this block's counter
+// When a block counts itself: kernel_end does so behind the block's last store and then waits for the answer, so the end time is no
+// earlier than any block's last store.  A kernel can instead call kernel_arrive when all that it reads is there and only its
+// results are left to work out and write, and kernel_finish at the end: the round trip is under way meanwhile.  (Not in front of
+// loads: operations complete in order, so a wait for these would wait for the answer too, 1.3 us a launch of the two-layer MLP.)
+// The block that was counted last then stamps the end behind its own last store, and one that was counted before it can still be
+// writing.  That is so by less than a block's results where every block has the same left to do, and only such a launch may be
+// counted early (`even`): not one with blocks that have nothing to do or with blocks of different kinds.  Where the end itself is
+// acted upon a launch counts at its end all the same: behind a gate (how much of it fell into the bubble, how far it ran past it),
+// and with kCountAtEnd (what calibration times, and the last kernel of a gradient bucket, whose exchange begins then).
+// (Everything counted at the end: one request of 77 tokens 602 -> 634 us, two-layer decoder of 256 tokens 280 -> 296, six layers
+// on 2008 tokens 1671 -> 1718; as it is 604, 285 and 1679.  Chains of launches that load and store 256 floats a block, counted
+// early: 16, 72 and 256 blocks 2.23, 2.56 and 2.79 us, of which 1.70 to 1.76 without the monitor; counted at the end and with four
+// words of the record read 2.55, 3.18 and 3.31.)
+// (`first`: whether this is the thread that counts for its block, the same one in all calls.)
+constexpr uint32_t kDirect = 128;
+struct Arrival {
+  enum : uint32_t { kNotCounted, kCounted, kNotLast, kLast } state;
+  uint32_t before;                         // kCounted: blocks that had counted themselves on this block's counter
+};
 
 __device__ __forceinline__ uint32_t arrival_levels(uint32_t total) { return total <= 512u ? 4u : (total <= 2048u ? 5u : 6u); }
 
-template <uint32_t DIRECT = kDirectEarly>
-__device__ __forceinline__ Arrival kernel_arrive(const KCtl& c, bool first = first_thread()) {
-  Arrival a = {0};
+__device__ __forceinline__ uint32_t count_block(const KCtl& c) {
   const uint32_t total = grid_blocks();
-  if (c.rec != nullptr && total > 1u && first) {
-    uint32_t* p = total > DIRECT ? c.rec->done_sub + (linear_block() & ((1u << arrival_levels(total)) - 1u)) * 32u : &c.rec->done_top;
-    asm("" : "+v"(p));                     // (an address of the lane's own: else the compiler counts lanes first and waits here)
-    a.before = __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  if (total == 1u) return 0;
+  uint32_t at = total > kDirect ? (uint32_t)offsetof(StreamRec, done_sub) + (linear_block() & ((1u << arrival_levels(total)) - 1u)) * 128u : (uint32_t)offsetof(StreamRec, done_top);
+  asm("" : "+v"(at));                      // (an address of the lane's own: else the compiler counts lanes first and waits here)
+  uint32_t* p = reinterpret_cast<uint32_t*>(reinterpret_cast<unsigned char*>(c.rec) + at);
+  return __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ Arrival kernel_arrive(const KCtl& c, bool even = true, bool first = first_thread()) {
+  Arrival a = {even && c.gate == nullptr && !(c.flags & kCountAtEnd) ? Arrival::kCounted : Arrival::kNotCounted, 0};
+  if (c.rec != nullptr && first && a.state == Arrival::kCounted) a.before = count_block(c);
   return a;
 }
 
-// rearm: the kernel hands out its tiles through the record's work counters
-template <uint32_t DIRECT = kDirectEarly>
-__device__ __forceinline__ void kernel_finish(const KCtl& c, const Arrival& a, bool first = first_thread(), bool rearm = false) {
-  if (c.rec == nullptr || !first) return;
+// Takes the answer: whether the block was the last to be counted; that one re-arms the counters.
+__device__ __forceinline__ void kernel_answer(const KCtl& c, Arrival& a, bool first = first_thread()) {
+  if (c.rec == nullptr || !first || a.state != Arrival::kCounted) return;
   const uint32_t total = grid_blocks();
-  if (total > DIRECT) {
+  a.state = Arrival::kNotLast;
+  if (total > kDirect) {
     const uint32_t lg = arrival_levels(total), n_sub = 1u << lg, sub = linear_block() & (n_sub - 1u);
     if (a.before + 1u != (total - sub + n_sub - 1u) >> lg) return;
     st_relaxed(&c.rec->done_sub[sub * 32u], 0u);
@@ -304,6 +319,17 @@ __device__ __forceinline__ void kernel_finish(const KCtl& c, const Arrival& a, b
     return;
   }
   st_relaxed(&c.rec->done_top, 0u);
+  a.state = Arrival::kLast;
+}
+
+// Every thread calls it after its last global store.  rearm: the kernel hands out its tiles through the record's work counters
+__device__ __forceinline__ void kernel_finish(const KCtl& c, Arrival a, bool first = first_thread(), bool rearm = false) {
+  if (c.rec == nullptr) return;
+  __syncthreads();
+  if (!first) return;
+  if (a.state == Arrival::kNotCounted) a = {Arrival::kCounted, count_block(c)};
+  kernel_answer(c, a, first);
+  if (a.state != Arrival::kLast) return;
   if (rearm) {
 #pragma unroll
     for (int x = 0; x < 8; ++x) st_relaxed(&c.rec->tile_next[x * 32], 0u);
@@ -356,9 +382,7 @@ __device__ __forceinline__ void kernel_finish(const KCtl& c, const Arrival& a, b
 // Every thread calls it after its last global store.  (A kernel with one-dimensional blocks and no register to spare says `first`
 // by the one coordinate that it holds anyway.)
 __device__ __forceinline__ void kernel_end(const KCtl& c, bool ran, bool first = first_thread()) {
-  if (c.rec == nullptr || !ran) return;
-  __syncthreads();
-  kernel_finish<kDirectAtEnd>(c, kernel_arrive<kDirectAtEnd>(c, first), first, true);
+  if (ran) kernel_finish(c, Arrival{Arrival::kNotCounted, 0}, first, true);
 }
 
 }  // namespace sif

@@ -44,8 +44,7 @@ __global__ __launch_bounds__(256) void layernorm_fwd_kernel(const bf16_t* __rest
   // the row is the same for the whole wavefront: as a scalar it can index the segment table in the kernel arguments
   const uint32_t lane = threadIdx.x & 63, nv = d >> 3, n_waves = gridDim.x * 4;
   uint32_t row = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
-  Arrival arrival = {0};                       // the block is counted with the last row of its first wavefront
-  if (row >= rows) arrival = kernel_arrive(ctl);
+  Arrival arrival = {Arrival::kNotCounted, 0};                // the block is counted when the last row of its first wavefront is there
   auto out_row = [&](uint32_t r_) -> uint4* {
     if (segs.n != 0) {
       uint32_t r = 0;
@@ -72,7 +71,6 @@ __global__ __launch_bounds__(256) void layernorm_fwd_kernel(const bf16_t* __rest
     }
     while (row < rows) {
       const uint32_t next = __builtin_amdgcn_readfirstlane(row + n_waves);
-      if (next >= rows) arrival = kernel_arrive(ctl);
       if (next < rows) fetch(nx, next);
       uint4* yr = out_row(row);
       float s = 0.f, f[8];
@@ -80,6 +78,7 @@ __global__ __launch_bounds__(256) void layernorm_fwd_kernel(const bf16_t* __rest
       for (int t = 0; t < MAXV; ++t)
         if (lane + 64 * t < nv) { unpack8(cx[t], f); for (int i = 0; i < 8; ++i) s += f[i]; }
       const float mean = wave_sum(s) / (float)d;
+      if (next >= rows) arrival = kernel_arrive(ctl);
       float q = 0.f;
 #pragma unroll
       for (int t = 0; t < MAXV; ++t)
@@ -100,7 +99,6 @@ __global__ __launch_bounds__(256) void layernorm_fwd_kernel(const bf16_t* __rest
     }
   } else {
     for (; row < rows; row = __builtin_amdgcn_readfirstlane(row + n_waves)) {
-      if (row + n_waves >= rows) arrival = kernel_arrive(ctl);
       const uint4* xr = reinterpret_cast<const uint4*>(x + (size_t)row * d);
       uint4* yr = out_row(row);
       float s = 0.f, f[8];
@@ -497,7 +495,6 @@ __global__ __launch_bounds__(1024) void colsum_fin_kernel(const float* __restric
 __global__ __launch_bounds__(1024) void fin_batch_kernel(const FinItem* __restrict__ items, uint32_t acc, KCtl ctl) {
   __shared__ float sm[1024];
   if (!kernel_begin(ctl)) { kernel_end(ctl, false); return; }
-  const Arrival arrival = kernel_arrive(ctl);
   const FinItem it = items[blockIdx.y];
   if (blockIdx.x * 64 < it.n) {                       // uniform over the block
     const uint32_t c = blockIdx.x * 64 + (threadIdx.x & 63);
@@ -507,7 +504,7 @@ __global__ __launch_bounds__(1024) void fin_batch_kernel(const FinItem* __restri
       if (threadIdx.x < 64 && c < it.n && out != nullptr) out[c] = f2bf(acc ? bf2f(out[c]) + t : t);
     }
   }
-  kernel_finish(ctl, arrival);
+  kernel_end(ctl, true);
 }
 
 __global__ __launch_bounds__(256) void colsum_f32_kernel(const float* __restrict__ x, uint32_t ld, float* __restrict__ out,
@@ -529,8 +526,8 @@ constexpr int SM_MAXT = 8;   // 4 columns per lane per step: cols <= 2048
 __global__ __launch_bounds__(256) void softmax_fwd_kernel(const float* __restrict__ s, bf16_t* __restrict__ p, uint32_t rows,
                                                           uint32_t cols, uint32_t ld_s, uint32_t ld_p, uint32_t causal, KCtl ctl) {
   if (!kernel_begin(ctl)) { kernel_end(ctl, false); return; }
-  const Arrival arrival = kernel_arrive(ctl);
   const uint32_t row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  Arrival arrival = {Arrival::kNotCounted, 0};
   if (row < rows) {
     const size_t r = (size_t)blockIdx.y * rows + row;
     const uint32_t valid = causal ? min(cols, row + 1) : cols;
@@ -548,6 +545,7 @@ __global__ __launch_bounds__(256) void softmax_fwd_kernel(const float* __restric
 #pragma unroll
       for (int i = 0; i < 4; ++i) mx = fmaxf(mx, v[t][i]);
     }
+    arrival = kernel_arrive(ctl);              // (what follows takes as long for a short row)
     mx = wave_max(mx);
     float sum = 0.f;
 #pragma unroll
@@ -572,8 +570,8 @@ __global__ __launch_bounds__(256) void softmax_bwd_kernel(const float* __restric
                                                           bf16_t* __restrict__ ds, uint32_t rows, uint32_t cols, uint32_t ld,
                                                           float scale, uint32_t causal, KCtl ctl) {
   if (!kernel_begin(ctl)) { kernel_end(ctl, false); return; }
-  const Arrival arrival = kernel_arrive(ctl);
   const uint32_t row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  Arrival arrival = {Arrival::kNotCounted, 0};
   if (row < rows) {
     const size_t r = (size_t)blockIdx.y * rows + row;
     const uint32_t valid = causal ? min(cols, row + 1) : cols;
@@ -596,6 +594,7 @@ __global__ __launch_bounds__(256) void softmax_bwd_kernel(const float* __restric
         }
       }
     }
+    arrival = kernel_arrive(ctl);
     dot = wave_sum(dot);
     const uint32_t w_end = causal ? min(ld, (row / 128 + 1) * 128) : ld;
 #pragma unroll
@@ -621,7 +620,6 @@ __global__ __launch_bounds__(256) void embed_fwd_kernel(const int32_t* __restric
                                                         const bf16_t* __restrict__ wpe, bf16_t* __restrict__ x,
                                                         uint32_t tokens, uint32_t seq, uint32_t d, uint32_t vocab, KCtl ctl) {
   if (!kernel_begin(ctl)) { kernel_end(ctl, false); return; }
-  const Arrival arrival = kernel_arrive(ctl);
   const uint32_t t = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63, nv = d >> 3;
   if (t < tokens) {
     const uint4* a = reinterpret_cast<const uint4*>(wte + (size_t)clamp_id(ids[t], vocab) * d);
@@ -634,7 +632,7 @@ __global__ __launch_bounds__(256) void embed_fwd_kernel(const int32_t* __restric
       o[v] = pack8(r);
     }
   }
-  kernel_finish(ctl, arrival);
+  kernel_end(ctl, true);
 }
 
 // The same for several requests whose rows lie back to back in x: segment r reads its own token ids, positions
@@ -642,7 +640,6 @@ __global__ __launch_bounds__(256) void embed_fwd_kernel(const int32_t* __restric
 __global__ __launch_bounds__(256) void embed_fwd_segs_kernel(RowSegs segs, const bf16_t* __restrict__ wte, const bf16_t* __restrict__ wpe,
                                                              bf16_t* __restrict__ x, uint32_t tokens, uint32_t d, uint32_t vocab, KCtl ctl) {
   if (!kernel_begin(ctl)) { kernel_end(ctl, false); return; }
-  const Arrival arrival = kernel_arrive(ctl);
   const uint32_t t = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6)), lane = threadIdx.x & 63, nv = d >> 3;
   if (t < tokens) {
     uint32_t r = 0;
@@ -659,7 +656,7 @@ __global__ __launch_bounds__(256) void embed_fwd_segs_kernel(RowSegs segs, const
       o[v] = pack8(q);
     }
   }
-  kernel_finish(ctl, arrival);
+  kernel_end(ctl, true);
 }
 
 constexpr int EB_MAXC = 16;   // columns per thread: d <= 4096
@@ -847,14 +844,13 @@ __global__ __launch_bounds__(256) void embed_bwd_wte_lds_kernel(const int32_t* _
 __global__ __launch_bounds__(256) void embed_bwd_wpe_kernel(const bf16_t* __restrict__ dx, bf16_t* __restrict__ dwpe,
                                                             uint32_t tokens, uint32_t seq, uint32_t d, KCtl ctl) {
   if (!kernel_begin(ctl)) { kernel_end(ctl, false); return; }
-  const Arrival arrival = kernel_arrive(ctl);
   const uint32_t s = blockIdx.x;
   for (uint32_t c = threadIdx.x; c < d; c += 256) {
     float a = 0.f;
     for (uint32_t t = s; t < tokens; t += seq) a += bf2f(dx[(size_t)t * d + c]);
     dwpe[(size_t)s * d + c] = f2bf(a);
   }
-  kernel_finish(ctl, arrival);
+  kernel_end(ctl, true);
 }
 
 // ---------------------------------------------------------------------------------------------- cross entropy

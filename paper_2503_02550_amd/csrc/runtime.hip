@@ -648,6 +648,7 @@ static sif_status run_step(sif_ctx* c, const void* inputs, const void* targets, 
     } else {
       KCtl k = make_ctl(c, c->T, kKindTrain, (uint32_t)i, nullptr, 0);
       if (first_marks && i == 0) k.flags |= kFirstOfStep;
+      for (const TrainModel::DpBucket& b : tm.dp_buckets) if (b.ready_op == i) k.flags |= kCountAtEnd;      // (the bubble reads its end)
       if (last_marks && i + 1 == tm.plan.size()) { k.flags |= kLastOfStep; k.cost_ticks = c->step_no; }
       tm.last_kseq[i] = k.kseq;
       st = launch_op(c, op, s, k);
@@ -1045,6 +1046,7 @@ sif_status sif_calibrate(sif_ctx* c, uint32_t iters, const void* train_inputs_de
       for (uint32_t it = 0; it <= iters; ++it) {
         for (size_t i = 0; i < plan.size(); ++i) {
           KCtl k = make_ctl(c, c->I, kKindInfer, (uint32_t)i, nullptr, 0);
+          k.flags |= kCountAtEnd;
           kseqs[i] = k.kseq;
           st = plan[i].fn(c->I.stream, k);
           if (st != SIF_OK) return st;

@@ -839,3 +839,52 @@ def test_a_steps_record_spans_its_launches(mode):
             assert rec[5] == inside[-1][5] and all(a[5] <= b[4] for a, b in zip(inside, inside[1:]))
             begin = end + 1
         assert s.stats().step_ns_sum == sum(r[5] - r[4] for r in steps)
+
+
+def _launches(s, which, n_ops, passes):
+    """(t0, t1) in us of the newest `passes` passes over `n_ops` kernels, [pass][op]."""
+    runs = [r for r in S.sif_read_trace(s.ctx, which) if r[0] in (1, 2)]
+    return np.array([[r[4], r[5]] for r in runs[-passes * n_ops:]], float).reshape(passes, n_ops, 2) / 1e3
+
+
+def test_a_launch_of_unequal_blocks_ends_with_the_longest():
+    """The launch that finalizes the bias and LayerNorm gradients has a wide item (16384 columns) and narrow ones (64), whose grid
+    rows end in blocks without work.  Those leave first and are dispatched last; the end of the launch is that of the wide item's
+    blocks.  Bound: the next launch starts a launch gap (2 to 3 us here) after it, so of the 15 us from start to start at least 60 %
+    are the launch's (found by a block without work: 38 %)."""
+    c = dict(n_layers=1, d_model=64, n_heads=1, d_head=64, d_ffn=16384, vocab=0, max_pos=0, batch=16, seq=512)
+    shape = decoder_shape(c)
+    w = (np.random.default_rng(1).standard_normal(S.sif_model_n_params(shape)) * 0.02).astype(np.float32)
+    with Session() as s:
+        s.register_training(shape, w, lr=0.0)
+        x = bf(np.random.default_rng(2).standard_normal((16, 512, 64)))
+        torch.cuda.synchronize()
+        for _ in range(24):
+            s.step(x, x)
+        s.sync()
+        names = []
+        while (name := S.sif_train_op_name(s.ctx, s.train["handle"], len(names))) is not None:
+            names.append(name if isinstance(name, str) else name.decode())
+        fin = names.index("grad_fin")
+        tr = _launches(s, 0, len(names), 20)
+    took, until_next = np.median(tr[:, fin, 1] - tr[:, fin, 0]), np.median(tr[:, fin + 1, 0] - tr[:, fin, 0])
+    assert took >= 0.6 * until_next, (took, until_next)
+
+
+def test_calibration_times_launches_to_their_end():
+    """What is predicted of a kernel is its time to the end of its last block.  Kernels that nothing waits for are counted while
+    their results are written and come out shorter by up to an atomic's round trip (0.3 us on average, 7 of 140 us for these 23)."""
+    c = dict(n_layers=3, d_model=768, n_heads=12, d_head=64, d_ffn=3072, vocab=512, max_pos=128, batch=1, seq=77)
+    shape = encoder_shape(c)
+    with Session() as s:
+        m = s.register_inference(shape, P.pack(shape, Y.encoder_params(2, c)))
+        ids = i32(Y.token_ids(5, 1, 77, 512))
+        out = torch.zeros((1, 77, 768), device=DEV, dtype=torch.bfloat16)
+        torch.cuda.synchronize()
+        for _ in range(30):
+            s.wait(s.submit_offline(m, ids, out, 1, 77), 10.0)
+        free = _launches(s, 1, 23, 24)
+        S.sif_calibrate(s.ctx, 30)
+        timed = _launches(s, 1, 23, 24)
+    free, timed = (np.median(t[:, 1:, 1] - t[:, 1:, 0], axis=0) for t in (free, timed))
+    assert timed.sum() >= free.sum() + 2.0, (timed, free)

@@ -82,3 +82,31 @@ def test_only_the_fetches_use_m0(tmp_path):
                     assert re.match(r"s_mov_b32 m0, s\d+$", line) and code[k + 1] == "s_nop 0" and re.match(r"buffer_load_dwordx4 .* lds$", code[k + 2]), (name, code[k:k + 3])
                     fetches += 1
     assert fetches > 100
+
+
+def _kernel_code(tmp_path, having):
+    """(name, instructions) of every kernel in the code objects that hold `having`."""
+    objdump = "/opt/rocm/llvm/bin/llvm-objdump"
+    if not os.path.exists(objdump):
+        pytest.skip("no disassembler")
+    for i, elf in enumerate(_code_objects()):
+        if having not in elf:
+            continue
+        (tmp_path / f"{i}.co").write_bytes(elf)
+        text = subprocess.run([objdump, "-d", "--no-show-raw-insn", "--mcpu=gfx950", tmp_path / f"{i}.co"], capture_output=True, text=True, check=True).stdout
+        for part in re.split(r"\n[0-9a-f]+ <", text)[1:]:
+            name, body = part.split(">:\n", 1)
+            yield name, [line.split("//")[0].strip() for line in body.splitlines()]
+
+
+def test_product_kernels_stamp_their_end_behind_their_results(tmp_path):
+    """The end of a launch is the clock read behind the stores of the results (buffer stores; the monitor's own are global ones),
+    in the wavefronts that only fetch as well."""
+    kernels = 0
+    for name, code in _kernel_code(tmp_path, b"gemm_ring_kernel"):
+        stores = [i for i, line in enumerate(code) if line.startswith("buffer_store")]
+        if not re.search("gemm_(ring|fed|pp)_kernel", name) or not stores:
+            continue
+        assert max(i for i, line in enumerate(code) if line.startswith("s_memrealtime")) > stores[-1], name
+        kernels += 1
+    assert kernels >= 12

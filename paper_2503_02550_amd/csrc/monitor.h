@@ -293,6 +293,9 @@ __device__ __forceinline__ uint32_t arrival_levels(uint32_t total) { return tota
 __device__ __forceinline__ uint32_t count_block(const KCtl& c) {
   const uint32_t total = grid_blocks();
   if (total == 1u) return 0;
+  // What block 0 left for the block that is found to be the last - the start time, and what it took off the sum of the times - is
+  // there before block 0 is counted.  (Its first thread counts it, or one behind a barrier in front of which that thread waited.)
+  if (linear_block() == 0) wait_vector_memory();
   uint32_t at = total > kDirect ? (uint32_t)offsetof(StreamRec, done_sub) + (linear_block() & ((1u << arrival_levels(total)) - 1u)) * 128u : (uint32_t)offsetof(StreamRec, done_top);
   asm("" : "+v"(at));                      // (an address of the lane's own: else the compiler counts lanes first and waits here)
   uint32_t* p = reinterpret_cast<uint32_t*>(reinterpret_cast<unsigned char*>(c.rec) + at);

@@ -110,3 +110,20 @@ def test_product_kernels_stamp_their_end_behind_their_results(tmp_path):
         assert max(i for i, line in enumerate(code) if line.startswith("s_memrealtime")) > stores[-1], name
         kernels += 1
     assert kernels >= 12
+
+
+def test_block_0_is_counted_behind_the_words_it_left(tmp_path):
+    """Block 0 takes a kernel's start off the sum of the times, and the block found to be the last reads that sum.  So the count of a
+    block (the atomic whose counter is chosen by the number of blocks, 0x801 being the border between two levels) stands behind a
+    wait for everything outstanding, under a branch on the block's number."""
+    counts = 0
+    for name, code in _kernel_code(tmp_path, b"gfx950"):
+        if not any(line.startswith("global_atomic_add_x2") for line in code):
+            continue
+        for i, line in enumerate(code):
+            window = code[max(0, i - 32):i]
+            if re.match(r"(global|flat)_atomic_add v.* sc0$", line) and any(re.match(r"s_cmpk_\w+ s\d+, 0x801$", w) for w in window[-24:]):
+                assert any(re.match(r"s_cmp_\w+ s\d+, 0$", a) and b.startswith("s_cbranch") and w == "s_waitcnt vmcnt(0)"
+                           for a, b, w in zip(window, window[1:], window[2:])), (name, window)
+                counts += 1
+    assert counts > 100

@@ -515,7 +515,7 @@ typedef struct sif_stats {
   uint32_t status_now, zc_now;
   uint32_t concurrent_share_ppm;  /* concurrent filling with feedback: the share of busy time now granted  */
   uint64_t tokens_now;
-  uint64_t steps;                 /* training steps completed                                           */
+  uint64_t steps;                 /* training steps completed (their results can be read)               */
   uint64_t step_ns_sum, step_ns_last, step_solo_ns;
   uint64_t bubble_ns;             /* total modelled idle time of completed bubbles                      */
   uint64_t filled_ns;             /* inference kernel time that fell inside bubbles                     */

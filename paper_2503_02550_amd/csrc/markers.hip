@@ -78,8 +78,21 @@ __global__ __launch_bounds__(64) void bubble_overlap_kernel(StreamRec* rec, Mirr
 __global__ __launch_bounds__(64) void step_marker_kernel(StreamRec* rec, Mirror* mir, Slot* slot, uint32_t end, uint32_t kind_id) {
   if (threadIdx.x != 0) return;
   const uint64_t t = now_ticks();
-  if (end) step_end(rec, mir, slot, kind_id, t);
-  else step_begin(rec, slot, t);
+  if (!end) { step_begin(rec, slot, t); return; }
+  const uint64_t step_t0 = ld_relaxed(&rec->step_t0), steps = rec->steps + 1, dt = t - step_t0, sum = rec->step_ticks_sum + dt;
+  rec->steps = steps;
+  rec->step_ticks_sum = sum;
+  rec->step_ticks_last = dt;
+  slot->kind_id = kind_id;
+  slot->decision = 1;
+  slot->t0 = step_t0;
+  slot->t1 = t;
+  // The host looks at the times when the step count has changed, so the count goes out when these have arrived.  (A
+  // system-scope release would do that too, at the price of writing back an L2 full of the step's results three times.)
+  st_sys_relaxed(&mir->step_ticks_last, dt);
+  st_sys_relaxed(&mir->step_ticks_sum, sum);
+  wait_vector_memory();
+  st_sys_relaxed(&mir->steps, steps);
 }
 
 // Clears the poison of the inference stream after the host has taken note of the first skipped launch.

@@ -536,7 +536,7 @@ static sif_status build_mlp_train(TrainModel& tm, Arena& ar, hipStream_t stream)
   // with the sum of the loss, a bias gradient with the weight gradient that reads the same tensor, and, where no bubble
   // (the exchange of the gradients) lies between, the update with the last gradient (nothing reads the weights it
   // changes any more).  Nine launches and the two markers took 48.3 us at 256 x 256 x 256, batch 32, these four and the markers
-  // 29.3, and these four, which mark the step's begin and end themselves, take 26.2.
+  // 29.3, and these four, of which the first marks the step's begin, with the end's marker 27.4.
   emit(p, "fc1", 5, [=](hipStream_t st, const KCtl& c) { return launch_gemm_f32((const float*)t->cur_inputs, di, 1, w1, 1, di, h, dh, B, dh, di, SIF_EPI_GELU, b1, z, st, c); });
   emit(p, "fc2_mse", 5, [=](hipStream_t st, const KCtl& c) {
     F32Launch l{};

@@ -81,16 +81,15 @@ struct KCtl {                       // by-value kernel argument
   Slot* slot;
   const StreamRec* gate;            // training record an inference kernel is gated on, or nullptr
   uint32_t kseq;                    // launch number on this stream (>= 1)
-  uint32_t cost_ticks;              // predicted duration; of a training launch with kLastOfStep the number of the step
+  uint32_t cost_ticks;              // predicted duration
   uint32_t kind_id;
   uint32_t flags;                   // bit 0: last kernel of its job; bit 1: gated on the poison only (runs beside training);
                                     // bits 8..15: 0, or 1 + log2 of the bound on the spins a block waits for block 0's decision;
-                                    // bits 16, 17: first, last launch of a training step (see step_begin, step_end);
-                                    // bit 18: its blocks count themselves when they end (see kernel_end)
+                                    // bit 16: first launch of a training step (see step_begin); bit 17: its blocks count themselves when they end (see kernel_end)
   uint32_t nth;                     // training launches: how many monitored kernels of the stream this makes (they are never
                                     // skipped, so the host knows the count and no block has to read it back)
 };
-constexpr uint32_t kDefaultSpinLog2 = 18, kFirstOfStep = 1u << 16, kLastOfStep = 1u << 17, kCountAtEnd = 1u << 18;
+constexpr uint32_t kDefaultSpinLog2 = 18, kFirstOfStep = 1u << 16, kCountAtEnd = 1u << 17;
 
 __device__ __forceinline__ uint64_t now_ticks() { return wall_clock64(); }
 
@@ -131,9 +130,10 @@ __device__ __forceinline__ void wait_vector_memory() { __builtin_amdgcn_s_waitcn
 __device__ __forceinline__ uint32_t grid_blocks() { return gridDim.x * gridDim.y * gridDim.z; }
 __device__ __forceinline__ bool first_thread() { return threadIdx.x == 0 && threadIdx.y == 0 && threadIdx.z == 0; }
 
-// The begin of a training step, and its end: the step's time, its trace record and the step count for the host.  A step's first
-// kernel does the one in its first block and its last kernel the other in the block that leaves last (a launch of its own each
-// costs 4 us; one where the step begins or ends with a bubble).  Their trace slots are the ones next to the kernels'.
+// The begin of a training step: done by its first kernel in its first block, with the trace slot before the kernel's own, or by a
+// marker where the step begins with a bubble (a launch more costs the two-layer MLP 1.9 us of 29.3).  The end - the step's time, its
+// trace record and the step count - is always a marker's: who sees the count may read the step's results, which are there when the
+// last kernel has ended and not while its last block still runs (from there it would be 1.1 us a step less, 26.3 for 27.4).
 __device__ __forceinline__ void step_begin(StreamRec* rec, Slot* slot, uint64_t t) {
   st_relaxed(&rec->step_t0, t);
   st_relaxed(&rec->state, kStateBusy);
@@ -141,22 +141,6 @@ __device__ __forceinline__ void step_begin(StreamRec* rec, Slot* slot, uint64_t 
   slot->decision = 0;
   slot->t0 = t;
   slot->t1 = t;
-}
-__device__ __forceinline__ void step_end(StreamRec* rec, Mirror* mir, Slot* slot, uint32_t kind_id, uint64_t t) {
-  const uint64_t step_t0 = ld_relaxed(&rec->step_t0), steps = rec->steps + 1, dt = t - step_t0, sum = rec->step_ticks_sum + dt;
-  rec->steps = steps;
-  rec->step_ticks_sum = sum;
-  rec->step_ticks_last = dt;
-  slot->kind_id = kind_id;
-  slot->decision = 1;
-  slot->t0 = step_t0;
-  slot->t1 = t;
-  // The host looks at the times when the step count has changed, so the count goes out when these have arrived.  (A
-  // system-scope release would do that too, at the price of writing back an L2 full of the step's results three times.)
-  st_sys_relaxed(&mir->step_ticks_last, dt);
-  st_sys_relaxed(&mir->step_ticks_sum, sum);
-  wait_vector_memory();
-  st_sys_relaxed(&mir->steps, steps);
 }
 
 // Decision of the first block of a gated launch: run only if no earlier launch of this speculation window was
@@ -344,8 +328,6 @@ __device__ __forceinline__ void kernel_finish(const KCtl& c, Arrival a, bool fir
   st_relaxed(&r->t_end, t1);
   if ((c.kind_id >> 28) == kKindTrain) {
     st_sys_relaxed(&m->t_completed, c.nth);         // also the count of training kernels run (the host takes differences)
-    if (c.flags & kLastOfStep)
-      step_end(r, m, (c.kseq + 1) % kRingSlots == 0 ? c.slot - (kRingSlots - 1) : c.slot + 1, (kKindStep << 28) | (c.cost_ticks & 0x0FFFFFFFu), t1);
     return;
   }
   // The statistics travel to the host mailbox with the last kernel of a job and with every eighth launch (each store to host

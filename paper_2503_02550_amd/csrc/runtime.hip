@@ -613,8 +613,8 @@ static sif_status run_step(sif_ctx* c, const void* inputs, const void* targets, 
   TrainModel& tm = *c->train;
   tm.cur_inputs = inputs; tm.cur_targets = targets; tm.cur_loss = loss;
   hipStream_t s = c->T.stream;
-  // the step's begin and end are marked by its first and last kernel, where it begins and ends with one
-  const bool first_marks = tm.plan.size() > 1 && tm.plan.front().bubble_site < 0, last_marks = tm.plan.size() > 1 && tm.plan.back().bubble_site < 0;
+  // the step's begin is marked by its first kernel, where it begins with one
+  const bool first_marks = tm.plan.size() > 1 && tm.plan.front().bubble_site < 0;
   KCtl k0 = make_ctl(c, c->T, kKindStep, c->step_no, nullptr, 0);
   sif_status st = first_marks ? SIF_OK : launch_step_marker(s, c->T.rec, c->mir, k0.slot, 0, k0.kind_id);
   if (st != SIF_OK) return st;
@@ -649,7 +649,6 @@ static sif_status run_step(sif_ctx* c, const void* inputs, const void* targets, 
       KCtl k = make_ctl(c, c->T, kKindTrain, (uint32_t)i, nullptr, 0);
       if (first_marks && i == 0) k.flags |= kFirstOfStep;
       for (const TrainModel::DpBucket& b : tm.dp_buckets) if (b.ready_op == i) k.flags |= kCountAtEnd;      // (the bubble reads its end)
-      if (last_marks && i + 1 == tm.plan.size()) { k.flags |= kLastOfStep; k.cost_ticks = c->step_no; }
       tm.last_kseq[i] = k.kseq;
       st = launch_op(c, op, s, k);
     }
@@ -657,7 +656,7 @@ static sif_status run_step(sif_ctx* c, const void* inputs, const void* targets, 
   }
   KCtl k1 = make_ctl(c, c->T, kKindStep, c->step_no, nullptr, 0);
   ++c->step_no;
-  return last_marks ? SIF_OK : launch_step_marker(s, c->T.rec, c->mir, k1.slot, 1, k1.kind_id);
+  return launch_step_marker(s, c->T.rec, c->mir, k1.slot, 1, k1.kind_id);
 }
 
 static uint64_t workspace_layout(uint64_t* rec_t, uint64_t* rec_i, uint64_t* ring_t, uint64_t* ring_i) {

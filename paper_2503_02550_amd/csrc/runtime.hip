@@ -26,7 +26,9 @@ static inline uint64_t host_now_ns() {
 static inline void cpu_relax(int n) { for (int i = 0; i < n; ++i) __builtin_ia32_pause(); }
 
 constexpr uint32_t kBubbleTable = 4096;
-constexpr uint64_t kLookNs = 50000;       // how long sif_wait looks before it sleeps
+// How long sif_wait looks before it sleeps.  (A request of two 3 us kernels, submission to answer, medians of ten processes with 1200
+// requests each: 29.6 us where it looks, 33.4 where it sleeps at once; 95th percentiles 40 and 44.)
+constexpr uint64_t kLookNs = 50000;
 
 struct sif_ctx {
   sif_config cfg;
@@ -58,6 +60,7 @@ struct sif_ctx {
   // jobs
   std::mutex mu;
   std::condition_variable cv;
+  std::atomic<uint64_t> results{0};    // counts on when a job's result is there: looked at without the lock
   std::deque<Job*> online_q;
   std::vector<std::deque<Job*>> offline_q;      // one FIFO per inference instance (indexed like models)
   size_t offline_queued = 0;
@@ -240,20 +243,23 @@ static void finish_job(sif_ctx* c, Job* j, int32_t result) {
     c->groups.erase(std::remove_if(c->groups.begin(), c->groups.end(), [&](const std::unique_ptr<Job>& g) { return g.get() == j; }), c->groups.end());
     return;
   }
-  std::lock_guard<std::mutex> lk(c->mu);
-  j->t_done_ns = host_now_ns();
-  j->result = result;
-  if (result == 0) {
-    if (j->online) {
-      c->online_done.fetch_add(1);
-      c->latency.add(j->t_done_ns > j->t_arrival_ns ? j->t_done_ns - j->t_arrival_ns : 0);
-    } else {
-      c->offline_batches.fetch_add(1);
-      c->offline_samples.fetch_add(j->batch);
+  {
+    std::lock_guard<std::mutex> lk(c->mu);
+    j->t_done_ns = host_now_ns();
+    j->result = result;
+    if (result == 0) {
+      if (j->online) {
+        c->online_done.fetch_add(1);
+        c->latency.add(j->t_done_ns > j->t_arrival_ns ? j->t_done_ns - j->t_arrival_ns : 0);
+      } else {
+        c->offline_batches.fetch_add(1);
+        c->offline_samples.fetch_add(j->batch);
+      }
     }
+    j->plan.clear();
+    c->cv.notify_all();
   }
-  j->plan.clear();
-  c->cv.notify_all();
+  c->results.fetch_add(1, std::memory_order_release);      // (behind the lock, which who sees it takes next; the job may be gone)
 }
 
 static uint64_t predicted_remaining_ns(sif_ctx* c) {
@@ -776,6 +782,7 @@ sif_status sif_destroy(sif_ctx* c) {
     for (auto& kv : c->jobs) if (kv.second->result == 1) kv.second->result = SIF_E_CANCELLED;
     c->cv.notify_all();
   }
+  c->results.fetch_add(1, std::memory_order_release);
   process_gate_checks(c, true);
   if (c->mir) (void)hipHostFree(c->mir);
   for (hipEvent_t e : c->prof_ev) (void)hipEventDestroy(e);
@@ -939,12 +946,13 @@ sif_status sif_wait(sif_ctx* c, sif_ticket t, uint64_t timeout_ns) {
   if (!c) return fail(SIF_E_INVAL, "wait: null");
   std::unique_lock<std::mutex> lk(c->mu);
   auto it = c->jobs.find(t);
-  // A small request is done before a thread that went to sleep is awake again: looked at for a while first.  (The lock is given
-  // up between two looks, so the ticket is looked up anew: another waiter may have taken it.)
+  // A small request is done before a thread that went to sleep is awake again: looked at for a while first, without the lock, which the
+  // thread that launches the request takes all the time.  (The ticket is looked up anew: another waiter may have taken it.)
   const uint64_t begin = host_now_ns(), look_until = begin + std::min<uint64_t>(timeout_ns, kLookNs);
   while (it != c->jobs.end() && it->second->result == 1 && host_now_ns() < look_until) {
+    const uint64_t seen = c->results.load(std::memory_order_relaxed);
     lk.unlock();
-    cpu_relax(20);
+    while (c->results.load(std::memory_order_acquire) == seen && host_now_ns() < look_until) cpu_relax(4);
     lk.lock();
     it = c->jobs.find(t);
   }

@@ -889,3 +889,52 @@ def test_calibration_times_launches_to_their_end():
         timed = _launches(s, 1, 23, 24)
     free, timed = (np.median(t[:, 1:, 1] - t[:, 1:, 0], axis=0) for t in (free, timed))
     assert timed.sum() >= free.sum() + 2.0, (timed, free)
+
+
+def test_waiters_look_and_sleep_for_what_they_wait_for():
+    """sif_wait looks for 50 us, without the lock, before it sleeps: answers that come at once, ones that take longer than the look,
+    time-outs below and above the look, a ticket that is gone, and waiters of different tickets beside each other."""
+    import threading
+    import time
+    rng = np.random.default_rng(3)
+    shape = mlp_shape(64, 64, 64, 8)
+    c = dict(n_layers=12, d_model=64, n_heads=1, d_head=64, d_ffn=128, vocab=64, max_pos=64, batch=4, seq=64)
+    slow_shape = encoder_shape(c)
+    with Session() as s:
+        m = s.register_inference(shape, (rng.standard_normal(S.sif_model_n_params(shape)) * 0.05).astype(np.float32))
+        slow = s.register_inference(slow_shape, P.pack(slow_shape, Y.encoder_params(2, c)))
+        x, out = f32(rng.standard_normal((8, 64))), [torch.zeros((8, 64), device=DEV) for _ in range(4)]
+        ids, slow_out = i32(Y.token_ids(5, 4, 64, 64)), torch.zeros((4, 64, 64), device=DEV, dtype=torch.bfloat16)
+        torch.cuda.synchronize()
+        s.wait(s.submit_offline(m, x, out[0], 8), 10.0)                 # within the look
+        want = out[0].clone()
+        s.wait(s.submit_offline(slow, ids, slow_out, 4, 64), 10.0)      # 86 launches: asleep by then
+        tickets = [s.submit_offline(slow, ids, slow_out, 4, 64) for _ in range(20)]
+        for t in (0.0, 20e-6, 200e-6):                                  # none, within the look, beyond it
+            begin = time.perf_counter()
+            with pytest.raises(S.SifError) as e:
+                s.wait(tickets[-1], t)
+            assert e.value.status == S.SIF_E_TIMEOUT and time.perf_counter() - begin >= t
+        for t in tickets:
+            s.wait(t, 10.0)
+        got, errors = [], []
+
+        def one(k):
+            try:
+                for _ in range(50):
+                    s.wait(s.submit_offline(m, x, out[k], 8), 10.0)
+                got.append(k)
+            except Exception as ex:      # noqa: BLE001 (reported below)
+                errors.append(ex)
+
+        threads = [threading.Thread(target=one, args=(k,)) for k in range(4)]
+        for th in threads:
+            th.start()
+        for th in threads:
+            th.join()
+        assert not errors and sorted(got) == [0, 1, 2, 3]
+        torch.cuda.synchronize()
+        assert all(torch.equal(o, want) for o in out)
+        with pytest.raises(S.SifError) as e:
+            s.wait(tickets[0], 1.0)                                     # gone
+        assert e.value.status == S.SIF_E_INVAL

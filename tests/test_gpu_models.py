@@ -288,3 +288,33 @@ def test_pipeline_stage_sizes_its_bubbles_from_measured_pass_times():
 def OB_bubbles(stage, stages, micro):
     from oracle import bubbles as OB
     return OB.pp_1f1b_bubbles(stage, stages, micro, 1000, 2000)
+
+
+@pytest.mark.parametrize("more", [0, 8, 808])
+@pytest.mark.parametrize("vocab,blocks_per_cu", [(97, 16), (1000, 4), (5000, 3), (13000, 2)])
+def test_cross_entropy_of_a_step_hands_out_its_rows(vocab, blocks_per_cu, more):
+    """In a training step the blocks of the cross entropy take two rows each and get the others, where there are any, from a
+    counter that is re-armed from step to step: as many rows as that, a few more, and many more, for every number of vectors per
+    thread.  Gradient and loss have the bits of the same kernel without a counter on the same logits."""
+    tokens = 2 * blocks_per_cu * torch.cuda.get_device_properties(0).multi_processor_count + more
+    c = dict(n_layers=1, d_model=64, n_heads=1, d_head=64, d_ffn=128, vocab=vocab, max_pos=tokens // 8, batch=8, seq=tokens // 8)
+    shape = decoder_shape(c)
+    ld = (vocab + 63) // 64 * 64 if vocab >= 8192 else (vocab + 7) // 8 * 8
+    ids, tg = i32(Y.token_ids(3, 8, c["seq"], vocab)), i32(Y.token_ids(4, 8, c["seq"], vocab))
+    loss, rows, mean = torch.zeros(1, device=DEV), torch.zeros(tokens, device=DEV), torch.zeros(1, device=DEV)
+    with Session() as s:
+        s.register_training(shape, P.pack(shape, Y.decoder_params(1, c)), lr=0.0)
+        for step in range(3):
+            loss.zero_()
+            torch.cuda.synchronize()
+            s.step(ids, tg, loss)
+            s.sync()
+            got = s.train_tensor("logits").clone()
+            wte = s.train_tensor("work")[:vocab * 64]
+            logits = torch.zeros(tokens * ld, device=DEV, dtype=torch.bfloat16)
+            S.sif_k_gemm_bf16(s.train_tensor("lnf"), wte, logits, tokens, vocab, 64, 64, 64, ld)
+            S.sif_k_xent_fwd_bwd(logits, tg, rows, tokens, vocab, ld)
+            S.sif_k_reduce_sum(rows, mean, tokens, 1.0 / tokens)
+            torch.cuda.synchronize()
+            assert torch.equal(got.view(torch.int16), logits.view(torch.int16)), step
+            assert loss.item() == mean.item(), step

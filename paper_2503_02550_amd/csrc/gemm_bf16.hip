@@ -428,14 +428,16 @@ __device__ __forceinline__ void gemm_store_f32(const GemmP& p, floatx4 (&acc)[2 
 
 // bf16 results of the other combinations - a residual together with GELU or GELU' - and of rows further apart than the offsets
 // above reach: vectors too, but 64-bit addresses and decisions while it runs.  The first tensor that is read is requested 32
-// rows ahead, the residual beside an auxiliary tensor with its pass.  (One element at a time 4096 x
-// 4096 x 512 on 256x256 tiles took 115 us with GELU and a residual, 148 with GELU' and a residual, 75 with both of GELU and
-// GELU'; now 29, 43 and 38, with the residual alone 26; 77 x 768 x 768 with rows of 2 M elements 6.8 and now 5.4.)
+// rows ahead (64 where a wavefront has as many), the residual beside an auxiliary tensor for 32 rows at once (16 on 256x256 tiles, which
+// have no registers for more): a wait for it also waits for the stores before it.  (One element at a time 4096 x 4096 x 512 on
+// 256x256 tiles took 115 us with GELU and a residual, 148 with GELU' and a residual, 75 with both of GELU and GELU'; now 27, 39 and
+// 36, with the residual alone 25.5; 77 x 768 x 768 with rows of 2 M elements 6.8 and now 5.6.  With a request for every 8 rows, and
+// 32 ahead everywhere, 28, 43 and 38; on 128x128 tiles GELU and a residual 31, now 28, with the pre-activation 42 and 37.)
 template <int TI, int TJ>
 __device__ __forceinline__ void gemm_store_mixed(const GemmP& p, floatx4 (&acc)[2 * TI][2 * TJ], float* sW, uint32_t mw, uint32_t nw, size_t c_off, uint32_t lane,
                                                  const bf16_t* bias_s) {
   typedef Staging<TJ> S;
-  constexpr int PER = 2 * S::PASSES;
+  constexpr int PER = 2 * S::PASSES, AHEAD = TI == 2 ? 2 : 1, LATE = TI > 2 ? PER / 2 : PER;
   const uint32_t c8 = lane % S::CPR, n = nw + c8 * 8, row0 = mw + S::row_of(lane / S::CPR);
   const bool grad = (p.epi & SIF_EPI_GELU_GRAD) != 0, gelu = (p.epi & SIF_EPI_GELU) != 0, residual = (p.epi & SIF_EPI_RESIDUAL) != 0;
   const bf16_t* const res = reinterpret_cast<const bf16_t*>(p.res);
@@ -443,19 +445,22 @@ __device__ __forceinline__ void gemm_store_mixed(const GemmP& p, floatx4 (&acc)[
   // a lane's row in a pass, and where what is read for it lies: beyond the last row or column, in these
   auto row_of = [&](int pass) { return row0 + pass / S::PASSES * 16 + pass % S::PASSES * S::RPG; };
   auto read_at = [&](int pass) { return c_off + (size_t)min(row_of(pass), p.m - 1) * p.ldc + min(n, p.n - 8); };
-  uint4 ahead[PER];
+  uint4 ahead[AHEAD][PER], late[LATE];          // late: the residual where it is not the tensor requested ahead
   auto request = [&](int i) {
     if (first == nullptr) return;
 #pragma unroll
-    for (int k = 0; k < PER; ++k) ahead[k] = *reinterpret_cast<const uint4*>(first + read_at(i * PER + k));
+    for (int k = 0; k < PER; ++k) ahead[i % AHEAD][k] = *reinterpret_cast<const uint4*>(first + read_at(i * PER + k));
   };
-  request(0);
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) request(i);
   float bias[8];
   unpack_bf8(p.bias != nullptr ? *reinterpret_cast<const uint4*>(bias_s + c8 * 8) : make_uint4(0, 0, 0, 0), bias);
 #pragma unroll
   for (int pass = 0; pass < TI * PER; ++pass) {
-    uint4 late;                                // the residual where it is not the tensor requested ahead
-    if (residual && grad) late = *reinterpret_cast<const uint4*>(res + read_at(pass));
+    if (residual && grad && pass % LATE == 0) {
+#pragma unroll
+      for (int k = 0; k < LATE; ++k) late[k] = *reinterpret_cast<const uint4*>(res + read_at(pass + k));
+    }
     S::put(sW, acc[pass / S::PASSES], pass % S::PASSES, lane);
     lanes_in_order();
     float4 q[2];
@@ -471,7 +476,7 @@ __device__ __forceinline__ void gemm_store_mixed(const GemmP& p, floatx4 (&acc)[
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[e] = gelu_fast(v[e]);
     }
-    const uint4 a = ahead[pass % PER];
+    const uint4 a = ahead[pass / PER % AHEAD][pass % PER];
     float x[8];
     if (grad) {
       unpack_bf8(a, x);
@@ -479,7 +484,7 @@ __device__ __forceinline__ void gemm_store_mixed(const GemmP& p, floatx4 (&acc)[
       for (int e = 0; e < 8; ++e) v[e] *= gelu_grad_fast(x[e]);
     }
     if (residual) {
-      unpack_bf8(grad ? late : a, x);
+      unpack_bf8(grad ? late[pass % LATE] : a, x);
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[e] += x[e];
     }
@@ -487,47 +492,51 @@ __device__ __forceinline__ void gemm_store_mixed(const GemmP& p, floatx4 (&acc)[
     const u32x4 y = {w.x, w.y, w.z, w.w};
     if (inside) __builtin_nontemporal_store(y, reinterpret_cast<u32x4*>(reinterpret_cast<bf16_t*>(p.c) + idx));
     lanes_in_order();
-    if (pass % PER == PER - 1 && pass / PER + 1 < TI) request(pass / PER + 1);
+    if (pass % PER == PER - 1 && pass / PER + AHEAD < TI) request(pass / PER + AHEAD);
     __builtin_amdgcn_sched_barrier(0);
   }
 }
 
-// fp32 results with anything else.  The residual is read with its pass: requested ahead it only lies in front of the stores and is
-// waited for longer (47 us instead of 43 at the size below).  The auxiliary tensor is requested ahead as above.  (4096 x 4096 x 512
-// on 256x256 tiles with a residual 43 us, with GELU' 44, with both GELU and a residual 50, one element at a time 98, 101, 134.)
+// fp32 results with anything else, the auxiliary tensor and the residual requested as above.  (4096 x 4096 x 512 on 256x256 tiles with a
+// residual 41 us, with GELU' 41, with both GELU and a residual 48; with a request for every 8 rows 50, 45 and 60, one element at a
+// time 98, 101 and 134.  On 128x128 tiles 43, 40 and 51; with a request for every 8 rows 53, 47 and 63.)
 template <int TI, int TJ>
 __device__ __forceinline__ void gemm_store_f32_mixed(const GemmP& p, floatx4 (&acc)[2 * TI][2 * TJ], float* sW, uint32_t mw, uint32_t nw, size_t c_off, uint32_t lane,
                                                      const bf16_t* bias_s) {
   typedef Staging<TJ> S;
-  constexpr int CPR = S::W / 4, PER = 2 * S::PASSES;
+  constexpr int CPR = S::W / 4, PER = 2 * S::PASSES, AHEAD = TI == 2 ? 2 : 1, LATE = TI > 2 ? PER / 2 : PER;
   const uint32_t t = lane / CPR, c4 = lane % CPR, n = nw + c4 * 4, row0 = mw + S::row_of(t);
   const bool grad = (p.epi & SIF_EPI_GELU_GRAD) != 0, gelu = (p.epi & SIF_EPI_GELU) != 0, residual = (p.epi & SIF_EPI_RESIDUAL) != 0;
   const float* const res = reinterpret_cast<const float*>(p.res);
   auto row_of = [&](int pass, int it) { return row0 + pass / S::PASSES * 16 + pass % S::PASSES * S::RPG + it * 8; };      // (it: as in gemm_store_f32)
   auto read_at = [&](int pass, int it) { return c_off + (size_t)min(row_of(pass, it), p.m - 1) * p.ldc + min(n, p.n - 4); };
-  uint2 z[PER][2];
+  uint2 z[AHEAD][PER][2];
+  float4 r[LATE][2];
   auto request = [&](int i) {
     if (!grad) return;
 #pragma unroll
     for (int k = 0; k < PER; ++k)
 #pragma unroll
-      for (int it = 0; it < 2; ++it) z[k][it] = *reinterpret_cast<const uint2*>(p.aux + read_at(i * PER + k, it));
+      for (int it = 0; it < 2; ++it) z[i % AHEAD][k][it] = *reinterpret_cast<const uint2*>(p.aux + read_at(i * PER + k, it));
   };
-  request(0);
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) request(i);
   const uint2 bq = p.bias != nullptr ? *reinterpret_cast<const uint2*>(bias_s + c4 * 4) : make_uint2(0, 0);
   const float bias[4] = {bflo(bq.x), bfhi(bq.x), bflo(bq.y), bfhi(bq.y)};
 #pragma unroll
   for (int pass = 0; pass < TI * PER; ++pass) {
+    if (residual && pass % LATE == 0) {
+#pragma unroll
+      for (int k = 0; k < LATE; ++k)
+#pragma unroll
+        for (int it = 0; it < 2; ++it) r[k][it] = *reinterpret_cast<const float4*>(res + read_at(pass + k, it));
+    }
     S::put(sW, acc[pass / S::PASSES], pass % S::PASSES, lane);
     lanes_in_order();
-    float4 s[2], r[2];
+    float4 s[2];
 #pragma unroll
     for (int it = 0; it < 2; ++it) s[it] = *reinterpret_cast<const float4*>(sW + S::at(t + it * (S::ROWS / 2), c4 * 4));
     lanes_in_order();
-    if (residual) {
-#pragma unroll
-      for (int it = 0; it < 2; ++it) r[it] = *reinterpret_cast<const float4*>(res + read_at(pass, it));
-    }
 #pragma unroll
     for (int it = 0; it < 2; ++it) {
       const uint32_t m = row_of(pass, it);
@@ -542,29 +551,30 @@ __device__ __forceinline__ void gemm_store_f32_mixed(const GemmP& p, floatx4 (&a
         for (int e = 0; e < 4; ++e) v[e] = gelu_fast(v[e]);
       }
       if (grad) {
-        const uint2 q = z[pass % PER][it];
+        const uint2 q = z[pass / PER % AHEAD][pass % PER][it];
         const float x[4] = {bflo(q.x), bfhi(q.x), bflo(q.y), bfhi(q.y)};
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] *= gelu_grad_fast(x[e]);
       }
       if (residual) {
-        const float4 x = r[it];
+        const float4 x = r[pass % LATE][it];
         v[0] += x.x; v[1] += x.y; v[2] += x.z; v[3] += x.w;
       }
       if (inside) *reinterpret_cast<float4*>(reinterpret_cast<float*>(p.c) + idx) = make_float4(v[0], v[1], v[2], v[3]);
     }
-    if (pass % PER == PER - 1 && pass / PER + 1 < TI) request(pass / PER + 1);
+    if (pass % PER == PER - 1 && pass / PER + AHEAD < TI) request(pass / PER + AHEAD);
     __builtin_amdgcn_sched_barrier(0);
   }
 }
 
-// A column count that is no multiple of eight: one element at a time, consecutive ones in consecutive lanes, what is read for
-// four of them at once.  (4096 x 4093 x 512 with a residual: 92 us with a wait for each element, now 40; plain 38, now 32.)
+// A column count that is no multiple of eight: one element at a time, consecutive ones in consecutive lanes, what is read for a pass'
+// eight of them at once (four on 256x256 tiles: unrolled for eight the passes are more than the compiler keeps in registers, and take
+// four times as long).  (4096 x 4093 x 512 with a residual: 92 us with a wait for each element, now 41; plain 38, now 33.  4096 x
+// 777 x 512, on smaller tiles, takes 0.89 to 0.93 of its time with four at once.)
 template <int TI, int TJ>
 __device__ __forceinline__ void gemm_store_single(const GemmP& p, floatx4 (&acc)[2 * TI][2 * TJ], float* sW, uint32_t mw, uint32_t nw, size_t c_off, uint32_t lane) {
   typedef Staging<TJ> S;
-  constexpr int W = S::W, AT_ONCE = 4, PER_ITEM = 64 / W;                 // rows of the staging that the lanes cover
-  static_assert(S::ROWS * W % (64 * AT_ONCE) == 0, "whole turns");
+  constexpr int W = S::W, PER_ITEM = 64 / W, AT_ONCE = S::ROWS / PER_ITEM / (TI > 2 ? 2 : 1);      // PER_ITEM: rows of the staging that the lanes cover
   const bool grad = (p.epi & SIF_EPI_GELU_GRAD) != 0, gelu = (p.epi & SIF_EPI_GELU) != 0, residual = (p.epi & SIF_EPI_RESIDUAL) != 0, f32 = (p.epi & SIF_EPI_OUT_F32) != 0;
   const uint32_t col = lane % W, n = nw + col, n_read = min(n, p.n - 1);
   const float bias = p.bias != nullptr ? bf2f(p.bias[n_read]) : 0.f;
@@ -593,7 +603,7 @@ __device__ __forceinline__ void gemm_store_single(const GemmP& p, floatx4 (&acc)
         for (int e = 0; e < AT_ONCE; ++e) res[e] = bf2f(reinterpret_cast<const bf16_t*>(p.res)[read_at(e)]);
       }
 #pragma unroll
-      for (int e = 0; e < AT_ONCE; ++e) x[e] = sW[S::at(t(e), col)] * p.alpha + bias;
+      for (int e = 0; e < AT_ONCE; ++e) x[e] = sW[t(e) * W + (col ^ (S::key(t(e)) << 2))] * p.alpha + bias;      // (S::at, the key of the whole row)
       if (gelu) {
         if (p.aux != nullptr) {
 #pragma unroll

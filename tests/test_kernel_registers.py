@@ -84,8 +84,8 @@ def test_only_the_fetches_use_m0(tmp_path):
     assert fetches > 100
 
 
-def _kernel_code(tmp_path, having):
-    """(name, instructions) of every kernel in the code objects that hold `having`."""
+def _kernel_code(tmp_path, having, comments=False):
+    """(name, instructions) of every kernel in the code objects that hold `having`; comments: with their addresses behind them."""
     objdump = "/opt/rocm/llvm/bin/llvm-objdump"
     if not os.path.exists(objdump):
         pytest.skip("no disassembler")
@@ -96,20 +96,42 @@ def _kernel_code(tmp_path, having):
         text = subprocess.run([objdump, "-d", "--no-show-raw-insn", "--mcpu=gfx950", tmp_path / f"{i}.co"], capture_output=True, text=True, check=True).stdout
         for part in re.split(r"\n[0-9a-f]+ <", text)[1:]:
             name, body = part.split(">:\n", 1)
-            yield name, [line.split("//")[0].strip() for line in body.splitlines()]
+            yield name, [line.strip() if comments else line.split("//")[0].strip() for line in body.splitlines()]
+
+
+def _reached(code, successors, begin, without=()):
+    """The instructions that can follow one of `begin`, on paths that touch none of `without`."""
+    seen, todo = set(), [j for i in begin for j in successors[i]]
+    while todo:
+        i = todo.pop()
+        if i not in seen and i not in without:
+            seen.add(i)
+            todo += successors[i]
+    return seen
 
 
 def test_product_kernels_stamp_their_end_behind_their_results(tmp_path):
-    """The end of a launch is the clock read behind the stores of the results (buffer stores; the monitor's own are global ones),
-    in the wavefronts that only fetch as well."""
+    """The end of a launch is the clock read behind the block's results.  On no path from a fetch of operands to that read (a clock
+    read that a count of blocks leads to) may a wavefront be without a barrier that the stores of the results lead to: those that
+    only fetch wait there for the others."""
     kernels = 0
-    for name, code in _kernel_code(tmp_path, b"gemm_ring_kernel"):
-        stores = [i for i, line in enumerate(code) if line.startswith("buffer_store")]
-        if not re.search("gemm_(ring|fed|pp)_kernel", name) or not stores:
-            continue
-        assert max(i for i, line in enumerate(code) if line.startswith("s_memrealtime")) > stores[-1], name
+    for name, code in _kernel_code(tmp_path, b"gemm_ring_kernel", comments=True):
+        if not re.search("gemm_(ring|fed|pp)_kernel", name) or not any(line.startswith("buffer_store") for line in code):
+            continue                       # (the rare epilogues store to plain addresses; their kernels are the same otherwise)
+        at = {int(re.search(r"// ([0-9A-F]+):", line)[1], 16): i for i, line in enumerate(code) if "// " in line}
+        first = min(at)
+        successors = []
+        for i, line in enumerate(code):
+            to = re.search(r"<\S+?(?:\+0x([0-9a-f]+))?>$", line) if re.match("s_c?branch", line) else None
+            successors.append([] if line.startswith("s_endpgm") else ([i + 1] if not line.startswith("s_branch") and i + 1 < len(code) else []) + ([at[first + int(to[1] or "0", 16)]] if to else []))
+        having = lambda pattern: [i for i, line in enumerate(code) if re.match(pattern, line)]      # noqa: E731
+        counts = [i for i in having(r"(global|flat)_atomic_add v.* sc0 ") if any("0x801" in line for line in code[max(0, i - 24):i])]
+        ends = set(having("s_memrealtime")) & _reached(code, successors, counts)
+        barriers = set(having("s_barrier")) & _reached(code, successors, having("buffer_store"))
+        assert counts and ends, name
+        assert not ends & _reached(code, successors, having(r"buffer_load_dwordx4 .* lds"), without=barriers), name
         kernels += 1
-    assert kernels >= 12
+    assert kernels >= 40
 
 
 def test_block_0_is_counted_behind_the_words_it_left(tmp_path):

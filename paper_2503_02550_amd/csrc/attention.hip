@@ -306,7 +306,9 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_kernel(const bf16_t* _
 // With a causal mask a (batch, head)'s blocks differ in length.  The grid's slow index counts them from the longest, which start
 // first.  Where all of a launch's blocks find room at once, two per CU, that puts long ones together: from `fold` on, where the CUs'
 // second blocks begin, the shortest come first instead.  (2 x 16 heads of 128, 2048 rows, 512 blocks: 101.7 us, now 97.2; the
-// forward kernel takes 66 either way.)
+// forward kernel takes 66 either way.  The whole backward pass at nine shapes of 320 to 512 blocks, 4 to 128 (batch, head) pairs, 512 to
+// 12000 rows, where the two orders differ: with heads of 128 0.5 to 2.9 % less, 1.7 on average, with heads of 64 up to 0.7, 0.3 on
+// average, at none of them more.)
 template <int DH, int CAUSAL>
 __global__ __launch_bounds__(AT_THREADS, 2) void attn_bwd_dq_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
                                                                  const bf16_t* __restrict__ d_o, const float* __restrict__ lse,

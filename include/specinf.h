@@ -573,7 +573,10 @@ typedef struct sif_trace_rec {
   uint32_t id;          /* kernel sequence number / bubble site / step index                            */
   uint32_t decision;    /* inference kernels: 1 ran, 2 skipped                                          */
   uint32_t reserved;
-  uint64_t t0_ns, t1_ns;/* device wall clock                                                            */
+  uint64_t t0_ns, t1_ns;/* device wall clock.  The end of a kernel that nothing waits for (training, or inference without a
+                           training instance) is that of the block counted last: another may still be writing its results,
+                           for less than half a microsecond.  Kernels in bubbles, in calibration and at the end of a gradient
+                           bucket end with their last block                                             */
 } sif_trace_rec;
 /* Copies the newest records of a stream's ring (0 = training, 1 = inference) to out[0..max), oldest first;
  * synchronises both streams first.  Returns the count in *n. */

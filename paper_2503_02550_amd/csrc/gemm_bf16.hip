@@ -1241,13 +1241,13 @@ static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 // ---------------------------------------------------------------------------------------------- configurations
 // What a launch costs, per configuration: 2 us, and per round of tiles `fixed` + `step` * (K steps of 64) us with `slots`
 // tiles on a CU at a time, `step1` with one.  Least squares over 37 shapes from 77 x 768 x 3072 to 8192^3, three operand
-// layouts and three epilogues.  Checked against every configuration's time at 665 other shapes, plain products launched back
-// to back: the modelled times are 0.7 to 1.5 of the measured ones, the choice is on average 1.0 % slower than the best
-// configuration and at worst 21 % (at 6 us; 18 % at 8192 x 3072 x 768, 51 us on 256x128, 43 on 128x128).  A fit to those
-// would not be better: inside the training step, with its epilogues and with operands that come from memory, that product
-// takes 67.6 us on 256x128 and 71.2 on 128x128.  Tiles with wavefronts that only fetch are faster than the constants say, where
-// the small tiles were the choice already: over 477 products of 32 to 4096 rows with weights from memory the choice is on
-// average 0.4 % above the best, as it is with constants fitted to those.
+// layouts and three epilogues, of kernels on 32x32x16 MFMAs.  Checked against every configuration's time on the present ones at 638
+// other shapes, plain products launched back to back: the modelled times are 0.65 to 1.4 of the measured ones (the two largest tiles
+// are 1.25 times as fast as modelled, the small ones as modelled), the choice is on average 0.9 % slower than the best
+// configuration, 6 % in the 95th percentile, and at worst 54 % (1299 x 3000 x 7296: 110 us on 64x64, 71 on 256x128).  8192 x 3072 x
+// 768 takes 44 us on 256x128 and 40 on 256x256; inside the training step, with its epilogues and with operands that come from
+// memory, it took 67.6 on 256x128 and 71.2 on 128x128 with the kernels before.  Over 477 products of 32 to 4096 rows with
+// weights from memory the choice was 0.4 % above the best on average, as it was with constants fitted to those.
 struct GemmTiles { uint32_t bm, bn, slots; double fixed, step, step1; };
 enum { kT32x64, kT64x64, kT128x64, kT128x128x1, kT128x128, kT256x128, kT256x256, kNTiles };
 static const GemmTiles kGemmTiles[kNTiles] = {

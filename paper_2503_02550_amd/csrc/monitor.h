@@ -260,7 +260,8 @@ __device__ __forceinline__ bool kernel_begin(const KCtl& c) {
 // writing.  That is so by less than a block's results where every block has the same left to do, and only such a launch may be
 // counted early (`even`): not one with blocks that have nothing to do or with blocks of different kinds.  Where the end itself is
 // acted upon a launch counts at its end all the same: behind a gate (how much of it fell into the bubble, how far it ran past it),
-// and with kCountAtEnd (what calibration times, and the last kernel of a gradient bucket, whose exchange begins then).
+// and with kCountAtEnd (what calibration times, and the last kernel of a gradient bucket, whose exchange begins then).  What reads
+// the end besides: the trace, the busy time of inference without a gate, and the count of completed kernels.
 // (Everything counted at the end: one request of 77 tokens 602 -> 634 us, two-layer decoder of 256 tokens 280 -> 296, six layers
 // on 2008 tokens 1671 -> 1718; as it is 604, 285 and 1679.  Chains of launches that load and store 256 floats a block, counted
 // early: 16, 72 and 256 blocks 2.23, 2.56 and 2.79 us, of which 1.70 to 1.76 without the monitor; counted at the end and with four

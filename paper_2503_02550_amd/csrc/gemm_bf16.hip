@@ -583,24 +583,24 @@ __device__ __forceinline__ void gemm_store_single(const GemmP& p, floatx4 (&acc)
     S::put(sW, acc[pass / S::PASSES], pass % S::PASSES, lane);
     lanes_in_order();
 #pragma clang loop unroll(disable)
-    for (uint32_t t0 = lane / W; t0 < (uint32_t)S::ROWS; t0 += PER_ITEM * AT_ONCE) {
+    for (uint32_t t0 = W == 64 ? 0u : lane / W; t0 < (uint32_t)S::ROWS; t0 += PER_ITEM * AT_ONCE) {
       const uint32_t m = mw + pass / S::PASSES * 16 + pass % S::PASSES * S::RPG;
       auto t = [&](int e) { return t0 + e * PER_ITEM; };
       auto row = [&](int e) { return m + S::row_of(t(e)); };
       auto inside = [&](int e) { return row(e) < p.m && n < p.n; };
-      auto idx = [&](int e) { return c_off + (size_t)row(e) * p.ldc + n; };
-      auto read_at = [&](int e) { return c_off + (size_t)min(row(e), p.m - 1) * p.ldc + n_read; };
+      auto at = [&](auto* base, int e) { return base + (c_off + (size_t)row(e) * p.ldc) + n; };      // (a row is the same for all lanes, or for half of them)
+      auto read = [&](const auto* base, int e) { return (base + (c_off + (size_t)min(row(e), p.m - 1) * p.ldc))[n_read]; };
       float x[AT_ONCE], z[AT_ONCE], res[AT_ONCE];
       if (grad) {
 #pragma unroll
-        for (int e = 0; e < AT_ONCE; ++e) z[e] = bf2f(p.aux[read_at(e)]);
+        for (int e = 0; e < AT_ONCE; ++e) z[e] = bf2f(read(p.aux, e));
       }
       if (residual && f32) {
 #pragma unroll
-        for (int e = 0; e < AT_ONCE; ++e) res[e] = reinterpret_cast<const float*>(p.res)[read_at(e)];
+        for (int e = 0; e < AT_ONCE; ++e) res[e] = read(reinterpret_cast<const float*>(p.res), e);
       } else if (residual) {
 #pragma unroll
-        for (int e = 0; e < AT_ONCE; ++e) res[e] = bf2f(reinterpret_cast<const bf16_t*>(p.res)[read_at(e)]);
+        for (int e = 0; e < AT_ONCE; ++e) res[e] = bf2f(read(reinterpret_cast<const bf16_t*>(p.res), e));
       }
 #pragma unroll
       for (int e = 0; e < AT_ONCE; ++e) x[e] = sW[t(e) * W + (col ^ (S::key(t(e)) << 2))] * p.alpha + bias;      // (S::at, the key of the whole row)
@@ -609,7 +609,7 @@ __device__ __forceinline__ void gemm_store_single(const GemmP& p, floatx4 (&acc)
 #pragma unroll
           for (int e = 0; e < AT_ONCE; ++e) {
             z[e] = grad ? bf2f(f2bf(x[e])) : z[e];       // (GELU' of what is written)
-            if (inside(e)) p.aux[idx(e)] = f2bf(x[e]);
+            if (inside(e)) *at(p.aux, e) = f2bf(x[e]);
           }
         }
 #pragma unroll
@@ -625,10 +625,10 @@ __device__ __forceinline__ void gemm_store_single(const GemmP& p, floatx4 (&acc)
       }
       if (f32) {
 #pragma unroll
-        for (int e = 0; e < AT_ONCE; ++e) { if (inside(e)) reinterpret_cast<float*>(p.c)[idx(e)] = x[e]; }
+        for (int e = 0; e < AT_ONCE; ++e) { if (inside(e)) *at(reinterpret_cast<float*>(p.c), e) = x[e]; }
       } else {
 #pragma unroll
-        for (int e = 0; e < AT_ONCE; ++e) { if (inside(e)) reinterpret_cast<bf16_t*>(p.c)[idx(e)] = f2bf(x[e]); }
+        for (int e = 0; e < AT_ONCE; ++e) { if (inside(e)) *at(reinterpret_cast<bf16_t*>(p.c), e) = f2bf(x[e]); }
       }
     }
     lanes_in_order();

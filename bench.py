@@ -36,7 +36,7 @@ HBM_PEAK_TBPS = 8.0
 # Average bytes per dispatch of the bf16 product with both operands K-contiguous that pass between the L2s and the memory side
 # in the headline workload, from the FETCH_SIZE / WRITE_SIZE counter runs summarised in the file named beside it (counters cannot be
 # read from inside a timed run).
-GEMM00_HBM_BYTES_PER_LAUNCH = 743.0e6
+GEMM00_HBM_BYTES_PER_LAUNCH = 742.0e6
 GEMM00_HBM_BYTES_SOURCE = "constant from profiles/bench_cfg2_hbm_traffic.md (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this command)"
 PROF_SAMPLED = 3     # sif_profile_gemm: event pairs around every third launch of the a_layout = b_layout = 0 variant per stream
 N_RING = 64          # distinct input / output buffers the queued requests cycle through (a coalesced group is 32)
